@@ -115,8 +115,8 @@ lamp_status lamp_rmsprop_step(int32_t count, const int64_t *numel, float *const 
  *   bias      : nullable, fp32 [Co].
  *   stats_out : nullable, fp32 [N][Co][2] = (mean, rstd = 1/sqrt(biased var + eps)) of the STORED
  *               z over d,h,w -- the InstanceNorm statistics, produced in the conv epilogue.
- * bf16 requires pointers 16-byte aligned; any Ci, Co >= 1 is accepted (multiples of 32 take the
- * matrix-core kernels).
+ * bf16 requires pointers 16-byte aligned; any Ci, Co >= 1 is accepted (Co a multiple of 8 takes the
+ * matrix-core kernels, whatever Ci, where w and ws are 16-byte aligned).
  */
 size_t lamp_conv3d_fwd_workspace_bytes(const lamp_tensor_desc *xd, const lamp_tensor_desc *zd, int want_stats);
 lamp_status lamp_conv3d_fwd(const lamp_tensor_desc *xd, const void *x, const lamp_norm_in *xnorm,

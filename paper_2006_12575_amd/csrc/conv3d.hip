@@ -760,6 +760,46 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
     }
 }
 
+// ---- channel counts that are no multiple of 8 on the matrix-core kernels ---------------------------
+// The matrix-core kernels copy 16-byte pieces (8 channels).  An input with fewer channels than that, or whose voxels do
+// not start on 16 bytes -- a two- or four-channel image in front of a first layer -- is copied once into whole pieces with
+// zero channels behind the real ones: 16 bytes written per voxel and piece, against the 2 * C_out bytes that the conv
+// writes.  (2->16 channels on 2 x 64 x 80 x 96 voxels, forward to weight gradient: 1972 -> 196 us.)  One thread per voxel and piece.
+__global__ __launch_bounds__(256) void conv_pad_kernel(const bf16_t* __restrict__ x, int ldx, int C, bf16_t* __restrict__ xp,
+                                                       int gpv, int64_t granules) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= granules) return;
+    const int64_t v = gpv == 1 ? i : i / gpv;
+    const int c0 = (int)(i - v * gpv) * 8;
+    const bf16_t* p = x + v * ldx + c0;
+    uint32_t r[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (c0 + e < C) r[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+    *reinterpret_cast<uint4*>(xp + i * 8) = make_uint4(r[0], r[1], r[2], r[3]);
+}
+// The padded tensor of x; false where x needs no padding.
+static bool pad_desc(const lamp_tensor_desc* xd, lamp_tensor_desc& xp) {
+    if (xd->dtype != LAMP_BF16 || (xd->c % 8 == 0 && xd->ldc % 8 == 0)) return false;
+    xp = *xd;
+    xp.c = xp.ldc = (xd->c + 7) / 8 * 8;
+    return true;
+}
+static size_t pad_bytes(const lamp_tensor_desc* xp) { return align_up((size_t)nvox(xp) * xp->c * 2); }
+static lamp_status launch_pad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* xp, void* out, hipStream_t s) {
+    const int64_t granules = nvox(xp) * (xp->c / 8);
+    hipLaunchKernelGGL(conv_pad_kernel, dim3(cdiv(granules, 256)), dim3(256), 0, s, (const bf16_t*)x, xd->ldc, xd->c, (bf16_t*)out,
+                       xp->c / 8, granules);
+    LAMP_CHECK_LAUNCH();
+    return LAMP_OK;
+}
+static bool has_norm(const lamp_norm_in* nm) { return nm && nm->mean_rstd && nm->c_norm > 0; }
+// The matrix-core kernels read the weights in 16-byte pieces.  Where the scalar kernels serve a channel count as well (they
+// take any alignment), a weight or workspace off 16 bytes goes to those; elsewhere it is the error it always was.
+static bool mfma_takes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, const void* w, const void* ws) {
+    return (xd->c % 16 == 0 && zd->c % 32 == 0) || (aligned16(w) && aligned16(ws));
+}
+
 template <bool DGRAD>
 static lamp_status launch_direct(const lamp_tensor_desc* xd, const void* x, NormIn nm, const void* w, const float* bias,
                                  const lamp_tensor_desc* zd, void* z, hipStream_t s) {
@@ -806,6 +846,8 @@ extern "C" size_t lamp_conv3d_fwd_workspace_bytes(const lamp_tensor_desc* xd, co
         const size_t c = cin1_tile_ws_bytes(zd);
         if (c > a) a = c;
     }
+    lamp_tensor_desc xp;
+    if (pad_desc(xd, xp) && mfma_conv_supported(&xp, zd, nullptr, nullptr)) b = pad_bytes(&xp) + mfma_conv_ws_bytes(&xp, zd, want_stats);
     return a > b ? a : b;
 }
 
@@ -820,13 +862,19 @@ extern "C" lamp_status lamp_conv3d_fwd(const lamp_tensor_desc* xd, const void* x
     if (ws_bytes < lamp_conv3d_fwd_workspace_bytes(xd, zd, stats_out != nullptr) || (ws_bytes && !ws))
         return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    if (mfma_conv_supported(xd, zd, xnorm, bias))
+    if (mfma_conv_supported(xd, zd, xnorm, bias) && mfma_takes(xd, zd, w, ws))
         return mfma_conv_fwd(xd, x, w, false, zd, z, stats_out, eps, ws, ws_bytes, s, nullptr, bias, xnorm);
     if (cin1_fwd_ok(xd, zd, xnorm, bias, z)) {
         if (cin1_tile_ok(zd)) return cin1_tile_fwd(xd, x, w, zd, z, stats_out, eps, ws, ws_bytes, s);
         hipLaunchKernelGGL(conv3d_cin1_fwd_kernel, dim3(cdiv(nvox(zd), 256)), dim3(256), 0, s, (const bf16_t*)x, xd->ldc,
                            (const bf16_t*)w, (bf16_t*)z, zd->ldc, zd->n, zd->d, zd->h, zd->w, zd->c);
         LAMP_CHECK_LAUNCH();
+    } else if (lamp_tensor_desc xp; !has_norm(xnorm) && pad_desc(xd, xp) && mfma_conv_supported(&xp, zd, nullptr, bias) &&
+                                    aligned16(w) && aligned16(ws)) {
+        const size_t pb = pad_bytes(&xp);
+        if ((st = launch_pad(xd, x, &xp, ws, s)) != LAMP_OK) return st;
+        return mfma_conv_fwd(&xp, ws, w, false, zd, z, stats_out, eps, (char*)ws + pb, ws_bytes - pb, s, nullptr, bias, nullptr, nullptr,
+                             xd->c);
     } else {
         st = launch_direct<false>(xd, x, make_norm(xnorm), w, bias, zd, z, s);
         if (st != LAMP_OK) return st;
@@ -837,6 +885,8 @@ extern "C" lamp_status lamp_conv3d_fwd(const lamp_tensor_desc* xd, const void* x
 
 extern "C" size_t lamp_conv3d_dgrad_workspace_bytes(const lamp_tensor_desc* dzd, const lamp_tensor_desc* dxd) {
     if (!desc_ok(dzd) || !desc_ok(dxd)) return 0;
+    lamp_tensor_desc zp;
+    if (pad_desc(dzd, zp) && mfma_conv_supported(&zp, dxd, nullptr, nullptr)) return pad_bytes(&zp) + mfma_conv_ws_bytes(&zp, dxd, 0);
     return mfma_conv_ws_bytes(dzd, dxd, 0);
 }
 
@@ -847,8 +897,15 @@ extern "C" lamp_status lamp_conv3d_dgrad(const lamp_tensor_desc* dzd, const void
     if (!w) return LAMP_ERR_NULL;
     if (ws_bytes < lamp_conv3d_dgrad_workspace_bytes(dzd, dxd) || (ws_bytes && !ws)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    if (mfma_conv_supported(dzd, dxd, nullptr, nullptr))
+    if (mfma_conv_supported(dzd, dxd, nullptr, nullptr) && mfma_takes(dzd, dxd, w, ws))
         return mfma_conv_fwd(dzd, dz, w, true, dxd, dx, nullptr, 0.f, ws, ws_bytes, s);
+    lamp_tensor_desc zp;
+    if (pad_desc(dzd, zp) && mfma_conv_supported(&zp, dxd, nullptr, nullptr) && aligned16(w) && aligned16(ws)) {
+        const size_t pb = pad_bytes(&zp);
+        if ((st = launch_pad(dzd, dz, &zp, ws, s)) != LAMP_OK) return st;
+        return mfma_conv_fwd(&zp, ws, w, true, dxd, dx, nullptr, 0.f, (char*)ws + pb, ws_bytes - pb, s, nullptr, nullptr, nullptr, nullptr,
+                             dzd->c);
+    }
     return launch_direct<true>(dzd, dz, make_norm(nullptr), w, nullptr, dxd, dx, s);
 }
 
@@ -907,6 +964,8 @@ extern "C" size_t lamp_conv3d_wgrad_workspace_bytes(const lamp_tensor_desc* xd, 
         const size_t e = cin1_wtile_ws_bytes(xd, dzd);
         if (e > a) a = e;
     }
+    lamp_tensor_desc xp;
+    if (pad_desc(xd, xp) && mfma_wgrad_supported(&xp, dzd, nullptr)) b = pad_bytes(&xp) + mfma_wgrad_ws_bytes(&xp, dzd);
     return (a > b ? a : b) + c;
 }
 
@@ -929,7 +988,8 @@ extern "C" lamp_status lamp_conv3d_wgrad(const lamp_tensor_desc* xd, const void*
     }
     ws = (char*)ws + cs;
     ws_bytes -= cs;
-    if (mfma_wgrad_supported(xd, dzd, xnorm)) return mfma_wgrad(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
+    if (mfma_wgrad_supported(xd, dzd, xnorm) && ((xd->c % 32 == 0 && dzd->c % 32 == 0) || aligned16(ws)))
+        return mfma_wgrad(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
     if (xd->dtype == LAMP_BF16 && xd->c == 1 && !(xnorm && xnorm->mean_rstd && xnorm->c_norm > 0) && cin1_wtile_ok(xd, dzd, dz))
         return cin1_wtile(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
     if (cin1_wgrad_ok(xd, dzd, xnorm)) {
@@ -940,6 +1000,12 @@ extern "C" lamp_status lamp_conv3d_wgrad(const lamp_tensor_desc* xd, const void*
                            (const bf16_t*)dz, dzd->ldc, (float*)ws, xd->n, xd->d, xd->h, xd->w, dzd->c, groups, gpw);
         LAMP_CHECK_LAUNCH();
         return launch_reduce_partials((const float*)ws, blocks * 4, (int64_t)dzd->c * 27, dw, beta, s);
+    }
+    lamp_tensor_desc xp;
+    if (!has_norm(xnorm) && pad_desc(xd, xp) && mfma_wgrad_supported(&xp, dzd, nullptr) && aligned16(ws)) {
+        const size_t pb = pad_bytes(&xp);
+        if ((st = launch_pad(xd, x, &xp, ws, s)) != LAMP_OK) return st;
+        return mfma_wgrad(&xp, ws, dzd, dz, dw, beta, (char*)ws + pb, ws_bytes - pb, s, nullptr, 0, xd->c);
     }
     const int64_t V = nvox(xd);
     const int S = wgrad_splits(V, O);

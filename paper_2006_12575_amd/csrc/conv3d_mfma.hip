@@ -85,7 +85,7 @@ __device__ __forceinline__ bf16x8 lds_frag(const char* p) {
 
 __global__ __launch_bounds__(256) void repack_weights_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp,
                                                              int Cout, int Cin, int dgrad, int bykh) {
-    repack_tile_gran(w, wp, (int64_t)blockIdx.x * 256 + threadIdx.x, Cout, Cin, Cout % 64 == 0 ? 64 : 32, dgrad, bykh);
+    repack_tile_gran(w, wp, (int64_t)blockIdx.x * 256 + threadIdx.x, Cout, Cin, conv_wrows(Cout), dgrad, bykh);
 }
 
 // All the repacks of a network pass in one launch: block -> job by the jobs' first-block table.
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void repack_batch_kernel(RepackBatch b) {
     while (k + 1 < b.n && (int)blockIdx.x >= b.j[k + 1].blk0) ++k;
     const RepackBatch::J& q = b.j[k];
     const int64_t i = (int64_t)((int)blockIdx.x - q.blk0) * 256 + threadIdx.x;
-    repack_tile_gran(q.w, q.wp, i, q.Cout, q.Cin, q.Cout % 64 == 0 ? 64 : 32, q.dgrad, q.kind);
+    repack_tile_gran(q.w, q.wp, i, q.Cout, q.Cin, conv_wrows(q.Cout), q.dgrad, q.kind);
 }
 
 lamp_status launch_repack_batch(const RepackJob* jobs, int n, hipStream_t s) {
@@ -111,7 +111,7 @@ lamp_status launch_repack_batch(const RepackJob* jobs, int n, hipStream_t s) {
         b.j[k].w = (const bf16_t*)jobs[k].w; b.j[k].wp = (bf16_t*)jobs[k].wp;
         b.j[k].Cout = jobs[k].Cout; b.j[k].Cin = jobs[k].Cin; b.j[k].dgrad = jobs[k].dgrad; b.j[k].kind = jobs[k].kind;
         b.j[k].blk0 = (int)blk;
-        blk += cdiv((int64_t)27 * jobs[k].Cout * jobs[k].Cin / 8, 256);
+        blk += cdiv(repack_elems(jobs[k].Cout, jobs[k].Cin) / 8, 256);
         if (blk >= ((int64_t)1 << 31)) return LAMP_ERR_SHAPE;
     }
     hipLaunchKernelGGL(repack_batch_kernel, dim3((unsigned)blk), dim3(256), 0, s, b);
@@ -323,18 +323,19 @@ struct CopyCtx {
     float relu_floor;
     int H, W, ldx;          // strides of the input tensor
     int wv, lane;
+    bool tail;              // the incoming chunk holds 8 channels only: its upper half comes from the zero source (RAG)
 };
 
 // One halo copy slot: 32 voxels, both halves of their 32 bytes (lanes 2i, 2i + 1 = voxel i).
 template <int TDT, bool LEAN>
 __device__ __forceinline__ void halo_copy_slot(int j, const HaloLane& hl, const HaloTile& ht, int H, int W, int ldx, int64_t choff,
-                                               const bf16_t* zero16, uint32_t hb_a, int wv, int lane) {
+                                               const bf16_t* zero16, uint32_t hb_a, int wv, int lane, bool tail) {
     typedef Geo<TDT> GE;
     const int blk = wv + 8 * j;
     if (blk < GE::HBLK && blk * 32 + (lane >> 1) < GE::HALO_VOX) {
         int hd, hh, hw, plane;
         hl.template coords<LEAN>(j, lane, hd, hh, hw, plane);
-        const bool in = hl.inside(j, ht);
+        const bool in = hl.inside(j, ht) && !(tail && plane);
         // ((hd*H + hh)*W + hw)*ldx with 24-bit multiply-adds (full rate, where a 32-bit multiply takes four passes):
         // hd*H + hh and W*ldx stay below 2^24 (checked on the host)
         const int rel = LEAN ? (int)(__umul24(__umul24(hd, H) + hh, W * ldx) + __umul24(hw, ldx) + plane * 8) : hl.rel[j];
@@ -378,7 +379,7 @@ __device__ __forceinline__ void copy_portion(const CopyCtx& c, const HaloLane& h
         if (c.pf_halo) {
 #pragma unroll
             for (int j = HF; j < HF + HC; ++j)
-                halo_copy_slot<TDT, (COB == 2 && TDT == 8)>(j, hl, ht, c.H, c.W, c.ldx, c.pf_choff, c.zero16, c.hb_next_a, c.wv, c.lane);
+                halo_copy_slot<TDT, (COB == 2 && TDT == 8)>(j, hl, ht, c.H, c.W, c.ldx, c.pf_choff, c.zero16, c.hb_next_a, c.wv, c.lane, c.tail);
         }
     }
 }
@@ -526,7 +527,13 @@ __device__ __forceinline__ void conv_group(f32x16 (&acc)[COB][Geo<TDT>::ND], Fra
 // SPLIT: the input-channel chunks are divided among gridDim.z workgroups per tile, each of which
 // writes its fp32 partial sums; a second kernel adds them in a fixed order.  For small volumes with
 // many channels, where the tiles alone cannot fill the chip.
-template <int COB, int TDT, bool SPLIT = false, bool NORM = false, bool BSUM = false>
+// RAG: channel counts that are multiples of 8 but not of 16 (input) or 32 (output).  The weights are padded with zero rows and
+// columns to whole chunks and blocks; the upper half of an 8-channel last chunk comes from the zero source like the
+// padding of the volume; 16-byte pieces of channels past the last one are neither stored nor summed.  A flag of its own,
+// so that the kernels of the common channel counts carry none of it.  Bound: matrix cores, of whose work the padded
+// share is lost (96->48 as 96->64: a quarter).  Conv unit 48->96 on 83 x 61 x 97 (forward, norm passes, data and weight
+// gradient): 60.2 -> 0.59 ms, of which the scalar kernels' data gradient took 9.8 and their weight gradient 50.3.
+template <int COB, int TDT, bool SPLIT = false, bool NORM = false, bool BSUM = false, bool RAG = false>
 __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
     typedef Geo<TDT> GE;
     typedef Lds<TDT, COB> LD;
@@ -543,7 +550,8 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
     const int l32 = lane & 31, half = lane >> 5;
     const int cbi = a.cb_inner ? (int)(blockIdx.x >> 3) % a.cb_inner : (int)blockIdx.y;   // output-channel block
     const int co0 = cbi * (32 * COB);
-    const int nchunks = a.Cin >> 4;
+    const int nchunks = RAG ? (a.Cin + 15) >> 4 : a.Cin >> 4;
+    auto tail = [&](int chunk) { return RAG && chunk * 16 + 8 >= a.Cin; };   // the chunk's upper 8 channels do not exist
     const int c_lo = SPLIT ? (int)blockIdx.z * a.cps : 0;
     const int c_hi = SPLIT ? min(c_lo + a.cps, nchunks) : nchunks;
     // element offset of a 16-channel chunk from channel 0 of the (first) input tensor
@@ -680,7 +688,7 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
     {
         const HaloTile t0 = ht_cur;
 #pragma unroll
-        for (int j = 0; j < HJ; ++j) halo_copy_slot<TDT, (COB == 2 && TDT == 8)>(j, hl, t0, a.H, a.W, a.ldx, choff(c_lo), a.zero16, lds_a, wv, lane);
+        for (int j = 0; j < HJ; ++j) halo_copy_slot<TDT, (COB == 2 && TDT == 8)>(j, hl, t0, a.H, a.W, a.ldx, choff(c_lo), a.zero16, lds_a, wv, lane, tail(c_lo));
         if constexpr (NORM) {
             if (wv == 0 && lane < 8)
                 g2lds16a(reinterpret_cast<const char*>(a.ab + (int64_t)pos.n * a.Cin + c_lo * 16) + lane * 16, tab_a);
@@ -706,7 +714,7 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
     // behind the next barrier that every wave has passed with its rows written.
     int pending_tile = -1, pending_count = 0;
     auto flush_sums = [&]() __attribute__((always_inline)) {
-        if (tid < WROWS * 2) {
+        if (tid < WROWS * 2 && (!RAG || co0 + (tid >> 1) < a.Cout)) {
             const float* sred = reinterpret_cast<const float*>(lds + LD::SUMS_OFF);
             const int c = tid >> 1, k = tid & 1;
             float v = 0.f;
@@ -747,6 +755,7 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
         cc.hb_next = hb_next; cc.hb_next_a = hb_next_a; cc.pf_halo = pf; cc.pf_choff = choff(pf_chunk); cc.zero16 = a.zero16;
         cc.abp = nullptr; cc.relu_floor = a.relu_floor; cc.wv = wv; cc.lane = lane;
         cc.tab = lds + LD::TAB_OFF; cc.tab_a = tab_a; cc.H = a.H; cc.W = a.W; cc.ldx = a.ldx;
+        cc.tail = tail(pf_chunk);
         if constexpr (NORM) {
             const int n_pf = last_chunk && next_tile < tile_hi ? pos_next.n : pos.n;
             cc.abp = a.ab + (int64_t)n_pf * a.Cin + pf_chunk * 16;
@@ -865,6 +874,7 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
         // stride, are fixed; the tile origin is wave-uniform; what is left per store is a small offset
         // inside the tile.  Tiles that lie inside the volume (all but the ragged rim) skip the bounds tests.
         const int ch = co0 + part * 8;
+        const bool chok = !RAG || ch < a.Cout;   // this lane's channels exist
         const bool second = ch >= a.zsplit;
         const int ldo = second ? a.ldz2 : a.ldz;
         const int hb0 = h0 + hs;
@@ -891,7 +901,9 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
             for (int cb = 0; cb < COB; ++cb)
 #pragma unroll
                 for (int rg = 0; rg < 4; ++rg) {
-                    const float4 bv = *reinterpret_cast<const float4*>(a.bias + co0 + cb * 32 + rg * 8 + half * 4);
+                    const int bc = co0 + cb * 32 + rg * 8 + half * 4;
+                    if (RAG && bc >= a.Cout) continue;
+                    const float4 bv = *reinterpret_cast<const float4*>(a.bias + bc);
 #pragma unroll
                     for (int vb = 0; vb < NVB; ++vb) {
                         acc[cb][vb][rg * 4 + 0] += bv.x; acc[cb][vb][rg * 4 + 1] += bv.y;
@@ -931,13 +943,13 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
                 for (int i = 0; i < 32 / RPI; ++i) {
                     const int row = prow + i * RPI;          // voxel index inside the 32-voxel block
                     qv[i] = *reinterpret_cast<const uint4*>(patch + row * ROWB + part * 16);
-                    bool ok = true;
+                    bool ok = chok;
                     if constexpr (!FULL) {
                         const int rg8 = row >> 3;
                         const int rw = (row & 7) + 8 * (rg8 >> 1), rh = 4 * ((rg8 ^ (rg8 >> 1)) & 1);
                         const int gd = gd0 + vb;
                         const int gh = hb0 + rh, gw = w0 + rw;
-                        ok = gd < a.D && gh < a.H && gw < a.W;
+                        ok = chok && gd < a.D && gh < a.H && gw < a.W;
                     }
                     if (ok) {
                         // streaming store: the output is not read again by this kernel and should not displace
@@ -1075,6 +1087,8 @@ static void tile_dims(const lamp_tensor_desc* t, int TD, int& td, int& th, int& 
     td = (t->d + TD - 1) / TD; th = (t->h + TH - 1) / TH; tw = (t->w + TW - 1) / TW;
 }
 
+// channel counts the tiled kernel serves with padding (RAG instantiations)
+static bool conv_ragged(int cin, int cout) { return cin % 16 || cout % 32; }
 struct PackPlan { int gh, gw, hp, wp; };
 static bool conv_pack_plan(const lamp_tensor_desc* zd, PackPlan& best);
 static int conv_splits(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd);
@@ -1083,7 +1097,7 @@ bool mfma_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd,
                          const float* bias) {
     if (xd->dtype != LAMP_BF16) return false;
     if (bias && (((uintptr_t)bias) & 15u)) return false;   // the epilogue reads it four floats at a time
-    if (xd->c % 16 || zd->c % 32 || xd->ldc % 8 || zd->ldc % 8) return false;
+    if (xd->c % 8 || zd->c % 8 || xd->ldc % 8 || zd->ldc % 8) return false;
     // element offsets inside a tile's halo (10 slices of H x W voxels) are kept in 32 bits
     const int64_t ldmax = xd->ldc > zd->ldc ? xd->ldc : zd->ldc;
     if ((int64_t)10 * zd->h * zd->w * ldmax >= ((int64_t)1 << 31)) return false;
@@ -1094,7 +1108,7 @@ bool mfma_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd,
         // normalise on load: every input channel normalised, on the plain tiled kernel (no packed batch of tiny
         // volumes, no input-channel split: those layers are small and keep the generic path)
         PackPlan pp;
-        if (xnorm->c_norm != xd->c || conv_pack_plan(zd, pp) || conv_splits(xd, zd) > 1) return false;
+        if (xnorm->c_norm != xd->c || conv_ragged(xd->c, zd->c) || conv_pack_plan(zd, pp) || conv_splits(xd, zd) > 1) return false;
     }
     return true;
 }
@@ -1111,7 +1125,7 @@ static int conv_tile_depth(const lamp_tensor_desc* zd) {
     // tile costs 1.9 four-deep ones.  (Measured on 15 layer shapes from 32^3 to 176 x 128 x 144 with 32 to 256
     // channels: the cheaper side of this comparison was the faster kernel on every one.)
     const int64_t hw = (int64_t)zd->n * ((zd->h + TH - 1) / TH) * ((zd->w + TW - 1) / TW);
-    const int64_t ncb = (zd->c + (zd->c % 64 == 0 ? 64 : 32) - 1) / (zd->c % 64 == 0 ? 64 : 32);
+    const int64_t ncb = (zd->c + conv_wrows(zd->c) - 1) / conv_wrows(zd->c);
     const int64_t rounds8 = (hw * ((zd->d + 7) / 8) * ncb + 255) / 256, rounds4 = (hw * ((zd->d + 3) / 4) * ncb + 255) / 256;
     return 19 * rounds8 <= 10 * rounds4 ? 8 : 4;
 }
@@ -1223,13 +1237,13 @@ int conv_repack_kind(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, boo
     return 1;   // one layout for both tile depths: tap groups by in-plane row kh
 }
 size_t conv_repack_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
-    return align_up((size_t)27 * xd->c * zd->c * 2 + 2 * xd->c + 64);
+    return align_up((size_t)repack_elems(zd->c, xd->c) * 2 + 2 * xd->c + 64);
 }
 
 // Number of input-channel splits for the tiled kernel (1 = none): only where the 4-deep tiling with 64
 // output channels per workgroup leaves at least half of the chip idle and there are chunks to share out.
 static int conv_splits(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
-    if (tune("no_split", 0) || zd->c % 64 || conv_tile_depth(zd) != 4) return 1;
+    if (tune("no_split", 0) || zd->c % 64 || xd->c % 16 || conv_tile_depth(zd) != 4) return 1;
     int td, th, tw;
     tile_dims(zd, 4, td, th, tw);
     const int64_t wgs = (int64_t)zd->n * td * th * tw * (zd->c / 64);
@@ -1249,7 +1263,7 @@ size_t mfma_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd
     tile_dims(zd, 4, td, th, tw);  // the finer tiling bounds the partial count
     const size_t tiles = (size_t)td * th * tw;
     // repacked weights + a run of zeros (source of the zero padding) + 16 bytes that absorb masked stores
-    size_t b = align_up((size_t)27 * xd->c * zd->c * 2 + 2 * xd->c + 64);
+    size_t b = conv_repack_bytes(xd, zd);
     if (want_stats) {
         // partial statistics: one per tile, or one per (sample, workgroup walk) -- at most 256 walks
         const size_t parts = tiles > 256 ? tiles : 256;
@@ -1268,11 +1282,11 @@ size_t mfma_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd
     return b + ab_bytes;
 }
 
-template <int COB, int TDT, bool SPLIT = false, bool NORM = false, bool BSUM = false>
+template <int COB, int TDT, bool SPLIT = false, bool NORM = false, bool BSUM = false, bool RAG = false>
 static lamp_status launch_igemm(const ConvArgs& a, dim3 grid, hipStream_t s) {
     const int shm = Lds<TDT, COB>::LDS_BYTES;
-    if (ensure_dyn_lds((const void*)conv3d_igemm_kernel<COB, TDT, SPLIT, NORM, BSUM>, shm) != LAMP_OK) return LAMP_ERR_HIP;
-    hipLaunchKernelGGL((conv3d_igemm_kernel<COB, TDT, SPLIT, NORM, BSUM>), grid, dim3(512), shm, s, a);
+    if (ensure_dyn_lds((const void*)conv3d_igemm_kernel<COB, TDT, SPLIT, NORM, BSUM, RAG>, shm) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL((conv3d_igemm_kernel<COB, TDT, SPLIT, NORM, BSUM, RAG>), grid, dim3(512), shm, s, a);
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }
@@ -1282,7 +1296,7 @@ static lamp_status launch_igemm(const ConvArgs& a, dim3 grid, hipStream_t s) {
 bool mfma_bsum_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
     if (tune("no_bsum", 0) || !mfma_conv_supported(xd, zd, nullptr, nullptr)) return false;
     PackPlan pp;
-    return !conv_pack_plan(zd, pp) && conv_splits(xd, zd) == 1;
+    return !conv_ragged(xd->c, zd->c) && !conv_pack_plan(zd, pp) && conv_splits(xd, zd) == 1;
 }
 size_t mfma_bsum_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
     return mfma_conv_ws_bytes(xd, zd, 1) + align_up((size_t)zd->n * zd->c * sizeof(float2));
@@ -1291,7 +1305,9 @@ size_t mfma_bsum_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd
 lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void* w, bool dgrad,
                           const lamp_tensor_desc* zd, void* z, float* stats_out, float eps, void* ws, size_t ws_bytes,
                           hipStream_t s, const ConvParts* parts, const float* bias, const lamp_norm_in* xnorm,
-                          const ConvBsum* bsum) {
+                          const ConvBsum* bsum, int wcin) {
+    if (!wcin) wcin = xd->c;
+    const bool rag = conv_ragged(xd->c, zd->c);
     const bool two_in = parts && parts->x2, two_out = parts && parts->z2;
     const bool norm = xnorm && xnorm->mean_rstd && xnorm->c_norm > 0;
     if (norm && (two_in || !mfma_conv_supported(xd, zd, xnorm, bias))) return LAMP_ERR_UNSUPPORTED;
@@ -1315,7 +1331,7 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
                            two_in ? (const bf16_t*)parts->x2 : (const bf16_t*)x, two_in ? parts->x_c1 : xd->c, xpk, xd->n, xd->d,
                            xd->h, xd->w, xd->c, pp.gw, pp.hp, pp.wp);
         LAMP_CHECK_LAUNCH();
-        lamp_status st = mfma_conv_fwd(&xp, xpk, w, dgrad, &zp, zpk, nullptr, 0.f, iws, inner, s, nullptr, bias);
+        lamp_status st = mfma_conv_fwd(&xp, xpk, w, dgrad, &zp, zpk, nullptr, 0.f, iws, inner, s, nullptr, bias, nullptr, nullptr, wcin);
         if (st != LAMP_OK) return st;
         hipLaunchKernelGGL(conv_unpack_kernel, dim3(zd->n, cdiv(zd->c, 64)), dim3(256), 0, s, zpk, (bf16_t*)z, zd->ldc, zd->n,
                            zd->d, zd->h, zd->w, zd->c, pp.gw, pp.hp, pp.wp, eps, stats_out);
@@ -1327,14 +1343,16 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
     tile_dims(zd, TDT, td, th, tw);
     const int tiles_per_n = td * th * tw;
     Carver cv(ws, ws_bytes);
-    bf16_t* wp = (bf16_t*)cv.take((size_t)27 * xd->c * zd->c * 2 + 16);
+    const int64_t wtotal = repack_elems(zd->c, xd->c);
+    bf16_t* wp = (bf16_t*)cv.take((size_t)wtotal * 2 + 16);
     float* part = nullptr;
     int32_t* counts = nullptr;
     // one persistent workgroup per CU (LDS-limited), 32 per XCD; fewer where there are fewer tiles
     int wgx = 256;
     while (wgx > 8 && (wgx / 8) > (tiles_per_n * zd->n + 7) / 8) wgx -= 8;
     // statistics per walk: 32-channel block, at least four tiles to a walk (below that the per-tile partials are as few)
-    const bool walk = stats_out && !bsum && zd->c % 64 != 0 && conv_splits(xd, zd) == 1 && !tune("no_walk_stats", 0) &&
+    const int cob = conv_wrows(zd->c) / 32;
+    const bool walk = stats_out && !bsum && cob == 1 && conv_splits(xd, zd) == 1 && !tune("no_walk_stats", 0) &&
                       (int64_t)tiles_per_n * zd->n >= 4 * wgx;
     if (stats_out) {
         const size_t parts = walk ? (size_t)wgx : (size_t)tiles_per_n;
@@ -1357,17 +1375,16 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
         hipLaunchKernelGGL(norm_coeff_kernel, dim3(cdiv((int64_t)xd->n * xd->c, 256)), dim3(256), 0, s, make_norm(xnorm), xd->n, xd->c, ab);
         LAMP_CHECK_LAUNCH();
     }
-    const int64_t wtotal = (int64_t)27 * xd->c * zd->c;
-    if (const bf16_t* pre = find_prepacked(w, dgrad, 1, zd->c, xd->c)) {
+    if (const bf16_t* pre = find_prepacked(w, dgrad, 1, zd->c, wcin)) {
         wp = const_cast<bf16_t*>(pre);
     } else {
-        hipLaunchKernelGGL(repack_weights_kernel, dim3(cdiv(wtotal / 8, 256)), dim3(256), 0, s, (const bf16_t*)w, wp, zd->c, xd->c,
+        hipLaunchKernelGGL(repack_weights_kernel, dim3(cdiv(wtotal / 8, 256)), dim3(256), 0, s, (const bf16_t*)w, wp, zd->c, wcin,
                            dgrad ? 1 : 0, 1);
         LAMP_CHECK_LAUNCH();
     }
     ConvArgs a;
     a.x = (const bf16_t*)x; a.ldx = xd->ldc; a.wp = wp; a.z = (bf16_t*)z; a.ldz = zd->ldc; a.part = part; a.counts = counts;
-    a.zero16 = wp + (size_t)27 * xd->c * zd->c;
+    a.zero16 = wp + wtotal;
     a.bias = bias;
     a.ab = norm ? ab : nullptr;
     a.zb = bsum ? (const bf16_t*)bsum->z : nullptr;
@@ -1377,9 +1394,8 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
     a.tiles_d = td; a.tiles_h = th; a.tiles_w = tw; a.tiles_per_n = tiles_per_n;
     a.tiles_total = tiles_per_n * zd->n;
     a.tiles_per_xcd = (a.tiles_total + 7) / 8;
-    const int cob = (zd->c % 64 == 0) ? 2 : 1;
     a.walk_parts = walk ? wgx : 0;
-    dim3 grid(wgx, zd->c / (32 * cob));
+    dim3 grid(wgx, cdiv(zd->c, 32 * cob));
     a.zpart = nullptr; a.cps = 0;
     a.xcd_rot = a.tiles_total < 32 ? 1 : 0;
     a.cb_inner = 0;
@@ -1412,7 +1428,10 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
         if (st != LAMP_OK) return st;
         return launch_bsum_finalize(part, tiles_per_n, zd->n, zd->c, bsum->stats, bsum->sums_out, s);
     }
-    if (norm) {
+    if (rag) {
+        if (TDT == 8) st = cob == 2 ? launch_igemm<2, 8, false, false, false, true>(a, grid, s) : launch_igemm<1, 8, false, false, false, true>(a, grid, s);
+        else st = cob == 2 ? launch_igemm<2, 4, false, false, false, true>(a, grid, s) : launch_igemm<1, 4, false, false, false, true>(a, grid, s);
+    } else if (norm) {
         if (TDT == 8) st = cob == 2 ? launch_igemm<2, 8, false, true>(a, grid, s) : launch_igemm<1, 8, false, true>(a, grid, s);
         else st = cob == 2 ? launch_igemm<2, 4, false, true>(a, grid, s) : launch_igemm<1, 4, false, true>(a, grid, s);
     } else if (TDT == 8) st = cob == 2 ? launch_igemm<2, 8>(a, grid, s) : launch_igemm<1, 8>(a, grid, s);
@@ -1454,6 +1473,7 @@ struct WgradArgs {
     int N, D, H, W, Cin, Cout;
     int tiles_d, tiles_h, tiles_w, tiles_per_n, tiles_total, tiles_per_wg;
     const bf16_t* x2; int xsplit;   // two-part x: input channels from xsplit on live in x2 (same channel stride)
+    int xc;             // channels of x in memory (a multiple of 8, >= Cin: a narrow x is padded with zeros)
 };
 
 __device__ __forceinline__ bf16x8 lds_frag_tr(const char* p) {
@@ -1632,7 +1652,8 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
         if (hv >= WX_VOX) hv = 0;
         const int hw = hv % WHW, hh = (hv / WHW) % WHH, hd = hv / (WHW * WHH);
         wl.xrel[i] = ((hd * a.H + hh) * a.W + hw) * a.ldx + cp * 8;
-        wl.xpk[i] = hd | (hh << 8) | (hw << 16);
+        // channels past the last one: a slice number no tile has, so that the copies take the zero source
+        wl.xpk[i] = (ci0 + cp * 8 < a.xc ? hd : 255) | (hh << 8) | (hw << 16);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1640,7 +1661,7 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
         const int hf = q / 16, vx = (q % 16) * 16 + cv;   // (for COB == 1 only q < 16 is used: hf = 0)
         const int w = vx % WTW, h = (vx / WTW) % WTH, d = vx / (WTW * WTH);
         wl.zrel[i] = ((d * a.H + h) * a.W + w) * a.lddz + hf * 32 + cp * 8;
-        wl.zpk[i] = d | (h << 8) | (w << 16);
+        wl.zpk[i] = (co0 + hf * 32 + cp * 8 < a.Cout ? d : 255) | (h << 8) | (w << 16);
     }
     // tiles are numbered d-fastest: consecutive tiles of a workgroup's walk share two of their four halo
     // d-slices, which the second one then finds in the XCD's L2
@@ -1673,15 +1694,16 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
     };
     auto run_tile = [&](bool pf, const char* st, char* st_next) {
         const int n = fn, d0 = fd0, h0 = fh0, w0 = fw0;
+        const int dhi = min(a.D - d0, 254);   // below the slice number of missing channels
         // (voxel indices fit 32 bits: checked on the host)
         const bf16_t* xorg = xpart + (int64_t)(((n * a.D + (d0 - 1)) * a.H + (h0 - 1)) * a.W + (w0 - 1)) * a.ldx;
         const bf16_t* zorg = a.dz + (int64_t)(((n * a.D + d0) * a.H + h0) * a.W + w0) * a.lddz + co0;
         if (has4)
-            wgrad_tile<COB, 4>(acc, fr, st, st_next, pf, wl, xorg, zorg, 1 - d0, a.D - d0, 1 - h0, a.H - h0, 1 - w0, a.W - w0,
-                               a.D - d0, a.H - h0, a.W - w0, a.zero16, coloff, extoff, loff, wv);
+            wgrad_tile<COB, 4>(acc, fr, st, st_next, pf, wl, xorg, zorg, 1 - d0, dhi, 1 - h0, a.H - h0, 1 - w0, a.W - w0,
+                               dhi, a.H - h0, a.W - w0, a.zero16, coloff, extoff, loff, wv);
         else
-            wgrad_tile<COB, 3>(acc, fr, st, st_next, pf, wl, xorg, zorg, 1 - d0, a.D - d0, 1 - h0, a.H - h0, 1 - w0, a.W - w0,
-                               a.D - d0, a.H - h0, a.W - w0, a.zero16, coloff, extoff, loff, wv);
+            wgrad_tile<COB, 3>(acc, fr, st, st_next, pf, wl, xorg, zorg, 1 - d0, dhi, 1 - h0, a.H - h0, 1 - w0, a.W - w0,
+                               dhi, a.H - h0, a.W - w0, a.zero16, coloff, extoff, loff, wv);
     };
 
     if (tile_lo < tile_hi) {
@@ -1689,6 +1711,7 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
         // only the copies are wanted here, so issue them directly)
         int n, d0, h0, w0;
         tile_coords(tile_lo, n, d0, h0, w0);
+        const int dhi = min(a.D - d0, 254);
         const bf16_t* xorg = xpart + ((((int64_t)n * a.D + (d0 - 1)) * a.H + (h0 - 1)) * a.W + (w0 - 1)) * a.ldx;
         const bf16_t* zorg = a.dz + ((((int64_t)n * a.D + d0) * a.H + h0) * a.W + w0) * a.lddz + co0;
 #pragma unroll
@@ -1697,7 +1720,7 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
             if (q < WX_VOX / 16) {
                 const int pk = wl.xpk[i];
                 const int hd = pk & 255, hh = (pk >> 8) & 255, hw = pk >> 16;
-                const bool in = hd >= 1 - d0 && hd <= a.D - d0 && hh >= 1 - h0 && hh <= a.H - h0 && hw >= 1 - w0 && hw <= a.W - w0;
+                const bool in = hd >= 1 - d0 && hd <= dhi && hh >= 1 - h0 && hh <= a.H - h0 && hw >= 1 - w0 && hw <= a.W - w0;
                 g2lds16(in ? xorg + wl.xrel[i] : a.zero16, lds + q * 1024);
             }
         }
@@ -1705,7 +1728,7 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
         for (int i = 0; i < COB * WTILE_VOX / 128; ++i) {
             const int q = wv + 8 * i;
             const int pk = wl.zpk[i];
-            const bool in = (pk & 255) < a.D - d0 && ((pk >> 8) & 255) < a.H - h0 && (pk >> 16) < a.W - w0;
+            const bool in = (pk & 255) < dhi && ((pk >> 8) & 255) < a.H - h0 && (pk >> 16) < a.W - w0;
             g2lds16(in ? zorg + wl.zrel[i] : a.zero16, lds + WX_BYTES + q * 1024);
         }
     }
@@ -1733,7 +1756,7 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int co = co0 + cb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    pb[((int64_t)co * 27 + t) * a.Cin + ci0 + l32] = acc[cb][i][r];
+                    if (co < a.Cout && ci0 + l32 < a.Cin) pb[((int64_t)co * 27 + t) * a.Cin + ci0 + l32] = acc[cb][i][r];
                 }
         }
     }
@@ -1747,8 +1770,8 @@ static int wgrad_slots(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) 
     int td, th, tw;
     wtile_dims(xd, td, th, tw);
     const int64_t tiles = (int64_t)td * th * tw * xd->n;
-    const int cob = (dzd->c % 64 == 0) ? 2 : 1;
-    const int types = (xd->c / 32) * (dzd->c / (32 * cob));
+    const int cob = conv_wrows(dzd->c) / 32;
+    const int types = cdiv(xd->c, 32) * cdiv(dzd->c, 32 * cob);
     int64_t s = 256 / types;
     if (s < 1) s = 1;
     if (s >= 8) s = s / 8 * 8;  // keep the types of one tile range on one XCD
@@ -1759,7 +1782,7 @@ static int wgrad_slots(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) 
 bool mfma_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, const lamp_norm_in* xnorm) {
     if (xd->dtype != LAMP_BF16) return false;
     if (xnorm && xnorm->mean_rstd && xnorm->c_norm > 0) return false;
-    if (xd->c % 32 || dzd->c % 32 || xd->ldc % 8 || dzd->ldc % 8) return false;
+    if (xd->c % 8 || dzd->c % 8 || xd->ldc % 8 || dzd->ldc % 8) return false;
     // element offsets inside a tile's halo (4 slices of H x W voxels) are kept in 32 bits
     const int64_t ldmax = xd->ldc > dzd->ldc ? xd->ldc : dzd->ldc;
     if ((int64_t)4 * xd->h * xd->w * ldmax + 4096 >= ((int64_t)1 << 31)) return false;
@@ -1787,7 +1810,8 @@ size_t mfma_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* d
 
 
 lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dzd, const void* dz, float* dw,
-                       float beta, void* ws, size_t ws_bytes, hipStream_t s, const void* x2, int x_c1) {
+                       float beta, void* ws, size_t ws_bytes, hipStream_t s, const void* x2, int x_c1, int wcin) {
+    if (!wcin) wcin = xd->c;
     if ((((uintptr_t)x) & 15u) || (((uintptr_t)dz) & 15u) || (((uintptr_t)ws) & 15u)) return LAMP_ERR_ALIGN;
     if (x2 && ((((uintptr_t)x2) & 15u) || x_c1 % 32 || x_c1 <= 0 || x_c1 >= xd->c)) return LAMP_ERR_ALIGN;
     if (ws_bytes < mfma_wgrad_ws_bytes(xd, dzd)) return LAMP_ERR_WORKSPACE;
@@ -1809,12 +1833,12 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
         hipLaunchKernelGGL(conv_pack_kernel, dim3(cdiv(gz, 256)), dim3(256), 0, s, (const bf16_t*)dz, dzd->ldc, (const bf16_t*)dz,
                            dzd->c, zpk, dzd->n, dzd->d, dzd->h, dzd->w, dzd->c, pp.gw, pp.hp, pp.wp);
         LAMP_CHECK_LAUNCH();
-        return mfma_wgrad(&xp, xpk, &zp, zpk, dw, beta, iws, inner, s, nullptr, 0);
+        return mfma_wgrad(&xp, xpk, &zp, zpk, dw, beta, iws, inner, s, nullptr, 0, wcin);
     }
     WgradArgs a;
     a.x = (const bf16_t*)x; a.ldx = xd->ldc; a.dz = (const bf16_t*)dz; a.lddz = dzd->ldc; a.part = (float*)ws;
     a.x2 = (const bf16_t*)x2; a.xsplit = x2 ? x_c1 : 0x7fffffff;
-    a.N = xd->n; a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Cin = xd->c; a.Cout = dzd->c;
+    a.N = xd->n; a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Cin = wcin; a.xc = xd->c; a.Cout = dzd->c;
     wtile_dims(xd, a.tiles_d, a.tiles_h, a.tiles_w);
     a.tiles_per_n = a.tiles_d * a.tiles_h * a.tiles_w;
     a.tiles_total = a.tiles_per_n * xd->n;
@@ -1826,8 +1850,8 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
     if (direct) a.part = dw;
     a.zero16 = device_zero16();
     if (!a.zero16) return LAMP_ERR_HIP;
-    const int cob = (dzd->c % 64 == 0) ? 2 : 1;
-    dim3 grid(S, xd->c / 32, dzd->c / (32 * cob));
+    const int cob = conv_wrows(dzd->c) / 32;
+    dim3 grid(S, cdiv(xd->c, 32), cdiv(dzd->c, 32 * cob));
     if (cob == 2) {
         if (ensure_dyn_lds((const void*)conv3d_wgrad_kernel<2>, WG_LDS_BYTES) != LAMP_OK) return LAMP_ERR_HIP;
         hipLaunchKernelGGL((conv3d_wgrad_kernel<2>), grid, dim3(512), WG_LDS_BYTES, s, a);
@@ -1837,7 +1861,7 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
     }
     LAMP_CHECK_LAUNCH();
     if (direct) return LAMP_OK;
-    return launch_reduce_partials((const float*)ws, S, (int64_t)dzd->c * 27 * xd->c, dw, beta, s);
+    return launch_reduce_partials((const float*)ws, S, (int64_t)dzd->c * 27 * wcin, dw, beta, s);
 }
 
 }  // namespace lamp

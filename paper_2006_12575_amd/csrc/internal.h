@@ -75,6 +75,7 @@ lamp_status head_ce_run(const lamp_tensor_desc* xd, const void* x, const lamp_no
 // the 2x2x2 max-pool of the result: writes the activated tensor to yfull (channel stride ldyf) and the pooled one to y.
 lamp_status inorm_relu_maxpool2(const lamp_tensor_desc* xd, const void* z, const lamp_norm_in* xnorm, void* yfull, int ldyf,
                                 const lamp_tensor_desc* yd, void* y, hipStream_t s);
+// wcin of the calls below: the weight's input channels where x holds more (a narrow x padded with zero channels); 0: x's.
 bool mfma_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, const lamp_norm_in* xnorm,
                          const float* bias);
 size_t mfma_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, int want_stats);
@@ -92,12 +93,12 @@ size_t mfma_bsum_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd
 lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void* w, bool dgrad,
                           const lamp_tensor_desc* zd, void* z, float* stats_out, float eps,
                           void* ws, size_t ws_bytes, hipStream_t s, const ConvParts* parts = nullptr,
-                          const float* bias = nullptr, const lamp_norm_in* xnorm = nullptr, const ConvBsum* bsum = nullptr);
+                          const float* bias = nullptr, const lamp_norm_in* xnorm = nullptr, const ConvBsum* bsum = nullptr, int wcin = 0);
 bool mfma_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, const lamp_norm_in* xnorm);
 size_t mfma_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd);
 lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dzd, const void* dz,
                        float* dw, float beta, void* ws, size_t ws_bytes, hipStream_t s, const void* x2 = nullptr,
-                       int x_c1 = 0);
+                       int x_c1 = 0, int wcin = 0);
 
 // ---- convtr_mfma.hip ------------------------------------------------------------------------
 bool mfma_convtr_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* yd, const lamp_norm_in* xnorm);

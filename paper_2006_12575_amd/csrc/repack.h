@@ -5,6 +5,14 @@
 
 namespace lamp {
 
+// Output channels a workgroup of the tiled kernel covers: 64 where the 32-channel blocks pair up, else 32.
+__host__ __device__ inline int conv_wrows(int Cout) { return ((Cout + 31) / 32) % 2 == 0 ? 64 : 32; }
+// Elements of the repacked weights: input channels in whole chunks of 16, output channels in whole blocks.
+__host__ __device__ inline int64_t repack_elems(int Cout, int Cin) {
+    const int r = conv_wrows(Cout);
+    return (int64_t)27 * ((Cin + 15) / 16 * 16) * ((Cout + r - 1) / r * r);
+}
+
 // One thread moves one granule of 8 consecutive input channels (16 bytes) of the repacked layout.
 // Forward: the granule is contiguous in W as well (one 16-byte load).  Data gradient: its 8 elements
 // come from 8 rows of W; the threads are numbered with the output channel fastest, which is the
@@ -22,13 +30,14 @@ __device__ __forceinline__ uint4 repack_gather8(const bf16_t* __restrict__ p, in
 // gathered 64 pieces of 16 bytes from 64 rows, and for many input channels those rows no longer stayed in
 // L2).  Tap of (g, t9): kd = g, (kh, kw) = (t9/3, t9%3); bykh (8-deep tile, taps walked kh-major): kh = g,
 // (kd, kw) = (t9/3, t9%3).  Values: forward W[oc][tap][ic], data gradient W[ic][26-tap][oc].
-// 16 zero bytes behind the weights are the source of the zero padding.  g: granule index, Cin % 16 == 0.
+// Channel counts that do not fill the last chunk or block are padded with zeros there.
+// 16 zero bytes behind the weights are the source of the zero padding.  g: granule index.
 __device__ __forceinline__ void repack_tile_gran(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int64_t g, int Cout,
                                                  int Cin, int wrows, int dgrad, int bykh) {
-    const int64_t total = (int64_t)27 * Cout * Cin;
+    const int64_t total = repack_elems(Cout, Cin);
     if (g == 0) *reinterpret_cast<uint4*>(wp + total) = make_uint4(0, 0, 0, 0);
     if (g >= total / 8) return;
-    const int nchunks = Cin >> 4;
+    const int nchunks = (Cin + 15) >> 4;
     int64_t r = g;
     const int row = (int)(r % wrows); r /= wrows;
     const int plane = (int)(r % 2); r /= 2;
@@ -38,8 +47,14 @@ __device__ __forceinline__ void repack_tile_gran(const bf16_t* __restrict__ w, b
     const int blk = (int)(r / nchunks);
     const int oc = blk * wrows + row, ic0 = chunk * 16 + plane * 8;
     const int t = bykh ? (t9 / 3) * 9 + grp * 3 + (t9 % 3) : grp * 9 + t9;
-    uint4 v;
-    if (!dgrad) v = *reinterpret_cast<const uint4*>(w + ((int64_t)oc * 27 + t) * Cin + ic0);
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (oc >= Cout || ic0 >= Cin) {
+    } else if (ic0 + 8 > Cin || (!dgrad && Cin % 8)) {   // a granule cut short, or rows without 16-byte alignment
+        uint32_t q[4] = {0, 0, 0, 0};
+        for (int e = 0; e < 8 && ic0 + e < Cin; ++e)
+            q[e >> 1] |= (uint32_t)(dgrad ? w[((int64_t)(ic0 + e) * 27 + (26 - t)) * Cout + oc] : w[((int64_t)oc * 27 + t) * Cin + ic0 + e]) << (16 * (e & 1));
+        v = make_uint4(q[0], q[1], q[2], q[3]);
+    } else if (!dgrad) v = *reinterpret_cast<const uint4*>(w + ((int64_t)oc * 27 + t) * Cin + ic0);
     else v = repack_gather8(w + ((int64_t)ic0 * 27 + (26 - t)) * Cout + oc, (int64_t)27 * Cout);
     *reinterpret_cast<uint4*>(wp + g * 8) = v;
 }

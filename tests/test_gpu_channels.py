@@ -1,0 +1,109 @@
+"""Channel counts that do not fill the matrix-core kernels' chunks of 16 and blocks of 32: every conv pass against the
+CPU oracle, on both tile depths, both block widths, with bias, statistics, channel slices and accumulation."""
+import numpy as np
+import pytest
+import torch
+
+import lamp_synth as S
+import oracle as O
+from gpu_util import DEV, as64, check, to_dev
+
+pytestmark = pytest.mark.gpu
+
+BF, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.fixture(scope="module")
+def L():
+    import paper_2006_12575_amd as L
+    L.lib()
+    return L
+
+
+def rng(seed):
+    return np.random.Generator(np.random.PCG64(seed))
+
+
+def conv_passes(L, dtype, shape, seed, wgrad_tol, dgrad=True):
+    """Forward (bias, statistics, into a slice of a wider buffer), data gradient, weight gradient (from slices, beta 0 and
+    1) of one shape; inputs sit in wider buffers whose other channels are NaN, so that a read past the slice shows."""
+    N, D, H, W, Ci, Co = shape
+    r = rng(seed + sum(shape))
+    nan = float("nan")
+
+    def sliced(c, ref=None):   # c channels behind 8 others, 8 more behind them
+        buf = torch.full((N, D, H, W, c + 16), nan, dtype=dtype, device=DEV)
+        if ref is not None:
+            buf[..., 8:8 + c] = to_dev(ref, dtype)
+        return buf, buf[..., 8:8 + c]
+
+    _, x = sliced(Ci, S.normal(r, (N, D, H, W, Ci)) + 0.25)
+    w = to_dev(S.kaiming_conv(r, Co, Ci), dtype)
+    b = to_dev(S.normal(r, (Co,), 0.1), F32)
+    zbuf, z = sliced(Co)
+    stats = torch.full((N, Co, 2), nan, dtype=F32, device=DEV)
+    L.lamp_conv3d_fwd(x, w, z, bias=b, stats_out=stats)
+    check(as64(z), O.conv3d_fwd(as64(x), as64(w), as64(b)), dtype, "conv fwd")
+    assert torch.isnan(zbuf[..., :8]).all() and torch.isnan(zbuf[..., 8 + Co:]).all(), "wrote outside the channel slice"
+    _, st_ref = O.inorm_relu(as64(z))
+    check(as64(stats)[..., 0], st_ref[..., 0], F32, "stats mean", tol=1e-4)
+    if D * H * W > 1:
+        np.testing.assert_allclose(as64(stats)[..., 1], st_ref[..., 1], rtol=2e-4)
+    z2 = torch.empty((N, D, H, W, Co), dtype=dtype, device=DEV)
+    L.lamp_conv3d_fwd(x.contiguous(), w, z2, bias=b)
+    assert torch.equal(z2, z)
+    _, dz = sliced(Co, S.normal(r, (N, D, H, W, Co)))
+    if dgrad:
+        dxbuf, dx = sliced(Ci)
+        L.lamp_conv3d_dgrad(dz, w, dx)
+        check(as64(dx), O.conv3d_dgrad(as64(dz), as64(w)), dtype, "conv dgrad")
+        assert torch.isnan(dxbuf[..., :8]).all() and torch.isnan(dxbuf[..., 8 + Ci:]).all(), "wrote outside the channel slice"
+    dw = torch.full((Co, 3, 3, 3, Ci), nan, dtype=F32, device=DEV)
+    db = torch.full((Co,), nan, dtype=F32, device=DEV)
+    L.lamp_conv3d_wgrad(x, dz, dw, dbias=db)
+    dw_ref, db_ref = O.conv3d_wgrad(as64(x), as64(dz), want_db=True)
+    check(as64(dw), dw_ref, dtype, "conv wgrad", tol=wgrad_tol)
+    check(as64(db), db_ref, dtype, "conv dbias", tol=1e-4)
+    L.lamp_conv3d_wgrad(x, dz, dw, dbias=db, beta=1.0)
+    check(as64(dw), 2 * dw_ref, dtype, "conv wgrad beta=1", tol=wgrad_tol)
+
+
+# bf16 tolerances: one rounding to storage (1e-2 as everywhere, 2e-3 for the fp32 weight gradient of bf16 inputs)
+@pytest.mark.parametrize("shape", [
+    (1, 9, 10, 18, 8, 8),        # one half chunk, a quarter of a block
+    (2, 5, 9, 17, 24, 40),       # half a last chunk; 40 = 64-wide block with 24 channels missing
+    (1, 6, 17, 20, 48, 96),      # whole chunks, three 32-wide blocks; data gradient with 48 outputs
+    (2, 8, 8, 16, 16, 72),       # three blocks, the last with 8 channels
+    (1, 3, 5, 7, 104, 120),
+    (6, 4, 4, 4, 24, 40),        # batch of tiny volumes in the packed layout
+    (1, 260, 3, 5, 8, 16),       # more slices than the missing-channel mark of the weight gradient's copies
+    (1, 64, 64, 64, 24, 24),     # 8-deep tile, 32-wide block
+    (1, 64, 64, 60, 16, 48),     # 8-deep tile, 64-wide block
+    (2, 64, 96, 112, 8, 24),     # statistics partials per walk
+    (1, 1, 1, 1, 40, 8),
+], ids=lambda s: "x".join(map(str, s)))
+def test_conv3d_ragged_channels_bf16(L, shape):
+    conv_passes(L, BF, shape, 2100, 2e-3)
+
+
+@pytest.mark.parametrize("shape", [(1, 6, 9, 33, 2, 16), (2, 5, 6, 7, 3, 24), (1, 7, 9, 16, 12, 64), (1, 5, 6, 9, 4, 32),
+                                   (5, 4, 4, 4, 20, 32), (1, 4, 5, 6, 1, 40)], ids=lambda s: "x".join(map(str, s)))
+def test_conv3d_narrow_input_bf16(L, shape):
+    """Input channels that fill no 16-byte piece: padded with zero channels in the workspace."""
+    conv_passes(L, BF, shape, 2200, 2e-3)
+
+
+def test_conv3d_ragged_channels_unaligned_weights(L):
+    """Channel counts outside 16 / 32 take weights at any alignment (the scalar kernels read them)."""
+    r = rng(2300)
+    x = to_dev(S.normal(r, (1, 4, 5, 9, 24)), BF)
+    wh = to_dev(S.kaiming_conv(r, 40, 24), BF)
+    flat = torch.empty(wh.numel() + 1, dtype=BF, device=DEV)
+    flat[1:] = wh.reshape(-1)
+    w = flat[1:].view(wh.shape)
+    z = torch.empty((1, 4, 5, 9, 40), dtype=BF, device=DEV)
+    L.lamp_conv3d_fwd(x, w, z)
+    check(as64(z), O.conv3d_fwd(as64(x), as64(wh)), BF, "conv fwd")
+    dx = torch.empty_like(x)
+    L.lamp_conv3d_dgrad(z, w, dx)
+    check(as64(dx), O.conv3d_dgrad(as64(z), as64(wh)), BF, "conv dgrad")
