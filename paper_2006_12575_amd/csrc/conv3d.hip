@@ -1,6 +1,6 @@
 // 3x3x3 convolution: public entry points, argument checking, kernel selection, and the generic
-// direct kernels (any dtype / channel count) that serve the fp32 path and odd channel counts.
-// Shapes with channel counts in multiples of 32 in bf16 go to the matrix-core kernels.
+// direct kernels (any dtype / channel count) behind the matrix-core ones: bf16 odd channel counts and normalise-on-load of a
+// part of the channels, fp32 past the limits of conv3d_f32.hip.
 #include "internal.h"
 #include "vec.h"
 
@@ -620,8 +620,7 @@ static lamp_status check_conv_pair(const lamp_tensor_desc* a, const void* pa, co
     return LAMP_OK;
 }
 
-// The same sum with register tiling, for channel counts that are small multiples of 8 (the fp32 path of small
-// nets): a thread owns OCG output channels of one voxel; the weights of a chunk of 8 input channels sit in
+// The same sum with register tiling, for output channels in multiples of 8 (bf16 weights off 16 bytes): a thread owns OCG output channels of one voxel; the weights of a chunk of 8 input channels sit in
 // LDS as [tap][ic][oc] (every lane of a wave reads the same few addresses), the input voxel is read once per
 // (tap, ic) and used OCG times.  Input-channel chunks are taken in order, taps inside a chunk: a fixed order.
 template <typename T, bool DGRAD, int OCG>
@@ -804,19 +803,15 @@ template <bool DGRAD>
 static lamp_status launch_direct(const lamp_tensor_desc* xd, const void* x, NormIn nm, const void* w, const float* bias,
                                  const lamp_tensor_desc* zd, void* z, hipStream_t s) {
     const int Cout = zd->c, Cin = xd->c;
-    if (!nm.mean_rstd && Cout % 8 == 0 && Cout <= 64) {
+    if (xd->dtype == LAMP_BF16 && !nm.mean_rstd && Cout % 8 == 0 && Cout <= 64) {
         const int G = Cout / 8, vpb = 256 / G;
         const size_t shm = (size_t)27 * 8 * Cout * sizeof(float);   // at most 55 KB
         const dim3 grid(cdiv(nvox(zd), vpb));
         // 16-byte loads of a voxel's 8-channel chunk need aligned rows
         const int xvec = aligned16(x) && (xd->ldc * esize(xd->dtype)) % 16 == 0 ? 1 : 0;
         const int wvec = aligned16(w) && ((DGRAD ? Cout : Cin) * esize(xd->dtype)) % 16 == 0 ? 1 : 0;
-        if (xd->dtype == LAMP_BF16)
-            hipLaunchKernelGGL((conv3d_regtile_kernel<bf16_t, DGRAD, 8>), grid, dim3(256), shm, s, (const bf16_t*)x, xd->ldc,
-                               (const bf16_t*)w, bias, (bf16_t*)z, zd->ldc, zd->n, zd->d, zd->h, zd->w, Cin, Cout, xvec, wvec);
-        else
-            hipLaunchKernelGGL((conv3d_regtile_kernel<float, DGRAD, 8>), grid, dim3(256), shm, s, (const float*)x, xd->ldc,
-                               (const float*)w, bias, (float*)z, zd->ldc, zd->n, zd->d, zd->h, zd->w, Cin, Cout, xvec, wvec);
+        hipLaunchKernelGGL((conv3d_regtile_kernel<bf16_t, DGRAD, 8>), grid, dim3(256), shm, s, (const bf16_t*)x, xd->ldc,
+                           (const bf16_t*)w, bias, (bf16_t*)z, zd->ldc, zd->n, zd->d, zd->h, zd->w, Cin, Cout, xvec, wvec);
         LAMP_CHECK_LAUNCH();
         return LAMP_OK;
     }
@@ -846,6 +841,7 @@ extern "C" size_t lamp_conv3d_fwd_workspace_bytes(const lamp_tensor_desc* xd, co
         const size_t c = cin1_tile_ws_bytes(zd);
         if (c > a) a = c;
     }
+    if (f32_conv_supported(xd, zd)) b = f32_conv_ws_bytes(zd, want_stats);
     lamp_tensor_desc xp;
     if (pad_desc(xd, xp) && mfma_conv_supported(&xp, zd, nullptr, nullptr)) b = pad_bytes(&xp) + mfma_conv_ws_bytes(&xp, zd, want_stats);
     return a > b ? a : b;
@@ -864,6 +860,8 @@ extern "C" lamp_status lamp_conv3d_fwd(const lamp_tensor_desc* xd, const void* x
     hipStream_t s = (hipStream_t)stream;
     if (mfma_conv_supported(xd, zd, xnorm, bias) && mfma_takes(xd, zd, w, ws))
         return mfma_conv_fwd(xd, x, w, false, zd, z, stats_out, eps, ws, ws_bytes, s, nullptr, bias, xnorm);
+    if (f32_conv_supported(xd, zd))
+        return f32_conv(xd, (const float*)x, make_norm(xnorm), (const float*)w, bias, false, zd, (float*)z, stats_out, eps, ws, ws_bytes, s);
     if (cin1_fwd_ok(xd, zd, xnorm, bias, z)) {
         if (cin1_tile_ok(zd)) return cin1_tile_fwd(xd, x, w, zd, z, stats_out, eps, ws, ws_bytes, s);
         hipLaunchKernelGGL(conv3d_cin1_fwd_kernel, dim3(cdiv(nvox(zd), 256)), dim3(256), 0, s, (const bf16_t*)x, xd->ldc,
@@ -899,6 +897,8 @@ extern "C" lamp_status lamp_conv3d_dgrad(const lamp_tensor_desc* dzd, const void
     hipStream_t s = (hipStream_t)stream;
     if (mfma_conv_supported(dzd, dxd, nullptr, nullptr) && mfma_takes(dzd, dxd, w, ws))
         return mfma_conv_fwd(dzd, dz, w, true, dxd, dx, nullptr, 0.f, ws, ws_bytes, s);
+    if (f32_conv_supported(dzd, dxd))
+        return f32_conv(dzd, (const float*)dz, make_norm(nullptr), (const float*)w, nullptr, true, dxd, (float*)dx, nullptr, 0.f, nullptr, 0, s);
     lamp_tensor_desc zp;
     if (pad_desc(dzd, zp) && mfma_conv_supported(&zp, dxd, nullptr, nullptr) && aligned16(w) && aligned16(ws)) {
         const size_t pb = pad_bytes(&zp);
@@ -955,6 +955,7 @@ extern "C" size_t lamp_conv3d_wgrad_workspace_bytes(const lamp_tensor_desc* xd, 
     const int64_t O = (int64_t)dzd->c * 27 * xd->c;
     size_t a = align_up((size_t)wgrad_splits(nvox(xd), O) * O * sizeof(float));
     size_t b = mfma_wgrad_ws_bytes(xd, dzd);
+    if (f32_wgrad_supported(xd, dzd)) b = f32_wgrad_ws_bytes(xd, dzd);
     size_t c = colsum_ws_bytes(nvox(dzd), dzd->c);
     if (cin1_wgrad_ok(xd, dzd, nullptr)) {
         const size_t e = align_up((size_t)cin1_wgrad_blocks(nvox(xd)) * 4 * dzd->c * 27 * sizeof(float));
@@ -990,6 +991,8 @@ extern "C" lamp_status lamp_conv3d_wgrad(const lamp_tensor_desc* xd, const void*
     ws_bytes -= cs;
     if (mfma_wgrad_supported(xd, dzd, xnorm) && ((xd->c % 32 == 0 && dzd->c % 32 == 0) || aligned16(ws)))
         return mfma_wgrad(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
+    if (f32_wgrad_supported(xd, dzd))
+        return f32_wgrad(xd, (const float*)x, make_norm(xnorm), dzd, (const float*)dz, dw, beta, ws, ws_bytes, s);
     if (xd->dtype == LAMP_BF16 && xd->c == 1 && !(xnorm && xnorm->mean_rstd && xnorm->c_norm > 0) && cin1_wtile_ok(xd, dzd, dz))
         return cin1_wtile(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
     if (cin1_wgrad_ok(xd, dzd, xnorm)) {

@@ -100,6 +100,18 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
                        float* dw, float beta, void* ws, size_t ws_bytes, hipStream_t s, const void* x2 = nullptr,
                        int x_c1 = 0, int wcin = 0);
 
+// ---- conv3d_f32.hip -------------------------------------------------------------------------
+// The same three passes on fp32 tensors, any channel counts, strides and alignment; unsupported only past grid and
+// 32-bit offset limits.
+bool f32_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd);
+size_t f32_conv_ws_bytes(const lamp_tensor_desc* zd, int want_stats);
+lamp_status f32_conv(const lamp_tensor_desc* xd, const float* x, const NormIn& nm, const float* w, const float* bias, bool dgrad,
+                     const lamp_tensor_desc* zd, float* z, float* stats_out, float eps, void* ws, size_t ws_bytes, hipStream_t s);
+bool f32_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd);
+size_t f32_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd);
+lamp_status f32_wgrad(const lamp_tensor_desc* xd, const float* x, const NormIn& nm, const lamp_tensor_desc* dzd, const float* dz,
+                      float* dw, float beta, void* ws, size_t ws_bytes, hipStream_t s);
+
 // ---- convtr_mfma.hip ------------------------------------------------------------------------
 bool mfma_convtr_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* yd, const lamp_norm_in* xnorm);
 size_t mfma_convtr_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* yd);

@@ -107,3 +107,53 @@ def test_conv3d_ragged_channels_unaligned_weights(L):
     dx = torch.empty_like(x)
     L.lamp_conv3d_dgrad(z, w, dx)
     check(as64(dx), O.conv3d_dgrad(as64(z), as64(wh)), BF, "conv dgrad")
+
+
+# fp32: a sum of K <= 27 * 80 products carries about sqrt(K) * 2^-24 = 3e-6 of its terms' scale; weight gradients sum over up to
+# 70000 voxels (1.6e-5) in partials of at most a few thousand
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1, 1, 1, 1),
+    (1, 5, 6, 7, 1, 8),          # channel chunks of 4: one, two, three, four channels; 64-voxel tiles
+    (2, 5, 9, 17, 2, 17),        # one channel in the last block; 32-voxel tiles, waves share out the channels
+    (1, 6, 9, 33, 3, 33),
+    (2, 3, 20, 12, 4, 16),
+    (1, 7, 9, 10, 5, 24),        # chunks of 8 cut short
+    (1, 8, 8, 8, 8, 8),
+    (3, 4, 5, 6, 20, 40),
+    (1, 9, 10, 11, 32, 16),      # chunks of 16
+    (1, 4, 4, 4, 80, 72),
+    (1, 33, 32, 34, 16, 16),     # 128-voxel tiles
+    (1, 33, 32, 34, 8, 48),
+    (1, 41, 40, 44, 16, 24),     # 256-voxel tiles
+    (2, 33, 40, 47, 2, 8),
+    (1, 41, 40, 44, 9, 12),
+], ids=lambda s: "x".join(map(str, s)))
+def test_conv3d_f32(L, shape):
+    conv_passes(L, F32, shape, 2400, 1e-4)
+
+
+def test_conv3d_f32_unaligned(L):
+    """fp32 tensors and weights off 16 bytes, channel strides that are no multiple of 4; a partial normalise-on-load."""
+    r = rng(2500)
+    N, D, H, W, Ci, Co = 2, 5, 6, 19, 16, 20
+
+    def off(ref, extra):   # channels 1.. of a buffer with `extra` more channels
+        buf = torch.full((*ref.shape[:-1], ref.shape[-1] + extra), float("nan"), dtype=F32, device=DEV)
+        buf[..., 1:1 + ref.shape[-1]] = to_dev(ref, F32)
+        return buf[..., 1:1 + ref.shape[-1]]
+
+    x = off(S.normal(r, (N, D, H, W, Ci)), 3)
+    dz = off(S.normal(r, (N, D, H, W, Co)), 2)
+    wh = S.kaiming_conv(r, Co, Ci)
+    flat = torch.empty(wh.size + 1, dtype=F32, device=DEV)
+    flat[1:] = to_dev(wh, F32).reshape(-1)
+    w = flat[1:].view(wh.shape)
+    z = off(np.zeros((N, D, H, W, Co)), 2)
+    L.lamp_conv3d_fwd(x, w, z)
+    check(as64(z), O.conv3d_fwd(as64(x), as64(w)), F32, "conv fwd")
+    dx = off(np.zeros((N, D, H, W, Ci)), 3)
+    L.lamp_conv3d_dgrad(dz, w, dx)
+    check(as64(dx), O.conv3d_dgrad(as64(dz), as64(w)), F32, "conv dgrad")
+    dw = torch.empty(wh.shape, dtype=F32, device=DEV)
+    L.lamp_conv3d_wgrad(x, dz, dw)
+    check(as64(dw), O.conv3d_wgrad(as64(x), as64(dz))[0], F32, "conv wgrad")
