@@ -43,6 +43,17 @@ int stats_chunks(int64_t v) {
     return (int)((v + r - 1) / r);
 }
 
+// Chunks of the two-tensor reductions (backward sums, squeeze): 1024 blocks are four to a CU, which is what their registers allow;
+// 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's backward 126 -> 118).
+static int bwd_rows(int64_t v) {
+    const int64_t r = (v + 1023) / 1024;
+    return (int)(r < 32 ? 32 : r);
+}
+int bwd_chunks(int64_t v) {
+    const int r = bwd_rows(v);
+    return (int)((v + r - 1) / r);
+}
+
 size_t stats_ws_bytes(const lamp_tensor_desc* zd) {
     int64_t V = (int64_t)zd->d * zd->h * zd->w;
     int ch = stats_chunks(V);
@@ -55,7 +66,7 @@ template <typename T, int VEC>
 __global__ __launch_bounds__(256) void stats_partial_kernel(const T* __restrict__ z, int ld, int64_t V, int C,
                                                             int cthreads, int rl, int rows_per_chunk,
                                                             float* __restrict__ partial, int32_t* __restrict__ counts) {
-    __shared__ float red[2][256 * VEC];
+    __shared__ float red[2 * 256 * VEC], part[256];
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
@@ -63,7 +74,8 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const T* __restrict_
     const int64_t rbeg = (int64_t)chunk * rows_per_chunk;
     int64_t rend = rbeg + rows_per_chunk;
     if (rend > V) rend = V;
-    float s[VEC], q[VEC];
+    float sq[2][VEC];
+    auto &s = sq[0], &q = sq[1];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) { s[i] = 0.f; q[i] = 0.f; }
     const bool active = r0 < rl && cv * VEC < C;
@@ -87,21 +99,10 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const T* __restrict_
             for (int i = 0; i < VEC; ++i) { s[i] += v[i]; q[i] = fmaf(v[i], v[i], q[i]); }
         }
     }
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) { red[0][tid * VEC + i] = s[i]; red[1][tid * VEC + i] = q[i]; }
-    __syncthreads();
-    if (r0 == 0 && cv * VEC < C) {
-        for (int i = 0; i < VEC; ++i) {
-            float ss = 0.f, qq = 0.f;
-            for (int r = 0; r < rl; ++r) {
-                ss += red[0][(r * cthreads + cl) * VEC + i];
-                qq += red[1][(r * cthreads + cl) * VEC + i];
-            }
-            size_t o = (((size_t)n * chunks + chunk) * C + (size_t)cv * VEC + i) * 2;
-            partial[o] = ss;
-            partial[o + 1] = qq;
-        }
-    }
+    block_fold(sq, cthreads, rl, red, part, [&](int k, int e, float t) {
+        const int c = blockIdx.z * 256 * VEC + e;
+        if (c < C) partial[(((size_t)n * chunks + chunk) * C + c) * 2 + k] = t;
+    });
     if (counts && n == 0 && blockIdx.z == 0 && tid == 0) counts[chunk] = (int32_t)(rend - rbeg);
 }
 
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
                                                             int zsplit, int64_t V, int C,
                                                             int cthreads, int rl, int rows_per_chunk,
                                                             float* __restrict__ partial, int32_t* __restrict__ counts) {
-    __shared__ float red[2][256 * 8];
+    __shared__ float red[2 * 256 * 8], part[256];
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
@@ -200,7 +201,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     const int64_t rbeg = (int64_t)chunk * rows_per_chunk;
     int64_t rend = rbeg + rows_per_chunk;
     if (rend > V) rend = V;
-    float s[8], q[8];
+    float sq[2][8];
+    auto &s = sq[0], &q = sq[1];
 #pragma unroll
     for (int i = 0; i < 8; ++i) { s[i] = 0.f; q[i] = 0.f; }
     if (r0 < rl && cv * 8 < C) {
@@ -230,21 +232,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
         }
     }
     if (!partial) return;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { red[0][tid * 8 + i] = s[i]; red[1][tid * 8 + i] = q[i]; }
-    __syncthreads();
-    if (r0 == 0 && cv * 8 < C) {
-        for (int i = 0; i < 8; ++i) {
-            float ss = 0.f, qq = 0.f;
-            for (int r = 0; r < rl; ++r) {
-                ss += red[0][(r * cthreads + cl) * 8 + i];
-                qq += red[1][(r * cthreads + cl) * 8 + i];
-            }
-            size_t o = (((size_t)n * chunks + chunk) * C + (size_t)cv * 8 + i) * 2;
-            partial[o] = ss;
-            partial[o + 1] = qq;
-        }
-    }
+    block_fold(sq, cthreads, rl, red, part, [&](int k, int e, float t) {
+        const int c = blockIdx.z * 256 * 8 + e;
+        if (c < C) partial[(((size_t)n * chunks + chunk) * C + c) * 2 + k] = t;
+    });
     if (n == 0 && blockIdx.z == 0 && tid == 0) counts[chunk] = (int32_t)(rend - rbeg);
 }
 
@@ -301,13 +292,13 @@ __global__ __launch_bounds__(256) void inorm_apply_kernel(const T* __restrict__ 
 // ---- backward -------------------------------------------------------------------------------
 // partial[((n*chunks+chunk)*C + c)*2] = (sum g, sum g*zh) over the chunk's rows.
 template <typename T, int VEC>
-__global__ __launch_bounds__(256) void inorm_bwd_partial_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z,
+__global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z,
                                                                 int ldz, int64_t V, int C, int cthreads, int rl,
                                                                 int rows_per_chunk, const float* __restrict__ stats,
                                                                 const float* __restrict__ gamma,
                                                                 const float* __restrict__ beta,
                                                                 float* __restrict__ partial) {
-    __shared__ float red[2][256 * VEC];
+    __shared__ float red[2 * 256 * VEC], part[256];
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
@@ -315,7 +306,8 @@ __global__ __launch_bounds__(256) void inorm_bwd_partial_kernel(const T* __restr
     const int64_t rbeg = (int64_t)chunk * rows_per_chunk;
     int64_t rend = rbeg + rows_per_chunk;
     if (rend > V) rend = V;
-    float s[VEC], q[VEC];
+    float sq[2][VEC];
+    auto &s = sq[0], &q = sq[1];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) { s[i] = 0.f; q[i] = 0.f; }
     if (r0 < rl && cv * VEC < C) {
@@ -342,14 +334,19 @@ __global__ __launch_bounds__(256) void inorm_bwd_partial_kernel(const T* __restr
         int64_t r = rbeg + r0;
         // four rows in flight; the additions keep the row order
         for (; r + 3 * (int64_t)rl < rend; r += 4 * (int64_t)rl) {
-            float v[4][VEC], g[4][VEC];
+            typename Vec<T, VEC>::raw vr[4], gr[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                Vec<T, VEC>::load(zb + (r + u * (int64_t)rl) * ldz, v[u]);
-                Vec<T, VEC>::load(gb + (r + u * (int64_t)rl) * ldg, g[u]);
+                vr[u] = Vec<T, VEC>::raw_load(zb + (r + u * (int64_t)rl) * ldz);
+                gr[u] = Vec<T, VEC>::raw_load(gb + (r + u * (int64_t)rl) * ldg);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) add_row(v[u], g[u]);
+            for (int u = 0; u < 4; ++u) {
+                float v[VEC], g[VEC];
+                Vec<T, VEC>::unpack(vr[u], v);
+                Vec<T, VEC>::unpack(gr[u], g);
+                add_row(v, g);
+            }
         }
         for (; r < rend; r += rl) {
             float v[VEC], g[VEC];
@@ -358,21 +355,10 @@ __global__ __launch_bounds__(256) void inorm_bwd_partial_kernel(const T* __restr
             add_row(v, g);
         }
     }
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) { red[0][tid * VEC + i] = s[i]; red[1][tid * VEC + i] = q[i]; }
-    __syncthreads();
-    if (r0 == 0 && cv * VEC < C) {
-        for (int i = 0; i < VEC; ++i) {
-            float ss = 0.f, qq = 0.f;
-            for (int r = 0; r < rl; ++r) {
-                ss += red[0][(r * cthreads + cl) * VEC + i];
-                qq += red[1][(r * cthreads + cl) * VEC + i];
-            }
-            size_t o = (((size_t)n * chunks + chunk) * C + (size_t)cv * VEC + i) * 2;
-            partial[o] = ss;
-            partial[o + 1] = qq;
-        }
-    }
+    block_fold(sq, cthreads, rl, red, part, [&](int k, int e, float t) {
+        const int c = blockIdx.z * 256 * VEC + e;
+        if (c < C) partial[(((size_t)n * chunks + chunk) * C + c) * 2 + k] = t;
+    });
 }
 
 // sums[n][c][2] = (sum g, sum g*zh) over all parts, fp64, fixed order (strided per thread with four
@@ -524,7 +510,7 @@ extern "C" lamp_status lamp_inorm_relu_noalloc(const lamp_tensor_desc* zd, const
 extern "C" size_t lamp_inorm_relu_bwd_workspace_bytes(const lamp_tensor_desc* zd) {
     if (!desc_ok(zd)) return 0;
     int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    int ch = stats_chunks(V);
+    int ch = bwd_chunks(V);
     return align_up((size_t)zd->n * ch * zd->c * 2 * sizeof(float)) + align_up((size_t)zd->n * zd->c * 2 * sizeof(float));
 }
 
@@ -541,14 +527,14 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
     if (!ws || ws_bytes < lamp_inorm_relu_bwd_workspace_bytes(zd)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int chunks = stats_chunks(V);
+    const int chunks = bwd_chunks(V);
     float* partial = (float*)ws;
     float* sums = (float*)((char*)ws + align_up((size_t)zd->n * chunks * zd->c * 2 * sizeof(float)));
     const int vec = pick_vec(zd->dtype, zd->c, {zd->ldc, dyd->ldc, dzd->ldc}, {z, dy, dz});
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(zd->c, VEC);
         hipLaunchKernelGGL((inorm_bwd_partial_kernel<T, VEC>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s,
-                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, rows_per_chunk(V),
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V),
                            stats, gamma, beta, partial);
     });
     LAMP_CHECK_LAUNCH();

@@ -19,12 +19,12 @@ namespace lamp {
 // MODE 1 (backward): sum dy*a, sum dy*mask, sum dy*mask*zhat
 // partial[((n*chunks + chunk)*C + c)*3 + k]
 template <typename T, int VEC, int MODE>
-__global__ __launch_bounds__(256) void se_partial_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z, int ldz,
+__global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z, int ldz,
                                                          int64_t V, int C, int cthreads, int rl, int rows_per_chunk,
                                                          const float* __restrict__ stats, const float* __restrict__ gamma,
                                                          const float* __restrict__ beta, float* __restrict__ partial) {
     constexpr int K = 3;
-    __shared__ float red[K][256 * VEC];
+    __shared__ float red[K * 256 * VEC], part[256];
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
@@ -69,14 +69,19 @@ __global__ __launch_bounds__(256) void se_partial_kernel(const T* __restrict__ d
         int64_t r = rbeg + r0;
         // four rows in flight; the additions keep the row order
         for (; r + 3 * (int64_t)rl < rend; r += 4 * (int64_t)rl) {
-            float v[4][VEC], g[4][VEC];
+            typename Vec<T, VEC>::raw vr[4], gr[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                Vec<T, VEC>::load(zb + (r + u * (int64_t)rl) * ldz, v[u]);
-                if (MODE == 1) Vec<T, VEC>::load(gb + (r + u * (int64_t)rl) * ldg, g[u]);
+                vr[u] = Vec<T, VEC>::raw_load(zb + (r + u * (int64_t)rl) * ldz);
+                if (MODE == 1) gr[u] = Vec<T, VEC>::raw_load(gb + (r + u * (int64_t)rl) * ldg);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) add_row(v[u], g[u]);
+            for (int u = 0; u < 4; ++u) {
+                float v[VEC], g[VEC];
+                Vec<T, VEC>::unpack(vr[u], v);
+                if (MODE == 1) Vec<T, VEC>::unpack(gr[u], g);
+                add_row(v, g);
+            }
         }
         for (; r < rend; r += rl) {
             float v[VEC], g[VEC];
@@ -85,21 +90,10 @@ __global__ __launch_bounds__(256) void se_partial_kernel(const T* __restrict__ d
             add_row(v, g);
         }
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) red[k][tid * VEC + i] = s[k][i];
-    __syncthreads();
-    if (r0 == 0 && cv * VEC < C) {
-        for (int i = 0; i < VEC; ++i) {
-            const size_t o = (((size_t)n * chunks + chunk) * C + (size_t)cv * VEC + i) * K;
-            for (int k = 0; k < K; ++k) {
-                float t = 0.f;
-                for (int r = 0; r < rl; ++r) t += red[k][(r * cthreads + cl) * VEC + i];
-                partial[o + k] = t;
-            }
-        }
-    }
+    block_fold(s, cthreads, rl, red, part, [&](int k, int e, float t) {
+        const int c = blockIdx.z * 256 * VEC + e;
+        if (c < C) partial[(((size_t)n * chunks + chunk) * C + c) * K + k] = t;
+    });
 }
 
 // sums[(n*C + c)*K + k] = sum over the chunks, fp64, fixed order.
@@ -371,7 +365,7 @@ extern "C" size_t lamp_inorm_relu_se_workspace_bytes(const lamp_tensor_desc* zd,
     if (!zd || se_check(zd, cr) != LAMP_OK) return 0;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
     const size_t nc = (size_t)zd->n * zd->c;
-    return align_up(nc * stats_chunks(V) * 3 * sizeof(float)) + align_up(nc * 3 * sizeof(float)) +
+    return align_up(nc * bwd_chunks(V) * 3 * sizeof(float)) + align_up(nc * 3 * sizeof(float)) +
            align_up(nc * 2 * sizeof(float)) + 2 * align_up(nc * sizeof(float)) +
            align_up((size_t)zd->n * cr * sizeof(float)) + 256;
 }
@@ -394,7 +388,7 @@ extern "C" lamp_status lamp_inorm_relu_se(const lamp_tensor_desc* zd, const void
     if (!ws || ws_bytes < lamp_inorm_relu_se_workspace_bytes(zd, cr)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int C = zd->c, chunks = stats_chunks(V);
+    const int C = zd->c, chunks = bwd_chunks(V);
     const int rpc = (int)((V + chunks - 1) / chunks);
     Carver cv(ws, ws_bytes);
     float* partial = (float*)cv.take((size_t)zd->n * C * chunks * 3 * sizeof(float));
@@ -442,7 +436,7 @@ extern "C" lamp_status lamp_inorm_relu_se_bwd(const lamp_tensor_desc* dyd, const
     if (!ws || ws_bytes < lamp_inorm_relu_se_workspace_bytes(zd, cr)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int C = zd->c, N = zd->n, chunks = stats_chunks(V);
+    const int C = zd->c, N = zd->n, chunks = bwd_chunks(V);
     const int rpc = (int)((V + chunks - 1) / chunks);
     const size_t nc = (size_t)N * C;
     Carver cv(ws, ws_bytes);

@@ -8,15 +8,20 @@ namespace lamp {
 
 template <typename T, int VEC> struct Vec;
 
+// load = raw_load + unpack: kernels with several rows in flight hold them packed.
 template <> struct Vec<bf16_t, 8> {
-    static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
-        uint4 q = *reinterpret_cast<const uint4*>(p);
-        uint32_t r[4] = {q.x, q.y, q.z, q.w};
+    typedef uint4 raw;
+    static __device__ __forceinline__ raw raw_load(const bf16_t* p) { return *reinterpret_cast<const uint4*>(p); }
+    static __device__ __forceinline__ void unpack(const raw& q, float (&v)[8]) {
+        const uint32_t r[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             v[2 * i] = __uint_as_float(r[i] << 16);
             v[2 * i + 1] = __uint_as_float(r[i] & 0xFFFF0000u);
         }
+    }
+    static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
+        unpack(raw_load(p), v);
     }
     static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8]) {
         uint32_t r[4];
@@ -26,15 +31,18 @@ template <> struct Vec<bf16_t, 8> {
     }
 };
 template <> struct Vec<float, 4> {
-    static __device__ __forceinline__ void load(const float* p, float (&v)[4]) {
-        float4 q = *reinterpret_cast<const float4*>(p);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    }
+    typedef float4 raw;
+    static __device__ __forceinline__ raw raw_load(const float* p) { return *reinterpret_cast<const float4*>(p); }
+    static __device__ __forceinline__ void unpack(const raw& q, float (&v)[4]) { v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w; }
+    static __device__ __forceinline__ void load(const float* p, float (&v)[4]) { unpack(raw_load(p), v); }
     static __device__ __forceinline__ void store(float* p, const float (&v)[4]) {
         *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
     }
 };
 template <typename T> struct Vec<T, 1> {
+    typedef float raw;
+    static __device__ __forceinline__ raw raw_load(const T* p) { return io<T>::ld(p); }
+    static __device__ __forceinline__ void unpack(const raw& q, float (&v)[1]) { v[0] = q; }
     static __device__ __forceinline__ void load(const T* p, float (&v)[1]) { v[0] = io<T>::ld(p); }
     static __device__ __forceinline__ void store(T* p, const float (&v)[1]) { io<T>::st(p, v[0]); }
 };
@@ -77,6 +85,40 @@ __device__ __forceinline__ void load_norm_vec(const T* p, const NormIn& nm, int 
                 if (nm.relu) u = u > 0.f ? u : 0.f;
                 v[i] = io<T>::rnd(u);
             }
+        }
+    }
+}
+
+// Sums NV sets of VEC values per thread over the row lanes of a block (thread = row lane * cthreads + channel-vector lane) and
+// hands each to put(set, channel of the block, sum).  All 256 threads add: with only the first row lane's cthreads threads at
+// work, a 16-channel bf16 tensor left 2 threads a serial chain of 2048 LDS reads, which was 45 of the 60 us of its backward sums
+// (2 x 64 x 80 x 96 voxels).  `red`: NV * 256 * VEC floats, `part`: 256 floats.  A fixed order for a given cthreads.
+template <int NV, int VEC, typename F>
+__device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthreads, int rl, float* red, float* part, F put) {
+    const int tid = threadIdx.x, nc = cthreads * VEC, nout = NV * nc;
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) red[k * (256 * VEC) + tid * VEC + i] = v[k][i];
+    __syncthreads();
+    if (nout <= 128) {   // several threads per sum, each a share of the rows, then the shares in order
+        const int P = 256 / nout, o = tid % nout, p = tid / nout, k = o / nc, e = o - k * nc;
+        float t = 0.f;
+        if (p < P)
+            for (int r = p; r < rl; r += P) t += red[k * (256 * VEC) + r * nc + e];
+        part[tid] = t;
+        __syncthreads();
+        if (tid < nout) {
+            t = part[tid];
+            for (int q = 1; q < P; ++q) t += part[q * nout + tid];
+            put(k, e, t);
+        }
+    } else {
+        for (int o = tid; o < nout; o += 256) {
+            const int k = o / nc, e = o - k * nc;
+            float t = 0.f;
+            for (int r = 0; r < rl; ++r) t += red[k * (256 * VEC) + r * nc + e];
+            put(k, e, t);
         }
     }
 }
