@@ -121,6 +121,8 @@ extern "C" lamp_status lamp_convtr3d(const lamp_tensor_desc* xd, const void* x, 
     if (ws_bytes < lamp_convtr3d_workspace_bytes(xd, yd) || (ws_bytes && !ws)) return LAMP_ERR_WORKSPACE;
     if (mfma_convtr_supported(xd, yd, xnorm) && aligned16(x) && aligned16(ws) && ((((uintptr_t)y) & 7u) == 0))
         return mfma_convtr_fwd(xd, x, wt, bias, yd, y, ws, ws_bytes, (hipStream_t)stream);
+    if (f32_convtr_supported(xd, yd, xnorm) && aligned16(x) && aligned16(y))
+        return f32_convtr_fwd(xd, (const float*)x, (const float*)wt, bias, yd, (float*)y, (hipStream_t)stream);
     NormIn nm = make_norm(xnorm);
     const int64_t total = nvox(yd) * yd->c;
     if (xd->dtype == LAMP_BF16)
@@ -141,6 +143,8 @@ extern "C" size_t lamp_convtr3d_bwd_workspace_bytes(const lamp_tensor_desc* xd, 
     size_t a = align_up((size_t)convtr_splits(nvox(xd), O) * O * sizeof(float));
     const size_t b = mfma_convtr_wgrad_ws_bytes(xd, dyd);
     if (b > a) a = align_up(b);
+    const size_t c = f32_convtr_wgrad_ws_bytes(xd, dyd);
+    if (c > a) a = c;
     return a + colsum_ws_bytes(nvox(dyd), dyd->c);
 }
 
@@ -163,6 +167,8 @@ extern "C" lamp_status lamp_convtr3d_bwd(const lamp_tensor_desc* xd, const void*
     const int Ci = xd->c, Co = dyd->c;
     if (dx && mfma_convtr_dgrad_supported(xd, dyd, dxd) && aligned16(dy) && aligned16(wt) && ((((uintptr_t)dx) & 7u) == 0)) {
         if ((st = mfma_convtr_dgrad(xd, wt, dyd, dy, dxd, dx, s)) != LAMP_OK) return st;
+    } else if (dx && f32_convtr_supported(xd, dyd, nullptr) && dxd->ldc % 4 == 0 && aligned16(dy) && aligned16(wt) && aligned16(dx)) {
+        if ((st = f32_convtr_dgrad(xd, (const float*)wt, dyd, (const float*)dy, dxd, (float*)dx, s)) != LAMP_OK) return st;
     } else if (dx) {
         const int64_t total = nvox(xd) * Ci;
         if (xd->dtype == LAMP_BF16)
@@ -178,6 +184,9 @@ extern "C" lamp_status lamp_convtr3d_bwd(const lamp_tensor_desc* xd, const void*
     const size_t pbytes = lamp_convtr3d_bwd_workspace_bytes(xd, dyd) - csb;
     if (dwt && mfma_convtr_wgrad_supported(xd, dyd, xnorm) && aligned16(x) && aligned16(dy) && aligned16(ws)) {
         if ((st = mfma_convtr_wgrad(xd, x, dyd, dy, dwt, beta, ws, pbytes, s)) != LAMP_OK) return st;
+    } else if (dwt && f32_convtr_supported(xd, dyd, xnorm)) {
+        if ((st = f32_convtr_wgrad(xd, (const float*)x, dyd, (const float*)dy, dwt, dbias, beta, ws, pbytes, s)) != LAMP_OK) return st;
+        dbias = nullptr;   // done
     } else if (dwt) {
         const int64_t V = nvox(xd);
         const int S = convtr_splits(V, O);

@@ -122,6 +122,17 @@ bool mfma_convtr_dgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_d
 lamp_status mfma_convtr_dgrad(const lamp_tensor_desc* xd, const void* wt, const lamp_tensor_desc* dyd, const void* dy,
                               const lamp_tensor_desc* dxd, void* dx, hipStream_t s);
 
+// ---- convtr_f32.hip -------------------------------------------------------------------------
+// fp32: pointers 16-byte aligned.  The weight gradient also takes the bias gradient (dbias may be nullptr).
+bool f32_convtr_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* yd, const lamp_norm_in* xnorm);
+lamp_status f32_convtr_fwd(const lamp_tensor_desc* xd, const float* x, const float* wt, const float* bias, const lamp_tensor_desc* yd,
+                           float* y, hipStream_t s);
+lamp_status f32_convtr_dgrad(const lamp_tensor_desc* xd, const float* wt, const lamp_tensor_desc* dyd, const float* dy,
+                             const lamp_tensor_desc* dxd, float* dx, hipStream_t s);
+size_t f32_convtr_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd);
+lamp_status f32_convtr_wgrad(const lamp_tensor_desc* xd, const float* x, const lamp_tensor_desc* dyd, const float* dy, float* dwt,
+                             float* dbias, float beta, void* ws, size_t ws_bytes, hipStream_t s);
+
 bool mfma_convtr_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_norm_in* xnorm);
 size_t mfma_convtr_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd);
 lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dyd, const void* dy,

@@ -157,3 +157,45 @@ def test_conv3d_f32_unaligned(L):
     dw = torch.empty(wh.shape, dtype=F32, device=DEV)
     L.lamp_conv3d_wgrad(x, dz, dw)
     check(as64(dw), O.conv3d_wgrad(as64(x), as64(dz))[0], F32, "conv wgrad")
+
+
+# the transposed conv: fp32 on both wave tilings and both channel-block widths, bf16 weight gradient with channels past its blocks;
+# tolerances as for the 3x3x3 passes, the bias gradient sums up to 8 * 66000 values in fp32 partials of about a thousand
+@pytest.mark.parametrize("shape", [
+    (F32, 1, 1, 1, 1, 4, 4), (F32, 2, 3, 5, 7, 20, 12), (F32, 1, 6, 7, 9, 16, 8), (F32, 3, 5, 4, 6, 64, 36), (F32, 1, 33, 40, 50, 32, 16),
+    (F32, 1, 41, 40, 41, 40, 4),
+    (BF, 1, 3, 4, 5, 16, 8), (BF, 2, 5, 6, 7, 32, 16), (BF, 1, 9, 8, 11, 80, 40), (BF, 1, 33, 40, 50, 48, 24),
+], ids=lambda s: "x".join(map(str, s)))
+def test_convtr3d_channels(L, shape):
+    dtype, N, D, H, W, Ci, Co = shape
+    r = rng(2600 + sum(shape[1:]))
+    nan = float("nan")
+
+    def sliced(dims, c, ref=None):
+        buf = torch.full((*dims, c + 16), nan, dtype=dtype, device=DEV)
+        if ref is not None:
+            buf[..., 8:8 + c] = to_dev(ref, dtype)
+        return buf, buf[..., 8:8 + c]
+
+    co, fi = (N, D, H, W), (N, 2 * D, 2 * H, 2 * W)
+    _, x = sliced(co, Ci, S.normal(r, (*co, Ci)))
+    wt = to_dev(S.kaiming_convtr(r, Ci, Co), dtype)
+    b = to_dev(S.normal(r, (Co,), 0.1), F32)
+    ybuf, y = sliced(fi, Co)
+    L.lamp_convtr3d(x, wt, y, bias=b)
+    check(as64(y), O.convtr3d_fwd(as64(x), as64(wt), as64(b)), dtype, "convtr fwd")
+    assert torch.isnan(ybuf[..., :8]).all() and torch.isnan(ybuf[..., 8 + Co:]).all()
+    _, dy = sliced(fi, Co, S.normal(r, (*fi, Co)) + 0.25)
+    dxbuf, dx = sliced(co, Ci)
+    dwt = torch.full(wt.shape, nan, dtype=F32, device=DEV)
+    db = torch.full((Co,), nan, dtype=F32, device=DEV)
+    L.lamp_convtr3d_bwd(x, wt, dy, dx=dx, dwt=dwt, dbias=db)
+    dx_ref, dwt_ref, db_ref = O.convtr3d_bwd(as64(x), as64(wt), as64(dy))
+    tol = 1e-4 if dtype == F32 else 2e-3
+    check(as64(dx), dx_ref, dtype, "convtr dgrad")
+    assert torch.isnan(dxbuf[..., :8]).all() and torch.isnan(dxbuf[..., 8 + Ci:]).all()
+    check(as64(dwt), dwt_ref, dtype, "convtr wgrad", tol=tol)
+    check(as64(db), db_ref, dtype, "convtr dbias", tol=1e-4)
+    L.lamp_convtr3d_bwd(x, wt, dy, dwt=dwt, dbias=db, beta=1.0)
+    check(as64(dwt), 2 * dwt_ref, dtype, "convtr wgrad beta=1", tol=tol)
+    check(as64(db), 2 * db_ref, dtype, "convtr dbias beta=1", tol=1e-4)
