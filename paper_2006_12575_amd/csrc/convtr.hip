@@ -183,7 +183,8 @@ extern "C" lamp_status lamp_convtr3d_bwd(const lamp_tensor_desc* xd, const void*
     const size_t csb = colsum_ws_bytes(nvox(dyd), Co);
     const size_t pbytes = lamp_convtr3d_bwd_workspace_bytes(xd, dyd) - csb;
     if (dwt && mfma_convtr_wgrad_supported(xd, dyd, xnorm) && aligned16(x) && aligned16(dy) && aligned16(ws)) {
-        if ((st = mfma_convtr_wgrad(xd, x, dyd, dy, dwt, beta, ws, pbytes, s)) != LAMP_OK) return st;
+        if ((st = mfma_convtr_wgrad(xd, x, dyd, dy, dwt, dbias, beta, ws, pbytes, s)) != LAMP_OK) return st;
+        dbias = nullptr;   // done
     } else if (dwt && f32_convtr_supported(xd, dyd, xnorm)) {
         if ((st = f32_convtr_wgrad(xd, (const float*)x, dyd, (const float*)dy, dwt, dbias, beta, ws, pbytes, s)) != LAMP_OK) return st;
         dbias = nullptr;   // done

@@ -505,7 +505,10 @@ lamp_status mfma_convtr_dgrad(const lamp_tensor_desc* xd, const void* wt, const 
 
 // ------------------------------------------------------------------------------------------------
 // Weight gradient  dWt[ci][tap][co] = sum_v x[v][ci] * dy[up(v,tap)][co]   (K = coarse voxels).
-// Workgroup = 4 waves on (split s, 64-wide ci block, 32-wide co block); wave w owns taps 2w, 2w+1.
+// Workgroup = 4 waves on (split s, 64-wide ci block, 32-wide co block); wave w owns taps 2w, 2w+1.  Channels past the end of the
+// last block come from the zero source.  Bound: HBM (dy is read once).  The bias gradient is a product of the same dy fragments
+// with a row of ones (2 more matrix instructions per 4), taken by the first ci block: a pass of its own over dy cost 48 of the 351 us
+// of 64->32 on 2 x 64^3, forward and backward.
 // Chunks of 64 coarse voxels are staged in LDS (x rows of 128 bytes, dy rows of 64 bytes per tap,
 // double buffered, register-free copies) and read with the transposing LDS load.
 // (inline assembly, so that the compiler's wait-count bookkeeping does not see the copies and keeps
@@ -527,6 +530,7 @@ struct CtWArgs {
     const bf16_t* x; int ldx;
     const bf16_t* dy; int ldy;
     float* part;              // [S][Ci][8][Co]
+    float* bpart;             // [S][4][Co] partial column sums of dy (one row per wave: two taps each); may be nullptr
     const bf16_t* zero16;
     int N, D, H, W, Ci, Co;
     int chunks_per_split;     // 64-voxel chunks per split
@@ -555,7 +559,7 @@ __device__ __forceinline__ void ctw_stage(const CtWArgs& a, char* __restrict__ s
         const int64_t v = v0 + (q & 3) * 16 + (lane >> 2);
         const int pc = lane & 3;
         const bf16_t* src = a.zero16;
-        if (v < nvox) {
+        if (v < nvox && co0 + pc * 8 < a.Co) {
             const int vi = (int)v;  // host guarantees nvox < 2^31
             const int w = vi % a.W;
             int r = vi / a.W;
@@ -569,7 +573,8 @@ __device__ __forceinline__ void ctw_stage(const CtWArgs& a, char* __restrict__ s
     }
 }
 
-__device__ __forceinline__ void ctw_compute(f32x16 (&acc)[2][2], const char* __restrict__ st, int wv, int lane) {
+template <bool BIAS>
+__device__ __forceinline__ void ctw_compute(f32x16 (&acc)[2][2], f32x16& bacc, const char* __restrict__ st, int wv, int lane) {
     const int b16 = lane >> 4, s16 = lane & 15;
     const uint32_t lx = (uint32_t)((8 * (b16 >> 1) + (s16 >> 2)) * 128 + 32 * (b16 & 1) + 8 * (s16 & 3));
     const uint32_t ly = (uint32_t)((8 * (b16 >> 1) + (s16 >> 2)) * 64 + 32 * (b16 & 1) + 8 * (s16 & 3));
@@ -584,6 +589,11 @@ __device__ __forceinline__ void ctw_compute(f32x16 (&acc)[2][2], const char* __r
         for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
             for (int t = 0; t < 2; ++t) acc[rb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[t], acc[rb][t], 0, 0, 0);
+        if constexpr (BIAS) {
+            const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) bacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, one), bf[t], bacc, 0, 0, 0);
+        }
     }
 }
 
@@ -603,6 +613,10 @@ __global__ __launch_bounds__(256) void convtr_wgrad_mfma_kernel(CtWArgs a) {
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[rb][t][r] = 0.f;
+    f32x16 bacc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) bacc[r] = 0.f;
+    const bool bias = a.bpart && blockIdx.y == 0;
     if (c_lo < c_hi) ctw_stage(a, lds, c_lo * 64, nvox, ci0, co0, wv, lane);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -610,7 +624,8 @@ __global__ __launch_bounds__(256) void convtr_wgrad_mfma_kernel(CtWArgs a) {
     for (int64_t c = c_lo; c < c_hi; ++c, par ^= 1) {
         if (c + 1 < c_hi) ctw_stage(a, lds + (par ^ 1) * CTW_STAGE, (c + 1) * 64, nvox, ci0, co0, wv, lane);
         __builtin_amdgcn_sched_barrier(0);
-        ctw_compute(acc, lds + par * CTW_STAGE, wv, lane);
+        if (bias) ctw_compute<true>(acc, bacc, lds + par * CTW_STAGE, wv, lane);
+        else ctw_compute<false>(acc, bacc, lds + par * CTW_STAGE, wv, lane);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
@@ -618,6 +633,8 @@ __global__ __launch_bounds__(256) void convtr_wgrad_mfma_kernel(CtWArgs a) {
     }
     float* pb = a.part + (int64_t)blockIdx.x * a.Ci * 8 * a.Co;
     const int l32 = lane & 31, half = lane >> 5;
+    if (co0 + l32 >= a.Co) return;
+    if (bias && half == 0) a.bpart[((int64_t)blockIdx.x * 4 + wv) * a.Co + co0 + l32] = bacc[0];   // every row is the sum
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
@@ -632,7 +649,7 @@ __global__ __launch_bounds__(256) void convtr_wgrad_mfma_kernel(CtWArgs a) {
 
 static int ctw_splits(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
     const int64_t chunks = (nvox(xd) + 63) / 64;
-    const int types = ((xd->c + 63) / 64) * (dyd->c / 32);
+    const int types = ((xd->c + 63) / 64) * ((dyd->c + 31) / 32);
     int64_t s = 512 / types;  // about two workgroups per CU; more only enlarges the partial sums
     if (s < 1) s = 1;
     if (s > chunks) s = chunks;
@@ -642,18 +659,19 @@ static int ctw_splits(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
 bool mfma_convtr_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_norm_in* xnorm) {
     if (xd->dtype != LAMP_BF16) return false;
     if (xnorm && xnorm->mean_rstd && xnorm->c_norm > 0) return false;
-    if (xd->c % 32 || dyd->c % 32 || xd->ldc % 8 || dyd->ldc % 8) return false;
+    if (xd->c % 8 || dyd->c % 8 || xd->ldc % 8 || dyd->ldc % 8) return false;
     if (nvox(xd) >= ((int64_t)1 << 31)) return false;
     return true;
 }
 
 size_t mfma_convtr_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
     if (!mfma_convtr_wgrad_supported(xd, dyd, nullptr)) return 0;
-    return align_up((size_t)ctw_splits(xd, dyd) * xd->c * 8 * dyd->c * sizeof(float)) + 256;
+    const size_t S = (size_t)ctw_splits(xd, dyd);
+    return align_up(S * xd->c * 8 * dyd->c * sizeof(float)) + align_up(S * 4 * dyd->c * sizeof(float));
 }
 
 lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dyd, const void* dy,
-                              float* dwt, float beta, void* ws, size_t ws_bytes, hipStream_t s) {
+                              float* dwt, float* dbias, float beta, void* ws, size_t ws_bytes, hipStream_t s) {
     if ((((uintptr_t)x) & 15u) || (((uintptr_t)dy) & 15u) || (((uintptr_t)ws) & 15u)) return LAMP_ERR_ALIGN;
     if (ws_bytes < mfma_convtr_wgrad_ws_bytes(xd, dyd)) return LAMP_ERR_WORKSPACE;
     const int S = ctw_splits(xd, dyd);
@@ -662,15 +680,20 @@ lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const l
     a.x = (const bf16_t*)x; a.ldx = xd->ldc; a.dy = (const bf16_t*)dy; a.ldy = dyd->ldc; a.part = (float*)ws;
     const bool direct = S == 1 && beta == 0.f;   // the only partial is the result: written in place
     if (direct) a.part = dwt;
+    a.bpart = dbias ? (float*)((char*)ws + align_up((size_t)S * O * sizeof(float))) : nullptr;
     a.zero16 = device_zero16();
     if (!a.zero16) return LAMP_ERR_HIP;
     a.N = xd->n; a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Ci = xd->c; a.Co = dyd->c;
     const int64_t chunks = (nvox(xd) + 63) / 64;
     a.chunks_per_split = (int)((chunks + S - 1) / S);
     if (ensure_dyn_lds((const void*)convtr_wgrad_mfma_kernel, 2 * CTW_STAGE) != LAMP_OK) return LAMP_ERR_HIP;
-    dim3 grid(S, (xd->c + 63) / 64, dyd->c / 32);
+    dim3 grid(S, (xd->c + 63) / 64, (dyd->c + 31) / 32);
     hipLaunchKernelGGL(convtr_wgrad_mfma_kernel, grid, dim3(256), 2 * CTW_STAGE, s, a);
     LAMP_CHECK_LAUNCH();
+    if (dbias) {
+        const lamp_status st = launch_reduce_partials(a.bpart, S * 4, a.Co, dbias, beta, s);
+        if (st != LAMP_OK) return st;
+    }
     if (direct) return LAMP_OK;
     return launch_reduce_partials((const float*)ws, S, O, dwt, beta, s);
 }

@@ -136,6 +136,6 @@ lamp_status f32_convtr_wgrad(const lamp_tensor_desc* xd, const float* x, const l
 bool mfma_convtr_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_norm_in* xnorm);
 size_t mfma_convtr_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd);
 lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dyd, const void* dy,
-                              float* dwt, float beta, void* ws, size_t ws_bytes, hipStream_t s);
+                              float* dwt, float* dbias, float beta, void* ws, size_t ws_bytes, hipStream_t s);   // dbias: may be nullptr
 
 }  // namespace lamp
