@@ -841,7 +841,7 @@ extern "C" size_t lamp_conv3d_fwd_workspace_bytes(const lamp_tensor_desc* xd, co
         const size_t c = cin1_tile_ws_bytes(zd);
         if (c > a) a = c;
     }
-    if (f32_conv_supported(xd, zd)) b = f32_conv_ws_bytes(zd, want_stats);
+    if (f32_conv_supported(xd, zd)) b = f32_conv_ws_bytes(xd, zd, want_stats);
     lamp_tensor_desc xp;
     if (pad_desc(xd, xp) && mfma_conv_supported(&xp, zd, nullptr, nullptr)) b = pad_bytes(&xp) + mfma_conv_ws_bytes(&xp, zd, want_stats);
     return a > b ? a : b;

@@ -35,152 +35,174 @@ static TileGeo pick_tile(int D, int H, int W, int vox, int halo) {
     return best;
 }
 
+// round-up reciprocal: e / d == (e * m) >> s for e < 2^31
+static void f32_magic(int d, uint32_t* m, int* s) {
+    int l = 0;
+    while ((1 << l) < d) ++l;
+    *s = 31 + l;
+    *m = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d);
+}
+
 // ---- forward and data gradient --------------------------------------------------------------------
 // Bound: the fp32 matrix rate (157 TFLOP/s; 32 input channels are 432 flops a byte).  D[co][voxel] += W[co][ci] * X[ci][voxel + tap]
 // with A = weights, B = voxels, so that a lane ends with 4 consecutive output channels of one voxel (a 16-byte store).  A
-// workgroup of 4 waves owns one tile of output voxels; its halo is staged KC channels at a time in LDS (through registers, the next
-// chunk's loads in flight during the multiplies), the weights come straight from the caches in their own layout (a 16x16x4 product
-// keeps a SIMD busy for 32 cycles: per 16 channels and tap a wave needs CB + VB 16-byte fragments for 4 * CB * VB products, and no
-// repacking launch stands in front of the call).  A lane's KC / 4 channels are consecutive, and product j of a chunk contracts the
-// j-th channel of every lane group: the order inside a sum is free, operands agree on it.  LDS entries are padded (80, 48, 16 bytes)
-// so that the 16 voxels a fragment read serves at a time fall on different banks.  32->32 on 41 x 56 x 47: 430 -> 82 us with the
-// statistics (73 TFLOP/s), data gradient 385 -> 98 us, against scalar multiply-adds and a separate statistics pass.
-// MAXK: halo pieces (4 channels of a voxel) a thread stages at most.  PT: taps whose weights are fetched together, one group ahead.
+// workgroup of 4 waves walks a contiguous range of tiles; halo and weights of KC input channels go through registers to LDS (the next
+// chunk's or tile's loads in flight during the multiplies; the weights stay where one chunk holds all channels).  Weights come in
+// their own layout, so no repacking launch stands in front of the call; read as fragments straight from the caches they cost every
+// wave 16 lines an instruction (16->8 on 2 x 64 x 48 x 80: 96 us, through LDS 85).  Product j of a chunk contracts channels 4j .. 4j + 3, one per lane group,
+// and the matrix unit adds its four products one after the other, each rounded: channels in chunks of 8, in a chunk the taps, in a tap
+// the channels -- bit for bit the sums of a thread that does so with fused multiply-adds (a chunk of 16 is walked as two of 8).
+// LDS voxel entries are padded (80, 48, 16 bytes) so that the 64 words of a fragment read fall on different banks.  32->32 on
+// 41 x 56 x 47 with the statistics: 430 -> 77 us (77 TFLOP/s; of 462 tiles a CU gets one or two, which alone is 12 %), data gradient
+// 385 -> 71 us, against scalar multiply-adds and a separate statistics pass; 16->8 on 2 x 64 x 48 x 80: 85 us, 8->8 46 us.
+// MAXK: halo pieces (4 channels of a voxel) a thread stages at most.
 struct F32ConvArgs {
     const float* x; const float* w; const float* bias; float* z;
     float* partial; int32_t* counts;   // [N][tiles][Co][2], [tiles]; nullptr: no statistics
     NormIn nm;
     int ldx, ldz, N, D, H, W, Ci, Co;
     TileGeo t;
-    int lvg;                           // log2 of the waves that share out the voxels; the others take further output channels
-    int xvec, zvec;                    // 16-byte accesses possible
+    int ntiles, per;                   // tiles of all samples; tiles per workgroup
+    int xvec, wvec, zvec;              // 16-byte accesses possible
+    uint32_t mHW, mHH; int sHW, sHH;   // division by the halo's sides
 };
 
-template <int KC> struct Frag;         // a lane's KC / 4 channels
-template <> struct Frag<16> { static constexpr int EST = 20; float v[4]; };
-template <> struct Frag<8> { static constexpr int EST = 12; float v[2]; };
-template <> struct Frag<4> { static constexpr int EST = 4; float v[1]; };
-template <int KC> __device__ __forceinline__ Frag<KC> frag_lds(const float* p) {
-    Frag<KC> f;
-    if constexpr (KC == 16) { const float4 q = *reinterpret_cast<const float4*>(p); f.v[0] = q.x; f.v[1] = q.y; f.v[2] = q.z; f.v[3] = q.w; }
-    else if constexpr (KC == 8) { const float2 q = *reinterpret_cast<const float2*>(p); f.v[0] = q.x; f.v[1] = q.y; }
-    else f.v[0] = *p;
-    return f;
+__host__ __device__ constexpr int f32_est(int kc) { return kc == 16 ? 20 : kc == 8 ? 12 : 4; }
+// sum over the 16 lanes of a row
+__device__ __forceinline__ float row_sum16(float v) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, true));
+    return v;
 }
 
-template <int KC, int CB, int VB, int MAXK, int PT, bool DGRAD>
-__global__ __launch_bounds__(256, 2) void conv3d_f32_kernel(F32ConvArgs a) {
+template <int KC, int CB, int VB, int MAXK, bool DGRAD>
+__global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32ConvArgs a) {
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
-    constexpr int EST = Frag<KC>::EST, KL = KC / 4, QE = KC / 4, NG = 27 / PT;
+    constexpr int EST = f32_est(KC), QE = KC / 4, KL = QE < 2 ? QE : 2, MAXW = (27 * QE * 16 * CB + 255) / 256;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, l16 = lane & 15, g = lane >> 4;
-    const int vg = wid & ((1 << a.lvg) - 1), cgrp = wid >> a.lvg;
     const int TD = 1 << a.t.ld, TH = 1 << a.t.lh, TW = 1 << a.t.lw;
     const int HH = TH + 2, HW = TW + 2, HV = (TD + 2) * HH * HW;
-    int tile = blockIdx.x;
-    const int tiles = a.t.nd * a.t.nh * a.t.nw;
-    const int n = tile / tiles;
-    tile -= n * tiles;
-    const int iw = tile % a.t.nw, r1 = tile / a.t.nw, ih = r1 % a.t.nh, idd = r1 / a.t.nh;
-    const int d0 = idd << a.t.ld, h0 = ih << a.t.lh, w0 = iw << a.t.lw;
-    const int co0 = (blockIdx.y * (4 >> a.lvg) + cgrp) * (16 * CB);
+    const int tiles = a.t.nd * a.t.nh * a.t.nw, nchunks = (a.Ci + KC - 1) / KC;
+    const int co0 = blockIdx.y * (16 * CB);
+    float* st = f32_lds;                // [4][16 * CB][2]
+    float* ws = f32_lds + 128 * CB;     // [27][CB][QE][16 channels out][4 channels in]
+    float* xs = ws + 27 * CB * 64 * QE; // [HV][EST]
 
-    // the halo pieces this thread stages: voxel offset from the tile's origin, or none
-    constexpr int NONE = (int)0x80000000;
+    // the halo pieces this thread stages: coordinates in the halo
     const int quad = tid & (QE - 1);
-    int vo[MAXK];
+    int hc[MAXK];
 #pragma unroll
     for (int k = 0; k < MAXK; ++k) {
-        const int e = (tid + 256 * k) / QE;
-        const int row = e / HW, hw = e - row * HW, hd = row / HH, hh = row - hd * HH;
-        const bool in = e < HV && (unsigned)(d0 - 1 + hd) < (unsigned)a.D && (unsigned)(h0 - 1 + hh) < (unsigned)a.H &&
-                        (unsigned)(w0 - 1 + hw) < (unsigned)a.W;
-        vo[k] = in ? ((hd - 1) * a.H + (hh - 1)) * a.W + (hw - 1) : NONE;
+        const uint32_t e = (uint32_t)(tid + 256 * k) / QE;
+        const uint32_t row = (uint32_t)(((uint64_t)e * a.mHW) >> a.sHW), hw = e - row * HW;
+        const uint32_t hd = (uint32_t)(((uint64_t)row * a.mHH) >> a.sHH), hh = row - hd * HH;
+        hc[k] = (int)e < HV ? (int)(hd << 20 | hh << 10 | hw) : 1 << 30;
     }
-    const float* xt = a.x + ((((int64_t)n * a.D + d0) * a.H + h0) * a.W + w0) * a.ldx;
-
-    float4 pre[MAXK];
-    auto fetch = [&](int c0) __attribute__((always_inline)) {
-        const int c = c0 + 4 * quad;
+    float4 px[MAXK], pw[MAXW];
+    uint32_t pin = 0;   // pieces inside the volume (the padding is zero behind the normalisation)
+    // once per tile: which pieces lie inside the volume, and where
+    int vo[MAXK];
+    const float* xt = a.x;
+    auto locate = [&](int tile) __attribute__((always_inline)) {
+        const int n = tile / tiles;
+        tile -= n * tiles;
+        const int iw = tile % a.t.nw, r1 = tile / a.t.nw, ih = r1 % a.t.nh, idd = r1 / a.t.nh;
+        const int d0 = (idd << a.t.ld) - 1, h0 = (ih << a.t.lh) - 1, w0 = (iw << a.t.lw) - 1;
+        xt = a.x + ((((int64_t)n * a.D + d0) * a.H + h0) * a.W + w0) * a.ldx + 4 * quad;
+        pin = 0;
+#pragma unroll
+        for (int k = 0; k < MAXK; ++k) {
+            asm volatile("" : "+v"(hc[k]));   // its parts are not worth registers of their own across the walk
+            const int hd = hc[k] >> 20, hh = hc[k] >> 10 & 1023, hw = hc[k] & 1023;
+            vo[k] = (hd * a.H + hh) * a.W + hw;
+            if (hc[k] < 1 << 30 && (unsigned)(d0 + hd) < (unsigned)a.D && (unsigned)(h0 + hh) < (unsigned)a.H &&
+                (unsigned)(w0 + hw) < (unsigned)a.W)
+                pin |= 1u << k;
+        }
+    };
+    auto fetch_x = [&](int c0) __attribute__((always_inline)) {
+        const int left = a.Ci - c0 - 4 * quad;
 #pragma unroll
         for (int k = 0; k < MAXK; ++k) {
             float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (vo[k] != NONE) {
-                const float* p = xt + (int64_t)vo[k] * a.ldx + c;
+            if (pin >> k & 1) {
+                const float* p = xt + ((int64_t)vo[k] * a.ldx + c0);
                 if (a.xvec) {
-                    if (c < a.Ci) q = *reinterpret_cast<const float4*>(p);
+                    if (left > 0) q = *reinterpret_cast<const float4*>(p);
                 } else {
-                    if (c < a.Ci) q.x = p[0];
-                    if (c + 1 < a.Ci) q.y = p[1];
-                    if (c + 2 < a.Ci) q.z = p[2];
-                    if (c + 3 < a.Ci) q.w = p[3];
+                    if (left > 0) q.x = p[0];
+                    if (left > 1) q.y = p[1];
+                    if (left > 2) q.z = p[2];
+                    if (left > 3) q.w = p[3];
                 }
             }
-            pre[k] = q;
+            px[k] = q;
         }
     };
-    auto stage = [&](int c0) __attribute__((always_inline)) {
-        float na[4] = {1.f, 1.f, 1.f, 1.f}, nb[4] = {0.f, 0.f, 0.f, 0.f};
-        bool on[4] = {false, false, false, false};
+    auto stage_x = [&](int n, int c0) __attribute__((always_inline)) {
         if (a.nm.mean_rstd) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c = c0 + 4 * quad + i;
-                on[i] = c < a.nm.c_norm;
-                if (on[i]) norm_coeffs(a.nm, n, c, na[i], nb[i]);
-            }
-        }
+            for (int j = 0; j < 4; ++j) {
+                const int c = c0 + 4 * quad + j;
+                if (c >= a.nm.c_norm) continue;
+                float na, nb;
+                norm_coeffs(a.nm, n, c, na, nb);
 #pragma unroll
-        for (int k = 0; k < MAXK; ++k) {
-            const int i = tid + 256 * k, e = i / QE;
-            if (e >= HV) continue;
-            float v[4] = {pre[k].x, pre[k].y, pre[k].z, pre[k].w};
-            if (a.nm.mean_rstd && vo[k] != NONE) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (on[j]) {
-                        const float u = norm_u(v[j], na[j], nb[j]);
-                        v[j] = !a.nm.relu || u > 0.f ? u : 0.f;
+                for (int k = 0; k < MAXK; ++k)
+                    if (pin >> k & 1) {
+                        float& v = j == 0 ? px[k].x : j == 1 ? px[k].y : j == 2 ? px[k].z : px[k].w;
+                        const float u = norm_u(v, na, nb);
+                        v = !a.nm.relu || u > 0.f ? u : 0.f;
                     }
             }
-            *reinterpret_cast<float4*>(f32_lds + e * EST + 4 * quad) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+        int ti = tid;
+        asm volatile("" : "+v"(ti));
+#pragma unroll
+        for (int k = 0; k < MAXK; ++k)
+            if (hc[k] < 1 << 30) *reinterpret_cast<float4*>(xs + (ti + 256 * k) / QE * EST + 4 * quad) = px[k];
+    };
+    // Weight pieces of 4 floats along the contiguous index, the other channel fastest over the lanes (whole LDS rows, and 16 or more
+    // lanes of a line): forward W[co][t][ci..], data gradient W[ci][26 - t][co..].  A thread's pieces differ in the tap only, by TS.
+    constexpr int TS = 256 / (16 * QE * CB);
+    const int wk = DGRAD ? tid % KC : tid / 16 % QE * 4, wc = DGRAD ? tid / KC % (4 * CB) * 4 : tid % 16 + tid / (16 * QE) % CB * 16;
+    const int wt0 = tid / (16 * QE * CB);
+    const float* wp = DGRAD ? a.w + ((int64_t)wk * 27 + (26 - wt0)) * a.Co + co0 + wc : a.w + ((int64_t)(co0 + wc) * 27 + wt0) * a.Ci + wk;
+    auto fetch_w = [&](int c0) __attribute__((always_inline)) {
+        const int left = DGRAD ? a.Co - co0 - wc : a.Ci - c0 - wk;   // elements of the row from the piece's first on
+        const bool on = left > 0 && (DGRAD ? c0 + wk < a.Ci : co0 + wc < a.Co);
+        const float* p = wp + (DGRAD ? (int64_t)c0 * 27 * a.Co : (int64_t)c0);
+        const int64_t step = DGRAD ? -(int64_t)TS * a.Co : (int64_t)TS * a.Ci;
+#pragma unroll
+        for (int u = 0; u < MAXW; ++u) {
+            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (on && wt0 + u * TS < 27) {
+                if (a.wvec) q = *reinterpret_cast<const float4*>(p + u * step);
+                else {
+                    q.x = p[u * step];
+                    if (left > 1) q.y = p[u * step + 1];
+                    if (left > 2) q.z = p[u * step + 2];
+                    if (left > 3) q.w = p[u * step + 3];
+                }
+            }
+            pw[u] = q;
         }
     };
-
-    // weights of tap group gi of chunk c0: forward W[co][t][ci], data gradient W[ci][26 - t][co]; a lane's byte offset stays, the
-    // rest of the address is the same for all lanes.  KC == 16 takes whole chunks only, elsewhere missing channels give zeros.
-    const int nchunks = (a.Ci + KC - 1) / KC;
-    uint32_t wl[CB];
+    auto stage_w = [&]() __attribute__((always_inline)) {
+        float* o0 = ws + ((wt0 * CB + wc / 16) * QE + wk / 4) * 64 + wc % 16 * 4 + wk % 4;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-        int co = co0 + 16 * cb + l16;
-        co = co < a.Co ? co : a.Co - 1;   // rows past the end are computed and not stored
-        wl[cb] = DGRAD ? (uint32_t)co * 4u : (uint32_t)co * (27u * 4u) * (uint32_t)a.Ci;
-        if (KC == 16) wl[cb] += DGRAD ? (uint32_t)(g * KL) * (27u * 4u) * (uint32_t)a.Co : (uint32_t)(g * KL) * 4u;
-    }
-    auto wload = [&](int c0, int gi, Frag<KC> (&f)[PT][CB]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int p = 0; p < PT; ++p) {
-            const int t = gi * PT + p;
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                if constexpr (KC == 16 && !DGRAD) {
-                    f[p][cb] = frag_lds<16>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.w + ((int64_t)t * a.Ci + c0)) + wl[cb]));
-                } else if constexpr (KC == 16) {
-#pragma unroll
-                    for (int j = 0; j < KL; ++j)
-                        f[p][cb].v[j] = *reinterpret_cast<const float*>(
-                            reinterpret_cast<const char*>(a.w + ((int64_t)(c0 + j) * 27 + (26 - t)) * a.Co) + wl[cb]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < KL; ++j) {
-                        const int ic = c0 + g * KL + j;
-                        const uint32_t icc = (uint32_t)(ic < a.Ci ? ic : a.Ci - 1);
-                        const uint32_t o = wl[cb] + (DGRAD ? icc * (27u * 4u) * (uint32_t)a.Co : icc * 4u);
-                        const float v = *reinterpret_cast<const float*>(
-                            reinterpret_cast<const char*>(a.w + (int64_t)(DGRAD ? (26 - t) * a.Co : t * a.Ci)) + o);
-                        f[p][cb].v[j] = ic < a.Ci ? v : 0.f;
-                    }
-                }
+        for (int u = 0; u < MAXW; ++u) {
+            if (wt0 + u * TS >= 27) continue;
+            float* o = o0 + u * (TS * CB * QE * 64);
+            if constexpr (DGRAD) {
+                o[0] = pw[u].x;
+                o[4] = pw[u].y;
+                o[8] = pw[u].z;
+                o[12] = pw[u].w;
+            } else {
+                *reinterpret_cast<float4*>(o) = pw[u];
             }
         }
     };
@@ -188,205 +210,415 @@ __global__ __launch_bounds__(256, 2) void conv3d_f32_kernel(F32ConvArgs a) {
     int base[VB];
 #pragma unroll
     for (int vb = 0; vb < VB; ++vb) {
-        const int p = (vg * VB + vb) * 16 + l16;
+        const int p = (wid * VB + vb) * 16 + l16;
         const int w = p & (TW - 1), h = (p >> a.t.lw) & (TH - 1), d = p >> (a.t.lw + a.t.lh);
-        base[vb] = ((d * HH + h) * HW + w) * EST + g * KL;
+        base[vb] = ((d * HH + h) * HW + w) * EST + g;
     }
+    const float* wl = ws + l16 * 4 + g;
     f32x4 acc[CB][VB];
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int vb = 0; vb < VB; ++vb) acc[cb][vb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    Frag<KC> wf[2][PT][CB];
-    fetch(0);
-    wload(0, 0, wf[0]);
-    for (int ch = 0; ch < nchunks; ++ch) {
-        if (ch) __syncthreads();   // every wave is done with the previous chunk
-        stage(ch * KC);
-        __syncthreads();
-        if (ch + 1 < nchunks) fetch((ch + 1) * KC);
+    const int t0 = blockIdx.x * a.per;
+    int t1 = t0 + a.per;
+    if (t1 > a.ntiles) t1 = a.ntiles;
+    if (t0 >= t1) return;
+    locate(t0);
+    fetch_x(0);
+    fetch_w(0);
+    for (int tile = t0; tile < t1; ++tile) {
+        const int n = tile / tiles, tl = tile - n * tiles;
+        float bs[CB][4];
 #pragma unroll
-        for (int gi = 0; gi < NG; ++gi) {
-            // NG is odd: the last group fetches into slot 0 what the next chunk starts with, behind its own use of it
-            if (gi + 1 < NG) wload(ch * KC, gi + 1, wf[(gi + 1) & 1]);
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int p = 0; p < PT; ++p) {
-                const int t = gi * PT + p;
-                const int toff = ((t / 9 * HH + t / 3 % 3) * HW + t % 3) * EST;
-                Frag<KC> b[VB];
+            for (int r = 0; r < 4; ++r) {
+                const int co = co0 + 16 * cb + 4 * g + r;
+                bs[cb][r] = a.bias && co < a.Co ? a.bias[co] : 0.f;
+            }
 #pragma unroll
-                for (int vb = 0; vb < VB; ++vb) b[vb] = frag_lds<KC>(f32_lds + base[vb] + toff);
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) acc[cb][vb] = f32x4{bs[cb][0], bs[cb][1], bs[cb][2], bs[cb][3]};
+        for (int ch = 0; ch < nchunks; ++ch) {
+            if (ch || tile > t0) __syncthreads();   // every wave is done with the previous chunk
+            stage_x(n, ch * KC);
+            if (nchunks > 1 || tile == t0) stage_w();
+            __syncthreads();
+            if (ch + 1 < nchunks) fetch_x((ch + 1) * KC);
+            else if (tile + 1 < t1) {
+                locate(tile + 1);
+                fetch_x(0);
+            }
+            if (nchunks > 1) fetch_w(ch + 1 < nchunks ? (ch + 1) * KC : 0);
+            __builtin_amdgcn_sched_barrier(0);
+            // every step's fragments are read one step ahead; a step is a tap of 8 (4) channels
+            constexpr int STEPS = 27 * QE / KL;
+            float wf[2][CB][KL], b[2][VB][KL];
+            auto frags = [&](int i) __attribute__((always_inline)) {
+                const int t = i % 27, q0 = i / 27 * KL;
+                const int toff = ((t / 9 * HH + t / 3 % 3) * HW + t % 3) * EST + q0 * 4;
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int j = 0; j < KL; ++j) wf[i & 1][cb][j] = wl[((t * CB + cb) * QE + q0 + j) * 64];
+#pragma unroll
+                for (int vb = 0; vb < VB; ++vb)
+#pragma unroll
+                    for (int j = 0; j < KL; ++j) b[i & 1][vb][j] = xs[base[vb] + toff + 4 * j];
+            };
+            frags(0);
+#pragma unroll
+            for (int i = 0; i < STEPS; ++i) {
+                if (i + 1 < STEPS) frags(i + 1);
 #pragma unroll
                 for (int j = 0; j < KL; ++j)
 #pragma unroll
                     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                         for (int vb = 0; vb < VB; ++vb)
-                            acc[cb][vb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[gi & 1][p][cb].v[j], b[vb].v[j], acc[cb][vb], 0, 0, 0);
+                            acc[cb][vb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[i & 1][cb][j], b[i & 1][vb][j], acc[cb][vb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (gi + 1 == NG && ch + 1 < nchunks) wload((ch + 1) * KC, 0, wf[0]);
         }
-    }
 
-    float bs[CB][4], s[CB][4], q[CB][4];
+        const int iw = tl % a.t.nw, r1 = tl / a.t.nw, ih = r1 % a.t.nh, idd = r1 / a.t.nh;
+        const int d0 = idd << a.t.ld, h0 = ih << a.t.lh, w0 = iw << a.t.lw;
+        float s[CB][4], q[CB][4];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int co = co0 + 16 * cb + 4 * g + r;
-            bs[cb][r] = a.bias && co < a.Co ? a.bias[co] : 0.f;
-            s[cb][r] = q[cb][r] = 0.f;
-        }
+            for (int r = 0; r < 4; ++r) s[cb][r] = q[cb][r] = 0.f;
+        int lo = l16;
+        asm volatile("" : "+v"(lo));
 #pragma unroll
-    for (int vb = 0; vb < VB; ++vb) {
-        const int p = (vg * VB + vb) * 16 + l16;
-        const int w = w0 + (p & (TW - 1)), h = h0 + ((p >> a.t.lw) & (TH - 1)), d = d0 + (p >> (a.t.lw + a.t.lh));
-        if (w >= a.W || h >= a.H || d >= a.D) continue;
-        float* zp = a.z + ((((int64_t)n * a.D + d) * a.H + h) * a.W + w) * a.ldz;
+        for (int vb = 0; vb < VB; ++vb) {
+            const int p = (wid * VB + vb) * 16 + lo;
+            const int w = w0 + (p & (TW - 1)), h = h0 + ((p >> a.t.lw) & (TH - 1)), d = d0 + (p >> (a.t.lw + a.t.lh));
+            if (w >= a.W || h >= a.H || d >= a.D) continue;
+            float* zp = a.z + ((((int64_t)n * a.D + d) * a.H + h) * a.W + w) * a.ldz;
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            const int co = co0 + 16 * cb + 4 * g;
-            float v[4];
+            for (int cb = 0; cb < CB; ++cb) {
+                const int co = co0 + 16 * cb + 4 * g;
+                float v[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                v[r] = acc[cb][vb][r] + bs[cb][r];
-                s[cb][r] += v[r];
-                q[cb][r] = fmaf(v[r], v[r], q[cb][r]);
+                for (int r = 0; r < 4; ++r) {
+                    v[r] = acc[cb][vb][r];
+                    s[cb][r] += v[r];
+                    q[cb][r] = fmaf(v[r], v[r], q[cb][r]);
+                }
+                if (a.zvec && co + 4 <= a.Co) *reinterpret_cast<float4*>(zp + co) = make_float4(v[0], v[1], v[2], v[3]);
+                else
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (co + r < a.Co) zp[co + r] = v[r];
             }
-            if (a.zvec && co + 4 <= a.Co) *reinterpret_cast<float4*>(zp + co) = make_float4(v[0], v[1], v[2], v[3]);
-            else
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (co + r < a.Co) zp[co + r] = v[r];
         }
-    }
-    if (!a.partial) return;
-    // sums of the tile per channel: 16 voxel lanes, then the waves that share the channels, in order
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) {
-                s[cb][r] += __shfl_xor(s[cb][r], o);
-                q[cb][r] += __shfl_xor(q[cb][r], o);
-            }
-    __syncthreads();
-    if (l16 == 0)
+        if (!a.partial) continue;
+        // sums of the tile per channel: 16 voxel lanes, then the waves that share the channels, in order
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                float* o = f32_lds + ((wid * CB + cb) * 16 + 4 * g + r) * 2;
-                o[0] = s[cb][r];
-                o[1] = q[cb][r];
+                s[cb][r] = row_sum16(s[cb][r]);
+                q[cb][r] = row_sum16(q[cb][r]);
             }
-    __syncthreads();
-    const int groups = 4 >> a.lvg;
-    if (tid < groups * CB * 16) {
-        const int cg = tid / (CB * 16), c = tid - cg * (CB * 16);
-        const int co = (blockIdx.y * groups + cg) * (16 * CB) + c;
-        float ss = 0.f, qq = 0.f;
-        for (int v = 0; v < (1 << a.lvg); ++v) {
-            const float* o = f32_lds + (((cg << a.lvg) + v) * CB * 16 + c) * 2;
-            ss += o[0];
-            qq += o[1];
+        if (l16 == 0)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    *reinterpret_cast<float2*>(st + ((wid * CB + cb) * 16 + 4 * g + r) * 2) = make_float2(s[cb][r], q[cb][r]);
+        __syncthreads();
+        if (tid < CB * 16) {
+            const int co = co0 + tid;
+            float ss = 0.f, qq = 0.f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float2 o = *reinterpret_cast<const float2*>(st + (v * CB * 16 + tid) * 2);
+                ss += o.x;
+                qq += o.y;
+            }
+            if (co < a.Co) *reinterpret_cast<float2*>(a.partial + (((int64_t)n * tiles + tl) * a.Co + co) * 2) = make_float2(ss, qq);
         }
-        if (co < a.Co) *reinterpret_cast<float2*>(a.partial + (((int64_t)n * tiles + tile) * a.Co + co) * 2) = make_float2(ss, qq);
-    }
-    if (n == 0 && blockIdx.y == 0 && tid == 0) {
-        const int cd = a.D - d0 < TD ? a.D - d0 : TD, chh = a.H - h0 < TH ? a.H - h0 : TH, cw = a.W - w0 < TW ? a.W - w0 : TW;
-        a.counts[tile] = cd * chh * cw;
+        if (n == 0 && blockIdx.y == 0 && tid == 0) {
+            const int cd = a.D - d0 < TD ? a.D - d0 : TD, chh = a.H - h0 < TH ? a.H - h0 : TH, cw = a.W - w0 < TW ? a.W - w0 : TW;
+            a.counts[tl] = cd * chh * cw;
+        }
     }
 }
 
-// Voxel blocks per wave (4, 2, 1) and how the four waves share out voxels and channels.
-struct F32Plan { int vb, cb, lvg; TileGeo t; };
-static F32Plan f32_plan(const lamp_tensor_desc* zd) {
+// Input channels per chunk (4, 8, 16), voxel blocks per wave (4, 2, 1), blocks of 16 output channels per workgroup (2, 1).
+struct F32Plan { int kc, vb, cb; TileGeo t; };
+static F32Plan f32_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
     F32Plan p;
     p.cb = zd->c > 16 ? 2 : 1;
-    p.lvg = 2;
     const int64_t v = (int64_t)zd->d * zd->h * zd->w;
     const int64_t cols = cdiv(zd->c, 16 * p.cb);
     // 256 voxels a workgroup where that gives every CU one, else 128, else 64
     auto blocks = [&](int vox) { return (int64_t)zd->n * ((v + vox - 1) / vox) * cols; };
     p.vb = blocks(256) >= 256 ? 4 : blocks(128) >= 256 ? 2 : 1;
-    if (p.vb == 1 && p.cb == 2 && blocks(64) < 256) { p.cb = 1; p.lvg = 1; }   // 32 voxels x 32 channels
-    const int vox = p.vb * 16 << p.lvg;
+    if (p.vb == 1 && p.cb == 2 && blocks(64) < 256) p.cb = 1;
+    // chunks of 16 where they are filled and registers and LDS hold them beside the weights
+    p.kc = xd->c <= 4 ? 4 : p.cb == 1 && p.vb < 4 && xd->c % 16 == 0 ? 16 : 8;
+    const int vox = p.vb * 64;
     p.t = pick_tile(zd->d, zd->h, zd->w, vox, p.vb == 4 ? 648 : p.vb == 2 ? 432 : 256);
     return p;
 }
 static size_t f32_partial_bytes(const lamp_tensor_desc* zd, const TileGeo& t) {
     return align_up((size_t)zd->n * t.nd * t.nh * t.nw * zd->c * 2 * sizeof(float));
 }
-size_t f32_conv_ws_bytes(const lamp_tensor_desc* zd, int want_stats) {
+size_t f32_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, int want_stats) {
     if (zd->dtype != LAMP_F32 || !want_stats) return 0;
-    const TileGeo t = f32_plan(zd).t;
+    const TileGeo t = f32_plan(xd, zd).t;
     return f32_partial_bytes(zd, t) + align_up((size_t)t.nd * t.nh * t.nw * sizeof(int32_t));
 }
-
-// The grid's limits, and 32-bit offsets inside the weights and the halo of a tile.
+// The grid's limits, and 32-bit voxel offsets inside the halo of a tile.
 bool f32_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
     if (xd->dtype != LAMP_F32) return false;
-    const F32Plan p = f32_plan(zd);
+    const F32Plan p = f32_plan(xd, zd);
     return (int64_t)p.t.nd * p.t.nh * p.t.nw * zd->n < ((int64_t)1 << 31) && cdiv(zd->c, 16) <= 65535 &&
-           (int64_t)xd->c * zd->c * 27 * 4 < ((int64_t)1 << 32) && (int64_t)zd->h * zd->w * 18 < ((int64_t)1 << 31);
+           (int64_t)zd->h * zd->w * 18 < ((int64_t)1 << 31);
 }
 
+static size_t f32_lds_bytes(const F32Plan& p) {
+    const int hv = ((1 << p.t.ld) + 2) * ((1 << p.t.lh) + 2) * ((1 << p.t.lw) + 2);
+    return ((size_t)hv * f32_est(p.kc) + (size_t)27 * p.cb * 16 * p.kc + 128 * p.cb) * sizeof(float);
+}
 template <int KC, bool DGRAD>
 static void f32_launch(const F32Plan& p, dim3 grid, hipStream_t s, const F32ConvArgs& a) {
     constexpr int Q = KC / 4;
-    const int hv = ((1 << p.t.ld) + 2) * ((1 << p.t.lh) + 2) * ((1 << p.t.lw) + 2);
-    size_t lds = (size_t)hv * Frag<KC>::EST * sizeof(float);
-    if (lds < 1024) lds = 1024;   // the statistics' 4 x 32 pairs
-#define LAMP_F32(CB, VB, MK, PT) hipLaunchKernelGGL((conv3d_f32_kernel<KC, CB, VB, MK, PT, DGRAD>), grid, dim3(256), lds, s, a)
+    const size_t lds = f32_lds_bytes(p);
+#define LAMP_F32(CB, VB, MK) hipLaunchKernelGGL((conv3d_f32_kernel<KC, CB, VB, MK, DGRAD>), grid, dim3(256), lds, s, a)
     constexpr int M4 = (648 * Q + 255) / 256, M2 = (432 * Q + 255) / 256, M1 = (256 * Q + 255) / 256;
-    if (p.cb == 2) {
-        if (p.vb == 4) LAMP_F32(2, 4, M4, 3);
-        else if (p.vb == 2) LAMP_F32(2, 2, M2, 3);
-        else LAMP_F32(2, 1, M1, 9);
-    } else {
-        if (p.vb == 4) LAMP_F32(1, 4, M4, 3);
-        else if (p.vb == 2) LAMP_F32(1, 2, M2, 9);
-        else LAMP_F32(1, 1, M1, 9);
-    }
+    if constexpr (KC < 16)
+        if (p.cb == 2) {
+            if (p.vb == 4) LAMP_F32(2, 4, M4);
+            else if (p.vb == 2) LAMP_F32(2, 2, M2);
+            else LAMP_F32(2, 1, M1);
+            return;
+        }
+    if constexpr (KC < 16)
+        if (p.vb == 4) {
+            LAMP_F32(1, 4, M4);
+            return;
+        }
+    if (p.vb == 2) LAMP_F32(1, 2, M2);
+    else LAMP_F32(1, 1, M1);
 #undef LAMP_F32
+}
+
+// More than 64 output channels: each channel of a voxel feeds 64 outputs of a wave, and both operands go straight from the caches to
+// fragments -- a wave = VB blocks of 16 consecutive voxels x CB of 16 output channels, no LDS, no barrier, operands DEPTH - 1
+// steps ahead.  Taps
+// outermost, in a tap the channels in order, one fused multiply-add after the other: bit for bit the sums of conv3d_direct_kernel.
+// Product j contracts channels 4j .. 4j + 3 of a step, one per lane group; a lane loads 4 consecutive ones, and a 4 x 4 transpose
+// between registers and lane groups (4 permlane swaps) hands each to its lane.  VEC: 16-byte loads possible, else 4-byte ones.
+// Bound: the fp32 matrix rate (154 TFLOP/s from registers), and the latency of a step's loads where few waves are in flight: 128->256 on
+// 20 x 28 x 36 55 TFLOP/s, 32->128 on 30 x 29 x 22 109 us; the whole conv unit of that size, forward and backward, 9.30 ms -> 251 us
+// against a thread per output or weight.
+__device__ __forceinline__ void lanes_transpose(float (&v)[4]) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[r]), __float_as_uint(v[r + 2]), false, false);
+        v[r] = __uint_as_float(q[0]);
+        v[r + 2] = __uint_as_float(q[1]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+        const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[r]), __float_as_uint(v[r + 1]), false, false);
+        v[r] = __uint_as_float(q[0]);
+        v[r + 1] = __uint_as_float(q[1]);
+    }
+}
+struct F32WideArgs {
+    const float* x; const float* w; const float* bias; float* z;
+    int ldx, ldz, D, H, W, Ci, Co;
+    int nvox;                          // of all samples
+    int zvec;
+    uint32_t mW, mH, mD; int sW, sH, sD;
+};
+template <bool VEC, int VB, int CB, int DEPTH>
+__global__ __launch_bounds__(256, 2) void conv3d_f32_wide_kernel(F32WideArgs a) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
+    const int v0 = (blockIdx.x * 4 + wid) * (16 * VB), co0 = blockIdx.y * (16 * CB);
+    if (v0 >= a.nvox) return;
+    int64_t xo[VB];                    // element offset of the lane's voxels
+    int pos[VB];                       // which neighbours lie inside: bits d-1, d+1, h-1, h+1, w-1, w+1, voxel itself
+#pragma unroll
+    for (int vb = 0; vb < VB; ++vb) {
+        const uint32_t v = (uint32_t)(v0 + 16 * vb + l16);
+        const uint32_t r = (uint32_t)(((uint64_t)v * a.mW) >> a.sW), w = v - r * (uint32_t)a.W;
+        const uint32_t r2 = (uint32_t)(((uint64_t)r * a.mH) >> a.sH), h = r - r2 * (uint32_t)a.H;
+        const uint32_t n = (uint32_t)(((uint64_t)r2 * a.mD) >> a.sD), d = r2 - n * (uint32_t)a.D;
+        const bool ok = (int)v < a.nvox;
+        xo[vb] = (int64_t)v * a.ldx;
+        pos[vb] = ok ? (d > 0 ? 1 : 0) | ((int)d < a.D - 1 ? 2 : 0) | (h > 0 ? 4 : 0) | ((int)h < a.H - 1 ? 8 : 0) | (w > 0 ? 16 : 0) |
+                           ((int)w < a.W - 1 ? 32 : 0) | 64 : 0;
+    }
+    uint32_t wl[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        int co = co0 + 16 * cb + l16;
+        co = co < a.Co ? co : a.Co - 1;   // rows past the end are computed and not stored
+        wl[cb] = (uint32_t)co * 27u * (uint32_t)a.Ci;
+    }
+    f32x4 acc[CB][VB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        float bs[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int co = co0 + 16 * cb + 4 * g + r;
+            bs[r] = a.bias && co < a.Co ? a.bias[co] : 0.f;
+        }
+#pragma unroll
+        for (int vb = 0; vb < VB; ++vb) acc[cb][vb] = f32x4{bs[0], bs[1], bs[2], bs[3]};
+    }
+    auto get = [&](const float* p, int k0, bool on, float (&f)[4]) __attribute__((always_inline)) {   // channels k0 .. k0 + 15 of p
+        f[0] = f[1] = f[2] = f[3] = 0.f;
+        if constexpr (VEC) {
+            if (on && k0 + 4 * g < a.Ci) {
+                const float4 q = *reinterpret_cast<const float4*>(p + k0 + 4 * g);
+                f[0] = q.x; f[1] = q.y; f[2] = q.z; f[3] = q.w;
+            }
+        } else if (on) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (k0 + 4 * j + g < a.Ci) f[j] = p[k0 + 4 * j + g];
+        }
+    };
+    int t = 0, k0 = 0;
+    auto load = [&](float (&fa)[CB][4], float (&fb)[VB][4]) __attribute__((always_inline)) {
+        const int kd = t / 9, kh = t / 3 - kd * 3, kw = t % 3;
+        const int need = (kd == 0 ? 1 : kd == 2 ? 2 : 0) | (kh == 0 ? 4 : kh == 2 ? 8 : 0) | (kw == 0 ? 16 : kw == 2 ? 32 : 0) | 64;
+        const int64_t off = (((int64_t)(kd - 1) * a.H + (kh - 1)) * a.W + (kw - 1)) * a.ldx;
+#pragma unroll
+        for (int vb = 0; vb < VB; ++vb) get(a.x + (xo[vb] + off), k0, (pos[vb] & need) == need, fb[vb]);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) get(a.w + (int64_t)t * a.Ci + wl[cb], k0, true, fa[cb]);
+        k0 += 16;
+        if (k0 >= a.Ci) { k0 = 0; ++t; }
+    };
+    auto mul = [&](float (&fa)[CB][4], float (&fb)[VB][4]) __attribute__((always_inline)) {
+        if constexpr (VEC) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) lanes_transpose(fa[cb]);
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) lanes_transpose(fb[vb]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int vb = 0; vb < VB; ++vb)
+                    acc[cb][vb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[cb][j], fb[vb][j], acc[cb][vb], 0, 0, 0);
+    };
+    float fa[DEPTH][CB][4], fb[DEPTH][VB][4];
+#pragma unroll
+    for (int u = 0; u < DEPTH - 1; ++u)
+        if (t < 27) load(fa[u], fb[u]);
+    const int steps = 27 * ((a.Ci + 15) / 16);
+    for (int i = 0; i < steps; i += DEPTH) {
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            if (t < 27) load(fa[(u + DEPTH - 1) % DEPTH], fb[(u + DEPTH - 1) % DEPTH]);
+            if (i + u < steps) mul(fa[u], fb[u]);
+        }
+    }
+#pragma unroll
+    for (int vb = 0; vb < VB; ++vb) {
+        if (!pos[vb]) continue;
+        float* zp = a.z + (int64_t)(v0 + 16 * vb + l16) * a.ldz;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const int co = co0 + 16 * cb + 4 * g;
+            if (a.zvec && co + 4 <= a.Co) *reinterpret_cast<float4*>(zp + co) = make_float4(acc[cb][vb][0], acc[cb][vb][1], acc[cb][vb][2], acc[cb][vb][3]);
+            else
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (co + r < a.Co) zp[co + r] = acc[cb][vb][r];
+        }
+    }
+}
+static bool f32_wide(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, const NormIn& nm, bool dgrad) {
+    return !dgrad && !nm.mean_rstd && zd->c > 64 && nvox(zd) < ((int64_t)1 << 30) && (int64_t)27 * xd->c * zd->c < ((int64_t)1 << 32) &&
+           cdiv(zd->c, 16) <= 65535;
+}
+static void f32_wide_launch(const lamp_tensor_desc* xd, const float* x, const float* w, const float* bias, const lamp_tensor_desc* zd,
+                            float* z, hipStream_t s) {
+    F32WideArgs a;
+    a.x = x; a.w = w; a.bias = bias; a.z = z;
+    a.ldx = xd->ldc; a.ldz = zd->ldc;
+    a.D = zd->d; a.H = zd->h; a.W = zd->w; a.Ci = xd->c; a.Co = zd->c;
+    a.nvox = (int)nvox(zd);
+    a.zvec = aligned16(z) && zd->ldc % 4 == 0;
+    f32_magic(a.W, &a.mW, &a.sW);
+    f32_magic(a.H, &a.mH, &a.sH);
+    f32_magic(a.D, &a.mD, &a.sD);
+    const bool vec = aligned16(x) && aligned16(w) && xd->c % 4 == 0 && xd->ldc % 4 == 0;
+    // 64 voxels x 64 channels a wave where that gives every CU half a workgroup at least, else 16 x 16 with more steps in flight
+    const bool big = (int64_t)cdiv(a.nvox, 256) * cdiv(a.Co, 64) >= 128;
+    const dim3 grid(cdiv(a.nvox, big ? 256 : 64), cdiv(a.Co, big ? 64 : 16));
+    if (big) {
+        if (vec) hipLaunchKernelGGL((conv3d_f32_wide_kernel<true, 4, 4, 2>), grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((conv3d_f32_wide_kernel<false, 4, 4, 2>), grid, dim3(256), 0, s, a);
+    } else {
+        if (vec) hipLaunchKernelGGL((conv3d_f32_wide_kernel<true, 1, 1, 8>), grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((conv3d_f32_wide_kernel<false, 1, 1, 8>), grid, dim3(256), 0, s, a);
+    }
 }
 
 lamp_status f32_conv(const lamp_tensor_desc* xd, const float* x, const NormIn& nm, const float* w, const float* bias, bool dgrad,
                      const lamp_tensor_desc* zd, float* z, float* stats_out, float eps, void* ws, size_t ws_bytes, hipStream_t s) {
-    const F32Plan p = f32_plan(zd);
-    const int64_t tiles = (int64_t)p.t.nd * p.t.nh * p.t.nw;
-    const int cols = cdiv(zd->c, 16 * p.cb * (4 >> p.lvg));
     if (!f32_conv_supported(xd, zd)) return LAMP_ERR_UNSUPPORTED;
+    if (f32_wide(xd, zd, nm, dgrad)) {
+        f32_wide_launch(xd, x, w, bias, zd, z, s);
+        LAMP_CHECK_LAUNCH();
+        return stats_out ? launch_stats(zd, z, eps, stats_out, ws, ws_bytes, s) : LAMP_OK;
+    }
+    const F32Plan p = f32_plan(xd, zd);
+    const int tiles = p.t.nd * p.t.nh * p.t.nw;
+    const int cols = cdiv(zd->c, 16 * p.cb);
     F32ConvArgs a;
     a.x = x; a.w = w; a.bias = bias; a.z = z; a.nm = nm;
     a.ldx = xd->ldc; a.ldz = zd->ldc;
     a.N = zd->n; a.D = zd->d; a.H = zd->h; a.W = zd->w; a.Ci = xd->c; a.Co = zd->c;
-    a.t = p.t; a.lvg = p.lvg;
+    a.t = p.t;
     a.xvec = aligned16(x) && xd->c % 4 == 0 && xd->ldc % 4 == 0;
     a.zvec = aligned16(z) && zd->ldc % 4 == 0;
-    // input channels per pass: 16, or 8 / 4 where those fill their chunks better
-    const int kc = xd->c <= 4 ? 4 : xd->c % 16 == 0 && aligned16(w) ? 16 : 8;
+    a.wvec = aligned16(w) && (dgrad ? zd->c : xd->c) % 4 == 0;
+    f32_magic((1 << p.t.lw) + 2, &a.mHW, &a.sHW);
+    f32_magic((1 << p.t.lh) + 2, &a.mHH, &a.sHH);
     a.partial = nullptr; a.counts = nullptr;
     if (stats_out) {
-        if (!ws || ws_bytes < f32_conv_ws_bytes(zd, 1)) return LAMP_ERR_WORKSPACE;
+        if (!ws || ws_bytes < f32_conv_ws_bytes(xd, zd, 1)) return LAMP_ERR_WORKSPACE;
         a.partial = (float*)ws;
         a.counts = (int32_t*)((char*)ws + f32_partial_bytes(zd, p.t));
     }
-    const dim3 grid((unsigned)(tiles * zd->n), cols);
+    // Tiles per workgroup: the CUs multiply at the same rate however many workgroups share one, so the longest CU's tiles count;
+    // of equals the longest walk (it keeps the weights of a single chunk and loads a tile ahead), two workgroups a CU at least.
+    a.ntiles = tiles * zd->n;
+    a.per = 1;
+    int64_t best = -1;
+    for (int per = 1; per <= 16 && (per == 1 || (int64_t)cdiv(a.ntiles, per) * cols > 256); ++per) {
+        const int64_t load = (int64_t)per * (((int64_t)cdiv(a.ntiles, per) * cols + 255) / 256);
+        if (best < 0 || load <= best) {
+            best = load;
+            a.per = per;
+        }
+    }
+    const dim3 grid((unsigned)((a.ntiles + a.per - 1) / a.per), cols);
     if (dgrad) {
-        if (kc == 16) f32_launch<16, true>(p, grid, s, a);
-        else if (kc == 8) f32_launch<8, true>(p, grid, s, a);
+        if (p.kc == 16) f32_launch<16, true>(p, grid, s, a);
+        else if (p.kc == 8) f32_launch<8, true>(p, grid, s, a);
         else f32_launch<4, true>(p, grid, s, a);
     } else {
-        if (kc == 16) f32_launch<16, false>(p, grid, s, a);
-        else if (kc == 8) f32_launch<8, false>(p, grid, s, a);
+        if (p.kc == 16) f32_launch<16, false>(p, grid, s, a);
+        else if (p.kc == 8) f32_launch<8, false>(p, grid, s, a);
         else f32_launch<4, false>(p, grid, s, a);
     }
     LAMP_CHECK_LAUNCH();
-    if (stats_out) return launch_stats_finalize(a.partial, a.counts, (int)tiles, zd->n, zd->c, eps, stats_out, s);
+    if (stats_out) return launch_stats_finalize(a.partial, a.counts, tiles, zd->n, zd->c, eps, stats_out, s);
     return LAMP_OK;
 }
 

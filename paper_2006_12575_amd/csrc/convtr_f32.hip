@@ -38,8 +38,10 @@ __device__ __forceinline__ float4 ctf_ld4(const float* p, bool ok) {
     return q;
 }
 
-// Forward (FWD) and data gradient.  One wave = VB blocks of 16 coarse voxels x RB blocks of 16 rows; a lane's 4 reduction indices of
-// a step are consecutive, so the voxel operand (and the data gradient's weights) arrive 16 bytes at a time, one step ahead.
+// Forward (FWD) and data gradient.  One wave = VB blocks of 16 coarse voxels x RB blocks of 16 rows; operands are loaded
+// one step of 16 reduction indices ahead.  Forward: product j of a step contracts channels 4j .. 4j + 3 one after the other, so a sum
+// starts from the bias and takes the channels in order.  Data gradient: a lane's 4 indices are consecutive, both operands arrive 16
+// bytes at a time.
 template <bool FWD, int VB, int RB>
 __global__ __launch_bounds__(256) void convtr_f32_kernel(CtF32Args a) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
@@ -63,20 +65,37 @@ __global__ __launch_bounds__(256) void convtr_f32_kernel(CtF32Args a) {
     }
     f32x4 acc[RB][VB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int rb = 0; rb < RB; ++rb) {
+        float bs[4] = {0.f, 0.f, 0.f, 0.f};
+        const int r = r0 + 16 * rb + 4 * g;   // Co % 4 == 0: 4 rows of one tap
+        if (FWD && a.bias && r < rows) {
+            const int co = r - (int)ctf_div((uint32_t)r, a.mC, a.sC) * a.Co;
 #pragma unroll
-        for (int vb = 0; vb < VB; ++vb) acc[rb][vb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < 4; ++i) bs[i] = a.bias[co + i];
+        }
+#pragma unroll
+        for (int vb = 0; vb < VB; ++vb) acc[rb][vb] = f32x4{bs[0], bs[1], bs[2], bs[3]};
+    }
     auto load = [&](int k0, float (&fa)[RB][4], float4 (&fb)[VB]) __attribute__((always_inline)) {
-        const int k = k0 + 4 * g;
-        const bool in = k < K;               // K is a multiple of 4
         if constexpr (FWD) {
 #pragma unroll
-            for (int vb = 0; vb < VB; ++vb) fb[vb] = ctf_ld4(a.x + (int64_t)v[vb] * a.ldx + k, ok[vb] && in);
+            for (int vb = 0; vb < VB; ++vb) {
+                const float* p = a.x + (int64_t)v[vb] * a.ldx + k0 + g;
+                fb[vb] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (ok[vb]) {                    // K is a multiple of 4
+                    fb[vb].x = p[0];
+                    if (k0 + 4 < K) fb[vb].y = p[4];
+                    if (k0 + 8 < K) fb[vb].z = p[8];
+                    if (k0 + 12 < K) fb[vb].w = p[12];
+                }
+            }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) fa[rb][j] = in ? a.w[(int64_t)(k + j) * ldw + row[rb]] : 0.f;
+                for (int j = 0; j < 4; ++j) fa[rb][j] = k0 + 4 * j < K ? a.w[(int64_t)(k0 + 4 * j + g) * ldw + row[rb]] : 0.f;
         } else {
+            const int k = k0 + 4 * g;
+            const bool in = k < K;               // K is a multiple of 4
             const int tap = (int)ctf_div((uint32_t)k, a.mC, a.sC), co = k - tap * a.Co;
             const int to = ctf_tap(a, tap);
 #pragma unroll
@@ -113,19 +132,15 @@ __global__ __launch_bounds__(256) void convtr_f32_kernel(CtF32Args a) {
         const int r = r0 + 16 * rb + 4 * g;
         if (r >= rows) continue;
         int64_t off = r;
-        float bs[4] = {0.f, 0.f, 0.f, 0.f};
         if (FWD) {
             const int tap = (int)ctf_div((uint32_t)r, a.mC, a.sC), co = r - tap * a.Co;
             off = (int64_t)ctf_tap(a, tap) * a.ldo + co;
-            if (a.bias)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) bs[i] = a.bias[co + i];
         }
 #pragma unroll
         for (int vb = 0; vb < VB; ++vb)
             if (ok[vb])
                 *reinterpret_cast<float4*>(a.out + (FWD ? fine[vb] : (int64_t)v[vb]) * a.ldo + off) =
-                    make_float4(acc[rb][vb][0] + bs[0], acc[rb][vb][1] + bs[1], acc[rb][vb][2] + bs[2], acc[rb][vb][3] + bs[3]);
+                    make_float4(acc[rb][vb][0], acc[rb][vb][1], acc[rb][vb][2], acc[rb][vb][3]);
     }
 }
 

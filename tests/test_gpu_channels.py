@@ -127,6 +127,10 @@ def test_conv3d_ragged_channels_unaligned_weights(L):
     (1, 41, 40, 44, 16, 24),     # 256-voxel tiles
     (2, 33, 40, 47, 2, 8),
     (1, 41, 40, 44, 9, 12),
+    (1, 5, 6, 7, 3, 72),         # more than 64 output channels: 16-voxel waves, 4-byte and 16-byte loads
+    (2, 4, 9, 11, 20, 100),
+    (1, 33, 32, 34, 16, 128),    # 64-voxel waves
+    (1, 33, 32, 34, 6, 130),
 ], ids=lambda s: "x".join(map(str, s)))
 def test_conv3d_f32(L, shape):
     conv_passes(L, F32, shape, 2400, 1e-4)
