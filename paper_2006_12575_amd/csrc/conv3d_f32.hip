@@ -544,6 +544,9 @@ static bool f32_wide(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, con
     return !dgrad && !nm.mean_rstd && zd->c > 64 && nvox(zd) < ((int64_t)1 << 30) && (int64_t)27 * xd->c * zd->c < ((int64_t)1 << 32) &&
            cdiv(zd->c, 16) <= 65535;
 }
+bool f32_norm_on_load(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
+    return f32_conv_supported(xd, zd) && !f32_wide(xd, zd, make_norm(nullptr), false);
+}
 static void f32_wide_launch(const lamp_tensor_desc* xd, const float* x, const float* w, const float* bias, const lamp_tensor_desc* zd,
                             float* z, hipStream_t s) {
     F32WideArgs a;

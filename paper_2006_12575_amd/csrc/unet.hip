@@ -90,10 +90,12 @@ static lamp_status block_fwd(Net& nt, int l, int Cin, int ldx, const void* x, in
     }
     if (st != LAMP_OK) return st;
     lamp_tensor_desc y1 = nt.td(l, Cout, c1.ldy);
-    // Forward only, the first unit's activated tensor has one consumer, the second conv: where that conv takes the
-    // matrix-core kernel it normalises the raw tensor while it loads it, and the tensor is never written.
+    // Forward only, the first unit's activated tensor has one consumer, the second conv: where that conv takes a
+    // matrix-core kernel it normalises the raw tensor while it loads it, and the tensor is never written (fp32 tiny net, where
+    // a pass more is a launch of 4 us: 162 -> 145 us).
     lamp_norm_in n1{c1.stats, u->affine ? (const float*)P[pi + 1] : nullptr, u->affine ? (const float*)P[pi + 2] : nullptr, Cout, 1};
-    if (nt.fwd_only && !u->se_ratio && !tune("no_norm_on_load", 0) && mfma_conv_supported(&zd, &zd, &n1, nullptr)) {
+    if (nt.fwd_only && !u->se_ratio && !tune("no_norm_on_load", 0) &&
+        (mfma_conv_supported(&zd, &zd, &n1, nullptr) || f32_norm_on_load(&zd, &zd))) {
         st = lamp_conv3d_fwd(&zd, c1.z, &n1, P[pi + pc], nullptr, &zd, c2.z, c2.stats, u->eps, nt.scratch, nt.scratch_bytes, nt.s);
     } else {
         st = lamp_inorm_relu(&zd, c1.z, n1.gamma, n1.beta, u->eps, &y1, c1.y, c1.stats, 1, nullptr, 0, nt.s);
