@@ -18,7 +18,8 @@ namespace lamp {
 // MODE 0 (forward):  sum a, sum mask, sum mask*zhat        (the last two are kept for the backward)
 // MODE 1 (backward): sum dy*a, sum dy*mask, sum dy*mask*zhat
 // partial[((n*chunks + chunk)*C + c)*3 + k]
-template <typename T, int VEC, int MODE>
+// NT (backward): z is read past the caches, so that what they hold at the end is dy for the apply pass.
+template <typename T, int VEC, int MODE, bool NT>
 __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z, int ldz,
                                                          int64_t V, int C, int cthreads, int rl, int rows_per_chunk,
                                                          const float* __restrict__ stats, const float* __restrict__ gamma,
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict_
             typename Vec<T, VEC>::raw vr[4], gr[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                vr[u] = Vec<T, VEC>::raw_load(zb + (r + u * (int64_t)rl) * ldz);
+                vr[u] = Vec<T, VEC>::template raw_load<NT>(zb + (r + u * (int64_t)rl) * ldz);
                 if (MODE == 1) gr[u] = Vec<T, VEC>::raw_load(gb + (r + u * (int64_t)rl) * ldg);
             }
 #pragma unroll
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(256) void se_gate_kernel(const float* __restrict__ 
     }
 }
 
-template <typename T, int VEC, bool RES>
+template <typename T, int VEC, bool RES, bool NT>
 __global__ __launch_bounds__(256) void se_apply_kernel(const T* __restrict__ z, int ldz, const T* __restrict__ res, int ldr,
                                                        T* __restrict__ y, int ldy, int64_t V, int C, int Cr, int cthreads,
                                                        int rl, const float* __restrict__ stats,
@@ -177,18 +178,29 @@ __global__ __launch_bounds__(256) void se_apply_kernel(const T* __restrict__ z, 
     const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
     const T* rb = RES ? res + ((int64_t)n * V) * ldr + (int64_t)cv * VEC : nullptr;
     T* yb = y + ((int64_t)n * V) * ldy + (int64_t)cv * VEC;
-    for (int64_t r = (int64_t)blockIdx.x * rl + r0; r < V; r += (int64_t)gridDim.x * rl) {
-        float v[VEC], q[VEC];
-        Vec<T, VEC>::load(zb + r * ldz, v);
-        if (RES) Vec<T, VEC>::load(rb + r * ldr, q);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            const float u = norm_u(v[i], a[i], b[i]);
-            const float act = u > 0.f ? u : 0.f;
-            v[i] = RES ? fmaf(act, e[i], q[i]) : act * e[i];
+    block_rows(V, rl, r0, [&](int64_t r, bool second) {
+        typename Vec<T, VEC>::raw zq[2], rq[2];
+        zq[0] = Vec<T, VEC>::template raw_load<NT>(zb + r * ldz);
+        if (RES) rq[0] = Vec<T, VEC>::template raw_load<NT>(rb + r * ldr);
+        if (second) {
+            zq[1] = Vec<T, VEC>::template raw_load<NT>(zb + (r + rl) * ldz);
+            if (RES) rq[1] = Vec<T, VEC>::template raw_load<NT>(rb + (r + rl) * ldr);
         }
-        Vec<T, VEC>::store(yb + r * ldy, v);
-    }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (k && !second) break;
+            float v[VEC], q[VEC];
+            Vec<T, VEC>::unpack(zq[k], v);
+            if (RES) Vec<T, VEC>::unpack(rq[k], q);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                const float u = norm_u(v[i], a[i], b[i]);
+                const float act = u > 0.f ? u : 0.f;
+                v[i] = RES ? fmaf(act, e[i], q[i]) : act * e[i];
+            }
+            Vec<T, VEC>::template store<NT>(yb + (r + k * rl) * ldy, v);
+        }
+    });
 }
 
 // Backward of the gate, one workgroup per sample.  s3[n][c][3] as written by the MODE 1 sums.
@@ -274,7 +286,7 @@ __global__ void se_dgb_kernel(const float* __restrict__ sums2, int N, int C, flo
 }
 
 // dz = gamma*rstd * (g - mean_v(g) - zhat * mean_v(g*zhat)),  g = mask * (dy*e + dm/V)
-template <typename T, int VEC>
+template <typename T, int VEC, bool NT>
 __global__ __launch_bounds__(256) void se_bwd_apply_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z, int ldz,
                                                            T* __restrict__ dz, int ldo, int64_t V, int C, int Cr,
                                                            int cthreads, int rl, const float* __restrict__ stats,
@@ -303,19 +315,30 @@ __global__ __launch_bounds__(256) void se_bwd_apply_kernel(const T* __restrict__
     const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
     const T* gb = dy + ((int64_t)n * V) * ldg + (int64_t)cv * VEC;
     T* ob = dz + ((int64_t)n * V) * ldo + (int64_t)cv * VEC;
-    for (int64_t r = (int64_t)blockIdx.x * rl + r0; r < V; r += (int64_t)gridDim.x * rl) {
-        float v[VEC], g[VEC];
-        Vec<T, VEC>::load(zb + r * ldz, v);
-        Vec<T, VEC>::load(gb + r * ldg, g);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            const float u = norm_u(v[i], a[i], b[i]);
-            const float gg = u > 0.f ? fmaf(g[i], e[i], dm[i]) : 0.f;
-            const float zh = (v[i] - mean[i]) * rstd[i];
-            v[i] = a[i] * (gg - c1[i] - zh * c2[i]);
+    block_rows(V, rl, r0, [&](int64_t r, bool second) {
+        typename Vec<T, VEC>::raw q[2], p[2];
+        q[0] = Vec<T, VEC>::template raw_load<NT>(zb + r * ldz);
+        p[0] = Vec<T, VEC>::template raw_load<NT>(gb + r * ldg);
+        if (second) {
+            q[1] = Vec<T, VEC>::template raw_load<NT>(zb + (r + rl) * ldz);
+            p[1] = Vec<T, VEC>::template raw_load<NT>(gb + (r + rl) * ldg);
         }
-        Vec<T, VEC>::store(ob + r * ldo, v);
-    }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (k && !second) break;
+            float v[VEC], g[VEC];
+            Vec<T, VEC>::unpack(q[k], v);
+            Vec<T, VEC>::unpack(p[k], g);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                const float u = norm_u(v[i], a[i], b[i]);
+                const float gg = u > 0.f ? fmaf(g[i], e[i], dm[i]) : 0.f;
+                const float zh = (v[i] - mean[i]) * rstd[i];
+                v[i] = a[i] * (gg - c1[i] - zh * c2[i]);
+            }
+            Vec<T, VEC>::template store<NT>(ob + (r + k * rl) * ldo, v);
+        }
+    });
 }
 
 static int se_apply_blocks(int64_t V, int rl) {
@@ -395,9 +418,10 @@ extern "C" lamp_status lamp_inorm_relu_se(const lamp_tensor_desc* zd, const void
     float* asum = (float*)cv.take((size_t)zd->n * C * 3 * sizeof(float));
     if (!cv.ok()) return LAMP_ERR_WORKSPACE;
     const int vec = pick_vec(zd->dtype, C, {zd->ldc, yd->ldc, residual ? rd->ldc : 0}, {z, y, residual});
+    const bool nt3 = beyond_cache((residual ? 3 : 2) * nvox(zd) * C * (int64_t)esize(zd->dtype));
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(C, VEC);
-        hipLaunchKernelGGL((se_partial_kernel<T, VEC, 0>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s, (const T*)nullptr, 0,
+        hipLaunchKernelGGL((se_partial_kernel<T, VEC, 0, false>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s, (const T*)nullptr, 0,
                            (const T*)z, zd->ldc, V, C, m.cthreads, m.rl, rpc, stats, gamma, beta, partial);
     });
     LAMP_CHECK_LAUNCH();
@@ -409,12 +433,21 @@ extern "C" lamp_status lamp_inorm_relu_se(const lamp_tensor_desc* zd, const void
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(C, VEC);
         const dim3 grid(se_apply_blocks(V, m.rl), zd->n, m.ctiles);
-        if (residual)
-            hipLaunchKernelGGL((se_apply_kernel<T, VEC, true>), grid, dim3(256), 0, s, (const T*)z, zd->ldc, (const T*)residual,
-                               rd->ldc, (T*)y, yd->ldc, V, C, cr, m.cthreads, m.rl, stats, gamma, beta, gate_save);
-        else
-            hipLaunchKernelGGL((se_apply_kernel<T, VEC, false>), grid, dim3(256), 0, s, (const T*)z, zd->ldc, (const T*)nullptr,
-                               0, (T*)y, yd->ldc, V, C, cr, m.cthreads, m.rl, stats, gamma, beta, gate_save);
+        if (nt3) {
+            if (residual)
+                hipLaunchKernelGGL((se_apply_kernel<T, VEC, true, true>), grid, dim3(256), 0, s, (const T*)z, zd->ldc, (const T*)residual,
+                                   rd->ldc, (T*)y, yd->ldc, V, C, cr, m.cthreads, m.rl, stats, gamma, beta, gate_save);
+            else
+                hipLaunchKernelGGL((se_apply_kernel<T, VEC, false, true>), grid, dim3(256), 0, s, (const T*)z, zd->ldc, (const T*)nullptr,
+                                   0, (T*)y, yd->ldc, V, C, cr, m.cthreads, m.rl, stats, gamma, beta, gate_save);
+        } else {
+            if (residual)
+                hipLaunchKernelGGL((se_apply_kernel<T, VEC, true, false>), grid, dim3(256), 0, s, (const T*)z, zd->ldc, (const T*)residual,
+                                   rd->ldc, (T*)y, yd->ldc, V, C, cr, m.cthreads, m.rl, stats, gamma, beta, gate_save);
+            else
+                hipLaunchKernelGGL((se_apply_kernel<T, VEC, false, false>), grid, dim3(256), 0, s, (const T*)z, zd->ldc, (const T*)nullptr,
+                                   0, (T*)y, yd->ldc, V, C, cr, m.cthreads, m.rl, stats, gamma, beta, gate_save);
+        }
     });
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
@@ -448,10 +481,17 @@ extern "C" lamp_status lamp_inorm_relu_se_bwd(const lamp_tensor_desc* dyd, const
     float* dp1 = (float*)cv.take((size_t)N * cr * sizeof(float));
     if (!cv.ok()) return LAMP_ERR_WORKSPACE;
     const int vec = pick_vec(zd->dtype, C, {zd->ldc, dyd->ldc, dzd->ldc}, {z, dy, dz});
+    const int64_t bytes = nvox(zd) * C * (int64_t)esize(zd->dtype);
+    const bool nt2 = beyond_cache(2 * bytes), nt3 = beyond_cache(3 * bytes);
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(C, VEC);
-        hipLaunchKernelGGL((se_partial_kernel<T, VEC, 1>), dim3(chunks, N, m.ctiles), dim3(256), 0, s, (const T*)dy, dyd->ldc,
+        if (nt2) {
+            hipLaunchKernelGGL((se_partial_kernel<T, VEC, 1, true>), dim3(chunks, N, m.ctiles), dim3(256), 0, s, (const T*)dy, dyd->ldc,
                            (const T*)z, zd->ldc, V, C, m.cthreads, m.rl, rpc, stats, gamma, beta, partial);
+        } else {
+            hipLaunchKernelGGL((se_partial_kernel<T, VEC, 1, false>), dim3(chunks, N, m.ctiles), dim3(256), 0, s, (const T*)dy, dyd->ldc,
+                           (const T*)z, zd->ldc, V, C, m.cthreads, m.rl, rpc, stats, gamma, beta, partial);
+        }
     });
     LAMP_CHECK_LAUNCH();
     hipLaunchKernelGGL(se_finalize_kernel<3>, dim3(C, N), dim3(256), 0, s, partial, chunks, C, s3);
@@ -470,9 +510,15 @@ extern "C" lamp_status lamp_inorm_relu_se_bwd(const lamp_tensor_desc* dyd, const
     }
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(C, VEC);
-        hipLaunchKernelGGL((se_bwd_apply_kernel<T, VEC>), dim3(se_apply_blocks(V, m.rl), N, m.ctiles), dim3(256), 0, s,
+        if (nt3) {
+            hipLaunchKernelGGL((se_bwd_apply_kernel<T, VEC, true>), dim3(se_apply_blocks(V, m.rl), N, m.ctiles), dim3(256), 0, s,
                            (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, C, cr, m.cthreads, m.rl, stats,
                            gamma, beta, gate_save, dmv, sums2);
+        } else {
+            hipLaunchKernelGGL((se_bwd_apply_kernel<T, VEC, false>), dim3(se_apply_blocks(V, m.rl), N, m.ctiles), dim3(256), 0, s,
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, C, cr, m.cthreads, m.rl, stats,
+                           gamma, beta, gate_save, dmv, sums2);
+        }
     });
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
