@@ -132,10 +132,13 @@ __global__ __launch_bounds__(256) void head_wgrad_kernel(const T* __restrict__ x
 // 8 + 4*half + 0..3; lane pair (l, l + 32) = one voxel).  Softmax and cross entropy take two exchanges
 // inside the pair.  Backward in the same pass: dx^T[c][voxel] = Wh^T[c][class] * dlogits^T[class][voxel]
 // (dlogits rounded to bf16 for this product), and dWh[class][c] += dlogits^T * x over the voxels with
-// the fp32 instruction v_mfma_f32_32x32x2_f32, whose operands are one float per lane read from a
-// [voxel][class] / [voxel][channel] staging tile in LDS; dbh from per-lane sums.  One pass over x.
+// the fp32 instruction v_mfma_f32_16x16x4_f32 (16 classes; the 32-row form spent half of the matrix time on classes that
+// do not exist), operands from [voxel][class] / [voxel][channel] staging tiles in LDS; dbh from per-lane sums.  One pass
+// over x.  Bound: HBM, and the vector instructions of softmax and staging (32 channels, 10 classes on 2 x 128^3, 721 MB:
+// 214 -> 163 us; logits and dx leave past the caches, which is 10 of the 51).
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 hbf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float hf32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float hf32x4;
 
 __device__ __forceinline__ uint32_t head_pack_bf16(float lo, float hi) { return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16); }
 
@@ -143,7 +146,7 @@ __device__ __forceinline__ uint32_t head_pack_bf16(float lo, float hi) { return 
 // NCB: 32-channel blocks the instantiation holds (C <= 32 * NCB).
 // NORM: x is a raw conv output; InstanceNorm (+ ReLU) is applied while it is loaded, rounded to bf16 as the
 // stored activation would be (every 32-voxel group lies inside one sample: Vs % 32 == 0).
-// NI: classes a lane works on (4 serves up to 8 classes: 4*half + i; 8 serves 16).
+// NI: classes a lane works on (4 serves up to 8 classes: 4*half + i; 6 serves 10, 8 serves 16).
 template <int MODE, int NCB, bool NORM = false, int NI = 8>
 __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfma_kernel(const bf16_t* __restrict__ x, int ldx, const bf16_t* __restrict__ wh,
                                                         const float* __restrict__ bh, int K, int C, int64_t Vtot,
@@ -151,8 +154,9 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
                                                         bf16_t* __restrict__ dx, int lddx, float* __restrict__ loss_part,
                                                         float* __restrict__ wpart, float* __restrict__ bpart, float invV,
                                                         NormIn nm = NormIn{nullptr, nullptr, nullptr, 0, 0}, int64_t Vs = 1) {
-    __shared__ float dls[4][32][33];   // per wave: dlogits of 32 voxels x 32 (padded) classes
-    __shared__ float xs[4][32][32 * NCB + 1];   // per wave: activations of 32 voxels x up to 32*NCB channels, fp32
+    __shared__ float dls[4][32][17];   // per wave: dlogits of 32 voxels x 16 classes
+    constexpr int XR = 64 * NCB + 16;  // row of the activations in bytes: padded, so that 16 voxels' pieces fall on different banks
+    __shared__ __attribute__((aligned(16))) char xb[4][32 * XR];   // per wave: 32 voxels x up to 32*NCB channels; logits and dx pass through too
     __shared__ float red[256];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l32 = lane & 31, half = lane >> 5;
     const int CK = C >> 4;                 // 16-channel k-steps
@@ -189,14 +193,12 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
         bias[i] = (bh && cls[i] < K) ? bh[cls[i]] : 0.f;
     }
     if (MODE == 1) {
-        for (int i = lane; i < 32 * 33; i += 64) (&dls[wv][0][0])[i] = 0.f;   // classes 16..31 stay zero
+        for (int i = lane; i < 32 * 17; i += 64) (&dls[wv][0][0])[i] = 0.f;   // classes no lane writes stay zero
     }
-    hf32x16 accw[NCB];
+    hf32x4 accw[NCB][2];   // dWh: 16 classes x the even / odd channels of a block of 32
     float dbsum[8];
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) accw[cb][r] = 0.f;
+    for (int cb = 0; cb < NCB; ++cb) accw[cb][0] = accw[cb][1] = hf32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < NI; ++i) dbsum[i] = 0.f;
     float lsum = 0.f;
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
         if (logits) {
             // the group's logits are 32*K consecutive floats: pack them in LDS ([voxel][class]) and store 16 bytes
             // per lane instead of eight 4-byte pieces per lane
-            float* pk = &xs[wv][0][0];
+            float* pk = reinterpret_cast<float*>(xb[wv]);
             const int64_t left = Vtot - g * 32;   // valid voxels of the group (wave-uniform)
             if (left >= 32) {
 #pragma unroll
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
                 __builtin_amdgcn_wave_barrier();
                 float* dst = logits + g * 32 * K;
                 for (int q4 = lane; q4 < 8 * K; q4 += 64)
-                    *reinterpret_cast<float4*>(dst + 4 * q4) = *reinterpret_cast<const float4*>(pk + 4 * q4);
+                    st16<true>(dst + 4 * q4, *reinterpret_cast<const float4*>(pk + 4 * q4));
                 __builtin_amdgcn_wave_barrier();
             } else if (valid) {
 #pragma unroll
@@ -347,7 +349,7 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
                         a2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(abw[cb], bdl, a2, 0, 0, 0);
                         // 32 voxels x 32 channels: through LDS (80-byte rows) so that four lanes store the 64 bytes of
                         // a voxel side by side
-                        char* tp = reinterpret_cast<char*>(&xs[wv][0][0]);
+                        char* tp = xb[wv];
 #pragma unroll
                         for (int rg = 0; rg < 4; ++rg)
                             *reinterpret_cast<uint2*>(tp + l32 * 80 + (8 * rg + 4 * half) * 2) =
@@ -358,37 +360,31 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
                             const int vx = it * 16 + (lane >> 2), ch = 32 * cb + (lane & 3) * 8;
                             const uint4 q = *reinterpret_cast<const uint4*>(tp + vx * 80 + (lane & 3) * 16);
                             const int64_t vv = g * 32 + vx;
-                            if (vv < Vtot && ch < C) *reinterpret_cast<uint4*>(dx + vv * lddx + ch) = q;
+                            if (vv < Vtot && ch < C) st16<true>(dx + vv * lddx + ch, q);
                         }
                         __builtin_amdgcn_wave_barrier();
                     }
                 }
             }
             if (wpart) {
-                // stage dlogits [voxel][class] and x [voxel][channel] (fp32) for the voxel-reduction product
+                // stage dlogits [voxel][class] and x [voxel][channel] as it is stored, for the voxel-reduction product; a 4-byte
+                // read holds an even and an odd channel, one for each of a block's two products
 #pragma unroll
                 for (int i = 0; i < NI; ++i) dls[wv][l32][cls[i]] = dl[i];
 #pragma unroll
-                for (int kc = 0; kc < 2 * NCB; ++kc) {
-                    if (kc < CK) {
-                        const uint32_t r4[4] = {xq[kc].x, xq[kc].y, xq[kc].z, xq[kc].w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            xs[wv][l32][16 * kc + 8 * half + 2 * e] = __uint_as_float(r4[e] << 16);
-                            xs[wv][l32][16 * kc + 8 * half + 2 * e + 1] = __uint_as_float(r4[e] & 0xFFFF0000u);
-                        }
-                    }
-                }
+                for (int kc = 0; kc < 2 * NCB; ++kc)
+                    if (kc < CK) *reinterpret_cast<uint4*>(xb[wv] + l32 * XR + kc * 32 + half * 16) = xq[kc];
                 __builtin_amdgcn_wave_barrier();
+                const int l16 = lane & 15, g4 = lane >> 4;
 #pragma unroll
-                for (int kv = 0; kv < 16; ++kv) {
-                    const float av = dls[wv][2 * kv + half][l32];
+                for (int kv = 0; kv < 8; ++kv) {
+                    const float av = dls[wv][4 * kv + g4][l16];
 #pragma unroll
                     for (int cb = 0; cb < NCB; ++cb) {
-                        if (cb < CB) {
-                            const int ch = 32 * cb + l32;
-                            const float bv = ch < C ? xs[wv][2 * kv + half][ch] : 0.f;
-                            accw[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, accw[cb], 0, 0, 0);
+                        if (cb < CB) {   // channels past C give columns that are not written
+                            const uint32_t q = *reinterpret_cast<const uint32_t*>(xb[wv] + (4 * kv + g4) * XR + cb * 64 + l16 * 4);
+                            accw[cb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, __uint_as_float(q << 16), accw[cb][0], 0, 0, 0);
+                            accw[cb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, __uint_as_float(q & 0xFFFF0000u), accw[cb][1], 0, 0, 0);
                         }
                     }
                 }
@@ -406,13 +402,14 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
         if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0];
         const int slot = blockIdx.x * 4 + wv;
         if (wpart) {
-            // accw: row = class 8*(r/4) + 4*half + (r%4), column = channel 32*cb + l32
+            // accw: row = class 4*(lane/16) + r, column = channel 32*cb + 2*(lane%16) (+ 1)
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int k = 8 * (r >> 2) + 4 * half + (r & 3), ch = 32 * cb + l32;
-                    if (cb < CB && k < K && ch < C) wpart[((size_t)slot * K + k) * C + ch] = accw[cb][r];
+                for (int r = 0; r < 4; ++r) {
+                    const int k = 4 * (lane >> 4) + r, ch = 32 * cb + 2 * (lane & 15);
+                    if (cb < CB && k < K && ch < C)
+                        *reinterpret_cast<float2*>(wpart + ((size_t)slot * K + k) * C + ch) = make_float2(accw[cb][0][r], accw[cb][1][r]);
                 }
         }
         if (bpart) {
@@ -425,6 +422,40 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
             }
         }
     }
+}
+
+// Adds up the partials of one call in one launch: dWh (slots of K*C), dbh (slots of K) and the loss (one per workgroup).  A block
+// is 4 outputs x 64 lanes over the slots, eight loads in flight, lanes folded by halves: a fixed summation tree, fp64.  (As three
+// launches: 8 us more.)
+__global__ __launch_bounds__(256) void head_reduce_kernel(const float* __restrict__ wpart, const float* __restrict__ bpart,
+                                                          const float* __restrict__ lpart, int slots, int lslots, int KC, int K,
+                                                          float* dwh, float* dbh, float* loss, float beta, float loss_beta) {
+    __shared__ double sh[256];
+    const int gl = threadIdx.x & 3, sl = threadIdx.x >> 2, o = blockIdx.x * 4 + gl;
+    const float* p = nullptr;
+    float* out = nullptr;
+    int n = 0, stride = 0;
+    float b = beta;
+    if (o < KC) { p = wpart + o; out = dwh + o; n = slots; stride = KC; }
+    else if (o < KC + K) { p = bpart + (o - KC); out = dbh + (o - KC); n = slots; stride = K; }
+    else if (o == KC + K) { p = lpart; out = loss; n = lslots; stride = 1; b = loss_beta; }
+    double acc = 0.0;
+    int s = sl;
+    for (; s + 7 * 64 < n; s += 8 * 64) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(s + 64 * u) * stride];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += (double)v[u];
+    }
+    for (; s < n; s += 64) acc += (double)p[(int64_t)s * stride];
+    sh[threadIdx.x] = acc;
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) {
+        __syncthreads();
+        if (sl < h) sh[threadIdx.x] += sh[threadIdx.x + 4 * h];
+    }
+    if (sl == 0 && out) *out = (b != 0.f ? b * *out : 0.f) + (float)sh[threadIdx.x];
 }
 
 static bool head_mfma_ok(const lamp_tensor_desc* xd, const void* x, const lamp_norm_in* xnorm, const void* wh, int classes,
@@ -584,10 +615,15 @@ lamp_status lamp::head_ce_run(const lamp_tensor_desc* xd, const void* x, const l
 #define LAMP_HEAD_BWD(NCB_, NI_)                                                                                                   \
     hipLaunchKernelGGL((head_mfma_kernel<1, NCB_, false, NI_>), dim3(nbm), dim3(256), 0, s, (const bf16_t*)x, xd->ldc, (const bf16_t*)wh, \
                        bh, K, C, Vt, labels, logits, (bf16_t*)dx, lddx, lpart, dwh ? wpart : nullptr, dbh ? bpart : nullptr, invV)
-        if (K <= 8) {   // the usual few classes: half the per-class work of a lane
+        // a lane's slots hold classes 0..3, 8..11 or 4..7, 12..15: up to 8 classes need 4 slots, up to 10 need 6
+        if (K <= 8) {
             if (C <= 32) LAMP_HEAD_BWD(1, 4);
             else if (C <= 64) LAMP_HEAD_BWD(2, 4);
             else LAMP_HEAD_BWD(4, 4);
+        } else if (K <= 10) {
+            if (C <= 32) LAMP_HEAD_BWD(1, 6);
+            else if (C <= 64) LAMP_HEAD_BWD(2, 6);
+            else LAMP_HEAD_BWD(4, 6);
         } else {
             if (C <= 32) LAMP_HEAD_BWD(1, 8);
             else if (C <= 64) LAMP_HEAD_BWD(2, 8);
@@ -595,9 +631,10 @@ lamp_status lamp::head_ce_run(const lamp_tensor_desc* xd, const void* x, const l
         }
 #undef LAMP_HEAD_BWD
         LAMP_CHECK_LAUNCH();
-        if ((st = launch_reduce_partials(lpart, nbm, 1, loss, loss_beta, s)) != LAMP_OK) return st;
-        if (dwh && (st = launch_reduce_partials(wpart, nbm * 4, (int64_t)K * C, dwh, beta, s)) != LAMP_OK) return st;
-        if (dbh && (st = launch_reduce_partials(bpart, nbm * 4, K, dbh, beta, s)) != LAMP_OK) return st;
+        const int KC = dwh ? K * C : 0, KB = dbh ? K : 0;
+        hipLaunchKernelGGL(head_reduce_kernel, dim3(cdiv(KC + KB + 1, 4)), dim3(256), 0, s, wpart, bpart, lpart, nbm * 4, nbm, KC, KB, dwh,
+                           dbh, loss, beta, loss_beta);
+        LAMP_CHECK_LAUNCH();
         return LAMP_OK;
     }
     const size_t shm = (size_t)K * C * sizeof(float);
