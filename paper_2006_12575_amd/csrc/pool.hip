@@ -6,6 +6,118 @@
 
 namespace lamp {
 
+// The optional normalise+ReLU-on-load of VEC channels from c0 on, coefficients fetched once.
+template <typename T, int VEC> struct NormVec {
+    float a[VEC], b[VEC];
+    int left;    // channels of the vector that are normalised
+    int relu;
+    __device__ __forceinline__ NormVec(const NormIn& nm, int n, int c0) : left(nm.mean_rstd ? nm.c_norm - c0 : 0), relu(nm.relu) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            a[i] = 1.f;
+            b[i] = 0.f;
+            if (i < left) norm_coeffs(nm, n, c0 + i, a[i], b[i]);
+        }
+    }
+    __device__ __forceinline__ void apply(float (&v)[VEC]) const {
+        if (left <= 0) return;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i)
+            if (i < left) {
+                float u = norm_u(v[i], a[i], b[i]);
+                if (relu) u = u > 0.f ? u : 0.f;
+                v[i] = io<T>::rnd(u);
+            }
+    }
+};
+// Work item = (pooled voxel, channel vector), 64 consecutive ones to a wave.
+// PAIR: the two voxels of a w pair lie side by side in memory, so the lower 32 lanes fetch the first voxel of 32 items, the upper 32
+// the second: an instruction covers a contiguous run (with both voxels on one lane it touches every other 64 bytes at 32 channels),
+// and a swap of register halves between the lanes of two such fetches gives every lane both voxels of its own item; stores of the
+// full-resolution tensor go back the same way.  For passes beyond the memory-side cache, where it pairs with non-temporal accesses:
+// backward of 2 x 128^3 x 32 with the skip's gradient (840 MB) 195 -> 146 us; on 2 x 64^3 x 64, which the cache holds, the second
+// item's index arithmetic costs more than it gives (33 -> 40 us).
+struct PoolItem { int cv, n; int64_t ov, iv; bool ok; };   // channel vector, sample, pooled voxel, input voxel (2d, 2h, 2w)
+template <typename I> __device__ __forceinline__ PoolItem pool_item_t(I i, I total, int Do, int Ho, int Wo, int CV) {
+    PoolItem p;
+    p.ok = i < total;
+    if (!p.ok) i = 0;
+    const I ov = i / (I)CV, r = ov / (I)Wo, r2 = r / (I)Ho, n = r2 / (I)Do;
+    const int w = (int)(ov - r * (I)Wo), h = (int)(r - r2 * (I)Ho), d = (int)(r2 - n * (I)Do);
+    p.cv = (int)(i - ov * (I)CV);
+    p.n = (int)n;
+    p.ov = (int64_t)ov;
+    p.iv = (((int64_t)n * 2 * Do + 2 * d) * 2 * Ho + 2 * h) * 2 * Wo + 2 * w;
+    return p;
+}
+__device__ __forceinline__ PoolItem pool_item(int64_t i, int64_t total, int Do, int Ho, int Wo, int CV) {
+    if (total <= (int64_t)0x7FFFFFFF - 64) return pool_item_t<uint32_t>((uint32_t)i, (uint32_t)total, Do, Ho, Wo, CV);
+    return pool_item_t<int64_t>(i, total, Do, Ho, Wo, CV);
+}
+// Swaps the upper lanes of a with the lower lanes of b, dword by dword; applied twice it changes nothing.
+template <typename R> __device__ __forceinline__ void pair_swap(R& a, R& b) {
+    if constexpr (sizeof(R) == 16) {
+        vec_u32x4 u = __builtin_bit_cast(vec_u32x4, a), v = __builtin_bit_cast(vec_u32x4, b);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const auto q = __builtin_amdgcn_permlane32_swap(u[i], v[i], false, false);
+            u[i] = q[0];
+            v[i] = q[1];
+        }
+        a = __builtin_bit_cast(R, u);
+        b = __builtin_bit_cast(R, v);
+    } else {
+        const auto q = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+        a = __builtin_bit_cast(R, (uint32_t)q[0]);
+        b = __builtin_bit_cast(R, (uint32_t)q[1]);
+    }
+}
+// PAIR: the wave's two fetches (items j and j + 32) and this lane's own item; else the own item only.
+struct PoolWave { PoolItem f0, f1, own; int par; };
+template <bool PAIR> __device__ __forceinline__ PoolWave pool_wave(int64_t total, int Do, int Ho, int Wo, int CV) {
+    const int lane = threadIdx.x & 63;
+    if constexpr (!PAIR) {
+        const PoolItem o = pool_item((int64_t)blockIdx.x * 256 + threadIdx.x, total, Do, Ho, Wo, CV);
+        return PoolWave{o, o, o, 0};
+    }
+    const int64_t j = (int64_t)blockIdx.x * 256 + (threadIdx.x & ~63) + (lane & 31);
+    PoolWave w;
+    w.par = lane >> 5;
+    w.f0 = pool_item(j, total, Do, Ho, Wo, CV);
+    w.f1 = pool_item(j + 32, total, Do, Ho, Wo, CV);
+    w.own = PoolItem{w.par ? w.f1.cv : w.f0.cv, w.par ? w.f1.n : w.f0.n, w.par ? w.f1.ov : w.f0.ov, 0, w.par ? w.f1.ok : w.f0.ok};
+    return w;
+}
+// Both voxels of the own item in row pair (i, j): q0 the first, q1 the second of the w pair.
+template <typename T, int VEC, bool NT>
+__device__ __forceinline__ void pool_load(const T* x, int ld, const PoolWave& w, int64_t off, typename Vec<T, VEC>::raw& q0,
+                                          typename Vec<T, VEC>::raw& q1) {
+    q0 = q1 = typename Vec<T, VEC>::raw{};
+    if constexpr (!NT) {
+        if (!w.own.ok) return;
+        q0 = Vec<T, VEC>::raw_load(x + (w.own.iv + off) * ld + w.own.cv * VEC);
+        q1 = Vec<T, VEC>::raw_load(x + (w.own.iv + off + 1) * ld + w.own.cv * VEC);
+        return;
+    }
+    if (w.f0.ok) q0 = Vec<T, VEC>::template raw_load<NT>(x + (w.f0.iv + off + w.par) * ld + w.f0.cv * VEC);
+    if (w.f1.ok) q1 = Vec<T, VEC>::template raw_load<NT>(x + (w.f1.iv + off + w.par) * ld + w.f1.cv * VEC);
+    pair_swap(q0, q1);
+}
+template <typename T, int VEC, bool NT>
+__device__ __forceinline__ void pool_store(T* y, int ld, const PoolWave& w, int64_t off, const float (&v0)[VEC], const float (&v1)[VEC]) {
+    typename Vec<T, VEC>::raw q0 = Vec<T, VEC>::pack(v0), q1 = Vec<T, VEC>::pack(v1);
+    if constexpr (!NT) {
+        if (!w.own.ok) return;
+        Vec<T, VEC>::raw_store(y + (w.own.iv + off) * ld + w.own.cv * VEC, q0);
+        Vec<T, VEC>::raw_store(y + (w.own.iv + off + 1) * ld + w.own.cv * VEC, q1);
+        return;
+    }
+    pair_swap(q0, q1);
+    if (w.f0.ok) Vec<T, VEC>::template raw_store<NT>(y + (w.f0.iv + off + w.par) * ld + w.f0.cv * VEC, q0);
+    if (w.f1.ok) Vec<T, VEC>::template raw_store<NT>(y + (w.f1.iv + off + w.par) * ld + w.f1.cv * VEC, q1);
+}
+
+// Forward (paired fetches and non-temporal accesses cost here: 2 x 128^3 x 32 with the activated tensor written 105 -> 120 us).
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void maxpool2_fwd_kernel(const T* __restrict__ x, int ldx, NormIn nm, T* __restrict__ y,
                                                            int ldy, int N, int Do, int Ho, int Wo, int C,
@@ -64,51 +176,55 @@ __global__ __launch_bounds__(256) void maxpool2_fwd_kernel(const T* __restrict__
     Vec<T, VEC>::store(y + ov * ldy + cv * VEC, m);
 }
 
-template <typename T, int VEC>
+// Bound: HBM.  NT (passes beyond the memory-side cache): PAIR, and full-resolution tensors are read and written past the caches.
+template <typename T, int VEC, bool NT>
 __global__ __launch_bounds__(256) void maxpool2_bwd_kernel(const T* __restrict__ x, int ldx, NormIn nm,
                                                            const T* __restrict__ dy, int ldg, const T* __restrict__ add,
                                                            int lda, T* __restrict__ dx, int ldo, int N, int Do, int Ho,
                                                            int Wo, int C) {
     const int CV = C / VEC;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t total = (int64_t)N * Do * Ho * Wo * CV;
-    if (idx >= total) return;
-    const int cv = (int)(idx % CV);
-    int64_t ov = idx / CV;
-    const int w = (int)(ov % Wo);
-    int64_t r = ov / Wo;
-    const int h = (int)(r % Ho);
-    r /= Ho;
-    const int d = (int)(r % Do);
-    const int n = (int)(r / Do);
-    const int H = 2 * Ho, W = 2 * Wo, D = 2 * Do;
+    const PoolWave w = pool_wave<NT>(total, Do, Ho, Wo, CV);
+    typename Vec<T, VEC>::raw q[8], qa[8];
+    int64_t off[4];
+    auto gr = typename Vec<T, VEC>::raw{};
+    if (w.own.ok) gr = Vec<T, VEC>::raw_load(dy + w.own.ov * ldg + w.own.cv * VEC);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        off[t] = ((int64_t)(t >> 1) * 2 * Ho + (t & 1)) * 2 * Wo;
+        pool_load<T, VEC, NT>(x, ldx, w, off[t], q[2 * t], q[2 * t + 1]);
+        if (add) pool_load<T, VEC, NT>(add, lda, w, off[t], qa[2 * t], qa[2 * t + 1]);
+    }
+    NormVec<T, VEC> nv(nm, w.own.n, w.own.cv * VEC);
     float m[VEC];
     int arg[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) { m[i] = -INFINITY; arg[i] = 0; }
+#pragma unroll
     for (int t = 0; t < 8; ++t) {
-        int i = t >> 2, j = (t >> 1) & 1, k = t & 1;
-        const T* p = x + ((((int64_t)n * D + 2 * d + i) * H + 2 * h + j) * W + 2 * w + k) * ldx + cv * VEC;
         float v[VEC];
-        load_norm_vec<T, VEC>(p, nm, n, cv * VEC, v);
+        Vec<T, VEC>::unpack(q[t], v);
+        nv.apply(v);
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
             if (v[e] > m[e]) { m[e] = v[e]; arg[e] = t; }
     }
     float g[VEC];
-    Vec<T, VEC>::load(dy + ov * ldg + cv * VEC, g);
-    for (int t = 0; t < 8; ++t) {
-        int i = t >> 2, j = (t >> 1) & 1, k = t & 1;
-        int64_t iv = (((int64_t)n * D + 2 * d + i) * H + 2 * h + j) * W + 2 * w + k;
-        float o[VEC];
-        if (add) Vec<T, VEC>::load(add + iv * lda + cv * VEC, o);
-        else {
+    Vec<T, VEC>::unpack(gr, g);
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) o[e] = 0.f;
+    for (int t = 0; t < 4; ++t) {
+        float o[2][VEC];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (add) Vec<T, VEC>::unpack(qa[2 * t + k], o[k]);
+            else {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) o[k][e] = 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) o[k][e] += (arg[e] == 2 * t + k) ? g[e] : 0.f;
         }
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) o[e] += (arg[e] == t) ? g[e] : 0.f;
-        Vec<T, VEC>::store(dx + iv * ldo + cv * VEC, o);
+        pool_store<T, VEC, NT>(dx, ldo, w, off[t], o[0], o[1]);
     }
 }
 
@@ -141,7 +257,7 @@ lamp_status lamp::inorm_relu_maxpool2(const lamp_tensor_desc* xd, const void* z,
     LAMP_DISPATCH_TV(xd->dtype, vec, {
         int64_t total = nvox(yd) * (xd->c / VEC);
         hipLaunchKernelGGL((maxpool2_fwd_kernel<T, VEC>), dim3(cdiv(total, 256)), dim3(256), 0, s, (const T*)z, xd->ldc, nm,
-                           (T*)y, yd->ldc, yd->n, yd->d, yd->h, yd->w, xd->c, (T*)yfull, ldyf);
+                       (T*)y, yd->ldc, yd->n, yd->d, yd->h, yd->w, xd->c, (T*)yfull, ldyf);
     });
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
@@ -158,7 +274,7 @@ extern "C" lamp_status lamp_maxpool2_fwd(const lamp_tensor_desc* xd, const void*
     LAMP_DISPATCH_TV(xd->dtype, vec, {
         int64_t total = nvox(yd) * (xd->c / VEC);
         hipLaunchKernelGGL((maxpool2_fwd_kernel<T, VEC>), dim3(cdiv(total, 256)), dim3(256), 0, (hipStream_t)stream,
-                           (const T*)x, xd->ldc, nm, (T*)y, yd->ldc, yd->n, yd->d, yd->h, yd->w, xd->c);
+                       (const T*)x, xd->ldc, nm, (T*)y, yd->ldc, yd->n, yd->d, yd->h, yd->w, xd->c);
     });
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
@@ -182,11 +298,18 @@ extern "C" lamp_status lamp_maxpool2_bwd(const lamp_tensor_desc* xd, const void*
     if ((st = norm_ok(xnorm, xd)) != LAMP_OK) return st;
     const int vec = pick_vec(xd->dtype, xd->c, {xd->ldc, dyd->ldc, dxd->ldc, add ? lda : xd->ldc}, {x, dy, dx, add});
     NormIn nm = make_norm(xnorm);
+    const bool nt = beyond_cache(2 * nvox(xd) * xd->c * (int64_t)esize(xd->dtype));
     LAMP_DISPATCH_TV(xd->dtype, vec, {
         int64_t total = nvox(dyd) * (xd->c / VEC);
-        hipLaunchKernelGGL((maxpool2_bwd_kernel<T, VEC>), dim3(cdiv(total, 256)), dim3(256), 0, (hipStream_t)stream,
+        if (nt) {
+            hipLaunchKernelGGL((maxpool2_bwd_kernel<T, VEC, true>), dim3(cdiv(total, 256)), dim3(256), 0, (hipStream_t)stream,
                            (const T*)x, xd->ldc, nm, (const T*)dy, dyd->ldc, (const T*)add, lda, (T*)dx, dxd->ldc,
                            dyd->n, dyd->d, dyd->h, dyd->w, xd->c);
+        } else {
+            hipLaunchKernelGGL((maxpool2_bwd_kernel<T, VEC, false>), dim3(cdiv(total, 256)), dim3(256), 0, (hipStream_t)stream,
+                           (const T*)x, xd->ldc, nm, (const T*)dy, dyd->ldc, (const T*)add, lda, (T*)dx, dxd->ldc,
+                           dyd->n, dyd->d, dyd->h, dyd->w, xd->c);
+        }
     });
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;

@@ -37,27 +37,31 @@ template <> struct Vec<bf16_t, 8> {
     static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
         unpack(raw_load(p), v);
     }
-    template <bool NT = false> static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8]) {
+    static __device__ __forceinline__ raw pack(const float (&v)[8]) {
         uint32_t r[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) r[i] = (uint32_t)f2bf(v[2 * i]) | ((uint32_t)f2bf(v[2 * i + 1]) << 16);
-        st16<NT>(p, make_uint4(r[0], r[1], r[2], r[3]));
+        return make_uint4(r[0], r[1], r[2], r[3]);
     }
+    template <bool NT = false> static __device__ __forceinline__ void raw_store(bf16_t* p, const raw& q) { st16<NT>(p, q); }
+    template <bool NT = false> static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8]) { st16<NT>(p, pack(v)); }
 };
 template <> struct Vec<float, 4> {
     typedef float4 raw;
     template <bool NT = false> static __device__ __forceinline__ raw raw_load(const float* p) { return ld16<NT, raw>(p); }
     static __device__ __forceinline__ void unpack(const raw& q, float (&v)[4]) { v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w; }
     static __device__ __forceinline__ void load(const float* p, float (&v)[4]) { unpack(raw_load(p), v); }
-    template <bool NT = false> static __device__ __forceinline__ void store(float* p, const float (&v)[4]) {
-        st16<NT>(p, make_float4(v[0], v[1], v[2], v[3]));
-    }
+    static __device__ __forceinline__ raw pack(const float (&v)[4]) { return make_float4(v[0], v[1], v[2], v[3]); }
+    template <bool NT = false> static __device__ __forceinline__ void raw_store(float* p, const raw& q) { st16<NT>(p, q); }
+    template <bool NT = false> static __device__ __forceinline__ void store(float* p, const float (&v)[4]) { st16<NT>(p, pack(v)); }
 };
 template <typename T> struct Vec<T, 1> {
     typedef float raw;
     template <bool NT = false> static __device__ __forceinline__ raw raw_load(const T* p) { return io<T>::ld(p); }
     static __device__ __forceinline__ void unpack(const raw& q, float (&v)[1]) { v[0] = q; }
     static __device__ __forceinline__ void load(const T* p, float (&v)[1]) { v[0] = io<T>::ld(p); }
+    static __device__ __forceinline__ raw pack(const float (&v)[1]) { return v[0]; }
+    template <bool NT = false> static __device__ __forceinline__ void raw_store(T* p, const raw& q) { io<T>::st(p, q); }
     template <bool NT = false> static __device__ __forceinline__ void store(T* p, const float (&v)[1]) { io<T>::st(p, v[0]); }
 };
 
