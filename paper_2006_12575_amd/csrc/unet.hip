@@ -908,19 +908,28 @@ __global__ __launch_bounds__(256) void sw_gather_kernel(const T* __restrict__ vo
     win[idx] = vol[((((int64_t)(d0 + i)) * H + (h0 + j)) * W + (w0 + k)) * C + c];
 }
 
-// One thread per volume voxel: gathers every covering window in d-major, h, w order.
+// Weighted mean of every covering window's logits in d-major, h, w order.  A block = NU * 256 pieces of E consecutive floats of one
+// (d, h) row of the volume: whatever the classes, its lanes read consecutive memory of a window and write consecutive memory, and
+// the windows along d and h are the same for the whole block.  Bound: HBM (every window voxel is read once).  A thread per voxel with
+// its K floats touched 20 lines an instruction: 75 windows of 64^3 over 256 x 256 x 160, ten classes (1.2 GB): 432 -> 350 us.
+template <int E, int NU>
 __global__ __launch_bounds__(256) void sw_blend_kernel(const float* __restrict__ wl, float* __restrict__ out, int D, int H,
                                                        int W, int K, int P, int stride, int cd, int ch, int cw,
                                                        float inv2s2) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v >= (int64_t)D * H * W) return;
-    const int w = (int)(v % W), h = (int)((v / W) % H), d = (int)(v / ((int64_t)W * H));
+    const int row = blockIdx.y + (int)gridDim.y * blockIdx.z;
+    if (row >= D * H) return;
+    const int d = row / H, h = row - d * H;
     const float m = 0.5f * (P - 1);
-    const bool even = (K & 1) == 0;
-    float acc[16];
+    int fl[NU], w[NU];   // the piece's first float in the row, its voxel
+    float acc[NU][E], wsum[NU];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) acc[k] = 0.f;
-    float wsum = 0.f;
+    for (int u = 0; u < NU; ++u) {
+        fl[u] = ((blockIdx.x * NU + u) * 256 + threadIdx.x) * E;
+        w[u] = fl[u] < W * K ? fl[u] / K : -P;   // no window covers -P
+        wsum[u] = 0.f;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[u][e] = 0.f;
+    }
     for (int id = 0; id < cd; ++id) {
         int d0 = id * stride; if (d0 > D - P) d0 = D - P;
         if (d < d0 || d >= d0 + P) continue;
@@ -931,39 +940,45 @@ __global__ __launch_bounds__(256) void sw_blend_kernel(const float* __restrict__
             const float fh = (h - h0) - m;
             for (int iw = 0; iw < cw; ++iw) {
                 int w0 = iw * stride; if (w0 > W - P) w0 = W - P;
-                if (w < w0 || w >= w0 + P) continue;
-                const float fw = (w - w0) - m;
-                const float g = expf(-(fd * fd + fh * fh + fw * fw) * inv2s2);
                 const int wi = (id * ch + ih) * cw + iw;
-                const float* p = wl + ((((int64_t)wi * P + (d - d0)) * P + (h - h0)) * P + (w - w0)) * K;
-                if (even) {   // a voxel's K floats start on an 8-byte boundary: half as many load instructions
-                    const float2* p2 = reinterpret_cast<const float2*>(p);
+                const float* p = wl + ((((int64_t)wi * P + (d - d0)) * P + (h - h0)) * P - w0) * K;
 #pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        if (2 * k < K) {
-                            const float2 t = p2[k];
-                            acc[2 * k] = fmaf(g, t.x, acc[2 * k]);
-                            acc[2 * k + 1] = fmaf(g, t.y, acc[2 * k + 1]);
-                        }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 16; ++k)
-                        if (k < K) acc[k] = fmaf(g, p[k], acc[k]);
+                for (int u = 0; u < NU; ++u) {
+                    if (w[u] < w0 || w[u] >= w0 + P) continue;
+                    const float fw = (w[u] - w0) - m;
+                    const float g = expf(-(fd * fd + fh * fh + fw * fw) * inv2s2);
+                    if constexpr (E == 2) {
+                        const float2 t = *reinterpret_cast<const float2*>(p + fl[u]);
+                        acc[u][0] = fmaf(g, t.x, acc[u][0]);
+                        acc[u][1] = fmaf(g, t.y, acc[u][1]);
+                    } else {
+                        acc[u][0] = fmaf(g, p[fl[u]], acc[u][0]);
+                    }
+                    wsum[u] += g;
                 }
-                wsum += g;
             }
         }
     }
-    if (even) {
-        float2* o2 = reinterpret_cast<float2*>(out + v * K);
+    float* o = out + (int64_t)row * W * K;
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (2 * k < K) o2[k] = make_float2(acc[2 * k] / wsum, acc[2 * k + 1] / wsum);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-            if (k < K) out[v * K + k] = acc[k] / wsum;
+    for (int u = 0; u < NU; ++u) {
+        if (w[u] < 0) continue;
+        if constexpr (E == 2) *reinterpret_cast<float2*>(o + fl[u]) = make_float2(acc[u][0] / wsum[u], acc[u][1] / wsum[u]);
+        else o[fl[u]] = acc[u][0] / wsum[u];
     }
+}
+template <int E>
+static void sw_blend_launch(const float* wl, float* out, int D, int H, int W, int K, int P, int stride, int cd, int ch, int cw,
+                            float inv2s2, hipStream_t s) {
+    const int n = cdiv((int64_t)W * K, E), rows = D * H;
+    const int gy = rows < 65535 ? rows : 65535, gz = cdiv(rows, gy);
+    // as many pieces a thread as the row has, up to four: their loads are in flight together
+    if (n > 512)
+        hipLaunchKernelGGL((sw_blend_kernel<E, 4>), dim3(cdiv(n, 1024), gy, gz), dim3(256), 0, s, wl, out, D, H, W, K, P, stride, cd, ch, cw, inv2s2);
+    else if (n > 256)
+        hipLaunchKernelGGL((sw_blend_kernel<E, 2>), dim3(1, gy, gz), dim3(256), 0, s, wl, out, D, H, W, K, P, stride, cd, ch, cw, inv2s2);
+    else
+        hipLaunchKernelGGL((sw_blend_kernel<E, 1>), dim3(1, gy, gz), dim3(256), 0, s, wl, out, D, H, W, K, P, stride, cd, ch, cw, inv2s2);
 }
 
 }  // namespace lamp
@@ -1014,8 +1029,11 @@ extern "C" lamp_status lamp_sliding_window_fwd(const lamp_unet_desc* pd, const v
     LAMP_CHECK_LAUNCH();
     if ((st = lamp_unet_fwd(pd, params, win, wl, uws, ub, stream)) != LAMP_OK) return st;
     const float sg = sigma_scale * P;
-    hipLaunchKernelGGL(sw_blend_kernel, dim3(cdiv((int64_t)D * H * W, 256)), dim3(256), 0, s, wl, out, D, H, W, pd->classes,
-                       P, stride, cd, ch, cw, 0.5f / (sg * sg));
+    // two floats a piece where voxels and the caller's buffer start on 8 bytes
+    if (pd->classes % 2 == 0 && ((uintptr_t)out & 7u) == 0)
+        sw_blend_launch<2>(wl, out, D, H, W, pd->classes, P, stride, cd, ch, cw, 0.5f / (sg * sg), s);
+    else
+        sw_blend_launch<1>(wl, out, D, H, W, pd->classes, P, stride, cd, ch, cw, 0.5f / (sg * sg), s);
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }
