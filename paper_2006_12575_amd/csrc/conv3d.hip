@@ -769,7 +769,9 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
 // The matrix-core kernels copy 16-byte pieces (8 channels).  An input with fewer channels than that, or whose voxels do
 // not start on 16 bytes -- a two- or four-channel image in front of a first layer -- is copied once into whole pieces with
 // zero channels behind the real ones: 16 bytes written per voxel and piece, against the 2 * C_out bytes that the conv
-// writes.  (2->16 channels on 2 x 64 x 80 x 96 voxels, forward to weight gradient: 1972 -> 196 us.)  One thread per voxel and piece.
+// writes: for the data gradient and the weight gradient (2->16 channels on 2 x 64 x 80 x 96 voxels: 1.3 ms -> 53 us).  The forward pass
+// of such inputs keeps the scalar sums: on saturated image regions a sum that rounds the other way moves whole regions over the ReLU.
+// One thread per voxel and piece.
 __global__ __launch_bounds__(256) void conv_pad_kernel(const bf16_t* __restrict__ x, int ldx, int C, bf16_t* __restrict__ xp,
                                                        int gpv, int64_t granules) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -848,8 +850,6 @@ extern "C" size_t lamp_conv3d_fwd_workspace_bytes(const lamp_tensor_desc* xd, co
         if (c > a) a = c;
     }
     if (f32_conv_supported(xd, zd)) b = f32_conv_ws_bytes(xd, zd, want_stats);
-    lamp_tensor_desc xp;
-    if (pad_desc(xd, xp) && mfma_conv_supported(&xp, zd, nullptr, nullptr)) b = pad_bytes(&xp) + mfma_conv_ws_bytes(&xp, zd, want_stats);
     return a > b ? a : b;
 }
 
@@ -873,12 +873,6 @@ extern "C" lamp_status lamp_conv3d_fwd(const lamp_tensor_desc* xd, const void* x
         hipLaunchKernelGGL(conv3d_cin1_fwd_kernel, dim3(cdiv(nvox(zd), 256)), dim3(256), 0, s, (const bf16_t*)x, xd->ldc,
                            (const bf16_t*)w, (bf16_t*)z, zd->ldc, zd->n, zd->d, zd->h, zd->w, zd->c);
         LAMP_CHECK_LAUNCH();
-    } else if (lamp_tensor_desc xp; !has_norm(xnorm) && pad_desc(xd, xp) && mfma_conv_supported(&xp, zd, nullptr, bias) &&
-                                    aligned16(w) && aligned16(ws)) {
-        const size_t pb = pad_bytes(&xp);
-        if ((st = launch_pad(xd, x, &xp, ws, s)) != LAMP_OK) return st;
-        return mfma_conv_fwd(&xp, ws, w, false, zd, z, stats_out, eps, (char*)ws + pb, ws_bytes - pb, s, nullptr, bias, nullptr, nullptr,
-                             xd->c);
     } else {
         st = launch_direct<false>(xd, x, make_norm(xnorm), w, bias, zd, z, s);
         if (st != LAMP_OK) return st;
