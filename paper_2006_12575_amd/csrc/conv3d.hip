@@ -897,7 +897,7 @@ extern "C" lamp_status lamp_conv3d_dgrad(const lamp_tensor_desc* dzd, const void
     hipStream_t s = (hipStream_t)stream;
     if (mfma_conv_supported(dzd, dxd, nullptr, nullptr) && mfma_takes(dzd, dxd, w, ws))
         return mfma_conv_fwd(dzd, dz, w, true, dxd, dx, nullptr, 0.f, ws, ws_bytes, s);
-    if (f32_conv_supported(dzd, dxd))
+    if (dzd->dtype == LAMP_F32 && f32_conv_supported(dzd, dxd))
         return f32_conv(dzd, (const float*)dz, make_norm(nullptr), (const float*)w, nullptr, true, dxd, (float*)dx, nullptr, 0.f, nullptr, 0, s);
     lamp_tensor_desc zp;
     if (pad_desc(dzd, zp) && mfma_conv_supported(&zp, dxd, nullptr, nullptr) && aligned16(w) && aligned16(ws)) {

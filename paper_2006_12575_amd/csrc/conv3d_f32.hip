@@ -1,4 +1,4 @@
-// 3x3x3 convolution of fp32 tensors on the matrix cores: forward, data gradient and weight gradient, any channel counts.
+// 3x3x3 convolution of fp32 tensors (and the forward pass of narrow bf16 inputs) on the fp32 matrix instruction: forward, data gradient and weight gradient, any channel counts.
 // Products and sums stay fp32 (v_mfma_f32_16x16x4_f32, 256 flops per cycle and CU, twice the vector units' rate).
 #include "internal.h"
 #include "vec.h"
@@ -57,7 +57,7 @@ static void f32_magic(int d, uint32_t* m, int* s) {
 // 385 -> 71 us, against scalar multiply-adds and a separate statistics pass; 16->8 on 2 x 64 x 48 x 80: 85 us, 8->8 46 us.
 // MAXK: halo pieces (4 channels of a voxel) a thread stages at most.
 struct F32ConvArgs {
-    const float* x; const float* w; const float* bias; float* z;
+    const void* x; const void* w; const float* bias; void* z;   // storage type of the instantiation
     float* partial; int32_t* counts;   // [N][tiles][Co][2], [tiles]; nullptr: no statistics
     NormIn nm;
     int ldx, ldz, N, D, H, W, Ci, Co;
@@ -77,7 +77,7 @@ __device__ __forceinline__ float row_sum16(float v) {
     return v;
 }
 
-template <int KC, int CB, int VB, int MAXK, bool DGRAD>
+template <typename T, int KC, int CB, int VB, int MAXK, bool DGRAD>
 __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32ConvArgs a) {
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
     constexpr int EST = f32_est(KC), QE = KC / 4, KL = QE < 2 ? QE : 2, MAXW = (27 * QE * 16 * CB + 255) / 256;
@@ -104,13 +104,15 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
     uint32_t pin = 0;   // pieces inside the volume (the padding is zero behind the normalisation)
     // once per tile: which pieces lie inside the volume, and where
     int vo[MAXK];
-    const float* xt = a.x;
+    const T* const ax = static_cast<const T*>(a.x);
+    const T* const aw = static_cast<const T*>(a.w);
+    const T* xt = ax;
     auto locate = [&](int tile) __attribute__((always_inline)) {
         const int n = tile / tiles;
         tile -= n * tiles;
         const int iw = tile % a.t.nw, r1 = tile / a.t.nw, ih = r1 % a.t.nh, idd = r1 / a.t.nh;
         const int d0 = (idd << a.t.ld) - 1, h0 = (ih << a.t.lh) - 1, w0 = (iw << a.t.lw) - 1;
-        xt = a.x + ((((int64_t)n * a.D + d0) * a.H + h0) * a.W + w0) * a.ldx + 4 * quad;
+        xt = ax + ((((int64_t)n * a.D + d0) * a.H + h0) * a.W + w0) * a.ldx + 4 * quad;
         pin = 0;
 #pragma unroll
         for (int k = 0; k < MAXK; ++k) {
@@ -128,14 +130,14 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
         for (int k = 0; k < MAXK; ++k) {
             float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
             if (pin >> k & 1) {
-                const float* p = xt + ((int64_t)vo[k] * a.ldx + c0);
-                if (a.xvec) {
+                const T* p = xt + ((int64_t)vo[k] * a.ldx + c0);
+                if (sizeof(T) == 4 && a.xvec) {
                     if (left > 0) q = *reinterpret_cast<const float4*>(p);
                 } else {
-                    if (left > 0) q.x = p[0];
-                    if (left > 1) q.y = p[1];
-                    if (left > 2) q.z = p[2];
-                    if (left > 3) q.w = p[3];
+                    if (left > 0) q.x = io<T>::ld(p);
+                    if (left > 1) q.y = io<T>::ld(p + 1);
+                    if (left > 2) q.z = io<T>::ld(p + 2);
+                    if (left > 3) q.w = io<T>::ld(p + 3);
                 }
             }
             px[k] = q;
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
                     if (pin >> k & 1) {
                         float& v = j == 0 ? px[k].x : j == 1 ? px[k].y : j == 2 ? px[k].z : px[k].w;
                         const float u = norm_u(v, na, nb);
-                        v = !a.nm.relu || u > 0.f ? u : 0.f;
+                        v = io<T>::rnd(!a.nm.relu || u > 0.f ? u : 0.f);
                     }
             }
         }
@@ -169,22 +171,22 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
     constexpr int TS = 256 / (16 * QE * CB);
     const int wk = DGRAD ? tid % KC : tid / 16 % QE * 4, wc = DGRAD ? tid / KC % (4 * CB) * 4 : tid % 16 + tid / (16 * QE) % CB * 16;
     const int wt0 = tid / (16 * QE * CB);
-    const float* wp = DGRAD ? a.w + ((int64_t)wk * 27 + (26 - wt0)) * a.Co + co0 + wc : a.w + ((int64_t)(co0 + wc) * 27 + wt0) * a.Ci + wk;
+    const T* wp = DGRAD ? aw + ((int64_t)wk * 27 + (26 - wt0)) * a.Co + co0 + wc : aw + ((int64_t)(co0 + wc) * 27 + wt0) * a.Ci + wk;
     auto fetch_w = [&](int c0) __attribute__((always_inline)) {
         const int left = DGRAD ? a.Co - co0 - wc : a.Ci - c0 - wk;   // elements of the row from the piece's first on
         const bool on = left > 0 && (DGRAD ? c0 + wk < a.Ci : co0 + wc < a.Co);
-        const float* p = wp + (DGRAD ? (int64_t)c0 * 27 * a.Co : (int64_t)c0);
+        const T* p = wp + (DGRAD ? (int64_t)c0 * 27 * a.Co : (int64_t)c0);
         const int64_t step = DGRAD ? -(int64_t)TS * a.Co : (int64_t)TS * a.Ci;
 #pragma unroll
         for (int u = 0; u < MAXW; ++u) {
             float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
             if (on && wt0 + u * TS < 27) {
-                if (a.wvec) q = *reinterpret_cast<const float4*>(p + u * step);
+                if (sizeof(T) == 4 && a.wvec) q = *reinterpret_cast<const float4*>(p + u * step);
                 else {
-                    q.x = p[u * step];
-                    if (left > 1) q.y = p[u * step + 1];
-                    if (left > 2) q.z = p[u * step + 2];
-                    if (left > 3) q.w = p[u * step + 3];
+                    q.x = io<T>::ld(p + u * step);
+                    if (left > 1) q.y = io<T>::ld(p + u * step + 1);
+                    if (left > 2) q.z = io<T>::ld(p + u * step + 2);
+                    if (left > 3) q.w = io<T>::ld(p + u * step + 3);
                 }
             }
             pw[u] = q;
@@ -294,22 +296,26 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
             const int p = (wid * VB + vb) * 16 + lo;
             const int w = w0 + (p & (TW - 1)), h = h0 + ((p >> a.t.lw) & (TH - 1)), d = d0 + (p >> (a.t.lw + a.t.lh));
             if (w >= a.W || h >= a.H || d >= a.D) continue;
-            float* zp = a.z + ((((int64_t)n * a.D + d) * a.H + h) * a.W + w) * a.ldz;
+            T* zp = static_cast<T*>(a.z) + ((((int64_t)n * a.D + d) * a.H + h) * a.W + w) * a.ldz;
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
                 const int co = co0 + 16 * cb + 4 * g;
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    v[r] = acc[cb][vb][r];
+                    v[r] = io<T>::rnd(acc[cb][vb][r]);
                     s[cb][r] += v[r];
                     q[cb][r] = fmaf(v[r], v[r], q[cb][r]);
                 }
-                if (a.zvec && co + 4 <= a.Co) *reinterpret_cast<float4*>(zp + co) = make_float4(v[0], v[1], v[2], v[3]);
-                else
+                if (a.zvec && co + 4 <= a.Co) {
+                    if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(zp + co) = make_float4(v[0], v[1], v[2], v[3]);
+                    else
+                        *reinterpret_cast<uint2*>(zp + co) = make_uint2(__float_as_uint(v[0]) >> 16 | (__float_as_uint(v[1]) & 0xFFFF0000u),
+                                                                        __float_as_uint(v[2]) >> 16 | (__float_as_uint(v[3]) & 0xFFFF0000u));
+                } else
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (co + r < a.Co) zp[co + r] = v[r];
+                        if (co + r < a.Co) io<T>::st(zp + co + r, v[r]);
             }
         }
         if (!a.partial) continue;
@@ -367,13 +373,14 @@ static size_t f32_partial_bytes(const lamp_tensor_desc* zd, const TileGeo& t) {
     return align_up((size_t)zd->n * t.nd * t.nh * t.nw * zd->c * 2 * sizeof(float));
 }
 size_t f32_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, int want_stats) {
-    if (zd->dtype != LAMP_F32 || !want_stats) return 0;
+    if (!want_stats) return 0;
     const TileGeo t = f32_plan(xd, zd).t;
     return f32_partial_bytes(zd, t) + align_up((size_t)t.nd * t.nh * t.nw * sizeof(int32_t));
 }
 // The grid's limits, and 32-bit voxel offsets inside the halo of a tile.
 bool f32_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
-    if (xd->dtype != LAMP_F32) return false;
+    // bf16: the forward pass of two to four input channels, in the order of the scalar kernel (whole unit 2->16: 716 -> 147 us)
+    if (xd->dtype != LAMP_F32 && (xd->c < 2 || xd->c > 4 || zd->ldc % 4)) return false;
     const F32Plan p = f32_plan(xd, zd);
     return (int64_t)p.t.nd * p.t.nh * p.t.nw * zd->n < ((int64_t)1 << 31) && cdiv(zd->c, 16) <= 65535 &&
            (int64_t)zd->h * zd->w * 18 < ((int64_t)1 << 31);
@@ -383,11 +390,11 @@ static size_t f32_lds_bytes(const F32Plan& p) {
     const int hv = ((1 << p.t.ld) + 2) * ((1 << p.t.lh) + 2) * ((1 << p.t.lw) + 2);
     return ((size_t)hv * f32_est(p.kc) + (size_t)27 * p.cb * 16 * p.kc + 128 * p.cb) * sizeof(float);
 }
-template <int KC, bool DGRAD>
+template <typename T, int KC, bool DGRAD>
 static void f32_launch(const F32Plan& p, dim3 grid, hipStream_t s, const F32ConvArgs& a) {
     constexpr int Q = KC / 4;
     const size_t lds = f32_lds_bytes(p);
-#define LAMP_F32(CB, VB, MK) hipLaunchKernelGGL((conv3d_f32_kernel<KC, CB, VB, MK, DGRAD>), grid, dim3(256), lds, s, a)
+#define LAMP_F32(CB, VB, MK) hipLaunchKernelGGL((conv3d_f32_kernel<T, KC, CB, VB, MK, DGRAD>), grid, dim3(256), lds, s, a)
     constexpr int M4 = (648 * Q + 255) / 256, M2 = (432 * Q + 255) / 256, M1 = (256 * Q + 255) / 256;
     if constexpr (KC < 16)
         if (p.cb == 2) {
@@ -545,7 +552,7 @@ static bool f32_wide(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, con
            cdiv(zd->c, 16) <= 65535;
 }
 bool f32_norm_on_load(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
-    return f32_conv_supported(xd, zd) && !f32_wide(xd, zd, make_norm(nullptr), false);
+    return xd->dtype == LAMP_F32 && f32_conv_supported(xd, zd) && !f32_wide(xd, zd, make_norm(nullptr), false);
 }
 static void f32_wide_launch(const lamp_tensor_desc* xd, const float* x, const float* w, const float* bias, const lamp_tensor_desc* zd,
                             float* z, hipStream_t s) {
@@ -571,11 +578,11 @@ static void f32_wide_launch(const lamp_tensor_desc* xd, const float* x, const fl
     }
 }
 
-lamp_status f32_conv(const lamp_tensor_desc* xd, const float* x, const NormIn& nm, const float* w, const float* bias, bool dgrad,
-                     const lamp_tensor_desc* zd, float* z, float* stats_out, float eps, void* ws, size_t ws_bytes, hipStream_t s) {
+lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm, const void* w, const float* bias, bool dgrad,
+                     const lamp_tensor_desc* zd, void* z, float* stats_out, float eps, void* ws, size_t ws_bytes, hipStream_t s) {
     if (!f32_conv_supported(xd, zd)) return LAMP_ERR_UNSUPPORTED;
-    if (f32_wide(xd, zd, nm, dgrad)) {
-        f32_wide_launch(xd, x, w, bias, zd, z, s);
+    if (xd->dtype == LAMP_F32 && f32_wide(xd, zd, nm, dgrad)) {
+        f32_wide_launch(xd, (const float*)x, (const float*)w, bias, zd, (float*)z, s);
         LAMP_CHECK_LAUNCH();
         return stats_out ? launch_stats(zd, z, eps, stats_out, ws, ws_bytes, s) : LAMP_OK;
     }
@@ -612,13 +619,14 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const float* x, const NormIn& n
     }
     const dim3 grid((unsigned)((a.ntiles + a.per - 1) / a.per), cols);
     if (dgrad) {
-        if (p.kc == 16) f32_launch<16, true>(p, grid, s, a);
-        else if (p.kc == 8) f32_launch<8, true>(p, grid, s, a);
-        else f32_launch<4, true>(p, grid, s, a);
+        if (p.kc == 16) f32_launch<float, 16, true>(p, grid, s, a);
+        else if (p.kc == 8) f32_launch<float, 8, true>(p, grid, s, a);
+        else f32_launch<float, 4, true>(p, grid, s, a);
     } else {
-        if (p.kc == 16) f32_launch<16, false>(p, grid, s, a);
-        else if (p.kc == 8) f32_launch<8, false>(p, grid, s, a);
-        else f32_launch<4, false>(p, grid, s, a);
+        if (p.kc == 16) f32_launch<float, 16, false>(p, grid, s, a);
+        else if (p.kc == 8) f32_launch<float, 8, false>(p, grid, s, a);
+        else if (xd->dtype == LAMP_F32) f32_launch<float, 4, false>(p, grid, s, a);
+        else f32_launch<bf16_t, 4, false>(p, grid, s, a);
     }
     LAMP_CHECK_LAUNCH();
     if (stats_out) return launch_stats_finalize(a.partial, a.counts, tiles, zd->n, zd->c, eps, stats_out, s);
