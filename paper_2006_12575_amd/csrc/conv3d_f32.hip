@@ -639,8 +639,12 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
 // an image of one or two channels fills the product's columns with taps.  A workgroup walks a contiguous range of 128-voxel tiles:
 // x halo and dz tile go through registers to LDS (the next tile's loads in flight during the multiplies), where one 4-byte read per
 // fragment gives 16 channels of 4 voxels, 64 consecutive floats.  CG waves share out the column blocks, 4 / CG the voxels; each
-// writes its own partial [Co][27][Ci], added up in a fixed order by reduce_partials_kernel.  32->32 on 41 x 56 x 47: 2450 -> 93 us
-// (64 TFLOP/s) against a thread per weight; 16->8 on 2 x 64 x 48 x 80: 108 us.
+// writes its own partial [Co][27][Ci], added up in a fixed order by reduce_partials_kernel.  A wave adds up 128 voxels and puts them
+// to the sum of those before them: the walks grow with the volume, and a single chain over them would round like sqrt(walk) (8->8 on
+// 2 x 128^3, walks of 4096 voxels: relative error 8.9e-7 in one chain, 1.9e-7 so, 3.8e-7 with a thread per weight over 864 voxels).
+// 16-channel slabs of 32 outputs keep half of these sums in LDS, where each thread has its own slots: all of them in registers spill
+// (98 -> 106 us below; with the slots 100).  32->32 on 41 x 56 x 47: 2450 -> 100 us with the reduction against a thread per weight;
+// 16->8 on 2 x 64 x 48 x 80: 109 us.
 struct F32WgradArgs {
     const float* x; const float* dz; float* part;   // part [splits * VG][Co][27][Ci]
     NormIn nm;
@@ -661,6 +665,7 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
     extern __shared__ __attribute__((aligned(16))) float f32w_lds[];
     constexpr int CS = CIC < 4 ? 4 : CIC, QE = CS / 4, CG = WgradCols<CIC>::CG, VG = WgradCols<CIC>::VG, NBW = WgradCols<CIC>::NBW;
     constexpr int MX = (F32W_HALO * QE + 255) / 256, MZ = F32W_VOX * CBO * 4 / 256;
+    constexpr bool LS = CIC * CBO == 32;   // half of the sums in LDS
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, l16 = lane & 15, g = lane >> 4;
     const int cg = wid % CG, vg = wid / CG;
     const int ci0 = (blockIdx.y / a.cochunks) * CIC, co0 = (blockIdx.y % a.cochunks) * (16 * CBO);
@@ -696,11 +701,16 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
         const int t = c / CIC;
         col[i] = ((t / 9 * HH + t / 3 % 3) * HW + t % 3 + g) * CS + (c - t * CIC);
     }
-    f32x4 acc[CBO][NBW];
+    f32x4 acc[CBO][NBW], sum[LS ? 1 : CBO][NBW];   // the last 128 voxels of the wave, all before them
+    f32x4* const ls = reinterpret_cast<f32x4*>(zs + CBO * F32W_VOX * 16) + tid;   // LS: sum[1], [NBW][256]
 #pragma unroll
     for (int cb = 0; cb < CBO; ++cb)
 #pragma unroll
-        for (int i = 0; i < NBW; ++i) acc[cb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < NBW; ++i) {
+            acc[cb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (LS && cb) ls[i * 256] = acc[cb][i];
+            else sum[cb][i] = acc[cb][i];
+        }
 
     float4 px[MX], pz[MZ];
     uint32_t pin = 0;   // halo pieces inside the volume (the padding is zero behind the normalisation)
@@ -802,6 +812,7 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
             float ga[CBO], gb[NBW];
             const int nx = ks + VG < F32W_VOX / 4 ? ks + VG : ks;   // the last step reads its own again
             frags(nx, ga, gb);
+            if constexpr (LS) __builtin_amdgcn_sched_barrier(0);   // the reads stay in front of the multiplies, also where registers are short
 #pragma unroll
             for (int i = 0; i < NBW; ++i)
 #pragma unroll
@@ -811,6 +822,16 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
 #pragma unroll
             for (int i = 0; i < NBW; ++i) fb[i] = gb[i];
         }
+        if (((t - t0) & (VG - 1)) == VG - 1 && t + 1 < t1) {
+#pragma unroll
+            for (int cb = 0; cb < CBO; ++cb)
+#pragma unroll
+                for (int i = 0; i < NBW; ++i) {
+                    if (LS && cb) ls[i * 256] += acc[cb][i];
+                    else sum[cb][i] += acc[cb][i];
+                    acc[cb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
     }
     float* pb = a.part + ((int64_t)blockIdx.x * VG + vg) * a.Co * 27 * a.Ci;
 #pragma unroll
@@ -818,12 +839,14 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
         const int c = (cg * NBW + i) * 16 + l16, t = c / CIC, ci = ci0 + c - t * CIC;
         if (c >= 27 * CIC || ci >= a.Ci) continue;
 #pragma unroll
-        for (int cb = 0; cb < CBO; ++cb)
+        for (int cb = 0; cb < CBO; ++cb) {
+            const f32x4 all = (LS && cb ? ls[i * 256] : sum[LS ? 0 : cb][i]) + acc[cb][i];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int co = co0 + 16 * cb + 4 * g + r;
-                if (co < a.Co) pb[((int64_t)co * 27 + t) * a.Ci + ci] = acc[cb][i][r];
+                if (co < a.Co) pb[((int64_t)co * 27 + t) * a.Ci + ci] = all[r];
             }
+        }
     }
 }
 
@@ -862,12 +885,20 @@ bool f32_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd
 }
 
 template <int CIC>
-static void f32w_launch(const F32WPlan& p, hipStream_t s, const F32WgradArgs& a) {
+static lamp_status f32w_launch(const F32WPlan& p, hipStream_t s, const F32WgradArgs& a) {
     const int hv = ((1 << p.t.ld) + 2) * ((1 << p.t.lh) + 2) * ((1 << p.t.lw) + 2);
-    const size_t lds = ((size_t)hv * (CIC < 4 ? 4 : CIC) + (size_t)p.cbo * F32W_VOX * 16) * sizeof(float);
+    size_t lds = ((size_t)hv * (CIC < 4 ? 4 : CIC) + (size_t)p.cbo * F32W_VOX * 16) * sizeof(float);
     const dim3 grid(p.splits, p.cichunks * p.cochunks);
+    if (CIC * p.cbo == 32) {
+        const size_t ls = (size_t)WgradCols<CIC>::NBW * 256 * 16;
+        lds += ls;
+        const size_t most = ((size_t)F32W_HALO * CIC + 2 * F32W_VOX * 16) * sizeof(float) + ls;
+        if (ensure_dyn_lds((const void*)conv3d_wgrad_f32_kernel<CIC, 2>, (int)most) != LAMP_OK) return LAMP_ERR_HIP;
+    }
     if (p.cbo == 2) hipLaunchKernelGGL((conv3d_wgrad_f32_kernel<CIC, 2>), grid, dim3(256), lds, s, a);
     else hipLaunchKernelGGL((conv3d_wgrad_f32_kernel<CIC, 1>), grid, dim3(256), lds, s, a);
+    LAMP_CHECK_LAUNCH();
+    return LAMP_OK;
 }
 
 lamp_status f32_wgrad(const lamp_tensor_desc* xd, const float* x, const NormIn& nm, const lamp_tensor_desc* dzd, const float* dz,
@@ -882,12 +913,12 @@ lamp_status f32_wgrad(const lamp_tensor_desc* xd, const float* x, const NormIn& 
     a.t = p.t; a.ntiles = (int)p.ntiles; a.per = p.per; a.cochunks = p.cochunks;
     a.xvec = aligned16(x) && xd->c % 4 == 0 && xd->ldc % 4 == 0;
     a.zvec = aligned16(dz) && dzd->c % 4 == 0 && dzd->ldc % 4 == 0;
-    if (p.cic == 16) f32w_launch<16>(p, s, a);
-    else if (p.cic == 8) f32w_launch<8>(p, s, a);
-    else if (p.cic == 4) f32w_launch<4>(p, s, a);
-    else if (p.cic == 2) f32w_launch<2>(p, s, a);
-    else f32w_launch<1>(p, s, a);
-    LAMP_CHECK_LAUNCH();
+    const lamp_status st = p.cic == 16  ? f32w_launch<16>(p, s, a)
+                           : p.cic == 8 ? f32w_launch<8>(p, s, a)
+                           : p.cic == 4 ? f32w_launch<4>(p, s, a)
+                           : p.cic == 2 ? f32w_launch<2>(p, s, a)
+                                        : f32w_launch<1>(p, s, a);
+    if (st != LAMP_OK) return st;
     return launch_reduce_partials((const float*)ws, p.splits * p.vgs, (int64_t)dzd->c * 27 * xd->c, dw, beta, s);
 }
 

@@ -1,0 +1,56 @@
+"""Rounding of the long fp32 sums against 64 bits.
+
+A chain of L additions of terms of either sign into one fp32 accumulator carries a relative error of about
+u * sqrt(L / 2), u = 2^-24 / sqrt(3) (the roundings of a sum that grows like sqrt(l)); a sum taken in chains of L whose results are
+added in chains of M carries u * sqrt((L + M) / 2).  Partials are added in fp64.  So a bound shows how a kernel cuts a sum."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+BF, F32 = torch.bfloat16, torch.float32
+U = 2.0 ** -24 / math.sqrt(3.0)
+
+
+@pytest.fixture(scope="module")
+def L():
+    import paper_2006_12575_amd as L
+    L.lib()
+    return L
+
+
+def chain(l, m=0):
+    return U * math.sqrt((l + m) / 2.0)
+
+
+def rel(a, ref):
+    return ((a.double() - ref).norm() / ref.norm()).item()
+
+
+def rand(seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return lambda shape, dtype=F32: torch.randn(shape, generator=g, device="cuda").to(dtype)
+
+
+def wgrad64(x, dz):
+    D, H, W = x.shape[1:4]
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1, 1, 1))
+    dzt = dz.double().reshape(-1, dz.shape[4]).t().contiguous()
+    taps = [xp[:, t // 9:t // 9 + D, t // 3 % 3:t // 3 % 3 + H, t % 3:t % 3 + W].reshape(-1, x.shape[4]) for t in range(27)]
+    return torch.stack([dzt @ t for t in taps], 1).reshape(dz.shape[4], 3, 3, 3, x.shape[4])
+
+
+# walks of up to about 4096 voxels in chains of 128: at most 32 of them
+@pytest.mark.parametrize("shape", [(2, 128, 128, 128, 8, 8), (1, 128, 128, 128, 16, 16), (1, 160, 160, 160, 1, 16), (2, 96, 96, 96, 2, 8),
+                                   (2, 96, 96, 96, 4, 24), (1, 96, 95, 97, 32, 32), (2, 64, 48, 80, 16, 8)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_conv3d_wgrad_f32(L, shape):
+    n, d, h, w, ci, co = shape
+    r = rand(41 + ci)
+    x, dz = torch.relu(r((n, d, h, w, ci))), r((n, d, h, w, co))
+    dw = torch.empty((co, 3, 3, 3, ci), dtype=F32, device="cuda")
+    L.lamp_conv3d_wgrad(x, dz, dw)
+    e = rel(dw, wgrad64(x, dz))
+    assert e <= chain(128, 32), f"{e:.2e} > {chain(128, 32):.2e}"
