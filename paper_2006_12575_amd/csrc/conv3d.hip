@@ -608,7 +608,7 @@ static int cin1_wgrad_blocks(int64_t V) {
     return (int)(b > 2048 ? 2048 : (b < 1 ? 1 : b));
 }
 
-static int wgrad_splits(int64_t V, int64_t O) {
+int wgrad_splits(int64_t V, int64_t O) {
     int64_t s = (V + 255) / 256;
     int64_t cap = (int64_t)(32u << 20) / (O * 4);
     if (cap < 1) cap = 1;
@@ -769,7 +769,7 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
 // The matrix-core kernels copy 16-byte pieces (8 channels).  An input with fewer channels than that, or whose voxels do
 // not start on 16 bytes -- a two- or four-channel image in front of a first layer -- is copied once into whole pieces with
 // zero channels behind the real ones: 16 bytes written per voxel and piece, against the 2 * C_out bytes that the conv
-// writes: for the data gradient and the weight gradient (2->16 channels on 2 x 64 x 80 x 96 voxels: 1.3 ms -> 53 us).  The forward pass
+// writes: for the data gradient and the weight gradient (weight gradient of 2->16 channels on 2 x 64 x 80 x 96 voxels: 1.2 ms -> 62 us).  The forward pass
 // of such inputs keeps the scalar sums: on saturated image regions a sum that rounds the other way moves whole regions over the ReLU.
 // One thread per voxel and piece.
 __global__ __launch_bounds__(256) void conv_pad_kernel(const bf16_t* __restrict__ x, int ldx, int C, bf16_t* __restrict__ xp,
@@ -966,7 +966,7 @@ extern "C" size_t lamp_conv3d_wgrad_workspace_bytes(const lamp_tensor_desc* xd, 
         if (e > a) a = e;
     }
     lamp_tensor_desc xp;
-    if (pad_desc(xd, xp) && mfma_wgrad_supported(&xp, dzd, nullptr)) b = pad_bytes(&xp) + mfma_wgrad_ws_bytes(&xp, dzd);
+    if (pad_desc(xd, xp) && mfma_wgrad_supported(&xp, dzd, nullptr)) b = pad_bytes(&xp) + mfma_wgrad_ws_bytes(&xp, dzd, xd->c);
     return (a > b ? a : b) + c;
 }
 

@@ -1474,6 +1474,7 @@ struct WgradArgs {
     int tiles_d, tiles_h, tiles_w, tiles_per_n, tiles_total, tiles_per_wg;
     const bf16_t* x2; int xsplit;   // two-part x: input channels from xsplit on live in x2 (same channel stride)
     int xc;             // channels of x in memory (a multiple of 8, >= Cin: a narrow x is padded with zeros)
+    int fold, dump, parts_per_wg;   // FOLD: tiles per chain, tiles per partial, partials per walk
 };
 
 __device__ __forceinline__ bf16x8 lds_frag_tr(const char* p) {
@@ -1615,7 +1616,11 @@ __device__ __forceinline__ void wgrad_tile(f32x16 (&acc)[COB][4], WFrags<COB>& f
     f.rb[2] = f.rb[4];
 }
 
-template <int COB>
+// FOLD (channel counts outside the multiples of 32): a walk leaves its sums as a partial every `fold` tiles, so that a chain is as
+// long as in the thread-per-weight kernel that served these counts before (wgrad_splits: 256 voxels where 32 MB of partials allow
+// it), where one chain over a walk rounds more the larger the volume.  Relative error of 2->16 on 2 x 64 x 80 x 96: 7.9e-8 a thread
+// per weight, 3.2e-7 a chain per walk (55 us), 7.9e-8 so (62 us); 48->96 on 83 x 61 x 97: 5.7e-7, 6.6e-7 (161 us), 4.5e-7 (164 us).
+template <int COB, bool FOLD>
 __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1636,12 +1641,47 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
     const uint32_t loff = (uint32_t)((8 * (b16 >> 1) + (s16 >> 2)) * 64 + 32 * (b16 & 1) + 8 * (s16 & 3));
 
     f32x16 acc[COB][4];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int cb = 0; cb < COB; ++cb)
+        for (int cb = 0; cb < COB; ++cb)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[cb][i][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[cb][i][r] = 0.f;
+    };
+    clear();
+    constexpr bool SUM = FOLD && COB == 1;
+    f32x16 sum[SUM ? 4 : 1];   // the chains of the partial that are done
+    auto clear_sum = [&]() __attribute__((always_inline)) {
+        if constexpr (SUM)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[i][r] = 0.f;
+    };
+    clear_sum();
+    // part[slot][co][tap][ci].  Output channels exist in whole groups of 8, so which ones is uniform, as are the offsets from one group
+    // and tap to the next.
+    auto write_partial = [&](int slot) __attribute__((always_inline)) {
+        int ln = lane;
+        if constexpr (FOLD) asm volatile("" : "+v"(ln));   // the address is not worth registers of its own across the walk
+        const int ci = ci0 + (ln & 31), wvu = __builtin_amdgcn_readfirstlane(wv);
+        if (ci >= a.Cin) return;
+        float* pb = a.part + ((int64_t)slot * a.Cout + co0 + 4 * (ln >> 5)) * 27 * a.Cin + ci;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = i < 3 ? wvu / 3 * 9 + i * 3 + wvu % 3 : 18 + wvu * 3 + 2;
+            if (i < 3 || wvu < 3) {
+#pragma unroll
+                for (int cb = 0; cb < COB; ++cb)
+#pragma unroll
+                    for (int rg = 0; rg < 4; ++rg)
+                        if (co0 + cb * 32 + 8 * rg < a.Cout)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) pb[(int64_t)((cb * 32 + 8 * rg + r) * 27 + t) * a.Cin] = SUM ? sum[SUM ? i : 0][4 * rg + r] : acc[cb][i][4 * rg + r];
+            }
+        }
+    };
 
     // ---- per-lane constants of the tile copies
     WgradLane wl;
@@ -1737,29 +1777,28 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
     if (has4) wgrad_first<COB, 4, 0>(fr, lds, coloff, extoff, loff);
     else wgrad_first<COB, 3, 0>(fr, lds, coloff, extoff, loff);
 
-    int par = 0;
+    int par = 0, in_chain = 0, in_part = 0, part = blockIdx.x * a.parts_per_wg;
     for (int tile = tile_lo; tile < tile_hi; ++tile, par ^= 1) {
         const bool pf = tile + 1 < tile_hi;
         if (pf) step_tile();
         run_tile(pf, lds + par * WBUF_STAGE, lds + (par ^ 1) * WBUF_STAGE);
-    }
-
-    // ---- write this workgroup's partial: part[slot][co][tap][ci]
-    float* pb = a.part + (int64_t)blockIdx.x * a.Cout * 27 * a.Cin;
-    const int l32 = lane & 31, half = lane >> 5;
+        if constexpr (FOLD) {
+            const bool out = !pf || ++in_part == a.dump;
+            if (out || ++in_chain == a.fold) {
+                if constexpr (SUM)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = i < 3 ? col_kd * 9 + i * 3 + col_kw : 18 + wv * 3 + 2;
-        if (i < 3 || has4) {
-#pragma unroll
-            for (int cb = 0; cb < COB; ++cb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int co = co0 + cb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    if (co < a.Cout && ci0 + l32 < a.Cin) pb[((int64_t)co * 27 + t) * a.Cin + ci0 + l32] = acc[cb][i][r];
+                    for (int i = 0; i < 4; ++i) sum[i] += acc[0][i];
+                in_chain = 0;
+                if (out) {
+                    write_partial(part++);
+                    in_part = 0;
+                    clear_sum();
                 }
+                clear();
+            }
         }
     }
+    if constexpr (!FOLD) write_partial(blockIdx.x);
 }
 
 static void wtile_dims(const lamp_tensor_desc* t, int& td, int& th, int& tw) {
@@ -1777,6 +1816,39 @@ static int wgrad_slots(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) 
     if (s >= 8) s = s / 8 * 8;  // keep the types of one tile range on one XCD
     if (s > tiles) s = tiles;
     return (int)s;
+}
+
+// Walks, tiles per walk, tiles per chain of additions (0: one chain per walk), tiles and number of partials.  wcin: the weight's input
+// channels.
+struct WgradPlan { int slots, per, fold, dump, parts_per_wg, parts; };
+static WgradPlan wgrad_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, int wcin) {
+    int td, th, tw;
+    wtile_dims(xd, td, th, tw);
+    const int tiles = td * th * tw * xd->n;
+    WgradPlan p;
+    p.slots = p.parts = wgrad_slots(xd, dzd);
+    p.per = p.dump = (tiles + p.slots - 1) / p.slots;
+    p.fold = 0;
+    p.parts_per_wg = 1;
+    if (wcin % 32 || dzd->c % 32) {
+        // f: tiles that hold the thread-per-weight kernel's chain.  A chain of matrix instructions (16 a tile) rounds like the scalar
+        // one of as many voxels with (17 f + 2) / 16 tiles, measured; what whole tiles leave of that goes to the additions of chains to
+        // the partial's sum, where a block has the registers for one (32 output channels).
+        const double f = (double)tiles / wgrad_splits(nvox(xd), (int64_t)dzd->c * 27 * wcin);
+        const bool sum = conv_wrows(dzd->c) == 32;
+        const int room = f < 1.0 ? 19 : (int)(17.0 * f) + 2;
+        p.fold = sum ? (int)f : room / 16;
+        if (p.fold > p.per) p.fold = p.per;
+        if (p.fold < 1) p.fold = 1;
+        int64_t dump = sum && room > 16 * p.fold ? (int64_t)(room - 16 * p.fold) * p.fold : p.fold;
+        if (dump > p.per) dump = p.per;
+        const int cuts = (int)((p.per + dump - 1) / dump);
+        p.dump = (p.per + cuts - 1) / cuts;
+        p.parts_per_wg = (p.per + p.dump - 1) / p.dump;
+        const int walks = (tiles + p.per - 1) / p.per, last = tiles - (walks - 1) * p.per;
+        p.parts = (walks - 1) * p.parts_per_wg + (last + p.dump - 1) / p.dump;
+    }
+    return p;
 }
 
 bool mfma_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, const lamp_norm_in* xnorm) {
@@ -1797,24 +1869,32 @@ bool mfma_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dz
 static bool wgrad_pack_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, PackPlan& pp) {
     return xd->c % 8 == 0 && dzd->c % 8 == 0 && conv_pack_plan(dzd, pp);
 }
-size_t mfma_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
+size_t mfma_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, int wcin) {
+    if (!wcin) wcin = xd->c;
     if (!mfma_wgrad_supported(xd, dzd, nullptr)) return 0;
     PackPlan pp;
     if (wgrad_pack_plan(xd, dzd, pp)) {
         lamp_tensor_desc xp, zp;
         pack_descs(xd, dzd, pp, xp, zp);
-        return align_up((size_t)nvox(&xp) * xp.c * 2) + align_up((size_t)nvox(&zp) * zp.c * 2) + mfma_wgrad_ws_bytes(&xp, &zp) + 512;
+        return align_up((size_t)nvox(&xp) * xp.c * 2) + align_up((size_t)nvox(&zp) * zp.c * 2) + mfma_wgrad_ws_bytes(&xp, &zp, wcin) + 512;
     }
-    return align_up((size_t)wgrad_slots(xd, dzd) * dzd->c * 27 * xd->c * sizeof(float)) + 256;
+    return align_up((size_t)wgrad_plan(xd, dzd, wcin).parts * dzd->c * 27 * wcin * sizeof(float)) + 256;
 }
 
+template <int COB, bool FOLD>
+static lamp_status launch_wgrad(const WgradArgs& a, dim3 grid, hipStream_t s) {
+    if (ensure_dyn_lds((const void*)conv3d_wgrad_kernel<COB, FOLD>, WG_LDS_BYTES) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL((conv3d_wgrad_kernel<COB, FOLD>), grid, dim3(512), WG_LDS_BYTES, s, a);
+    LAMP_CHECK_LAUNCH();
+    return LAMP_OK;
+}
 
 lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dzd, const void* dz, float* dw,
                        float beta, void* ws, size_t ws_bytes, hipStream_t s, const void* x2, int x_c1, int wcin) {
     if (!wcin) wcin = xd->c;
     if ((((uintptr_t)x) & 15u) || (((uintptr_t)dz) & 15u) || (((uintptr_t)ws) & 15u)) return LAMP_ERR_ALIGN;
     if (x2 && ((((uintptr_t)x2) & 15u) || x_c1 % 32 || x_c1 <= 0 || x_c1 >= xd->c)) return LAMP_ERR_ALIGN;
-    if (ws_bytes < mfma_wgrad_ws_bytes(xd, dzd)) return LAMP_ERR_WORKSPACE;
+    if (ws_bytes < mfma_wgrad_ws_bytes(xd, dzd, wcin)) return LAMP_ERR_WORKSPACE;
     PackPlan pp;
     if (wgrad_pack_plan(xd, dzd, pp)) {
         lamp_tensor_desc xp, zp;
@@ -1822,7 +1902,7 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
         Carver pc(ws, ws_bytes);
         bf16_t* xpk = (bf16_t*)pc.take((size_t)nvox(&xp) * xp.c * 2);
         bf16_t* zpk = (bf16_t*)pc.take((size_t)nvox(&zp) * zp.c * 2);
-        const size_t inner = mfma_wgrad_ws_bytes(&xp, &zp);
+        const size_t inner = mfma_wgrad_ws_bytes(&xp, &zp, wcin);
         void* iws = pc.take(inner);
         if (!pc.ok()) return LAMP_ERR_WORKSPACE;
         const int64_t gx = nvox(&xp) * (xp.c / 8), gz = nvox(&zp) * (zp.c / 8);
@@ -1842,24 +1922,24 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
     wtile_dims(xd, a.tiles_d, a.tiles_h, a.tiles_w);
     a.tiles_per_n = a.tiles_d * a.tiles_h * a.tiles_w;
     a.tiles_total = a.tiles_per_n * xd->n;
-    const int S = wgrad_slots(xd, dzd);
-    a.tiles_per_wg = (a.tiles_total + S - 1) / S;
-    // one slot and nothing to accumulate onto: the only partial IS the result (wide layers on small volumes,
+    const WgradPlan p = wgrad_plan(xd, dzd, wcin);
+    const int S = p.parts;
+    a.tiles_per_wg = p.per;
+    a.fold = p.fold;
+    a.dump = p.dump;
+    a.parts_per_wg = p.parts_per_wg;
+    // one partial and nothing to accumulate onto: the only partial IS the result (wide layers on small volumes,
     // whose dW runs to hundreds of megabytes), so the kernel writes it in place and no second pass is needed
     const bool direct = S == 1 && beta == 0.f;
     if (direct) a.part = dw;
     a.zero16 = device_zero16();
     if (!a.zero16) return LAMP_ERR_HIP;
     const int cob = conv_wrows(dzd->c) / 32;
-    dim3 grid(S, cdiv(xd->c, 32), cdiv(dzd->c, 32 * cob));
-    if (cob == 2) {
-        if (ensure_dyn_lds((const void*)conv3d_wgrad_kernel<2>, WG_LDS_BYTES) != LAMP_OK) return LAMP_ERR_HIP;
-        hipLaunchKernelGGL((conv3d_wgrad_kernel<2>), grid, dim3(512), WG_LDS_BYTES, s, a);
-    } else {
-        if (ensure_dyn_lds((const void*)conv3d_wgrad_kernel<1>, WG_LDS_BYTES) != LAMP_OK) return LAMP_ERR_HIP;
-        hipLaunchKernelGGL((conv3d_wgrad_kernel<1>), grid, dim3(512), WG_LDS_BYTES, s, a);
-    }
-    LAMP_CHECK_LAUNCH();
+    const dim3 grid(p.slots, cdiv(xd->c, 32), cdiv(dzd->c, 32 * cob));
+    lamp_status st;
+    if (p.fold) st = cob == 2 ? launch_wgrad<2, true>(a, grid, s) : launch_wgrad<1, true>(a, grid, s);
+    else st = cob == 2 ? launch_wgrad<2, false>(a, grid, s) : launch_wgrad<1, false>(a, grid, s);
+    if (st != LAMP_OK) return st;
     if (direct) return LAMP_OK;
     return launch_reduce_partials((const float*)ws, S, (int64_t)dzd->c * 27 * wcin, dw, beta, s);
 }

@@ -96,7 +96,9 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
                           void* ws, size_t ws_bytes, hipStream_t s, const ConvParts* parts = nullptr,
                           const float* bias = nullptr, const lamp_norm_in* xnorm = nullptr, const ConvBsum* bsum = nullptr, int wcin = 0);
 bool mfma_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, const lamp_norm_in* xnorm);
-size_t mfma_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd);
+size_t mfma_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, int wcin = 0);
+// Partials of the weight gradient's thread-per-weight kernel on V voxels and O weights: 256 voxels each, 32 MB of them at most.
+int wgrad_splits(int64_t V, int64_t O);
 lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dzd, const void* dz,
                        float* dw, float beta, void* ws, size_t ws_bytes, hipStream_t s, const void* x2 = nullptr,
                        int x_c1 = 0, int wcin = 0);

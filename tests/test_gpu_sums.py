@@ -54,3 +54,18 @@ def test_conv3d_wgrad_f32(L, shape):
     L.lamp_conv3d_wgrad(x, dz, dw)
     e = rel(dw, wgrad64(x, dz))
     assert e <= chain(128, 32), f"{e:.2e} > {chain(128, 32):.2e}"
+
+
+# bf16 channel counts outside the multiples of 32: a matrix instruction adds 16 voxels to a chain; `steps` of them (with the additions
+# of chains) stand for the chain a thread per weight would have, 256 voxels where 32 MB of partials allow it
+@pytest.mark.parametrize("shape,steps", [((2, 64, 80, 96, 2, 16), 19), ((2, 128, 128, 128, 2, 16), 36), ((2, 64, 80, 96, 8, 16), 28),
+                                         ((2, 128, 128, 128, 8, 8), 59), ((2, 96, 96, 96, 16, 24), 147), ((2, 96, 96, 96, 8, 40), 122)],
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_conv3d_wgrad_bf16_ragged(L, shape, steps):
+    n, d, h, w, ci, co = shape
+    r = rand(51 + ci)
+    x, dz = torch.relu(r((n, d, h, w, ci), BF)), r((n, d, h, w, co), BF)
+    dw = torch.empty((co, 3, 3, 3, ci), dtype=F32, device="cuda")
+    L.lamp_conv3d_wgrad(x, dz, dw)
+    e = rel(dw, wgrad64(x, dz))
+    assert e <= chain(steps), f"{e:.2e} > {chain(steps):.2e}"
