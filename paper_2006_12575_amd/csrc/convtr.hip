@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void convtr_wgrad_kernel(const T* __restrict__
     part[(int64_t)blockIdx.y * O + o] = acc;
 }
 
-static int convtr_splits(int64_t V, int64_t O) {
+int convtr_splits(int64_t V, int64_t O) {
     int64_t s = (V + 127) / 128;
     int64_t cap = (int64_t)(32u << 20) / (O * 4);
     if (cap < 1) cap = 1;

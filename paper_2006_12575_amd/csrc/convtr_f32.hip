@@ -146,9 +146,11 @@ __global__ __launch_bounds__(256) void convtr_f32_kernel(CtF32Args a) {
 
 // Weight gradient, voxels as the reduction dimension (4 per product).  One wave = RB blocks of 16 input channels x 8 blocks of 16
 // columns (tap, co) over a contiguous range of voxels, its own partial; a fragment is one 4-byte load, 16 channels of 4 voxels, two
-// steps loaded ahead.  The waves of the first channel block also add up dy per column for the bias gradient.
+// steps loaded ahead.  The waves of the first channel block also add up dy per column for the bias gradient.  Every 64 voxels go to a
+// second set of sums: one chain over a slab that grows with the volume rounds more than the thread per weight did (16->8 on
+// 2 x 64^3: 1.4e-7 a thread per weight, 2.1e-7 in one chain (62 us), 1.2e-7 so (65 us); 64->32: 4.1e-7, 4.1e-7, 1.3e-7).
 template <int RB>
-__global__ __launch_bounds__(256) void convtr_wgrad_f32_kernel(CtF32Args a) {
+__global__ __launch_bounds__(256, 2) void convtr_wgrad_f32_kernel(CtF32Args a) {
     constexpr int NB = 8, U = 2;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
     const int slab = blockIdx.x * 4 + wid, r0 = blockIdx.y * (16 * RB), c0 = blockIdx.z * (16 * NB);
@@ -162,13 +164,13 @@ __global__ __launch_bounds__(256) void convtr_wgrad_f32_kernel(CtF32Args a) {
         const int tap = con[i] ? (int)ctf_div((uint32_t)c, a.mC, a.sC) : 0;
         coff[i] = con[i] ? ctf_tap(a, tap) * a.ldy + (c - tap * a.Co) : 0;
     }
-    f32x4 acc[RB][NB];
-    float bsum[NB];
+    f32x4 acc[RB][NB], sum[RB][NB];   // the last 64 voxels, all before them
+    float bacc[NB], bsum[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        bsum[i] = 0.f;
+        bacc[i] = bsum[i] = 0.f;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) acc[rb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int rb = 0; rb < RB; ++rb) acc[rb][i] = sum[rb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const int steps = (a.nvox + 3) >> 2;
     const int s0 = slab * a.per < steps ? slab * a.per : steps, s1 = s0 + a.per < steps ? s0 + a.per : steps;
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(256) void convtr_wgrad_f32_kernel(CtF32Args a) {
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-                bsum[i] += fb[u][i];
+                bacc[i] += fb[u][i];
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) acc[rb][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][rb], fb[u][i], acc[rb][i], 0, 0, 0);
             }
@@ -202,6 +204,17 @@ __global__ __launch_bounds__(256) void convtr_wgrad_f32_kernel(CtF32Args a) {
         mul(fa, fb);
         load(s + 2 * U, fa, fb);
         mul(ga, gb);
+        if (((s - s0) & 15) == 16 - 2 * U)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                bsum[i] += bacc[i];
+                bacc[i] = 0.f;
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    sum[rb][i] += acc[rb][i];
+                    acc[rb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
     }
     float* pb = a.out + (int64_t)slab * a.Ci * cols;
 #pragma unroll
@@ -213,14 +226,14 @@ __global__ __launch_bounds__(256) void convtr_wgrad_f32_kernel(CtF32Args a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int ci = r0 + 16 * rb + 4 * g + r;
-                if (ci < a.Ci) pb[(int64_t)ci * cols + c] = acc[rb][i][r];
+                if (ci < a.Ci) pb[(int64_t)ci * cols + c] = sum[rb][i][r] + acc[rb][i][r];
             }
     }
     if (!a.bpart || blockIdx.y) return;
     __shared__ float bs[4][16 * NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        float t = bsum[i];
+        float t = bsum[i] + bacc[i];
         t += __shfl_xor(t, 16);
         t += __shfl_xor(t, 32);
         if (g == 0) bs[wid][16 * i + l16] = t;

@@ -508,7 +508,12 @@ lamp_status mfma_convtr_dgrad(const lamp_tensor_desc* xd, const void* wt, const 
 // Workgroup = 4 waves on (split s, 64-wide ci block, 32-wide co block); wave w owns taps 2w, 2w+1.  Channels past the end of the
 // last block come from the zero source.  Bound: HBM (dy is read once).  The bias gradient is a product of the same dy fragments
 // with a row of ones (2 more matrix instructions per 4), taken by the first ci block: a pass of its own over dy cost 48 of the 351 us
-// of 64->32 on 2 x 64^3, forward and backward.
+// of 64->32 on 2 x 64^3, forward and backward.  Its chain ends with every chunk (432 products in a row on 2 x 96^3 round more than
+// that pass did: 7.7e-8 against 6.3e-8; now 3.4e-8).
+// FOLD (channel counts outside the multiples of 32): sums are cut into chains, chains added to a second set of registers, and
+// partials leave the split where that would round too much, so that dWt is no further off than with the thread per weight that served
+// these counts before (128 voxels a chain where 32 MB of partials allow it): 16->8 on 2 x 64^3 5.6e-8 a thread per weight, 1.4e-7 one
+// chain per split (75 us), 5.8e-8 so (82 us); 32->16 on 2 x 96^3 1.5e-7, 3.0e-7 (219 us), 1.1e-7 (222 us).
 // Chunks of 64 coarse voxels are staged in LDS (x rows of 128 bytes, dy rows of 64 bytes per tap,
 // double buffered, register-free copies) and read with the transposing LDS load.
 // (inline assembly, so that the compiler's wait-count bookkeeping does not see the copies and keeps
@@ -534,6 +539,7 @@ struct CtWArgs {
     const bf16_t* zero16;
     int N, D, H, W, Ci, Co;
     int chunks_per_split;     // 64-voxel chunks per split
+    int fold, dump, parts_per_split;   // FOLD: chunks per chain, chunks per partial, partials per split
 };
 
 static constexpr int CTW_X = 64 * 128;            // x tile bytes
@@ -574,10 +580,14 @@ __device__ __forceinline__ void ctw_stage(const CtWArgs& a, char* __restrict__ s
 }
 
 template <bool BIAS>
-__device__ __forceinline__ void ctw_compute(f32x16 (&acc)[2][2], f32x16& bacc, const char* __restrict__ st, int wv, int lane) {
+__device__ __forceinline__ void ctw_compute(f32x16 (&acc)[2][2], double& bsum, const char* __restrict__ st, int wv, int lane) {
     const int b16 = lane >> 4, s16 = lane & 15;
     const uint32_t lx = (uint32_t)((8 * (b16 >> 1) + (s16 >> 2)) * 128 + 32 * (b16 & 1) + 8 * (s16 & 3));
     const uint32_t ly = (uint32_t)((8 * (b16 >> 1) + (s16 >> 2)) * 64 + 32 * (b16 & 1) + 8 * (s16 & 3));
+    f32x16 bacc;
+    if constexpr (BIAS)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bacc[r] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
         bf16x8 af[2], bf[2];
@@ -595,9 +605,11 @@ __device__ __forceinline__ void ctw_compute(f32x16 (&acc)[2][2], f32x16& bacc, c
             for (int t = 0; t < 2; ++t) bacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, one), bf[t], bacc, 0, 0, 0);
         }
     }
+    if constexpr (BIAS) bsum += (double)bacc[0];   // every row is the sum
 }
 
-__global__ __launch_bounds__(256) void convtr_wgrad_mfma_kernel(CtWArgs a) {
+template <bool FOLD>
+__global__ __launch_bounds__(256, 2) void convtr_wgrad_mfma_kernel(CtWArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int ci0 = blockIdx.y * 64, co0 = blockIdx.z * 32;
@@ -606,46 +618,77 @@ __global__ __launch_bounds__(256) void convtr_wgrad_mfma_kernel(CtWArgs a) {
     const int64_t c_lo = (int64_t)blockIdx.x * a.chunks_per_split;
     int64_t c_hi = c_lo + a.chunks_per_split;
     if (c_hi > nchunks) c_hi = nchunks;
-    f32x16 acc[2][2];
+    f32x16 acc[2][2], sum[FOLD ? 2 : 1][2];   // sum: the chains of the partial that are done
+    auto clear = [](f32x16& v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = 0.f;
+    };
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t) {
+            clear(acc[rb][t]);
+            if constexpr (FOLD) clear(sum[rb][t]);
+        }
+    // part[slot][ci][tap][co]; input channels exist in whole groups of 8
+    auto write_partial = [&](int64_t slot, const f32x16 (&v)[2][2]) __attribute__((always_inline)) {
+        int ln = lane;
+        if constexpr (FOLD) asm volatile("" : "+v"(ln));   // the address is not worth registers of its own across the split
+        const int co = co0 + (ln & 31), wvu = __builtin_amdgcn_readfirstlane(wv);
+        if (co >= a.Co) return;
+        float* pb = a.part + ((slot * a.Ci + ci0 + 4 * (ln >> 5)) * 8 + wvu * 2) * a.Co + co;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[rb][t][r] = 0.f;
-    f32x16 bacc;
+        for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) bacc[r] = 0.f;
+            for (int rg = 0; rg < 4; ++rg)
+                if (ci0 + rb * 32 + 8 * rg < a.Ci)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) pb[(int64_t)((rb * 32 + 8 * rg + r) * 8 + t) * a.Co] = v[rb][t][4 * rg + r];
+    };
+    double bsum = 0.0;
     const bool bias = a.bpart && blockIdx.y == 0;
     if (c_lo < c_hi) ctw_stage(a, lds, c_lo * 64, nvox, ci0, co0, wv, lane);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    int par = 0;
+    int par = 0, in_chain = 0, in_part = 0;
+    int64_t part = (int64_t)blockIdx.x * a.parts_per_split;
     for (int64_t c = c_lo; c < c_hi; ++c, par ^= 1) {
         if (c + 1 < c_hi) ctw_stage(a, lds + (par ^ 1) * CTW_STAGE, (c + 1) * 64, nvox, ci0, co0, wv, lane);
         __builtin_amdgcn_sched_barrier(0);
-        if (bias) ctw_compute<true>(acc, bacc, lds + par * CTW_STAGE, wv, lane);
-        else ctw_compute<false>(acc, bacc, lds + par * CTW_STAGE, wv, lane);
+        if (bias) ctw_compute<true>(acc, bsum, lds + par * CTW_STAGE, wv, lane);
+        else ctw_compute<false>(acc, bsum, lds + par * CTW_STAGE, wv, lane);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-    }
-    float* pb = a.part + (int64_t)blockIdx.x * a.Ci * 8 * a.Co;
-    const int l32 = lane & 31, half = lane >> 5;
-    if (co0 + l32 >= a.Co) return;
-    if (bias && half == 0) a.bpart[((int64_t)blockIdx.x * 4 + wv) * a.Co + co0 + l32] = bacc[0];   // every row is the sum
+        if constexpr (FOLD) {
+            const bool out = c + 1 == c_hi || ++in_part == a.dump;
+            if (out || ++in_chain == a.fold) {
+                in_chain = 0;
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+                for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+                    for (int t = 0; t < 2; ++t) {
+                        sum[rb][t] += acc[rb][t];
+                        clear(acc[rb][t]);
+                    }
+                if (out) {
+                    in_part = 0;
+                    write_partial(part++, sum);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ci = ci0 + rb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                if (ci < a.Ci) pb[((int64_t)ci * 8 + wv * 2 + t) * a.Co + co0 + l32] = acc[rb][t][r];
+                    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) clear(sum[rb][t]);
+                }
             }
+        }
+    }
+    if constexpr (!FOLD) write_partial(blockIdx.x, acc);
+    const int co = co0 + (lane & 31);
+    if (bias && lane < 32 && co < a.Co) a.bpart[((int64_t)blockIdx.x * 4 + wv) * a.Co + co] = (float)bsum;
 }
-
 
 static int ctw_splits(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
     const int64_t chunks = (nvox(xd) + 63) / 64;
@@ -654,6 +697,34 @@ static int ctw_splits(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
     if (s < 1) s = 1;
     if (s > chunks) s = chunks;
     return (int)s;
+}
+
+// Splits, chunks per split; FOLD: chunks per chain (0: one chain per split) and per partial; number of partials.
+struct CtwPlan { int splits, per, fold, dump, parts_per_split, parts; };
+static CtwPlan ctw_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
+    const int64_t chunks = (nvox(xd) + 63) / 64;
+    CtwPlan p;
+    p.splits = p.parts = ctw_splits(xd, dyd);
+    p.per = p.dump = (int)((chunks + p.splits - 1) / p.splits);
+    p.fold = 0;
+    p.parts_per_split = 1;
+    if (xd->c % 32 || dyd->c % 32) {
+        // A chain of matrix instructions (4 a chunk) rounds like the scalar chain of 15 times as many voxels, measured; `room` of them
+        // stand for the thread-per-weight kernel's chain.  F chunks a chain and room - 4 F chains a partial cover most where F is an
+        // eighth of it.
+        const double f = (double)nvox(xd) / convtr_splits(nvox(xd), (int64_t)xd->c * 8 * dyd->c);
+        const int room = f < 128.0 ? 8 : (int)(f / 15.0);
+        p.fold = room < 16 ? 1 : room / 8;
+        if (p.fold > p.per) p.fold = p.per;
+        int64_t dump = (int64_t)(room - 4 * p.fold) * p.fold;
+        if (dump > p.per) dump = p.per;
+        const int cuts = (int)((p.per + dump - 1) / dump);
+        p.dump = (p.per + cuts - 1) / cuts;
+        p.parts_per_split = (p.per + p.dump - 1) / p.dump;
+        const int64_t walks = (chunks + p.per - 1) / p.per, last = chunks - (walks - 1) * p.per;
+        p.parts = (int)((walks - 1) * p.parts_per_split + (last + p.dump - 1) / p.dump);
+    }
+    return p;
 }
 
 bool mfma_convtr_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_norm_in* xnorm) {
@@ -666,36 +737,41 @@ bool mfma_convtr_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_d
 
 size_t mfma_convtr_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
     if (!mfma_convtr_wgrad_supported(xd, dyd, nullptr)) return 0;
-    const size_t S = (size_t)ctw_splits(xd, dyd);
-    return align_up(S * xd->c * 8 * dyd->c * sizeof(float)) + align_up(S * 4 * dyd->c * sizeof(float));
+    const CtwPlan p = ctw_plan(xd, dyd);
+    return align_up((size_t)p.parts * xd->c * 8 * dyd->c * sizeof(float)) + align_up((size_t)p.splits * 4 * dyd->c * sizeof(float));
 }
 
 lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dyd, const void* dy,
                               float* dwt, float* dbias, float beta, void* ws, size_t ws_bytes, hipStream_t s) {
     if ((((uintptr_t)x) & 15u) || (((uintptr_t)dy) & 15u) || (((uintptr_t)ws) & 15u)) return LAMP_ERR_ALIGN;
     if (ws_bytes < mfma_convtr_wgrad_ws_bytes(xd, dyd)) return LAMP_ERR_WORKSPACE;
-    const int S = ctw_splits(xd, dyd);
+    const CtwPlan p = ctw_plan(xd, dyd);
     const int64_t O = (int64_t)xd->c * 8 * dyd->c;
     CtWArgs a;
     a.x = (const bf16_t*)x; a.ldx = xd->ldc; a.dy = (const bf16_t*)dy; a.ldy = dyd->ldc; a.part = (float*)ws;
-    const bool direct = S == 1 && beta == 0.f;   // the only partial is the result: written in place
+    const bool direct = p.parts == 1 && beta == 0.f;   // the only partial is the result: written in place
     if (direct) a.part = dwt;
-    a.bpart = dbias ? (float*)((char*)ws + align_up((size_t)S * O * sizeof(float))) : nullptr;
+    a.bpart = dbias ? (float*)((char*)ws + align_up((size_t)p.parts * O * sizeof(float))) : nullptr;
     a.zero16 = device_zero16();
     if (!a.zero16) return LAMP_ERR_HIP;
     a.N = xd->n; a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Ci = xd->c; a.Co = dyd->c;
-    const int64_t chunks = (nvox(xd) + 63) / 64;
-    a.chunks_per_split = (int)((chunks + S - 1) / S);
-    if (ensure_dyn_lds((const void*)convtr_wgrad_mfma_kernel, 2 * CTW_STAGE) != LAMP_OK) return LAMP_ERR_HIP;
-    dim3 grid(S, (xd->c + 63) / 64, (dyd->c + 31) / 32);
-    hipLaunchKernelGGL(convtr_wgrad_mfma_kernel, grid, dim3(256), 2 * CTW_STAGE, s, a);
+    a.chunks_per_split = p.per;
+    a.fold = p.fold; a.dump = p.dump; a.parts_per_split = p.parts_per_split;
+    const dim3 grid(p.splits, (xd->c + 63) / 64, (dyd->c + 31) / 32);
+    if (p.fold) {
+        if (ensure_dyn_lds((const void*)convtr_wgrad_mfma_kernel<true>, 2 * CTW_STAGE) != LAMP_OK) return LAMP_ERR_HIP;
+        hipLaunchKernelGGL(convtr_wgrad_mfma_kernel<true>, grid, dim3(256), 2 * CTW_STAGE, s, a);
+    } else {
+        if (ensure_dyn_lds((const void*)convtr_wgrad_mfma_kernel<false>, 2 * CTW_STAGE) != LAMP_OK) return LAMP_ERR_HIP;
+        hipLaunchKernelGGL(convtr_wgrad_mfma_kernel<false>, grid, dim3(256), 2 * CTW_STAGE, s, a);
+    }
     LAMP_CHECK_LAUNCH();
     if (dbias) {
-        const lamp_status st = launch_reduce_partials(a.bpart, S * 4, a.Co, dbias, beta, s);
+        const lamp_status st = launch_reduce_partials(a.bpart, p.splits * 4, a.Co, dbias, beta, s);
         if (st != LAMP_OK) return st;
     }
     if (direct) return LAMP_OK;
-    return launch_reduce_partials((const float*)ws, S, O, dwt, beta, s);
+    return launch_reduce_partials((const float*)ws, p.parts, O, dwt, beta, s);
 }
 
 }  // namespace lamp

@@ -137,6 +137,8 @@ size_t f32_convtr_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_d
 lamp_status f32_convtr_wgrad(const lamp_tensor_desc* xd, const float* x, const lamp_tensor_desc* dyd, const float* dy, float* dwt,
                              float* dbias, float beta, void* ws, size_t ws_bytes, hipStream_t s);
 
+// Partials of the transposed conv's thread-per-weight kernel: 128 voxels each, 32 MB of them at most.
+int convtr_splits(int64_t V, int64_t O);
 bool mfma_convtr_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_norm_in* xnorm);
 size_t mfma_convtr_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd);
 lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dyd, const void* dy,

@@ -69,3 +69,29 @@ def test_conv3d_wgrad_bf16_ragged(L, shape, steps):
     L.lamp_conv3d_wgrad(x, dz, dw)
     e = rel(dw, wgrad64(x, dz))
     assert e <= chain(steps), f"{e:.2e} > {chain(steps):.2e}"
+
+
+# fp32: slabs of up to about 1024 voxels in chains of 64.  bf16 outside the multiples of 32: matrix instructions in a row that stand for
+# a thread per weight's chain, 128 voxels where 32 MB of partials allow it
+@pytest.mark.parametrize("dtype,shape,bound", [(F32, (2, 64, 64, 64, 64, 32), (64, 16)), (F32, (1, 100, 100, 100, 8, 4), (64, 8)),
+                                               (BF, (2, 64, 64, 64, 16, 8), (8,)), (BF, (1, 100, 100, 100, 16, 8), (16,)),
+                                               (BF, (2, 96, 96, 96, 32, 16), (57,))], ids=str)
+def test_convtr3d_wgrad(L, dtype, shape, bound):
+    n, d, h, w, ci, co = shape
+    r = rand(61 + ci)
+    x, wt, dy = torch.relu(r((n, d, h, w, ci), dtype)), r((ci, 2, 2, 2, co), dtype), r((n, 2 * d, 2 * h, 2 * w, co), dtype)
+    dwt = torch.empty(wt.shape, dtype=F32, device="cuda")
+    L.lamp_convtr3d_bwd(x, wt, dy, dwt=dwt)
+    cols = dy.reshape(n, d, 2, h, 2, w, 2, co).permute(0, 1, 3, 5, 2, 4, 6, 7).reshape(-1, 8 * co).double()
+    e = rel(dwt, (x.double().reshape(-1, ci).t().contiguous() @ cols).reshape(wt.shape))
+    assert e <= chain(*bound), f"{e:.2e} > {chain(*bound):.2e}"
+
+
+def test_convtr3d_bias_gradient_bf16(L):
+    """128 values to a product chain, those added in fp64: what rounds is each of the 2048 partials, and the result."""
+    r = rand(71)
+    x, wt, dy = r((2, 96, 96, 96, 64), BF), r((64, 2, 2, 2, 32), BF), r((2, 192, 192, 192, 32), BF)
+    dwt, db = torch.empty(wt.shape, dtype=F32, device="cuda"), torch.empty(32, dtype=F32, device="cuda")
+    L.lamp_convtr3d_bwd(x, wt, dy, dwt=dwt, dbias=db)
+    e = rel(db, sum(dy[i].sum((0, 1, 2), dtype=torch.float64) for i in range(2)))
+    assert e <= math.sqrt(2.0) * U, f"{e:.2e} > {math.sqrt(2.0) * U:.2e}"
