@@ -341,21 +341,29 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
             }
         };
         int64_t r = rbeg + r0;
-        // four rows in flight; the additions keep the row order
-        for (; r + 3 * (int64_t)rl < rend; r += 4 * (int64_t)rl) {
-            typename Vec<T, VEC>::raw vr[4], gr[4];
+        // Four rows in flight; the additions keep the row order.  The first half of the rows leaves its sums in the thread's own slots
+        // of `red`, so that a chain is no longer than with twice as many chunks (128 channels on 96^3, fp32: relative error of dgamma
+        // 1.1e-7 with 2048 chunks, 1.5e-7 with 1024 in one chain, 1.0e-7 so).
+        const bool halves = rows_per_chunk >= 16 * rl;   // a chain worth cutting
+#pragma unroll 1
+        for (int half = halves ? 0 : 1; half < 2; ++half) {
+            const int64_t stop = half ? rend : half_rows(rbeg, rows_per_chunk, rl, rend);
+            for (; r + 3 * (int64_t)rl < stop; r += 4 * (int64_t)rl) {
+                typename Vec<T, VEC>::raw vr[4], gr[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                vr[u] = Vec<T, VEC>::template raw_load<NT>(zb + (r + u * (int64_t)rl) * ldz);
-                gr[u] = Vec<T, VEC>::raw_load(gb + (r + u * (int64_t)rl) * ldg);
-            }
+                for (int u = 0; u < 4; ++u) {
+                    vr[u] = Vec<T, VEC>::template raw_load<NT>(zb + (r + u * (int64_t)rl) * ldz);
+                    gr[u] = Vec<T, VEC>::raw_load(gb + (r + u * (int64_t)rl) * ldg);
+                }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                float v[VEC], g[VEC];
-                Vec<T, VEC>::unpack(vr[u], v);
-                Vec<T, VEC>::unpack(gr[u], g);
-                add_row(v, g);
+                for (int u = 0; u < 4; ++u) {
+                    float v[VEC], g[VEC];
+                    Vec<T, VEC>::unpack(vr[u], v);
+                    Vec<T, VEC>::unpack(gr[u], g);
+                    add_row(v, g);
+                }
             }
+            if (half == 0) stash(sq, red);
         }
         for (; r < rend; r += rl) {
             float v[VEC], g[VEC];
@@ -363,6 +371,7 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
             Vec<T, VEC>::load(gb + r * ldg, g);
             add_row(v, g);
         }
+        if (halves) unstash(sq, red);
     }
     block_fold(sq, cthreads, rl, red, part, [&](int k, int e, float t) {
         const int c = blockIdx.z * 256 * VEC + e;

@@ -119,10 +119,33 @@ __device__ __forceinline__ void load_norm_vec(const T* p, const NormIn& nm, int 
     }
 }
 
+// The first half of a chunk's rows, in whole groups of four row rounds; a thread's sums over it wait in its own slots of block_fold's
+// buffer (no barrier: nobody else touches them before the fold).
+__device__ __forceinline__ int64_t half_rows(int64_t rbeg, int rows, int rl, int64_t rend) {
+    const int64_t e = rbeg + (rows / 2 + 4 * rl - 1) / (4 * rl) * (4 * rl);
+    return e < rend ? e : rend;
+}
+template <int NV, int VEC> __device__ __forceinline__ void stash(float (&v)[NV][VEC], float* red) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            red[k * (256 * VEC) + threadIdx.x * VEC + i] = v[k][i];
+            v[k][i] = 0.f;
+        }
+}
+template <int NV, int VEC> __device__ __forceinline__ void unstash(float (&v)[NV][VEC], const float* red) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) v[k][i] += red[k * (256 * VEC) + threadIdx.x * VEC + i];
+}
+
 // Sums NV sets of VEC values per thread over the row lanes of a block (thread = row lane * cthreads + channel-vector lane) and
 // hands each to put(set, channel of the block, sum).  All 256 threads add: with only the first row lane's cthreads threads at
 // work, a 16-channel bf16 tensor left 2 threads a serial chain of 2048 LDS reads, which was 45 of the 60 us of its backward sums
-// (2 x 64 x 80 x 96 voxels).  `red`: NV * 256 * VEC floats, `part`: 256 floats.  A fixed order for a given cthreads.
+// (2 x 64 x 80 x 96 voxels).  The additions are fp64: these are the largest addends of a partial and would round most.  `red`:
+// NV * 256 * VEC floats, `part`: 256 floats.  A fixed order for a given cthreads.
 template <int NV, int VEC, typename F>
 __device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthreads, int rl, float* red, float* part, F put) {
     const int tid = threadIdx.x, nc = cthreads * VEC, nout = NV * nc;
@@ -133,22 +156,22 @@ __device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthrea
     __syncthreads();
     if (nout <= 128) {   // several threads per sum, each a share of the rows, then the shares in order
         const int P = 256 / nout, o = tid % nout, p = tid / nout, k = o / nc, e = o - k * nc;
-        float t = 0.f;
+        double t = 0.0;
         if (p < P)
-            for (int r = p; r < rl; r += P) t += red[k * (256 * VEC) + r * nc + e];
-        part[tid] = t;
+            for (int r = p; r < rl; r += P) t += (double)red[k * (256 * VEC) + r * nc + e];
+        part[tid] = (float)t;
         __syncthreads();
         if (tid < nout) {
-            t = part[tid];
-            for (int q = 1; q < P; ++q) t += part[q * nout + tid];
-            put(k, e, t);
+            t = (double)part[tid];
+            for (int q = 1; q < P; ++q) t += (double)part[q * nout + tid];
+            put(k, e, (float)t);
         }
     } else {
         for (int o = tid; o < nout; o += 256) {
             const int k = o / nc, e = o - k * nc;
-            float t = 0.f;
-            for (int r = 0; r < rl; ++r) t += red[k * (256 * VEC) + r * nc + e];
-            put(k, e, t);
+            double t = 0.0;
+            for (int r = 0; r < rl; ++r) t += (double)red[k * (256 * VEC) + r * nc + e];
+            put(k, e, (float)t);
         }
     }
 }

@@ -95,3 +95,17 @@ def test_convtr3d_bias_gradient_bf16(L):
     L.lamp_convtr3d_bwd(x, wt, dy, dwt=dwt, dbias=db)
     e = rel(db, sum(dy[i].sum((0, 1, 2), dtype=torch.float64) for i in range(2)))
     assert e <= math.sqrt(2.0) * U, f"{e:.2e} > {math.sqrt(2.0) * U:.2e}"
+
+
+# 1024 chunks of 864 rows, 864 / row lanes of them to a thread in two chains, half of the elements masked; then the row lanes in a chain
+@pytest.mark.parametrize("c,bound", [(256, (54, 4)), (128, (27, 8))], ids=["256", "128"])
+def test_inorm_bwd_sums(L, c, bound):
+    r = rand(81)
+    z, dy = r((1, 96, 96, 96, c)), r((1, 96, 96, 96, c))
+    st = torch.tensor([0.0, 1.0], device="cuda").repeat(1, c, 1).contiguous()   # zhat = z, mask = z > 0, both exact
+    dg, db, dz = torch.empty(c, device="cuda"), torch.empty(c, device="cuda"), torch.empty_like(z)
+    L.lamp_inorm_relu_bwd(dy, z, st, dz, gamma=torch.ones(c, device="cuda"), beta=torch.zeros(c, device="cuda"), dgamma=dg, dbeta=db)
+    g = torch.where(z > 0, dy, torch.zeros_like(dy)).double()
+    for got, ref in ((dg, (g * z.double()).sum((0, 1, 2, 3))), (db, g.sum((0, 1, 2, 3)))):
+        e = (got.double() - ref).square().mean().sqrt().item() / math.sqrt(z.numel() / c / 2.0)
+        assert e <= chain(*bound), f"{e:.2e} > {chain(*bound):.2e}"
