@@ -81,6 +81,9 @@ typedef struct {
  * and channels [c_norm, c) are read unchanged (the transposed-conv half of a concat buffer).
  * Zero padding is applied AFTER the transform (out-of-volume reads are literal zeros).
  * mean_rstd: fp32 [N][c_norm][2]; gamma, beta: fp32 [c_norm], NULL = 1 / 0.
+ * A call with the transform gives what the call on the transformed tensor gives, up to the order of the fp32 sums: the
+ * fp32 3x3x3 conv takes that order from its kernel, which is the same with and without the transform up to 64 output
+ * channels and another one above.
  */
 typedef struct {
     const float *mean_rstd;

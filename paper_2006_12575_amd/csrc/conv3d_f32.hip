@@ -547,6 +547,8 @@ __global__ __launch_bounds__(256, 2) void conv3d_f32_wide_kernel(F32WideArgs a) 
         }
     }
 }
+// Not with normalise-on-load, whose coefficients every tap would fetch anew (128->256 on 2 x 16^3: 855 us, the tiled kernel 154): above
+// 64 outputs a call with it takes the tiled kernel's order of sums and a call without it this one's.
 static bool f32_wide(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, const NormIn& nm, bool dgrad) {
     return !dgrad && !nm.mean_rstd && zd->c > 64 && nvox(zd) < ((int64_t)1 << 30) && (int64_t)27 * xd->c * zd->c < ((int64_t)1 << 32) &&
            cdiv(zd->c, 16) <= 65535;

@@ -110,7 +110,8 @@ bool f32_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd);
 size_t f32_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, int want_stats);
 lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm, const void* w, const float* bias, bool dgrad,
                      const lamp_tensor_desc* zd, void* z, float* stats_out, float eps, void* ws, size_t ws_bytes, hipStream_t s);
-// The forward pass with normalise-on-load gives bit for bit what it gives on the normalised tensor (one kernel, one order).
+// The forward pass with normalise-on-load gives bit for bit what it gives on the normalised tensor (one kernel, one order; up to 64
+// outputs).
 bool f32_norm_on_load(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd);
 bool f32_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd);
 size_t f32_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd);
