@@ -33,8 +33,8 @@ const bf16_t* device_zero16() {
 // Block = 256 / SL groups of VO consecutive outputs x SL lanes over the parts; every lane adds its strided parts in order, then
 // the lanes are folded by halves: a fixed summation tree, fp64.
 // Bound: HBM (the parts are read once).  VO = 4 makes a part's row a run of whole 64-byte pieces also where SL lanes leave a block
-// few outputs (64->32 transposed conv, 512 parts of 16384: 37 -> 12 us), and gives a thread enough in flight where there are few
-// parts of many outputs (256->256 conv weights, 4 parts of 1.8 M: 21.6 -> 10.6 us).
+// few outputs (64->32 transposed conv, 512 parts of 16384: 37 -> 12 us, with the right number of lanes less), and gives a thread
+// enough in flight where there are few parts of many outputs (256->256 conv weights, 4 parts of 1.8 M: 21.6 -> 10.6 us).
 template <int SL, int VO>
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ part, int S, int64_t O,
                                                               float* __restrict__ out, float beta) {
@@ -99,18 +99,27 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
     }
 }
 
-// Lanes over the parts: as few as give about 1024 blocks, never more than there are parts.
+// Lanes over the parts: as many as leave fewer than 1024 blocks (four a CU), never more than there are parts.  From 1024 blocks on the
+// short blocks of many lanes take turns, and their many small reads of every part's row cost more than a longer loop over the parts
+// (27648 outputs, 256 parts: 64 lanes 11.0 us, 32 to 8 lanes 3.7, one lane 14.8; 16384 x 512: 12.3, 4.3 with 32).  64 lanes pay for
+// a few outputs only (32 x 4096: 4.4 us, with 32 lanes 6.0; 864 x 3000: 6.9 and 5.4).
 template <int VO>
 static void reduce_launch(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s) {
     const int64_t g = O / VO;
-    if (g >= 256 * 1024 || S < 4)
-        hipLaunchKernelGGL((reduce_partials_kernel<1, VO>), dim3(cdiv(g, 256)), dim3(256), 0, s, part, S, O, out, beta);
-    else if (g >= 64 * 1024 || S < 16)
-        hipLaunchKernelGGL((reduce_partials_kernel<4, VO>), dim3(cdiv(g, 64)), dim3(256), 0, s, part, S, O, out, beta);
-    else if (g >= 16 * 1024 || S < 64)
-        hipLaunchKernelGGL((reduce_partials_kernel<16, VO>), dim3(cdiv(g, 16)), dim3(256), 0, s, part, S, O, out, beta);
-    else
-        hipLaunchKernelGGL((reduce_partials_kernel<64, VO>), dim3(cdiv(g, 4)), dim3(256), 0, s, part, S, O, out, beta);
+    int sl = 1;
+    while (2 * sl <= (O <= 256 ? 64 : 32) && 2 * sl <= S && (g * 2 * sl + 255) / 256 < 1024) sl *= 2;
+#define LAMP_REDUCE(SL) \
+    case SL: hipLaunchKernelGGL((reduce_partials_kernel<SL, VO>), dim3(cdiv(g, 256 / SL)), dim3(256), 0, s, part, S, O, out, beta); break
+    switch (sl) {
+        LAMP_REDUCE(1);
+        LAMP_REDUCE(2);
+        LAMP_REDUCE(4);
+        LAMP_REDUCE(8);
+        LAMP_REDUCE(16);
+        LAMP_REDUCE(32);
+        LAMP_REDUCE(64);
+    }
+#undef LAMP_REDUCE
 }
 
 lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s) {
