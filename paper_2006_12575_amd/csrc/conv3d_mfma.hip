@@ -1152,6 +1152,10 @@ static bool conv_pack_plan(const lamp_tensor_desc* zd, PackPlan& best) {
     }
     return found;
 }
+bool mfma_conv_packs(const lamp_tensor_desc* zd) {
+    PackPlan p;
+    return conv_pack_plan(zd, p);
+}
 static void pack_descs(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, const PackPlan& p, lamp_tensor_desc& xp,
                        lamp_tensor_desc& zp) {
     xp = *xd; xp.n = 1; xp.h = p.hp; xp.w = p.wp; xp.ldc = xd->c;

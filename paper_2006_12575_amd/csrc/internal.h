@@ -79,6 +79,7 @@ lamp_status inorm_relu_maxpool2(const lamp_tensor_desc* xd, const void* z, const
 // wcin of the calls below: the weight's input channels where x holds more (a narrow x padded with zero channels); 0: x's.
 bool mfma_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, const lamp_norm_in* xnorm,
                          const float* bias);
+bool mfma_conv_packs(const lamp_tensor_desc* zd);   // the batch of tiny volumes goes through a packed copy
 size_t mfma_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd, int want_stats);
 // Two-part tensors: a channel concat that is never materialised.  x2: second input tensor holding the
 // input channels from x_c1 on (same channel stride as x, x_c1 % 16 == 0); z2: second output tensor

@@ -93,6 +93,18 @@ def test_conv3d_narrow_input_bf16(L, shape):
     conv_passes(L, BF, shape, 2200, 2e-3)
 
 
+@pytest.mark.parametrize("shape", [(8, 4, 4, 4, 8, 8), (40, 6, 6, 6, 8, 1), (75, 7, 7, 7, 8, 8), (100, 7, 7, 7, 8, 8)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_conv3d_dgrad_tiny_batch_bf16(L, shape):
+    """8 channels on batches of tiny volumes: up to 32768 voxels the scalar kernel, above the matrix-core one on the packed batch."""
+    N, D, H, W, Ci, Co = shape
+    r = rng(2250 + N)
+    dz, w = to_dev(S.normal(r, (N, D, H, W, Co)), BF), to_dev(S.kaiming_conv(r, Co, Ci), BF)
+    dx = torch.full((N, D, H, W, Ci), float("nan"), dtype=BF, device=DEV)
+    L.lamp_conv3d_dgrad(dz, w, dx)
+    check(as64(dx), O.conv3d_dgrad(as64(dz), as64(w)), BF, "conv dgrad")
+
+
 def test_conv3d_ragged_channels_unaligned_weights(L):
     """Channel counts outside 16 / 32 take weights at any alignment (the scalar kernels read them)."""
     r = rng(2300)
