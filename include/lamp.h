@@ -118,8 +118,12 @@ lamp_status lamp_rmsprop_step(int32_t count, const int64_t *numel, float *const 
  *   bias      : nullable, fp32 [Co].
  *   stats_out : nullable, fp32 [N][Co][2] = (mean, rstd = 1/sqrt(biased var + eps)) of the STORED
  *               z over d,h,w -- the InstanceNorm statistics, produced in the conv epilogue.
- * bf16 requires pointers 16-byte aligned; any Ci, Co >= 1 is accepted (Co a multiple of 8 takes the
- * matrix-core kernels, whatever Ci, where w and ws are 16-byte aligned).
+ * bf16 requires x and z 16-byte aligned; any Ci, Co >= 1 is accepted.  Fast are Ci and Co in multiples of 8 (with
+ * channel strides in multiples of 8, w and ws 16-byte aligned), Ci = 2 to 4 (z's channel stride a multiple of 4) and
+ * Ci = 1 with Co = 32, 64 or 128 (no bias, no xnorm); the data gradient also from any Co and the weight gradient from any
+ * Ci where the other count is a multiple of 8.  Every other bf16 case runs on scalar kernels, so does xnorm from 5
+ * channels on where Ci is no multiple of 16, Co none of 32 or c_norm < Ci.  fp32: any counts, strides and alignments on
+ * the matrix cores.
  */
 size_t lamp_conv3d_fwd_workspace_bytes(const lamp_tensor_desc *xd, const lamp_tensor_desc *zd, int want_stats);
 lamp_status lamp_conv3d_fwd(const lamp_tensor_desc *xd, const void *x, const lamp_norm_in *xnorm,

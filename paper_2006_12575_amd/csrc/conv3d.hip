@@ -1,6 +1,6 @@
 // 3x3x3 convolution: public entry points, argument checking, kernel selection, and the generic
-// direct kernels (any dtype / channel count) behind the matrix-core ones: bf16 odd channel counts and normalise-on-load of a
-// part of the channels, fp32 past the limits of conv3d_f32.hip.
+// direct kernels (any dtype / channel count) behind the matrix-core ones: bf16 channel counts outside the multiples of 8 and
+// normalise-on-load of a part of the channels, fp32 past the limits of conv3d_f32.hip.
 #include "internal.h"
 #include "vec.h"
 
@@ -626,12 +626,14 @@ static lamp_status check_conv_pair(const lamp_tensor_desc* a, const void* pa, co
     return LAMP_OK;
 }
 
-// The same sum with register tiling, for output channels in multiples of 8 (bf16 weights off 16 bytes): a thread owns OCG output channels of one voxel; the weights of a chunk of 8 input channels sit in
-// LDS as [tap][ic][oc] (every lane of a wave reads the same few addresses), the input voxel is read once per
-// (tap, ic) and used OCG times.  Input-channel chunks are taken in order, taps inside a chunk: a fixed order.
-template <typename T, bool DGRAD, int OCG>
-__global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict__ x, int ldx, const T* __restrict__ w,
-                                                             const float* __restrict__ bias, T* __restrict__ z, int ldz, int N,
+// The same sum with register tiling, for bf16 tensors with 8 to 64 output channels in multiples of 8 that take no matrix-core kernel:
+// the forward pass of 5 to 7 input channels or of more that are no multiple of 8 (12, 20), weights or workspaces off 16 bytes, output
+// voxels off 8 bytes, data gradients of tiny batches (dgrad_tiny).  A thread owns OCG output channels of one voxel; the weights of a
+// chunk of 8 input channels sit in LDS as [tap][ic][oc] (every lane of a wave reads the same few addresses), the input voxel is read
+// once per (tap, ic) and used OCG times.  Input-channel chunks are taken in order, taps inside a chunk: a fixed order.
+template <bool DGRAD, int OCG>
+__global__ __launch_bounds__(256) void conv3d_regtile_kernel(const bf16_t* __restrict__ x, int ldx, const bf16_t* __restrict__ w,
+                                                             const float* __restrict__ bias, bf16_t* __restrict__ z, int ldz, int N,
                                                              int D, int H, int W, int Cin, int Cout, int xvec, int wvec) {
     extern __shared__ float wsm[];   // [27][ICH][Cout]
     constexpr int ICH = 8;
@@ -657,7 +659,7 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
         __syncthreads();
         // weights of the chunk -> LDS [tap][ic][oc].  16-byte granules where the layout allows (forward: along ic,
         // the contiguous index of W[oc][t][ic]; data gradient: along oc of W[ic][26-t][oc]); four granules in flight.
-        constexpr int VW = sizeof(T) == 2 ? 8 : 4;
+        constexpr int VW = 8;
         if (wvec && nic == ICH) {
             const int gtot = 27 * ICH * Cout / VW;
             for (int i0 = threadIdx.x; i0 < gtot; i0 += 1024) {
@@ -670,11 +672,11 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
                     if (i < gtot) {
                         if (DGRAD) {
                             const int ocv = i % (Cout / VW), r = i / (Cout / VW), ic = r % ICH, t = r / ICH;
-                            Vec<T, VW>::load(w + ((int64_t)(ic0 + ic) * 27 + (26 - t)) * Cout + ocv * VW, val[u]);
+                            Vec<bf16_t, VW>::load(w + ((int64_t)(ic0 + ic) * 27 + (26 - t)) * Cout + ocv * VW, val[u]);
                             dst[u] = (t * ICH + ic) * Cout + ocv * VW;
                         } else {
                             const int icv = i % (ICH / VW), r = i / (ICH / VW), t = r % 27, oc = r / 27;
-                            Vec<T, VW>::load(w + ((int64_t)oc * 27 + t) * Cin + ic0 + icv * VW, val[u]);
+                            Vec<bf16_t, VW>::load(w + ((int64_t)oc * 27 + t) * Cin + ic0 + icv * VW, val[u]);
                             dst[u] = (t * ICH + icv * VW) * Cout + oc;
                         }
                     }
@@ -691,7 +693,7 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
             for (int i = threadIdx.x; i < wtot; i += 256) {
                 const int ic = i % nic, r = i / nic;
                 int t, oc;
-                const T* src;
+                const bf16_t* src;
                 if (DGRAD) {
                     oc = r % Cout; t = r / Cout;
                     src = w + ((int64_t)(ic0 + ic) * 27 + (26 - t)) * Cout + oc;
@@ -699,7 +701,7 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
                     t = r % 27; oc = r / 27;
                     src = w + ((int64_t)oc * 27 + t) * Cin + ic0 + ic;
                 }
-                wsm[(t * ICH + ic) * Cout + oc] = io<T>::ld(src);
+                wsm[(t * ICH + ic) * Cout + oc] = io<bf16_t>::ld(src);
             }
         }
         __syncthreads();
@@ -712,19 +714,17 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
             for (int kw = 0; kw < 3; ++kw) {
                 const int iw = wv + kw - 1;
                 const bool in = rin && iw >= 0 && iw < W;
-                const T* xp = x + ((((int64_t)n * D + (rin ? id : d)) * H + (rin ? ih : h)) * W + (in ? iw : wv)) * ldx + ic0;
-                if (xvec && nic == ICH) {   // one or two 16-byte loads instead of eight narrow ones
-                    constexpr int VW = sizeof(T) == 2 ? 8 : 4;
+                const bf16_t* xp = x + ((((int64_t)n * D + (rin ? id : d)) * H + (rin ? ih : h)) * W + (in ? iw : wv)) * ldx + ic0;
+                if (xvec && nic == ICH) {   // one 16-byte load instead of eight narrow ones
                     if (in) {
-                        Vec<T, VW>::load(xp, *reinterpret_cast<float(*)[VW]>(&xr[kw][0]));
-                        if (VW == 4) Vec<T, VW>::load(xp + 4, *reinterpret_cast<float(*)[VW]>(&xr[kw][ICH - VW]));
+                        Vec<bf16_t, ICH>::load(xp, xr[kw]);
                     } else {
 #pragma unroll
                         for (int ic = 0; ic < ICH; ++ic) xr[kw][ic] = 0.f;
                     }
                 } else {
 #pragma unroll
-                    for (int ic = 0; ic < ICH; ++ic) xr[kw][ic] = (in && ic < nic) ? io<T>::ld(xp + ic) : 0.f;
+                    for (int ic = 0; ic < ICH; ++ic) xr[kw][ic] = (in && ic < nic) ? io<bf16_t>::ld(xp + ic) : 0.f;
                 }
             }
         };
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
     }
     if (active) {
 #pragma unroll
-        for (int o = 0; o < OCG; ++o) io<T>::st(z + v * ldz + og * OCG + o, acc[o]);
+        for (int o = 0; o < OCG; ++o) io<bf16_t>::st(z + v * ldz + og * OCG + o, acc[o]);
     }
 }
 
@@ -769,8 +769,10 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const T* __restrict
 // The matrix-core kernels copy 16-byte pieces (8 channels).  An input with fewer channels than that, or whose voxels do
 // not start on 16 bytes -- a two- or four-channel image in front of a first layer -- is copied once into whole pieces with
 // zero channels behind the real ones: 16 bytes written per voxel and piece, against the 2 * C_out bytes that the conv
-// writes: for the data gradient and the weight gradient (weight gradient of 2->16 channels on 2 x 64 x 80 x 96 voxels: 1.2 ms -> 62 us).  The forward pass
-// of such inputs keeps the scalar sums: on saturated image regions a sum that rounds the other way moves whole regions over the ReLU.
+// writes: for the data gradient and the weight gradient (weight gradient of 2->16 channels on 2 x 64 x 80 x 96 voxels: 1.2 ms -> 62 us).
+// The forward pass keeps the scalar kernel's order of sums, on saturated image regions a sum that rounds the other way moves whole
+// regions over the ReLU: 2 to 4 channels on the fp32 matrix instruction (conv3d_f32.hip), 1 on kernels of its own, the rest, which are
+// no images, on the scalar kernels, where they always were.
 // One thread per voxel and piece.
 __global__ __launch_bounds__(256) void conv_pad_kernel(const bf16_t* __restrict__ x, int ldx, int C, bf16_t* __restrict__ xp,
                                                        int gpv, int64_t granules) {
@@ -826,7 +828,7 @@ static lamp_status launch_direct(const lamp_tensor_desc* xd, const void* x, Norm
         // 16-byte loads of a voxel's 8-channel chunk need aligned rows
         const int xvec = aligned16(x) && (xd->ldc * esize(xd->dtype)) % 16 == 0 ? 1 : 0;
         const int wvec = aligned16(w) && ((DGRAD ? Cout : Cin) * esize(xd->dtype)) % 16 == 0 ? 1 : 0;
-        hipLaunchKernelGGL((conv3d_regtile_kernel<bf16_t, DGRAD, 8>), grid, dim3(256), shm, s, (const bf16_t*)x, xd->ldc,
+        hipLaunchKernelGGL((conv3d_regtile_kernel<DGRAD, 8>), grid, dim3(256), shm, s, (const bf16_t*)x, xd->ldc,
                            (const bf16_t*)w, bias, (bf16_t*)z, zd->ldc, zd->n, zd->d, zd->h, zd->w, Cin, Cout, xvec, wvec);
         LAMP_CHECK_LAUNCH();
         return LAMP_OK;
