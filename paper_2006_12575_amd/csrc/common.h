@@ -111,5 +111,12 @@ struct Carver {
 };
 
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+// round-up reciprocal for exact division of v < 2^31 by d: v / d == (v * m) >> s
+static inline void div_magic(int d, uint32_t* m, int* s) {
+    int l = 0;
+    while ((1ll << l) < d) ++l;
+    *s = 31 + l;
+    *m = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d);
+}
 
 }  // namespace lamp

@@ -529,12 +529,7 @@ static lamp_status cin1_tile_fwd(const lamp_tensor_desc* xd, const void* x, cons
     a.G = cin1_tile_groups(zd);
     a.WP = 32 * a.G + 2;
     a.RS = a.WP;
-    {   // round-up reciprocal: e / WP == (e * m) >> sh for e < 2^31
-        int l = 0;
-        while ((1 << l) < a.WP) ++l;
-        a.sWP = 31 + l;
-        a.mWP = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)a.WP - 1) / (uint64_t)a.WP);
-    }
+    div_magic(a.WP, &a.mWP, &a.sWP);
     const int gx = cin1_tile_gridx(zd);
     const int parts = gx * 4;
     a.partial = nullptr; a.counts = nullptr;
@@ -581,12 +576,7 @@ static lamp_status cin1_wtile(const lamp_tensor_desc* xd, const void* x, const l
     a.G = cin1_wtile_groups(xd);
     a.WP = 16 * a.G + 2;
     a.RS = a.WP;
-    {
-        int l = 0;
-        while ((1 << l) < a.WP) ++l;
-        a.sWP = 31 + l;
-        a.mWP = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)a.WP - 1) / (uint64_t)a.WP);
-    }
+    div_magic(a.WP, &a.mWP, &a.sWP);
     const int cb = dzd->c >= 128 ? 4 : (dzd->c >= 64 ? 2 : 1);   // channels per workgroup column: 32 * cb
     const int gx = cin1_wtile_gridx(xd);
     const dim3 grid(gx, dzd->c / (32 * cb));

@@ -35,14 +35,6 @@ static TileGeo pick_tile(int D, int H, int W, int vox, int halo) {
     return best;
 }
 
-// round-up reciprocal: e / d == (e * m) >> s for e < 2^31
-static void f32_magic(int d, uint32_t* m, int* s) {
-    int l = 0;
-    while ((1 << l) < d) ++l;
-    *s = 31 + l;
-    *m = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d);
-}
-
 // ---- forward and data gradient --------------------------------------------------------------------
 // Bound: the fp32 matrix rate (157 TFLOP/s; 32 input channels are 432 flops a byte).  D[co][voxel] += W[co][ci] * X[ci][voxel + tap]
 // with A = weights, B = voxels, so that a lane ends with 4 consecutive output channels of one voxel (a 16-byte store).  A
@@ -564,9 +556,9 @@ static void f32_wide_launch(const lamp_tensor_desc* xd, const float* x, const fl
     a.D = zd->d; a.H = zd->h; a.W = zd->w; a.Ci = xd->c; a.Co = zd->c;
     a.nvox = (int)nvox(zd);
     a.zvec = aligned16(z) && zd->ldc % 4 == 0;
-    f32_magic(a.W, &a.mW, &a.sW);
-    f32_magic(a.H, &a.mH, &a.sH);
-    f32_magic(a.D, &a.mD, &a.sD);
+    div_magic(a.W, &a.mW, &a.sW);
+    div_magic(a.H, &a.mH, &a.sH);
+    div_magic(a.D, &a.mD, &a.sD);
     const bool vec = aligned16(x) && aligned16(w) && xd->c % 4 == 0 && xd->ldc % 4 == 0;
     // 64 voxels x 64 channels a wave where that gives every CU half a workgroup at least, else 16 x 16 with more steps in flight
     const bool big = (int64_t)cdiv(a.nvox, 256) * cdiv(a.Co, 64) >= 128;
@@ -599,8 +591,8 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
     a.xvec = aligned16(x) && xd->c % 4 == 0 && xd->ldc % 4 == 0;
     a.zvec = aligned16(z) && zd->ldc % 4 == 0;
     a.wvec = aligned16(w) && (dgrad ? zd->c : xd->c) % 4 == 0;
-    f32_magic((1 << p.t.lw) + 2, &a.mHW, &a.sHW);
-    f32_magic((1 << p.t.lh) + 2, &a.mHH, &a.sHH);
+    div_magic((1 << p.t.lw) + 2, &a.mHW, &a.sHW);
+    div_magic((1 << p.t.lh) + 2, &a.mHH, &a.sHH);
     a.partial = nullptr; a.counts = nullptr;
     if (stats_out) {
         if (!ws || ws_bytes < f32_conv_ws_bytes(xd, zd, 1)) return LAMP_ERR_WORKSPACE;

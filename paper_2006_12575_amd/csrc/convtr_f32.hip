@@ -243,22 +243,15 @@ __global__ __launch_bounds__(256, 2) void convtr_wgrad_f32_kernel(CtF32Args a) {
     if (c < 16 * NB && c0 + c < cols) a.bpart[(int64_t)blockIdx.x * cols + c0 + c] = bs[0][c] + bs[1][c] + bs[2][c] + bs[3][c];
 }
 
-// round-up reciprocal: v / d == (v * m) >> s for v < 2^31
-static void ctf_magic(int d, uint32_t* m, int* s) {
-    int l = 0;
-    while ((1ll << l) < d) ++l;
-    *s = 31 + l;
-    *m = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d);
-}
 static CtF32Args ctf_args(const lamp_tensor_desc* xd, const lamp_tensor_desc* yd) {
     CtF32Args a = {};
     a.ldx = xd->ldc; a.ldy = yd->ldc;
     a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Ci = xd->c; a.Co = yd->c;
     a.nvox = (int)nvox(xd);
-    ctf_magic(a.W, &a.mW, &a.sW);
-    ctf_magic(a.H, &a.mH, &a.sH);
-    ctf_magic(a.D, &a.mD, &a.sD);
-    ctf_magic(a.Co, &a.mC, &a.sC);
+    div_magic(a.W, &a.mW, &a.sW);
+    div_magic(a.H, &a.mH, &a.sH);
+    div_magic(a.D, &a.mD, &a.sD);
+    div_magic(a.Co, &a.mC, &a.sC);
     return a;
 }
 

@@ -27,7 +27,7 @@ struct CtArgs {
     int N, D, H, W;       // coarse (input-resolution) dims
     int Ci, Co;
     int ldb, ldo;         // channel strides of b and out
-    uint32_t mW, mH, mD;  // v / d == (v * m) >> s for v < 2^31 (round-up reciprocal, see ct_magic)
+    uint32_t mW, mH, mD;  // v / d == (v * m) >> s for v < 2^31 (div_magic)
     int sW, sH, sD;
 };
 
@@ -402,17 +402,10 @@ __global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
     }
 }
 
-// round-up reciprocal for exact division of v < 2^31 by d: v / d == (v * m) >> s
-static void ct_magic(int d, uint32_t* m, int* s) {
-    int l = 0;
-    while ((1ll << l) < d) ++l;
-    *s = 31 + l;
-    *m = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d);
-}
 static void ct_set_magic(CtArgs& a) {
-    ct_magic(a.W, &a.mW, &a.sW);
-    ct_magic(a.H, &a.mH, &a.sH);
-    ct_magic(a.D, &a.mD, &a.sD);
+    div_magic(a.W, &a.mW, &a.sW);
+    div_magic(a.H, &a.mH, &a.sH);
+    div_magic(a.D, &a.mD, &a.sD);
 }
 
 // 32 rows per wave when the volume is small (more workgroups), up to 128 otherwise (measured: from 32768
