@@ -87,9 +87,13 @@ def test_conv3d_ragged_channels_bf16(L, shape):
 
 
 @pytest.mark.parametrize("shape", [(1, 6, 9, 33, 2, 16), (2, 5, 6, 7, 3, 24), (1, 7, 9, 16, 12, 64), (1, 5, 6, 9, 4, 32),
-                                   (5, 4, 4, 4, 20, 32), (1, 4, 5, 6, 1, 40)], ids=lambda s: "x".join(map(str, s)))
+                                   (5, 4, 4, 4, 20, 32), (1, 4, 5, 6, 1, 40),
+                                   # two to four channels forward: 256-voxel tiles with one and two blocks of 16 outputs, then 128 and 64
+                                   (1, 41, 40, 44, 2, 16), (1, 41, 40, 44, 3, 40), (1, 33, 32, 34, 2, 24), (1, 20, 28, 36, 4, 24)],
+                         ids=lambda s: "x".join(map(str, s)))
 def test_conv3d_narrow_input_bf16(L, shape):
-    """Input channels that fill no 16-byte piece: padded with zero channels in the workspace."""
+    """Input channels that fill no 16-byte piece: padded with zero channels in the workspace for the gradients, on the fp32 matrix
+    instruction (two to four) or the scalar kernels forward."""
     conv_passes(L, BF, shape, 2200, 2e-3)
 
 
@@ -125,8 +129,8 @@ def test_conv3d_ragged_channels_unaligned_weights(L):
 # 70000 voxels (1.6e-5) in partials of at most a few thousand
 @pytest.mark.parametrize("shape", [
     (1, 1, 1, 1, 1, 1),
-    (1, 5, 6, 7, 1, 8),          # channel chunks of 4: one, two, three, four channels; 64-voxel tiles
-    (2, 5, 9, 17, 2, 17),        # one channel in the last block; 32-voxel tiles, waves share out the channels
+    (1, 5, 6, 7, 1, 8),          # 64-voxel tiles; channel chunks of 4: one, two, three, four channels
+    (2, 5, 9, 17, 2, 17),        # one channel in the last block of 16
     (1, 6, 9, 33, 3, 33),
     (2, 3, 20, 12, 4, 16),
     (1, 7, 9, 10, 5, 24),        # chunks of 8 cut short
@@ -135,10 +139,17 @@ def test_conv3d_ragged_channels_unaligned_weights(L):
     (1, 9, 10, 11, 32, 16),      # chunks of 16
     (1, 4, 4, 4, 80, 72),
     (1, 33, 32, 34, 16, 16),     # 128-voxel tiles
-    (1, 33, 32, 34, 8, 48),
+    (1, 33, 32, 34, 8, 32),      # with blocks of 32 outputs; chunks of 8 and of 4
+    (1, 33, 32, 34, 2, 24),
+    (1, 33, 32, 34, 20, 8),      # the same in the data gradient
     (1, 41, 40, 44, 16, 24),     # 256-voxel tiles
+    (1, 33, 32, 34, 8, 48),
     (2, 33, 40, 47, 2, 8),
     (1, 41, 40, 44, 9, 12),
+    (1, 41, 40, 44, 3, 40),
+    (1, 41, 40, 44, 24, 3),
+    (1, 20, 28, 36, 2, 24),      # 64-voxel tiles with blocks of 32 outputs, forward and data gradient
+    (1, 20, 28, 36, 32, 4),
     (1, 5, 6, 7, 3, 72),         # more than 64 output channels: 16-voxel waves, 4-byte and 16-byte loads
     (2, 4, 9, 11, 20, 100),
     (1, 33, 32, 34, 16, 128),    # 64-voxel waves
@@ -149,7 +160,8 @@ def test_conv3d_f32(L, shape):
 
 
 def test_conv3d_f32_unaligned(L):
-    """fp32 tensors and weights off 16 bytes, channel strides that are no multiple of 4; a partial normalise-on-load."""
+    """fp32 tensors and weights off 16 bytes, channel strides that are no multiple of 4; a partial normalise-on-load, forward and in
+    the weight gradient."""
     r = rng(2500)
     N, D, H, W, Ci, Co = 2, 5, 6, 19, 16, 20
 
@@ -173,6 +185,16 @@ def test_conv3d_f32_unaligned(L):
     dw = torch.empty(wh.shape, dtype=F32, device=DEV)
     L.lamp_conv3d_wgrad(x, dz, dw)
     check(as64(dw), O.conv3d_wgrad(as64(x), as64(dz))[0], F32, "conv wgrad")
+    cn = 10
+    st = torch.stack([to_dev(S.normal(r, (N, cn), 0.1), F32), to_dev(S.normal(r, (N, cn)), F32).abs() + 0.5], -1).contiguous()
+    xh = as64(x).copy()
+    m = as64(st)[:, None, None, None]
+    xh[..., :cn] = np.maximum(0.0, (xh[..., :cn] - m[..., 0]) * m[..., 1])
+    nm = dict(mean_rstd=st, c_norm=cn, relu=1)
+    L.lamp_conv3d_fwd(x, w, z, xnorm=nm)
+    check(as64(z), O.conv3d_fwd(xh, as64(w)), F32, "conv fwd, normalise-on-load")
+    L.lamp_conv3d_wgrad(x, dz, dw, xnorm=nm)
+    check(as64(dw), O.conv3d_wgrad(xh, as64(dz))[0], F32, "conv wgrad, normalise-on-load")
 
 
 # the transposed conv: fp32 on both wave tilings and both channel-block widths, bf16 weight gradient with channels past its blocks;
