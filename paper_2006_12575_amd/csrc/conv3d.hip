@@ -759,7 +759,7 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const bf16_t* __res
 // The matrix-core kernels copy 16-byte pieces (8 channels).  An input with fewer channels than that, or whose voxels do
 // not start on 16 bytes -- a two- or four-channel image in front of a first layer -- is copied once into whole pieces with
 // zero channels behind the real ones: 16 bytes written per voxel and piece, against the 2 * C_out bytes that the conv
-// writes: for the data gradient and the weight gradient (weight gradient of 2->16 channels on 2 x 64 x 80 x 96 voxels: 1.2 ms -> 62 us).
+// writes: for the data gradient and the weight gradient (weight gradient of 2->16 channels on 2 x 64 x 80 x 96 voxels: 1.2 ms -> 58 us).
 // The forward pass keeps the scalar kernel's order of sums, on saturated image regions a sum that rounds the other way moves whole
 // regions over the ReLU: 2 to 4 channels on the fp32 matrix instruction (conv3d_f32.hip), 1 on kernels of its own, the rest, which are
 // no images, on the scalar kernels, where they always were.

@@ -1623,8 +1623,10 @@ __device__ __forceinline__ void wgrad_tile(f32x16 (&acc)[COB][4], WFrags<COB>& f
 // FOLD (channel counts outside the multiples of 32): a walk leaves its sums as a partial every `fold` tiles, so that a chain is as
 // long as in the thread-per-weight kernel that served these counts before (wgrad_splits: 256 voxels where 32 MB of partials allow
 // it), where one chain over a walk rounds more the larger the volume.  Relative error of 2->16 on 2 x 64 x 80 x 96: 7.9e-8 a thread
-// per weight, 3.2e-7 a chain per walk (55 us), 7.9e-8 so (62 us); 48->96 on 83 x 61 x 97: 5.7e-7, 6.6e-7 (161 us), 4.5e-7 (164 us).
-template <int COB, bool FOLD>
+// per weight, 3.2e-7 a chain per walk (55 us), 7.9e-8 with partials every three tiles (62 us); 48->96 on 83 x 61 x 97: 5.7e-7, 6.6e-7
+// (161 us), 4.5e-7 (164 us).  Up to 16 outputs use half of a block's accumulator rows, and the chains go to sums in fp64 for those
+// (S64): a walk is one partial again (2->16: 7.6e-8, 58 us).
+template <int COB, bool FOLD, bool S64>
 __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1655,13 +1657,15 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
     };
     clear();
     constexpr bool SUM = FOLD && COB == 1;
-    f32x16 sum[SUM ? 4 : 1];   // the chains of the partial that are done
+    typedef typename std::conditional<S64, double, float>::type sum_t;
+    constexpr int SR = S64 ? 8 : 16;          // accumulator rows in use
+    sum_t sum[SUM ? 4 : 1][SUM ? SR : 1];     // the chains of the partial that are done
     auto clear_sum = [&]() __attribute__((always_inline)) {
         if constexpr (SUM)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sum[i][r] = 0.f;
+                for (int r = 0; r < SR; ++r) sum[i][r] = 0;
     };
     clear_sum();
     // part[slot][co][tap][ci].  Output channels exist in whole groups of 8, so which ones is uniform, as are the offsets from one group
@@ -1679,10 +1683,11 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
 #pragma unroll
                 for (int cb = 0; cb < COB; ++cb)
 #pragma unroll
-                    for (int rg = 0; rg < 4; ++rg)
+                    for (int rg = 0; rg < SR / 4; ++rg)
                         if (co0 + cb * 32 + 8 * rg < a.Cout)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) pb[(int64_t)((cb * 32 + 8 * rg + r) * 27 + t) * a.Cin] = SUM ? sum[SUM ? i : 0][4 * rg + r] : acc[cb][i][4 * rg + r];
+                            for (int r = 0; r < 4; ++r)
+                                pb[(int64_t)((cb * 32 + 8 * rg + r) * 27 + t) * a.Cin] = SUM ? (float)sum[SUM ? i : 0][SUM ? 4 * rg + r : 0] : acc[cb][i][4 * rg + r];
             }
         }
     };
@@ -1791,7 +1796,9 @@ __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
             if (out || ++in_chain == a.fold) {
                 if constexpr (SUM)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) sum[i] += acc[0][i];
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int r = 0; r < SR; ++r) sum[i][r] += (sum_t)acc[0][i][r];
                 in_chain = 0;
                 if (out) {
                     write_partial(part++);
@@ -1837,14 +1844,14 @@ static WgradPlan wgrad_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* 
     if (wcin % 32 || dzd->c % 32) {
         // f: tiles that hold the thread-per-weight kernel's chain.  A chain of matrix instructions (16 a tile) rounds like the scalar
         // one of as many voxels with (17 f + 2) / 16 tiles, measured; what whole tiles leave of that goes to the additions of chains to
-        // the partial's sum, where a block has the registers for one (32 output channels).
+        // the partial's sum, where a block has the registers for one (32 output channels); in fp64 (up to 16) they need no room.
         const double f = (double)tiles / wgrad_splits(nvox(xd), (int64_t)dzd->c * 27 * wcin);
         const bool sum = conv_wrows(dzd->c) == 32;
         const int room = f < 1.0 ? 19 : (int)(17.0 * f) + 2;
         p.fold = sum ? (int)f : room / 16;
         if (p.fold > p.per) p.fold = p.per;
         if (p.fold < 1) p.fold = 1;
-        int64_t dump = sum && room > 16 * p.fold ? (int64_t)(room - 16 * p.fold) * p.fold : p.fold;
+        int64_t dump = dzd->c <= 16 ? p.per : sum && room > 16 * p.fold ? (int64_t)(room - 16 * p.fold) * p.fold : p.fold;
         if (dump > p.per) dump = p.per;
         const int cuts = (int)((p.per + dump - 1) / dump);
         p.dump = (p.per + cuts - 1) / cuts;
@@ -1885,10 +1892,10 @@ size_t mfma_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* d
     return align_up((size_t)wgrad_plan(xd, dzd, wcin).parts * dzd->c * 27 * wcin * sizeof(float)) + 256;
 }
 
-template <int COB, bool FOLD>
+template <int COB, bool FOLD, bool S64 = false>
 static lamp_status launch_wgrad(const WgradArgs& a, dim3 grid, hipStream_t s) {
-    if (ensure_dyn_lds((const void*)conv3d_wgrad_kernel<COB, FOLD>, WG_LDS_BYTES) != LAMP_OK) return LAMP_ERR_HIP;
-    hipLaunchKernelGGL((conv3d_wgrad_kernel<COB, FOLD>), grid, dim3(512), WG_LDS_BYTES, s, a);
+    if (ensure_dyn_lds((const void*)conv3d_wgrad_kernel<COB, FOLD, S64>, WG_LDS_BYTES) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL((conv3d_wgrad_kernel<COB, FOLD, S64>), grid, dim3(512), WG_LDS_BYTES, s, a);
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }
@@ -1941,7 +1948,7 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
     const int cob = conv_wrows(dzd->c) / 32;
     const dim3 grid(p.slots, cdiv(xd->c, 32), cdiv(dzd->c, 32 * cob));
     lamp_status st;
-    if (p.fold) st = cob == 2 ? launch_wgrad<2, true>(a, grid, s) : launch_wgrad<1, true>(a, grid, s);
+    if (p.fold) st = cob == 2 ? launch_wgrad<2, true>(a, grid, s) : dzd->c <= 16 ? launch_wgrad<1, true, true>(a, grid, s) : launch_wgrad<1, true>(a, grid, s);
     else st = cob == 2 ? launch_wgrad<2, false>(a, grid, s) : launch_wgrad<1, false>(a, grid, s);
     if (st != LAMP_OK) return st;
     if (direct) return LAMP_OK;
