@@ -637,8 +637,8 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
 // to the sum of those before them: the walks grow with the volume, and a single chain over them would round like sqrt(walk) (8->8 on
 // 2 x 128^3, walks of 4096 voxels: relative error 8.9e-7 in one chain, 1.9e-7 so, 3.8e-7 with a thread per weight over 864 voxels).
 // 16-channel slabs of 32 outputs keep half of these sums in LDS, where each thread has its own slots: all of them in registers spill
-// (98 -> 106 us below; with the slots 100).  32->32 on 41 x 56 x 47: 2450 -> 100 us with the reduction against a thread per weight;
-// 16->8 on 2 x 64 x 48 x 80: 109 us.
+// (32->32 on 41 x 56 x 47: 98 -> 106 us, with the slots 100).  With the reduction 32->32 on 41 x 56 x 47: 2450 -> 93 us against a
+// thread per weight; 16->8 on 2 x 64 x 48 x 80: 110 us.
 struct F32WgradArgs {
     const float* x; const float* dz; float* part;   // part [splits * VG][Co][27][Ci]
     NormIn nm;
