@@ -1943,7 +1943,7 @@ lamp_status mfma_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_ten
     // whose dW runs to hundreds of megabytes), so the kernel writes it in place and no second pass is needed
     const bool direct = S == 1 && beta == 0.f;
     if (direct) a.part = dw;
-    a.zero16 = device_zero16();
+    a.zero16 = device_zero16(s);
     if (!a.zero16) return LAMP_ERR_HIP;
     const int cob = conv_wrows(dzd->c) / 32;
     const dim3 grid(p.slots, cdiv(xd->c, 32), cdiv(dzd->c, 32 * cob));

@@ -745,7 +745,7 @@ lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const l
     const bool direct = p.parts == 1 && beta == 0.f;   // the only partial is the result: written in place
     if (direct) a.part = dwt;
     a.bpart = dbias ? (float*)((char*)ws + align_up((size_t)p.parts * O * sizeof(float))) : nullptr;
-    a.zero16 = device_zero16();
+    a.zero16 = device_zero16(s);
     if (!a.zero16) return LAMP_ERR_HIP;
     a.N = xd->n; a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Ci = xd->c; a.Co = dyd->c;
     a.chunks_per_split = p.per;

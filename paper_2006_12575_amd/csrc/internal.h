@@ -50,7 +50,7 @@ lamp_status launch_repack_batch(const RepackJob* jobs, int n, hipStream_t s);
 // nullptr outside a network entry point.
 void set_repack_table(const RepackTable* t);
 const bf16_t* find_prepacked(const void* w, bool dgrad, int kind, int Cout, int Cin);
-const bf16_t* device_zero16();  // 16 zero bytes on the current device, nullptr on failure
+const bf16_t* device_zero16(hipStream_t s);  // 16 zero bytes on the current device, nullptr on failure
 lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s);
 // Column sums of a [rows, C] tensor with row stride ld: out[c] = beta*out[c] + sum_r t[r][c].
 size_t colsum_ws_bytes(int64_t rows, int C);

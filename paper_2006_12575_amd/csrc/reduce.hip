@@ -9,9 +9,10 @@ namespace lamp {
 // copies.  A statically initialised device array that no kernel writes; `used` keeps it in the device
 // code object although no kernel names it (a const array would have internal linkage and be dropped
 // there, and the lookup below would then fail).  Its address is looked up once per device and checked
-// (device memory, reads back as zeros) before any kernel gets it.
+// (device memory, reads back as zeros) before any kernel gets it; a first call inside a graph capture on `s` goes without the
+// read-back, which a capture does not allow.
 __device__ __attribute__((used, aligned(16))) uint32_t lamp_zero16_storage[4] = {0u, 0u, 0u, 0u};
-const bf16_t* device_zero16() {
+const bf16_t* device_zero16(hipStream_t s) {
     static const bf16_t* cache[64] = {nullptr};
     static std::mutex mu;
     int dev = 0;
@@ -22,9 +23,13 @@ const bf16_t* device_zero16() {
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(lamp_zero16_storage)) != hipSuccess || !p) return nullptr;
         hipPointerAttribute_t at;
         if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice) return nullptr;
-        uint32_t back[4] = {1u, 1u, 1u, 1u};
-        if (hipMemcpy(back, p, sizeof(back), hipMemcpyDeviceToHost) != hipSuccess) return nullptr;
-        if (back[0] | back[1] | back[2] | back[3]) return nullptr;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) return nullptr;
+        if (cap == hipStreamCaptureStatusNone) {
+            uint32_t back[4] = {1u, 1u, 1u, 1u};
+            if (hipMemcpy(back, p, sizeof(back), hipMemcpyDeviceToHost) != hipSuccess) return nullptr;
+            if (back[0] | back[1] | back[2] | back[3]) return nullptr;
+        }
         cache[dev] = (const bf16_t*)p;
     }
     return cache[dev];
