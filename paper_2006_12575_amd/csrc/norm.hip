@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
         }
         if (halves) unstash(sq, red);
     }
-    block_fold(sq, cthreads, rl, red, part, [&](int k, int e, float t) {
+    block_fold<double>(sq, cthreads, rl, red, part, [&](int k, int e, float t) {
         const int c = blockIdx.z * 256 * VEC + e;
         if (c < C) partial[(((size_t)n * chunks + chunk) * C + c) * 2 + k] = t;
     });

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict_
         }
         if (halves) unstash(s, red);
     }
-    block_fold(s, cthreads, rl, red, part, [&](int k, int e, float t) {
+    block_fold<double>(s, cthreads, rl, red, part, [&](int k, int e, float t) {
         const int c = blockIdx.z * 256 * VEC + e;
         if (c < C) partial[(((size_t)n * chunks + chunk) * C + c) * K + k] = t;
     });

@@ -144,9 +144,9 @@ template <int NV, int VEC> __device__ __forceinline__ void unstash(float (&v)[NV
 // Sums NV sets of VEC values per thread over the row lanes of a block (thread = row lane * cthreads + channel-vector lane) and
 // hands each to put(set, channel of the block, sum).  All 256 threads add: with only the first row lane's cthreads threads at
 // work, a 16-channel bf16 tensor left 2 threads a serial chain of 2048 LDS reads, which was 45 of the 60 us of its backward sums
-// (2 x 64 x 80 x 96 voxels).  The additions are fp64: these are the largest addends of a partial and would round most.  `red`:
-// NV * 256 * VEC floats, `part`: 256 floats.  A fixed order for a given cthreads.
-template <int NV, int VEC, typename F>
+// (2 x 64 x 80 x 96 voxels).  `red`: NV * 256 * VEC floats, `part`: 256 floats.  A fixed order for a given cthreads.  A: double in the
+// backward sums, whose chunks are the longest: these are the largest addends of a partial and round most.
+template <typename A = float, int NV, int VEC, typename F>
 __device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthreads, int rl, float* red, float* part, F put) {
     const int tid = threadIdx.x, nc = cthreads * VEC, nout = NV * nc;
 #pragma unroll
@@ -156,21 +156,21 @@ __device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthrea
     __syncthreads();
     if (nout <= 128) {   // several threads per sum, each a share of the rows, then the shares in order
         const int P = 256 / nout, o = tid % nout, p = tid / nout, k = o / nc, e = o - k * nc;
-        double t = 0.0;
+        A t = 0;
         if (p < P)
-            for (int r = p; r < rl; r += P) t += (double)red[k * (256 * VEC) + r * nc + e];
+            for (int r = p; r < rl; r += P) t += (A)red[k * (256 * VEC) + r * nc + e];
         part[tid] = (float)t;
         __syncthreads();
         if (tid < nout) {
-            t = (double)part[tid];
-            for (int q = 1; q < P; ++q) t += (double)part[q * nout + tid];
+            t = (A)part[tid];
+            for (int q = 1; q < P; ++q) t += (A)part[q * nout + tid];
             put(k, e, (float)t);
         }
     } else {
         for (int o = tid; o < nout; o += 256) {
             const int k = o / nc, e = o - k * nc;
-            double t = 0.0;
-            for (int r = 0; r < rl; ++r) t += (double)red[k * (256 * VEC) + r * nc + e];
+            A t = 0;
+            for (int r = 0; r < rl; ++r) t += (A)red[k * (256 * VEC) + r * nc + e];
             put(k, e, (float)t);
         }
     }
