@@ -43,14 +43,19 @@ int stats_chunks(int64_t v) {
     return (int)((v + r - 1) / r);
 }
 
-// Chunks of the two-tensor reductions (backward sums, squeeze): 1024 blocks are four to a CU, which is what their registers allow;
-// 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's backward 126 -> 118).
-static int bwd_rows(int64_t v) {
-    const int64_t r = (v + 1023) / 1024;
+// Rows of one partial sum of the two-tensor reductions (backward sums, squeeze).  1024 chunks are four blocks to a CU, which is what
+// their registers allow; 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's
+// backward 126 -> 118).  At least four rows to every row lane, which are in flight together: with 32 rows whatever the width, a
+// 16-channel chunk (128 row lanes) kept a quarter of its threads busy with one row (backward sums of 16 channels on 3 x 28 x 43 x 39: 13.8 -> 6.3 us; squeeze of 16 channels on 3 x 45 x 44 x 92: 19.2 -> 10.4).
+static int bwd_rows(int64_t v, int C, int dtype) {
+    const int vec = dtype == LAMP_BF16 ? 8 : 4;
+    const int rl = C % vec ? 8 : make_rowmap(C, vec).rl;
+    int64_t r = (v + 1023) / 1024;
+    if (r < 4 * rl) r = 4 * rl;
     return (int)(r < 32 ? 32 : r);
 }
-int bwd_chunks(int64_t v) {
-    const int r = bwd_rows(v);
+int bwd_chunks(int64_t v, int C, int dtype) {
+    const int r = bwd_rows(v, C, dtype);
     return (int)((v + r - 1) / r);
 }
 
@@ -274,8 +279,7 @@ __global__ __launch_bounds__(256) void inorm_apply_kernel(const T* __restrict__ 
     if (r0 >= rl || cv * VEC >= C) return;
     NormIn nm{stats, gamma, beta, C, 1};
     float a[VEC], b[VEC];
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) norm_coeffs(nm, n, cv * VEC + i, a[i], b[i]);
+    norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b);
     const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
     T* yb = y + ((int64_t)n * V) * ldy + (int64_t)cv * VEC;
     block_rows(V, rl, r0, [&](int64_t r, bool second) {
@@ -322,12 +326,7 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
     if (r0 < rl && cv * VEC < C) {
         NormIn nm{stats, gamma, beta, C, 1};
         float a[VEC], b[VEC], mean[VEC], rstd[VEC];
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            norm_coeffs(nm, n, cv * VEC + i, a[i], b[i]);
-            mean[i] = stats[((size_t)n * C + cv * VEC + i) * 2];
-            rstd[i] = stats[((size_t)n * C + cv * VEC + i) * 2 + 1];
-        }
+        norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b, mean, rstd);
         const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
         const T* gb = dy + ((int64_t)n * V) * ldg + (int64_t)cv * VEC;
         auto add_row = [&](const float (&v)[VEC], const float (&g)[VEC]) {
@@ -416,19 +415,6 @@ __global__ __launch_bounds__(256) void inorm_bwd_finalize_kernel(const float* __
     }
 }
 
-__global__ void inorm_dgb_kernel(const float* __restrict__ sums, int N, int C, float* dgamma, float* dbeta,
-                                 float beta_acc) {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    double s = 0.0, q = 0.0;
-    for (int n = 0; n < N; ++n) {
-        s += (double)sums[((size_t)n * C + c) * 2 + 0];
-        q += (double)sums[((size_t)n * C + c) * 2 + 1];
-    }
-    if (dbeta) dbeta[c] = (beta_acc != 0.f ? beta_acc * dbeta[c] : 0.f) + (float)s;
-    if (dgamma) dgamma[c] = (beta_acc != 0.f ? beta_acc * dgamma[c] : 0.f) + (float)q;
-}
-
 // Bound: HBM.  64 channels at 128^3, sums and apply (1.34 GB): 262 -> 214 us with non-temporal accesses (loads too: both inputs are
 // read for the last time here).
 template <typename T, int VEC, bool NT>
@@ -437,22 +423,24 @@ __global__ __launch_bounds__(256) void inorm_bwd_apply_kernel(const T* __restric
                                                               int cthreads, int rl, const float* __restrict__ stats,
                                                               const float* __restrict__ gamma,
                                                               const float* __restrict__ beta,
-                                                              const float* __restrict__ sums) {
+                                                              const float* __restrict__ sums, float* __restrict__ dgamma,
+                                                              float* __restrict__ dbeta, float beta_acc) {
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
     const int n = blockIdx.y;
     if (r0 >= rl || cv * VEC >= C) return;
+    if (blockIdx.x == 0 && n == 0 && r0 == 0) affine_grads<VEC>(sums, gridDim.y, C, cv * VEC, dgamma, dbeta, beta_acc);
     NormIn nm{stats, gamma, beta, C, 1};
     float a[VEC], b[VEC], mean[VEC], rstd[VEC], c1[VEC], c2[VEC];
     const float invV = 1.0f / (float)V;
+    float sm[2 * VEC];
+    ld_floats<2 * VEC>(sums + ((size_t)n * C + cv * VEC) * 2, sm);
+    norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b, mean, rstd);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
-        norm_coeffs(nm, n, cv * VEC + i, a[i], b[i]);
-        mean[i] = stats[((size_t)n * C + cv * VEC + i) * 2];
-        rstd[i] = stats[((size_t)n * C + cv * VEC + i) * 2 + 1];
-        c1[i] = sums[((size_t)n * C + cv * VEC + i) * 2] * invV;
-        c2[i] = sums[((size_t)n * C + cv * VEC + i) * 2 + 1] * invV;
+        c1[i] = sm[2 * i] * invV;
+        c2[i] = sm[2 * i + 1] * invV;
     }
     const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
     const T* gb = dy + ((int64_t)n * V) * ldg + (int64_t)cv * VEC;
@@ -547,7 +535,7 @@ extern "C" lamp_status lamp_inorm_relu_noalloc(const lamp_tensor_desc* zd, const
 extern "C" size_t lamp_inorm_relu_bwd_workspace_bytes(const lamp_tensor_desc* zd) {
     if (!desc_ok(zd)) return 0;
     int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    int ch = bwd_chunks(V);
+    int ch = bwd_chunks(V, zd->c, zd->dtype);
     return align_up((size_t)zd->n * ch * zd->c * 2 * sizeof(float)) + align_up((size_t)zd->n * zd->c * 2 * sizeof(float));
 }
 
@@ -564,7 +552,7 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
     if (!ws || ws_bytes < lamp_inorm_relu_bwd_workspace_bytes(zd)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int chunks = bwd_chunks(V);
+    const int chunks = bwd_chunks(V, zd->c, zd->dtype);
     float* partial = (float*)ws;
     float* sums = (float*)((char*)ws + align_up((size_t)zd->n * chunks * zd->c * 2 * sizeof(float)));
     const int vec = pick_vec(zd->dtype, zd->c, {zd->ldc, dyd->ldc, dzd->ldc}, {z, dy, dz});
@@ -573,11 +561,11 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
         RowMap m = make_rowmap(zd->c, VEC);
         if (nt) {
             hipLaunchKernelGGL((inorm_bwd_partial_kernel<T, VEC, true>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s,
-                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V),
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V, zd->c, zd->dtype),
                            stats, gamma, beta, partial);
         } else {
             hipLaunchKernelGGL((inorm_bwd_partial_kernel<T, VEC, false>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s,
-                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V),
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V, zd->c, zd->dtype),
                            stats, gamma, beta, partial);
         }
     });
@@ -601,21 +589,16 @@ lamp_status lamp::launch_inorm_bwd_apply(const lamp_tensor_desc* dyd, const void
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
     const int vec = pick_vec(zd->dtype, zd->c, {zd->ldc, dyd->ldc, dzd->ldc}, {z, dy, dz});
     const bool nt = beyond_cache(3 * nvox(zd) * zd->c * (int64_t)esize(zd->dtype));
-    if (dgamma || dbeta) {
-        hipLaunchKernelGGL(inorm_dgb_kernel, dim3(cdiv(zd->c, 64)), dim3(64), 0, s, sums, zd->n, zd->c, dgamma, dbeta,
-                           beta_acc);
-        LAMP_CHECK_LAUNCH();
-    }
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(zd->c, VEC);
         if (nt) {
             hipLaunchKernelGGL((inorm_bwd_apply_kernel<T, VEC, true>), dim3(apply_blocks(V, m.rl), zd->n, m.ctiles), dim3(256), 0,
                            s, (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, zd->c, m.cthreads,
-                           m.rl, stats, gamma, beta, sums);
+                           m.rl, stats, gamma, beta, sums, dgamma, dbeta, beta_acc);
         } else {
             hipLaunchKernelGGL((inorm_bwd_apply_kernel<T, VEC, false>), dim3(apply_blocks(V, m.rl), zd->n, m.ctiles), dim3(256), 0,
                            s, (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, zd->c, m.cthreads,
-                           m.rl, stats, gamma, beta, sums);
+                           m.rl, stats, gamma, beta, sums, dgamma, dbeta, beta_acc);
         }
     });
     LAMP_CHECK_LAUNCH();

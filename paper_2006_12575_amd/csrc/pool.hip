@@ -16,8 +16,12 @@ template <typename T, int VEC> struct NormVec {
         for (int i = 0; i < VEC; ++i) {
             a[i] = 1.f;
             b[i] = 0.f;
-            if (i < left) norm_coeffs(nm, n, c0 + i, a[i], b[i]);
         }
+        if (left >= VEC) norm_coeffs_vec<VEC>(nm, n, c0, a, b);
+        else
+#pragma unroll
+            for (int i = 0; i < VEC; ++i)
+                if (i < left) norm_coeffs(nm, n, c0 + i, a[i], b[i]);
     }
     __device__ __forceinline__ void apply(float (&v)[VEC]) const {
         if (left <= 0) return;
@@ -142,8 +146,7 @@ __global__ __launch_bounds__(256) void maxpool2_fwd_kernel(const T* __restrict__
         // also write the activated input: all channels normalised, the coefficients of this thread's channels
         // fetched once, the two voxels of a w pair stored back to back
         float a[VEC], b[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) norm_coeffs(nm, n, cv * VEC + e, a[e], b[e]);
+        norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int i = t >> 1, j = t & 1;

@@ -41,12 +41,7 @@ __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict_
     if (r0 < rl && cv * VEC < C) {
         NormIn nm{stats, gamma, beta, C, 1};
         float a[VEC], b[VEC], mean[VEC], rstd[VEC];
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            norm_coeffs(nm, n, cv * VEC + i, a[i], b[i]);
-            mean[i] = stats[((size_t)n * C + cv * VEC + i) * 2];
-            rstd[i] = stats[((size_t)n * C + cv * VEC + i) * 2 + 1];
-        }
+        norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b, mean, rstd);
         const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
         const T* gb = MODE == 1 ? dy + ((int64_t)n * V) * ldg + (int64_t)cv * VEC : nullptr;
         auto add_row = [&](const float (&v)[VEC], const float (&g)[VEC]) {
@@ -177,11 +172,8 @@ __global__ __launch_bounds__(256) void se_apply_kernel(const T* __restrict__ z, 
     if (r0 >= rl || cv * VEC >= C) return;
     NormIn nm{stats, gamma, beta, C, 1};
     float a[VEC], b[VEC], e[VEC];
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-        norm_coeffs(nm, n, cv * VEC + i, a[i], b[i]);
-        e[i] = save[(size_t)n * (4 * C + Cr) + C + cv * VEC + i];
-    }
+    ld_floats<VEC>(save + (size_t)n * (4 * C + Cr) + C + cv * VEC, e);
+    norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b);
     const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
     const T* rb = RES ? res + ((int64_t)n * V) * ldr + (int64_t)cv * VEC : nullptr;
     T* yb = y + ((int64_t)n * V) * ldy + (int64_t)cv * VEC;
@@ -280,18 +272,6 @@ __global__ __launch_bounds__(256) void se_param_grad_kernel(const float* __restr
     }
 }
 
-__global__ void se_dgb_kernel(const float* __restrict__ sums2, int N, int C, float* dgamma, float* dbeta, float acc) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    double s = 0.0, q = 0.0;
-    for (int n = 0; n < N; ++n) {
-        s += (double)sums2[((size_t)n * C + c) * 2 + 0];
-        q += (double)sums2[((size_t)n * C + c) * 2 + 1];
-    }
-    if (dbeta) dbeta[c] = (acc != 0.f ? acc * dbeta[c] : 0.f) + (float)s;
-    if (dgamma) dgamma[c] = (acc != 0.f ? acc * dgamma[c] : 0.f) + (float)q;
-}
-
 // dz = gamma*rstd * (g - mean_v(g) - zhat * mean_v(g*zhat)),  g = mask * (dy*e + dm/V)
 template <typename T, int VEC, bool NT>
 __global__ __launch_bounds__(256) void se_bwd_apply_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z, int ldz,
@@ -299,25 +279,27 @@ __global__ __launch_bounds__(256) void se_bwd_apply_kernel(const T* __restrict__
                                                            int cthreads, int rl, const float* __restrict__ stats,
                                                            const float* __restrict__ gamma, const float* __restrict__ beta,
                                                            const float* __restrict__ save, const float* __restrict__ dmv,
-                                                           const float* __restrict__ sums2) {
+                                                           const float* __restrict__ sums2, float* __restrict__ dgamma,
+                                                           float* __restrict__ dbeta, float beta_acc) {
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
     const int n = blockIdx.y;
     if (r0 >= rl || cv * VEC >= C) return;
+    if (blockIdx.x == 0 && n == 0 && r0 == 0) affine_grads<VEC>(sums2, gridDim.y, C, cv * VEC, dgamma, dbeta, beta_acc);
     NormIn nm{stats, gamma, beta, C, 1};
     float a[VEC], b[VEC], mean[VEC], rstd[VEC], c1[VEC], c2[VEC], e[VEC], dm[VEC];
     const float invV = 1.0f / (float)V;
+    const size_t nc = (size_t)n * C + cv * VEC;
+    float sm[2 * VEC];
+    ld_floats<2 * VEC>(sums2 + nc * 2, sm);
+    ld_floats<VEC>(save + (size_t)n * (4 * C + Cr) + C + cv * VEC, e);
+    ld_floats<VEC>(dmv + nc, dm);
+    norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b, mean, rstd);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
-        const size_t nc = (size_t)n * C + cv * VEC + i;
-        norm_coeffs(nm, n, cv * VEC + i, a[i], b[i]);
-        mean[i] = stats[nc * 2];
-        rstd[i] = stats[nc * 2 + 1];
-        c1[i] = sums2[nc * 2] * invV;
-        c2[i] = sums2[nc * 2 + 1] * invV;
-        e[i] = save[(size_t)n * (4 * C + Cr) + C + cv * VEC + i];
-        dm[i] = dmv[nc];
+        c1[i] = sm[2 * i] * invV;
+        c2[i] = sm[2 * i + 1] * invV;
     }
     const T* zb = z + ((int64_t)n * V) * ldz + (int64_t)cv * VEC;
     const T* gb = dy + ((int64_t)n * V) * ldg + (int64_t)cv * VEC;
@@ -395,7 +377,7 @@ extern "C" size_t lamp_inorm_relu_se_workspace_bytes(const lamp_tensor_desc* zd,
     if (!zd || se_check(zd, cr) != LAMP_OK) return 0;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
     const size_t nc = (size_t)zd->n * zd->c;
-    return align_up(nc * bwd_chunks(V) * 3 * sizeof(float)) + align_up(nc * 3 * sizeof(float)) +
+    return align_up(nc * bwd_chunks(V, zd->c, zd->dtype) * 3 * sizeof(float)) + align_up(nc * 3 * sizeof(float)) +
            align_up(nc * 2 * sizeof(float)) + 2 * align_up(nc * sizeof(float)) +
            align_up((size_t)zd->n * cr * sizeof(float)) + 256;
 }
@@ -418,7 +400,7 @@ extern "C" lamp_status lamp_inorm_relu_se(const lamp_tensor_desc* zd, const void
     if (!ws || ws_bytes < lamp_inorm_relu_se_workspace_bytes(zd, cr)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int C = zd->c, chunks = bwd_chunks(V);
+    const int C = zd->c, chunks = bwd_chunks(V, zd->c, zd->dtype);
     const int rpc = (int)((V + chunks - 1) / chunks);
     Carver cv(ws, ws_bytes);
     float* partial = (float*)cv.take((size_t)zd->n * C * chunks * 3 * sizeof(float));
@@ -476,7 +458,7 @@ extern "C" lamp_status lamp_inorm_relu_se_bwd(const lamp_tensor_desc* dyd, const
     if (!ws || ws_bytes < lamp_inorm_relu_se_workspace_bytes(zd, cr)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int C = zd->c, N = zd->n, chunks = bwd_chunks(V);
+    const int C = zd->c, N = zd->n, chunks = bwd_chunks(V, zd->c, zd->dtype);
     const int rpc = (int)((V + chunks - 1) / chunks);
     const size_t nc = (size_t)N * C;
     Carver cv(ws, ws_bytes);
@@ -511,20 +493,16 @@ extern "C" lamp_status lamp_inorm_relu_se_bwd(const lamp_tensor_desc* dyd, const
                            dw1, db1, dw2, db2, beta_acc);
         LAMP_CHECK_LAUNCH();
     }
-    if (dgamma || dbeta) {
-        hipLaunchKernelGGL(se_dgb_kernel, dim3(cdiv(C, 64)), dim3(64), 0, s, sums2, N, C, dgamma, dbeta, beta_acc);
-        LAMP_CHECK_LAUNCH();
-    }
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(C, VEC);
         if (nt3) {
             hipLaunchKernelGGL((se_bwd_apply_kernel<T, VEC, true>), dim3(se_apply_blocks(V, m.rl), N, m.ctiles), dim3(256), 0, s,
                            (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, C, cr, m.cthreads, m.rl, stats,
-                           gamma, beta, gate_save, dmv, sums2);
+                           gamma, beta, gate_save, dmv, sums2, dgamma, dbeta, beta_acc);
         } else {
             hipLaunchKernelGGL((se_bwd_apply_kernel<T, VEC, false>), dim3(se_apply_blocks(V, m.rl), N, m.ctiles), dim3(256), 0, s,
                            (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, C, cr, m.cthreads, m.rl, stats,
-                           gamma, beta, gate_save, dmv, sums2);
+                           gamma, beta, gate_save, dmv, sums2, dgamma, dbeta, beta_acc);
         }
     });
     LAMP_CHECK_LAUNCH();

@@ -65,6 +65,49 @@ template <typename T> struct Vec<T, 1> {
     template <bool NT = false> static __device__ __forceinline__ void store(T* p, const float (&v)[1]) { io<T>::st(p, v[0]); }
 };
 
+// VEC consecutive floats, 4-byte aligned.
+template <int VEC> __device__ __forceinline__ void ld_floats(const float* p, float (&v)[VEC]) { __builtin_memcpy(v, p, sizeof(v)); }
+
+// norm_coeffs of VEC consecutive channels, and (mean, rstd) themselves.  Whole pieces, one branch per optional parameter: channel by
+// channel every gamma and beta was a branch and a wait of its own, a chain of sixteen memory latencies in front of a block's first row
+// (apply pass with gamma and beta, 64 channels on 83 x 61 x 97: 28.4 us where it took 21.9 without them).
+template <int VEC> __device__ __forceinline__ void norm_coeffs_vec(const NormIn& nm, int n, int c0, float (&a)[VEC], float (&b)[VEC],
+                                                                   float (&mean)[VEC], float (&rstd)[VEC]) {
+    float st[2 * VEC], g[VEC], bt[VEC];
+    ld_floats<2 * VEC>(nm.mean_rstd + ((size_t)n * nm.c_norm + c0) * 2, st);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) { g[i] = 1.f; bt[i] = 0.f; }
+    if (nm.gamma) ld_floats<VEC>(nm.gamma + c0, g);
+    if (nm.beta) ld_floats<VEC>(nm.beta + c0, bt);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+        mean[i] = st[2 * i];
+        rstd[i] = st[2 * i + 1];
+        a[i] = g[i] * rstd[i];
+        b[i] = bt[i] - mean[i] * a[i];
+    }
+}
+template <int VEC> __device__ __forceinline__ void norm_coeffs_vec(const NormIn& nm, int n, int c0, float (&a)[VEC], float (&b)[VEC]) {
+    float mean[VEC], rstd[VEC];
+    norm_coeffs_vec<VEC>(nm, n, c0, a, b, mean, rstd);
+}
+
+// dgamma, dbeta of VEC channels: the backward sums over the samples, fp64, in order.  By one block of the apply pass (a launch of its
+// own took 1.2 to 5 us).
+template <int VEC> __device__ __forceinline__ void affine_grads(const float* sums, int N, int C, int c0, float* dgamma, float* dbeta,
+                                                                float beta_acc) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+        double s = 0.0, q = 0.0;
+        for (int n = 0; n < N; ++n) {
+            s += (double)sums[((size_t)n * C + c0 + i) * 2 + 0];
+            q += (double)sums[((size_t)n * C + c0 + i) * 2 + 1];
+        }
+        if (dbeta) dbeta[c0 + i] = (beta_acc != 0.f ? beta_acc * dbeta[c0 + i] : 0.f) + (float)s;
+        if (dgamma) dgamma[c0 + i] = (beta_acc != 0.f ? beta_acc * dgamma[c0 + i] : 0.f) + (float)q;
+    }
+}
+
 // Thread mapping inside a 256-thread block: cthreads threads side by side cover the channel
 // vectors of one row, rl rows are in flight per block.  Channel-vector tiles beyond 256 go to
 // blockIdx.z.
@@ -76,6 +119,10 @@ inline RowMap make_rowmap(int C, int VEC) {
     int cv = C / VEC;
     m.cthreads = cv < 256 ? cv : 256;
     m.rl = 256 / m.cthreads;
+    // whole 128-byte lines to a round of rows where that idles a sixteenth of the threads at most
+    if (VEC > 1)
+        for (int r = m.rl; r * 16 >= m.rl * 15; --r)
+            if (r * m.cthreads % 8 == 0) { m.rl = r; break; }
     m.ctiles = (cv + 255) / 256;
     return m;
 }
