@@ -143,8 +143,9 @@ extern "C" size_t lamp_convtr3d_bwd_workspace_bytes(const lamp_tensor_desc* xd, 
     size_t a = align_up((size_t)convtr_splits(nvox(xd), O) * O * sizeof(float));
     const size_t b = mfma_convtr_wgrad_ws_bytes(xd, dyd);
     if (b > a) a = align_up(b);
-    const size_t c = f32_convtr_wgrad_ws_bytes(xd, dyd);
+    const size_t c = f32_convtr_wgrad_ws_bytes(xd, dyd), d = mfma_convtr_bwd_ws_bytes(xd, dyd);
     if (c > a) a = c;
+    if (d > a) a = d;
     return a + colsum_ws_bytes(nvox(dyd), dyd->c);
 }
 
@@ -165,6 +166,9 @@ extern "C" lamp_status lamp_convtr3d_bwd(const lamp_tensor_desc* xd, const void*
     if ((dwt || dbias) && (!ws || ws_bytes < lamp_convtr3d_bwd_workspace_bytes(xd, dyd))) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int Ci = xd->c, Co = dyd->c;
+    if (dx && dwt && mfma_convtr_bwd_supported(xd, dyd, dxd, xnorm) && aligned16(x) && aligned16(wt) && aligned16(dy) && aligned16(dx) &&
+        aligned16(ws))
+        return mfma_convtr_bwd(xd, x, wt, dyd, dy, dxd, dx, dwt, dbias, beta, ws, ws_bytes, s);
     if (dx && mfma_convtr_dgrad_supported(xd, dyd, dxd) && aligned16(dy) && aligned16(wt) && ((((uintptr_t)dx) & 7u) == 0)) {
         if ((st = mfma_convtr_dgrad(xd, wt, dyd, dy, dxd, dx, s)) != LAMP_OK) return st;
     } else if (dx && f32_convtr_supported(xd, dyd, nullptr) && dxd->ldc % 4 == 0 && aligned16(dy) && aligned16(wt) && aligned16(dx)) {

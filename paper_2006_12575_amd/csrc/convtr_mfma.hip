@@ -11,6 +11,7 @@
 // the transposing load, like the 3x3x3 weight gradient.
 #include <stdlib.h>
 #include "internal.h"
+#include "vec.h"
 
 namespace lamp {
 
@@ -180,11 +181,11 @@ __device__ __forceinline__ int64_t ct_tap_off(const CtArgs& a, int tap) {
 }
 
 // Forward.  One wave = VB*32 coarse voxels x one block of RB units (a unit is (tap, 32 output
-// channels) = 32 rows of the repacked weight).  With KS > 0 (K = 16*KS input channels) the wave's x
-// operand is fetched up front in one go.  Every load of a wave is issued before its first store:
+// channels) = 32 rows of the repacked weight).  For the input channel counts and the weights off 16 bytes that the
+// kernel with the weights in LDS does not take.  Every load of a wave is issued before its first store:
 // loads and stores complete in one queue, so a load behind a store would wait for the store; the
 // bias therefore sits in LDS.  Requires Co % 32 == 0, Co <= 256 * 4, Ci % 16 == 0, < 2^31 voxels.
-template <int RB, int VB, int KS>
+template <int RB, int VB>
 __global__ __launch_bounds__(256) void convtr_fwd32_kernel(CtArgs a) {
     constexpr int VW = 32 * VB;  // voxels per wave
     __shared__ __attribute__((aligned(16))) char tb[4][VW * CT_ROW];
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256) void convtr_fwd32_kernel(CtArgs a) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const int64_t nvox = (int64_t)a.N * a.D * a.H * a.W;
-    const int K = KS > 0 ? 16 * KS : a.K;
+    const int K = a.K;
     // workgroup id -> (voxel group, row block): ids are dealt round-robin to the 8 XCDs, so the row
     // blocks of one voxel group take consecutive slots of ONE XCD and share its L2 for x
     const int nblocks = a.rows / (32 * RB);
@@ -211,13 +212,6 @@ __global__ __launch_bounds__(256) void convtr_fwd32_kernel(CtArgs a) {
         xrow[vb] = a.b + v * a.ldb + 8 * half;
     }
     const bf16_t* arow = a.a + (int64_t)(r0 + l32) * K + 8 * half;
-    bf16x8 ball[KS > 0 ? KS : 1][VB];
-    if (KS > 0) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int vb = 0; vb < VB; ++vb) ball[ks][vb] = *reinterpret_cast<const bf16x8*>(xrow[vb] + ks * 16);
-    }
     // bias -> this wave's LDS copy
     for (int c = lane * 4; c < a.Co; c += 256) {
         float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -240,43 +234,29 @@ __global__ __launch_bounds__(256) void convtr_fwd32_kernel(CtArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[rb][vb][r] = 0.f;
 
-    if (KS > 0) {
+    // streaming reduction, operands fetched one step ahead
+    bf16x8 bfn[VB], afn[RB];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            bf16x8 af[RB];
+    for (int vb = 0; vb < VB; ++vb) bfn[vb] = *reinterpret_cast<const bf16x8*>(xrow[vb]);
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) af[rb] = *reinterpret_cast<const bf16x8*>(arow + rb * 32 * K + ks * 16);
+    for (int rb = 0; rb < RB; ++rb) afn[rb] = *reinterpret_cast<const bf16x8*>(arow + (int64_t)rb * 32 * K);
+    for (int k0 = 0; k0 < K; k0 += 16) {
+        bf16x8 bf[VB], af[RB];
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
+        for (int vb = 0; vb < VB; ++vb) bf[vb] = bfn[vb];
 #pragma unroll
-                for (int vb = 0; vb < VB; ++vb)
-                    acc[rb][vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], ball[ks][vb], acc[rb][vb], 0, 0, 0);
+        for (int rb = 0; rb < RB; ++rb) af[rb] = afn[rb];
+        if (k0 + 16 < K) {
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) bfn[vb] = *reinterpret_cast<const bf16x8*>(xrow[vb] + k0 + 16);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) afn[rb] = *reinterpret_cast<const bf16x8*>(arow + (int64_t)rb * 32 * K + k0 + 16);
         }
-    } else {
-        // streaming reduction, operands fetched one step ahead
-        bf16x8 bfn[VB], afn[RB];
 #pragma unroll
-        for (int vb = 0; vb < VB; ++vb) bfn[vb] = *reinterpret_cast<const bf16x8*>(xrow[vb]);
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) afn[rb] = *reinterpret_cast<const bf16x8*>(arow + (int64_t)rb * 32 * K);
-        for (int k0 = 0; k0 < K; k0 += 16) {
-            bf16x8 bf[VB], af[RB];
-#pragma unroll
-            for (int vb = 0; vb < VB; ++vb) bf[vb] = bfn[vb];
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) af[rb] = afn[rb];
-            if (k0 + 16 < K) {
-#pragma unroll
-                for (int vb = 0; vb < VB; ++vb) bfn[vb] = *reinterpret_cast<const bf16x8*>(xrow[vb] + k0 + 16);
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) afn[rb] = *reinterpret_cast<const bf16x8*>(arow + (int64_t)rb * 32 * K + k0 + 16);
-            }
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                for (int vb = 0; vb < VB; ++vb)
-                    acc[rb][vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[vb], acc[rb][vb], 0, 0, 0);
-        }
+            for (int vb = 0; vb < VB; ++vb)
+                acc[rb][vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[vb], acc[rb][vb], 0, 0, 0);
     }
 
     // lane holds, for voxel l32 of block vb, rows 8*(r/4) + 4*half + (r%4) of the unit
@@ -309,17 +289,145 @@ __global__ __launch_bounds__(256) void convtr_fwd32_kernel(CtArgs a) {
     }
 }
 
+// Forward with the weights in LDS, for 16, 32, 64 and 128 input channels.  The rows (tap, output channel) are cut into pairs of 32-row
+// units; a workgroup keeps up to four pairs (K = 16 * KS deep, transposed from the public layout on the way in) and its 8 waves walk
+// groups of 32 coarse voxels, the next group's x in flight during the current one's multiplies and stores.  A pair is 64 consecutive
+// rows, 128 bytes of output a voxel: with 32 output channels the two taps of a w pair, which lie side by side in memory, so a store
+// instruction covers 1 KB of consecutive bytes where a unit at a time wrote every other 64 bytes.
+// Bound: HBM.  64->32 on 2 x 64^3 (67 MB in, 268 MB out): 106 us with a wave per 32 voxels x 8 units, weights from the caches,
+// and a repacking launch in front -> 58 us.  Same products in the same order as convtr_fwd32_kernel.
+// Requires Co % 8 == 0, whole 16-byte pieces everywhere, tap offsets in 32 bits, fine voxels in 32 bits.
+static constexpr int CT_PROW = 144;                        // patch: 128 bytes a voxel, padded
+static constexpr int CT_PATCH = 32 * CT_PROW + 128;        // and the 32 voxels' fine origins
+static size_t ct_fwd_lds(int pb, int ks) { return (size_t)pb * (2 * ks * 1024 + 256 + 32) + 8 * CT_PATCH; }
+
+template <int KS, bool NT>
+__global__ __launch_bounds__(512, KS <= 4 ? 4 : 2) void convtr_fwd_lds_kernel(CtArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char ctl[];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, half = lane >> 5;
+    const int pairs = a.rows >> 6, nblocks = (pairs + 3) >> 2;
+    // row blocks of the same voxel groups take consecutive slots of one XCD and share its L2 for x
+    const int slot = (int)blockIdx.x >> 3, yb = slot % nblocks, walker = slot / nblocks * 8 + ((int)blockIdx.x & 7);
+    const int walkers = (int)gridDim.x / nblocks;
+    const int p0 = yb * 4, pb = min(4, pairs - p0);
+    char* const wl = ctl;                                                  // [unit][ks][half][32 rows][8 channels]
+    float* const bl = reinterpret_cast<float*>(ctl + pb * (2 * KS * 1024));  // bias of every row
+    int* const po = reinterpret_cast<int*>(bl + pb * 64);                  // output offset of every 8-row piece
+    char* const patch = reinterpret_cast<char*>(po + pb * 8) + wv * CT_PATCH;
+    uint32_t* const org = reinterpret_cast<uint32_t*>(patch + 32 * CT_PROW);
+
+    const uint32_t nvox = (uint32_t)((int64_t)a.N * a.D * a.H * a.W), ngroups = (nvox + 31) >> 5, step = (uint32_t)walkers * 8;
+    uint32_t g = (uint32_t)walker * 8 + wv;
+    auto voxel = [&](uint32_t grp) { return min(grp * 32 + l32, nvox - 1); };   // lanes past the end repeat the last voxel, same value
+    bf16x8 nx[KS];
+    auto fetch = [&](uint32_t grp) __attribute__((always_inline)) {
+        const bf16_t* p = a.b + (int64_t)voxel(grp) * a.ldb + 8 * half;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) nx[ks] = *reinterpret_cast<const bf16x8*>(p + ks * 16);
+    };
+    if (g < ngroups) fetch(g);
+
+    // weights: eight pieces of 8 rows, one per input channel, to eight pieces of 8 input channels
+    for (int i = tid; i < pb * 8 * 2 * KS; i += 512) {
+        const int rp = i % (pb * 8), kb = i / (pb * 8);
+        const bf16_t* src = a.a + (int64_t)(kb * 8) * a.rows + p0 * 64 + rp * 8;
+        vec_u32x4 q[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] = *reinterpret_cast<const vec_u32x4*>(src + (int64_t)e * a.rows);
+        char* dst = wl + (((rp >> 2) * KS + (kb >> 1)) * 2 + (kb & 1)) * 512 + (rp & 3) * 128;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            vec_u32x4 o;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) o[d] = __builtin_amdgcn_perm(q[2 * d + 1][j >> 1], q[2 * d][j >> 1], j & 1 ? 0x07060302u : 0x05040100u);
+            *reinterpret_cast<vec_u32x4*>(dst + j * 16) = o;
+        }
+    }
+    for (int i = tid; i < pb * 64; i += 512) bl[i] = a.bias ? a.bias[(p0 * 64 + i) % a.Co] : 0.f;
+    for (int i = tid; i < pb * 8; i += 512) {
+        const int row = (p0 * 8 + i) * 8, tap = row / a.Co, co = row - tap * a.Co;
+        po[i] = (int)ct_tap_off(a, tap) * a.ldo + co;
+    }
+    __syncthreads();
+
+    for (; g < ngroups; g += step) {
+        bf16x8 cx[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) cx[ks] = nx[ks];
+        fetch(g + step < ngroups ? g + step : g);
+        if (lane < 32) org[l32] = (uint32_t)ct_fine_origin(a, voxel(g));
+        __builtin_amdgcn_wave_barrier();
+        bf16_t* op[4];
+#pragma unroll
+        for (int it = 0; it < 4; ++it) op[it] = a.out + (int64_t)org[it * 8 + (lane >> 3)] * a.ldo;
+        for (int m = 0; m < pb; ++m) {
+            f32x16 acc[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[u][r] = 0.f;
+            const char* wp = wl + m * (2 * KS * 1024) + half * 512 + l32 * 16;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(wp + (u * KS + ks) * 1024), cx[ks],
+                                                                     acc[u], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) {
+                    const int c = u * 32 + rg * 8 + half * 4;
+                    const float4 bv = *reinterpret_cast<const float4*>(bl + m * 64 + c);
+                    *reinterpret_cast<uint2*>(patch + l32 * CT_PROW + c * 2) =
+                        make_uint2(ct_pack(acc[u][rg * 4 + 0] + bv.x, acc[u][rg * 4 + 1] + bv.y),
+                                   ct_pack(acc[u][rg * 4 + 2] + bv.z, acc[u][rg * 4 + 3] + bv.w));
+                }
+            __builtin_amdgcn_wave_barrier();
+            const int off = po[m * 8 + (lane & 7)];
+#pragma unroll
+            for (int it = 0; it < 4; ++it)
+                st16<NT>(op[it] + off, *reinterpret_cast<const vec_u32x4*>(patch + (it * 8 + (lane >> 3)) * CT_PROW + (lane & 7) * 16));
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+template <int KS>
+static lamp_status ct_fwd_lds_launch(const CtArgs& a, int64_t nv, hipStream_t s) {
+    const int pairs = a.rows / 64, nblocks = (pairs + 3) / 4, pb = pairs < 4 ? pairs : 4;
+    const size_t lds = ct_fwd_lds(pb, KS);
+    // as many workgroups as are resident at a time, fewer where the volume has fewer groups
+    const int per_cu = KS <= 4 ? 2 : 1;
+    int64_t walkers = 256 * per_cu / nblocks;
+    if (walkers > cdiv(nv, 256)) walkers = cdiv(nv, 256);
+    walkers = (walkers + 7) / 8 * 8;
+    const dim3 grid((unsigned)(walkers * nblocks));
+    const bool nt = beyond_cache(nv * (a.Ci + 8 * (int64_t)a.Co) * 2);
+    if (nt) {
+        if (ensure_dyn_lds((const void*)convtr_fwd_lds_kernel<KS, true>, (int)ct_fwd_lds(4, KS)) != LAMP_OK) return LAMP_ERR_HIP;
+        hipLaunchKernelGGL((convtr_fwd_lds_kernel<KS, true>), grid, dim3(512), lds, s, a);
+    } else {
+        if (ensure_dyn_lds((const void*)convtr_fwd_lds_kernel<KS, false>, (int)ct_fwd_lds(4, KS)) != LAMP_OK) return LAMP_ERR_HIP;
+        hipLaunchKernelGGL((convtr_fwd_lds_kernel<KS, false>), grid, dim3(512), lds, s, a);
+    }
+    LAMP_CHECK_LAUNCH();
+    return LAMP_OK;
+}
+
 // Data gradient.  One wave = 64 coarse voxels x RB blocks of 32 input channels; the reduction runs
 // over units of (tap, 32 output channels).  The 64-byte pieces of dy are gathered one unit ahead
 // into registers and handed to the matrix-core fragment order through the wave's double buffer.
+// SPLIT: the four waves of a workgroup share one group of 64 voxels, a quarter of the units each, and the first adds the four sums up
+// in order: a small volume has few voxel groups and, deep in the net, many units, whose gathers are one chain of memory latencies
+// (512->256 on 2 x 8^3: 57 -> 22 us).
 // Requires Co % 32 == 0, Ci % 32 == 0.
-template <int RB>
+template <int RB, bool SPLIT = false>
 __global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
     __shared__ __attribute__((aligned(16))) char tb[4][2][64 * CT_ROW];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const int64_t nvox = (int64_t)a.N * a.D * a.H * a.W;
-    const int64_t v0 = ((int64_t)blockIdx.x * 4 + wv) * 64;
+    const int64_t v0 = SPLIT ? (int64_t)blockIdx.x * 64 : ((int64_t)blockIdx.x * 4 + wv) * 64;
     if (v0 >= nvox) return;
     const int r0 = blockIdx.y * (32 * RB);
     const int nrb = min(RB, (a.rows - r0) >> 5);
@@ -331,7 +439,7 @@ __global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
         fs[it] = vs[it] < nvox ? ct_fine_origin(a, vs[it]) : -1;
     }
     const bf16_t* arow = a.a + (int64_t)(r0 + l32) * a.K + 8 * half;
-    const int cpt = a.Co >> 5, units = 8 * cpt;
+    const int cpt = a.Co >> 5, u0 = SPLIT ? wv * 2 * cpt : 0, units = SPLIT ? u0 + 2 * cpt : 8 * cpt;
 
     auto gather = [&](int u, uint4 (&q)[4]) {
         const int tap = u / cpt, c0 = (u - tap * cpt) << 5;
@@ -356,10 +464,10 @@ __global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
             for (int r = 0; r < 16; ++r) acc[rb][vb][r] = 0.f;
 
     uint4 q[4];
-    gather(0, q);
-    put(tb[wv][0], q);
+    gather(u0, q);
+    put(tb[wv][u0 & 1], q);
     __builtin_amdgcn_wave_barrier();
-    for (int u = 0; u < units; ++u) {
+    for (int u = u0; u < units; ++u) {
         if (u + 1 < units) gather(u + 1, q);
         const char* cur = tb[wv][u & 1];
 #pragma unroll
@@ -380,7 +488,30 @@ __global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
         __builtin_amdgcn_wave_barrier();
     }
 
-    char* mine = tb[wv][0];
+    if constexpr (SPLIT) {
+        static_assert(RB == 1, "two sums of 16 registers a wave");
+        float4* sh = reinterpret_cast<float4*>(tb[0][0]);   // [3][8][64]: 24 KB of the four buffers
+        __syncthreads();
+        if (wv)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const f32x16& v = acc[0][i >> 2];
+                const int r = 4 * (i & 3);
+                sh[((wv - 1) * 8 + i) * 64 + lane] = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+            }
+        __syncthreads();
+        if (wv) return;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float4 o = sh[(k * 8 + i) * 64 + lane];
+                f32x16& v = acc[0][i >> 2];
+                const int r = 4 * (i & 3);
+                v[r] += o.x; v[r + 1] += o.y; v[r + 2] += o.z; v[r + 3] += o.w;
+            }
+    }
+    char* mine = SPLIT ? tb[3][0] : tb[wv][0];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         if (rb >= nrb) break;
@@ -432,6 +563,16 @@ lamp_status mfma_convtr_fwd(const lamp_tensor_desc* xd, const void* x, const voi
     if ((((uintptr_t)x) & 15u) || (((uintptr_t)y) & 7u) || (((uintptr_t)ws) & 15u)) return LAMP_ERR_ALIGN;
     if (ws_bytes < mfma_convtr_ws_bytes(xd, yd)) return LAMP_ERR_WORKSPACE;
     const int Ci = xd->c, Co = yd->c;
+    if ((Ci == 16 || Ci == 32 || Ci == 64 || Ci == 128) && yd->ldc % 8 == 0 && aligned16(y) && aligned16(wt) &&
+        nvox(xd) < ((int64_t)1 << 29) && ((int64_t)2 * yd->h * yd->w + 2 * yd->w) * yd->ldc < ((int64_t)1 << 31)) {
+        CtArgs a;
+        a.a = (const bf16_t*)wt; a.b = (const bf16_t*)x; a.out = (bf16_t*)y; a.bias = bias; a.rows = 8 * Co; a.K = Ci;
+        a.N = xd->n; a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Ci = Ci; a.Co = Co; a.ldb = xd->ldc; a.ldo = yd->ldc;
+        ct_set_magic(a);
+        const int64_t nv = nvox(xd);
+        return Ci == 16 ? ct_fwd_lds_launch<1>(a, nv, s) : Ci == 32 ? ct_fwd_lds_launch<2>(a, nv, s) : Ci == 64 ? ct_fwd_lds_launch<4>(a, nv, s)
+                        : ct_fwd_lds_launch<8>(a, nv, s);
+    }
     bf16_t* wp = (bf16_t*)ws;
     hipLaunchKernelGGL(convtr_repack_kernel, dim3(cdiv((int64_t)Ci * 8 * Co, 256)), dim3(256), 0, s, (const bf16_t*)wt, wp, Ci, Co);
     LAMP_CHECK_LAUNCH();
@@ -441,22 +582,21 @@ lamp_status mfma_convtr_fwd(const lamp_tensor_desc* xd, const void* x, const voi
     if (Co % 32 == 0 && Co <= 1024 && yd->ldc % 8 == 0 && ((((uintptr_t)y) & 15u) == 0) && nvox(xd) < ((int64_t)1 << 31)) {
         const int64_t nv = nvox(xd);
         ct_set_magic(a);
-        if (Ci >= 256) {
-            // many input channels: a wave takes 64 voxels x 8 units (16 accumulator tiles), so that every weight
+        if (Ci >= 256 && (int64_t)cdiv(nv, 256) * (a.rows / 256) >= 128) {
+            // many input channels and enough voxels for a workgroup to every other CU (512->256 on 75 x 4^3, 152 workgroups, forward and
+            // backward: 170 us so, 194 with a unit a wave; on 2 x 8^3, 32 workgroups: 98 and 78): a wave takes 64 voxels x 8 units (16 accumulator tiles), so that every weight
             // fragment fetched from the cache feeds two matrix-core instructions and the row blocks re-read x less
             dim3 grid((unsigned)(cdiv(cdiv(nv, 256), 8) * 8 * (a.rows / 256)));
-            hipLaunchKernelGGL((convtr_fwd32_kernel<8, 2, 0>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((convtr_fwd32_kernel<8, 2>), grid, dim3(256), 0, s, a);
         } else if (nv >= 65536) {
             // a wave = 32 voxels x 8 units: for Co = 32 it writes all eight taps of its voxels
             const int64_t groups8 = cdiv(cdiv(nv, 128), 8) * 8;  // voxel groups, padded to whole XCD rounds
             dim3 grid((unsigned)(groups8 * (a.rows / 256)));
-            if (Ci == 64) hipLaunchKernelGGL((convtr_fwd32_kernel<8, 1, 4>), grid, dim3(256), 0, s, a);
-            else if (Ci == 128) hipLaunchKernelGGL((convtr_fwd32_kernel<8, 1, 8>), grid, dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((convtr_fwd32_kernel<8, 1, 0>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((convtr_fwd32_kernel<8, 1>), grid, dim3(256), 0, s, a);
         } else {
             const int64_t groups8 = cdiv(cdiv(nv, 256), 8) * 8;
             dim3 grid((unsigned)(groups8 * (a.rows / 32)));
-            hipLaunchKernelGGL((convtr_fwd32_kernel<1, 2, 0>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((convtr_fwd32_kernel<1, 2>), grid, dim3(256), 0, s, a);
         }
         LAMP_CHECK_LAUNCH();
         return LAMP_OK;
@@ -486,7 +626,7 @@ lamp_status mfma_convtr_dgrad(const lamp_tensor_desc* xd, const void* wt, const 
         dim3 grid(cdiv(nvox(xd), 256), cdiv(a.rows, 32 * rb));
         if (rb == 4) hipLaunchKernelGGL((convtr_dgrad32_kernel<4>), grid, dim3(256), 0, s, a);
         else if (rb == 2) hipLaunchKernelGGL((convtr_dgrad32_kernel<2>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((convtr_dgrad32_kernel<1>), grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((convtr_dgrad32_kernel<1, true>), dim3(cdiv(nvox(xd), 64), grid.y), dim3(256), 0, s, a);
         LAMP_CHECK_LAUNCH();
         return LAMP_OK;
     }
@@ -765,6 +905,215 @@ lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const l
     }
     if (direct) return LAMP_OK;
     return launch_reduce_partials((const float*)ws, p.parts, O, dwt, beta, s);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Data gradient and weight gradient (with the bias gradient) in one pass over dy, for 64 input and 32 output channels, the widest
+// volume of a base-32 net.  A workgroup (8 waves, one per CU) walks chunks of 64 coarse voxels, three stages of x and dy (40 KB
+// each) in LDS, so that two chunks are in flight while one is multiplied; waves 0-3 take a quadrant (32 input channels x 32 voxels) of
+// the data gradient each, its 16 weight fragments in registers for the whole walk, waves 4-7 two taps of the weight gradient each.
+// LDS rows are 128 bytes (64 channels of x; both voxels of a w pair of dy, which are 128 consecutive bytes of memory, so a copy
+// instruction fetches 1 KB in a row), their 16-byte pieces in an order that turns with the voxel pair, so that neither the plain reads
+// (16 voxels side by side) nor the transposing ones (4 voxels x 32 bytes) meet in a bank.
+// Sums of the weight gradient: chains of `fold` chunks, added to a second register set; a partial per workgroup.
+// Bound: HBM.  64->32 on 2 x 64^3: 402 MB, 182 us as separate data and weight gradients (dy read twice) and two reductions
+// -> 71 us and one of 5.
+struct CtBArgs {
+    const bf16_t* x; const bf16_t* wt; const bf16_t* dy; bf16_t* dx;
+    const bf16_t* zero16;
+    float* part;          // [workgroup][64][8][32], then [32] bias sums where `bias`
+    int slab;             // floats of a workgroup's partial
+    int ldx, lddx, bias, fold;
+    CtArgs g;             // geometry: dims and reciprocals, ldb = channel stride of dy
+};
+static constexpr int CTB_X = 64 * 128, CTB_STAGE = CTB_X + 4 * 64 * 128, CTB_PATCH = 32 * CT_ROW;
+static constexpr int CTB_LDS = 3 * CTB_STAGE + 4 * CTB_PATCH;
+
+__global__ __launch_bounds__(512, 2) void convtr_bwd_kernel(CtBArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char ctl[];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
+    const int nvox = a.g.N * a.g.D * a.g.H * a.g.W, nchunks = (nvox + 63) >> 6;
+    const int first = blockIdx.x, wgs = gridDim.x, mine = (nchunks - first + wgs - 1) / wgs;
+
+    // copies of a wave: 8 voxels of x, 4 x 8 voxels of one (i, j) row pair of dy
+    const int cij = wv >> 1, csub = wv & 1, cvox = lane >> 3;
+    const int64_t cijoff = ct_tap_off(a.g, cij * 2);
+    auto stage = [&](int chunk, int buf) __attribute__((always_inline)) {
+        const int v0 = chunk * 64;
+        char* st = ctl + buf * CTB_STAGE;
+        {
+            const int lv = wv * 8 + cvox, v = v0 + lv, pc = (lane & 7) ^ ((lv >> 1) & 7);
+            g2lds16_ct(v < nvox ? a.x + (int64_t)v * a.ldx + pc * 8 : a.zero16, st + wv * 1024);
+        }
+        const uint32_t fo = (uint32_t)ct_fine_origin(a.g, min(v0 + lane, nvox - 1));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int lv = (csub * 4 + i) * 8 + cvox, pc = (lane & 7) ^ ((lv >> 1) & 7);
+            const uint32_t f = (uint32_t)__builtin_amdgcn_ds_bpermute(lv * 4, (int)fo);
+            const bf16_t* src = a.dy + ((int64_t)f + cijoff + (pc >> 2)) * a.g.ldb + (pc & 3) * 8;
+            g2lds16_ct(v0 + lv < nvox ? src : a.zero16, st + CTB_X + (cij * 64 + (csub * 4 + i) * 8) * 128);
+        }
+    };
+    // transposing reads: voxel rows rr (and rr + 4), 32 channels of the lower or upper half of a 128-byte row
+    const int b16 = lane >> 4, s16 = lane & 15, rr = 8 * (b16 >> 1) + (s16 >> 2), pc0 = 2 * (b16 & 1) + ((s16 & 3) >> 1);
+    const uint32_t tlo = rr * 128 + ((pc0 ^ ((rr >> 1) & 7)) << 4) + (s16 & 1) * 8;
+    const uint32_t thi = (rr + 4) * 128 + ((pc0 ^ (((rr + 4) >> 1) & 7)) << 4) + (s16 & 1) * 8;
+    auto frag2 = [&](const char* p, uint32_t h64) __attribute__((always_inline)) {
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + (tlo ^ h64)));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + (thi ^ h64)));
+        typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+        const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    auto zero = [](f32x16& v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = 0.f;
+    };
+    // Entering chunk k of the walk: its copies have landed for every wave (the 5 youngest of a wave are the next chunk's; what a wave
+    // has stored since only makes it wait longer), every wave is done with chunk k - 1, whose buffer takes chunk k + 2.
+    auto enter = [&](int k) __attribute__((always_inline)) {
+        if (k + 1 < mine) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (k + 2 < mine) stage(first + (k + 2) * wgs, (k + 2) % 3);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    if (wv < 4) {
+        const int cb = wv & 1, vb = wv >> 1, row = vb * 32 + l32;
+        bf16x8 wf[16];
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) wf[ks] = *reinterpret_cast<const bf16x8*>(a.wt + (cb * 32 + l32) * 256 + ks * 16 + half * 8);
+        const uint32_t ro = row * 128 + ((half ^ ((row >> 1) & 7)) << 4);
+        char* const patch = ctl + 3 * CTB_STAGE + wv * CTB_PATCH;
+        stage(first, 0);
+        if (mine > 1) stage(first + wgs, 1);
+        for (int k = 0; k < mine; ++k) {
+            enter(k);
+            const char* st = ctl + (k % 3) * CTB_STAGE + CTB_X;
+            f32x16 acc;
+            zero(acc);
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks)   // tap ks / 2, 16 of its 32 channels
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    wf[ks], *reinterpret_cast<const bf16x8*>(st + (ks >> 2) * 8192 + (ro ^ (uint32_t)((ks & 3) << 5))), acc, 0, 0, 0);
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg)
+                *reinterpret_cast<uint2*>(patch + l32 * CT_ROW + (rg * 8 + half * 4) * 2) =
+                    make_uint2(ct_pack(acc[rg * 4 + 0], acc[rg * 4 + 1]), ct_pack(acc[rg * 4 + 2], acc[rg * 4 + 3]));
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const int lv = it * 16 + (lane >> 2), v = (first + k * wgs) * 64 + vb * 32 + lv;
+                const uint4 o = *reinterpret_cast<const uint4*>(patch + lv * CT_ROW + (lane & 3) * 16);
+                if (v < nvox) *reinterpret_cast<uint4*>(a.dx + (int64_t)v * a.lddx + cb * 32 + (lane & 3) * 8) = o;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (a.bias) __syncthreads();
+    } else {
+        const int ij = wv - 4;
+        f32x16 acc[2][2], sum[2][2];
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                zero(acc[rb][t]);
+                zero(sum[rb][t]);
+            }
+        double bsum = 0.0;
+        stage(first, 0);
+        if (mine > 1) stage(first + wgs, 1);
+        int chain = 0;
+        for (int k = 0; k < mine; ++k) {
+            enter(k);
+            const char* st = ctl + (k % 3) * CTB_STAGE;
+            f32x16 bacc;
+            zero(bacc);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                bf16x8 af[2], bf[2];
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb) af[rb] = frag2(st + ks * 2048, rb * 64);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) bf[t] = frag2(st + CTB_X + ij * 8192 + ks * 2048, t * 64);
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) acc[rb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[t], acc[rb][t], 0, 0, 0);
+                if (a.bias) {   // the column sums of dy: products with a row of ones
+                    const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) bacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, one), bf[t], bacc, 0, 0, 0);
+                }
+            }
+            bsum += (double)bacc[0];   // every row is the sum
+            if (++chain == a.fold || k + 1 == mine) {
+                chain = 0;
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        sum[rb][t] += acc[rb][t];
+                        zero(acc[rb][t]);
+                    }
+            }
+        }
+        float* pb = a.part + (int64_t)blockIdx.x * a.slab + (4 * half * 8 + ij * 2) * 32 + l32;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) pb[((rb * 32 + 8 * rg + r) * 8 + t) * 32] = sum[rb][t][4 * rg + r];
+        if (a.bias) {
+            double* bs = reinterpret_cast<double*>(ctl + 3 * CTB_STAGE + 2 * CTB_PATCH);   // where waves 2 and 3 have their patches
+            __syncthreads();
+            if (half == 0) bs[ij * 32 + l32] = bsum;
+        }
+    }
+    if (a.bias) {
+        __syncthreads();
+        const double* bs = reinterpret_cast<const double*>(ctl + 3 * CTB_STAGE + 2 * CTB_PATCH);
+        if (tid < 32) a.part[(int64_t)blockIdx.x * a.slab + 64 * 8 * 32 + tid] = (float)(((bs[tid] + bs[32 + tid]) + bs[64 + tid]) + bs[96 + tid]);
+    }
+}
+
+bool mfma_convtr_bwd_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_tensor_desc* dxd, const lamp_norm_in* xnorm) {
+    return mfma_convtr_wgrad_supported(xd, dyd, xnorm) && xd->c == 64 && dyd->c == 32 && dxd && dxd->ldc % 8 == 0 && nvox(xd) < ((int64_t)1 << 29);
+}
+static int ctb_wgs(const lamp_tensor_desc* xd) {
+    const int64_t chunks = (nvox(xd) + 63) / 64;
+    return (int)(chunks < 256 ? chunks : 256);
+}
+size_t mfma_convtr_bwd_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
+    if (!mfma_convtr_wgrad_supported(xd, dyd, nullptr) || xd->c != 64 || dyd->c != 32) return 0;
+    return align_up((size_t)ctb_wgs(xd) * (64 * 8 * 32 + 32) * sizeof(float));
+}
+lamp_status mfma_convtr_bwd(const lamp_tensor_desc* xd, const void* x, const void* wt, const lamp_tensor_desc* dyd, const void* dy,
+                            const lamp_tensor_desc* dxd, void* dx, float* dwt, float* dbias, float beta, void* ws, size_t ws_bytes,
+                            hipStream_t s) {
+    if (ws_bytes < mfma_convtr_bwd_ws_bytes(xd, dyd)) return LAMP_ERR_WORKSPACE;
+    CtBArgs a;
+    a.x = (const bf16_t*)x; a.wt = (const bf16_t*)wt; a.dy = (const bf16_t*)dy; a.dx = (bf16_t*)dx; a.part = (float*)ws;
+    a.ldx = xd->ldc; a.lddx = dxd->ldc; a.bias = dbias ? 1 : 0;
+    a.slab = 64 * 8 * 32 + (dbias ? 32 : 0);
+    a.fold = 8;   // 512 voxels, half of what the separate weight gradient chains on 2 x 64^3
+    a.zero16 = device_zero16(s);
+    if (!a.zero16) return LAMP_ERR_HIP;
+    a.g = CtArgs{};
+    a.g.N = xd->n; a.g.D = xd->d; a.g.H = xd->h; a.g.W = xd->w; a.g.Ci = 64; a.g.Co = 32; a.g.ldb = dyd->ldc;
+    ct_set_magic(a.g);
+    const int wgs = ctb_wgs(xd);
+    if (ensure_dyn_lds((const void*)convtr_bwd_kernel, CTB_LDS) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL(convtr_bwd_kernel, dim3(wgs), dim3(512), CTB_LDS, s, a);
+    LAMP_CHECK_LAUNCH();
+    return launch_reduce_partials((const float*)ws, wgs, a.slab, dwt, beta, s, dbias, 64 * 8 * 32);
 }
 
 }  // namespace lamp

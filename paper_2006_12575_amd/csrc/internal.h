@@ -51,7 +51,9 @@ lamp_status launch_repack_batch(const RepackJob* jobs, int n, hipStream_t s);
 void set_repack_table(const RepackTable* t);
 const bf16_t* find_prepacked(const void* w, bool dgrad, int kind, int Cout, int Cin);
 const bf16_t* device_zero16(hipStream_t s);  // 16 zero bytes on the current device, nullptr on failure
-lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s);
+// out2: the outputs from O1 on go there (nullptr: one tensor of O).
+lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s, float* out2 = nullptr,
+                                   int64_t O1 = 0);
 // Column sums of a [rows, C] tensor with row stride ld: out[c] = beta*out[c] + sum_r t[r][c].
 size_t colsum_ws_bytes(int64_t rows, int C);
 lamp_status launch_colsum(const void* t, int dtype, int64_t rows, int C, int ld, float* out, float beta,
@@ -127,6 +129,13 @@ lamp_status mfma_convtr_fwd(const lamp_tensor_desc* xd, const void* x, const voi
 bool mfma_convtr_dgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_tensor_desc* dxd);
 lamp_status mfma_convtr_dgrad(const lamp_tensor_desc* xd, const void* wt, const lamp_tensor_desc* dyd, const void* dy,
                               const lamp_tensor_desc* dxd, void* dx, hipStream_t s);
+
+// Data, weight and bias gradient (dbias may be nullptr) in one pass over dy; all pointers 16-byte aligned.
+bool mfma_convtr_bwd_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_tensor_desc* dxd, const lamp_norm_in* xnorm);
+size_t mfma_convtr_bwd_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd);
+lamp_status mfma_convtr_bwd(const lamp_tensor_desc* xd, const void* x, const void* wt, const lamp_tensor_desc* dyd, const void* dy,
+                            const lamp_tensor_desc* dxd, void* dx, float* dwt, float* dbias, float beta, void* ws, size_t ws_bytes,
+                            hipStream_t s);
 
 // ---- convtr_f32.hip -------------------------------------------------------------------------
 // fp32: pointers 16-byte aligned.  The weight gradient also takes the bias gradient (dbias may be nullptr).

@@ -42,7 +42,7 @@ const bf16_t* device_zero16(hipStream_t s) {
 // enough in flight where there are few parts of many outputs (256->256 conv weights, 4 parts of 1.8 M: 21.6 -> 10.6 us).
 template <int SL, int VO>
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ part, int S, int64_t O,
-                                                              float* __restrict__ out, float beta) {
+                                                              float* __restrict__ out, float beta, float* __restrict__ out2, int64_t O1) {
     constexpr int GPB = 256 / SL;
     __shared__ double sh[SL > 1 ? 256 * VO : 1];
     const int gl = threadIdx.x % GPB, sl = threadIdx.x / GPB;
@@ -91,6 +91,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
             for (int i = 0; i < VO; ++i) acc[i] = sh[i * 256 + threadIdx.x];
     }
     if (sl == 0 && o < O) {
+        if (o >= O1) out = out2 - O1;
         float v[VO];
         if (beta != 0.f) {
             Vec<float, VO>::load(out + o, v);
@@ -109,12 +110,12 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 // (27648 outputs, 256 parts: 64 lanes 11.0 us, 32 to 8 lanes 3.7, one lane 14.8; 16384 x 512: 12.3, 4.3 with 32).  64 lanes pay for
 // a few outputs only (32 x 4096: 4.4 us, with 32 lanes 6.0; 864 x 3000: 6.9 and 5.4).
 template <int VO>
-static void reduce_launch(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s) {
+static void reduce_launch(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s, float* out2, int64_t O1) {
     const int64_t g = O / VO;
     int sl = 1;
     while (2 * sl <= (O <= 256 ? 64 : 32) && 2 * sl <= S && (g * 2 * sl + 255) / 256 < 1024) sl *= 2;
 #define LAMP_REDUCE(SL) \
-    case SL: hipLaunchKernelGGL((reduce_partials_kernel<SL, VO>), dim3(cdiv(g, 256 / SL)), dim3(256), 0, s, part, S, O, out, beta); break
+    case SL: hipLaunchKernelGGL((reduce_partials_kernel<SL, VO>), dim3(cdiv(g, 256 / SL)), dim3(256), 0, s, part, S, O, out, beta, out2, O1); break
     switch (sl) {
         LAMP_REDUCE(1);
         LAMP_REDUCE(2);
@@ -127,9 +128,10 @@ static void reduce_launch(const float* part, int S, int64_t O, float* out, float
 #undef LAMP_REDUCE
 }
 
-lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s) {
-    if (O % 4 == 0 && aligned16(part) && aligned16(out)) reduce_launch<4>(part, S, O, out, beta, s);
-    else reduce_launch<1>(part, S, O, out, beta, s);
+lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s, float* out2, int64_t O1) {
+    if (!out2) O1 = O;
+    if (O % 4 == 0 && O1 % 4 == 0 && aligned16(part) && aligned16(out) && aligned16(out2)) reduce_launch<4>(part, S, O, out, beta, s, out2, O1);
+    else reduce_launch<1>(part, S, O, out, beta, s, out2, O1);
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }
