@@ -364,14 +364,16 @@ __global__ __launch_bounds__(256) void conv3d_cin1_wgrad_kernel(const bf16_t* __
     }
 }
 
-// Weight gradient for Cin == 1 with the operands staged in LDS (C_out = 32*CB per workgroup column):
-// dW[co][tap] = sum_v dz[v][co] * x[v + tap], voxels as the reduction dimension.  A workgroup walks
-// blocks of four output rows (one per wave) like the tiled forward kernel and stages the 3 x 6 input
-// rows the same way.  Per 16 voxels of its row a wave fetches dz with one 16-byte load per lane and
-// 32 channels (two groups ahead), passes it through a private LDS slot and reads the A operand
-// (dz^T, voxel-major per lane) with the transposing LDS load; the B operand -- 8 consecutive voxels
-// shifted by the lane's tap -- is 8 two-byte LDS reads at immediate offsets.  Every wave writes its
-// own partial [C_out][27] slab.
+// Weight gradient of 1 to 4 input channels: dW[co][column] = sum_v dz[v][co] * x[v + tap][ci], column = (tap, ci), voxels as the
+// reduction dimension.  The 27 * CI columns are cut into blocks of 32 whatever CI is (padding the channels to a copy of 8, in front of
+// the kernel that takes blocks of 32 channels, spent 16 times the products and a launch).  A workgroup walks L slices of a tile of
+// 8 x 16 G outputs (h, w; G up to 4), two rows to each of its four waves.  x: a ring of four slices in LDS, every channel three times,
+// shifted by kw, so that the 8 consecutive voxels of a fragment are one aligned 16-byte read for every tap; rows are padded to 144 bytes
+// to spread the taps of a read over the banks.  The slice after next is fetched during a step: one barrier a step.  dz: one 16-byte
+// load a lane and 16 voxels x 32 channels, a whole step ahead, through a private LDS slot to the transposing read.
+// Chains of additions: two steps (256 voxels) into a second register set, the four waves at the end, one partial a walk.
+// Bound: HBM (dz is read once) and the instructions per 16 voxels.  2->16 on 2 x 64 x 80 x 96: 58 us with padding and
+// reduction -> 25; 1->32 on 2 x 128^3 (268 MB): 139 us, staging all three slices anew for every four rows, -> 69 (3.9 TB/s).
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short c1_s16x4;
 __device__ __forceinline__ c1_bf16x8 c1_frag_tr(const char* p) {
     typedef __attribute__((address_space(3))) c1_s16x4 lds_s16x4;
@@ -382,106 +384,183 @@ __device__ __forceinline__ c1_bf16x8 c1_frag_tr(const char* p) {
     return __builtin_bit_cast(c1_bf16x8, v);
 }
 
-struct Cin1WArgs {
+struct NarrowWArgs {
     const bf16_t* x; int ldx;
     const bf16_t* dz; int lddz;
-    float* part;     // [waves][Co][27]
-    int N, D, H, W, Co;
-    int G;           // 16-voxel groups per row
-    int WP, RS;      // staged row: WP = 16*G + 2 elements (w = -1 .. 16*G), row stride RS elements
-    uint32_t mWP; int sWP;
+    float* part;      // [N * tiles * segs][Co][27][CI]
+    int D, H, W, Co;
+    int nth, ntw, G;  // tiles along h and w, 16-voxel groups of a tile row
+    int segs, L;      // walks of a tile, slices of a walk
 };
+static constexpr int NW_TH = 8, NW_ROW = 144, NW_PLANE = (NW_TH + 2) * NW_ROW;
+static size_t narrow_lds(int ci, int cb) { return (size_t)4 * ci * 3 * NW_PLANE + 4 * 2 * cb * 1024; }
 
-template <int CB, int NE>
-__global__ __launch_bounds__(256) void conv3d_cin1_wgrad_tile_kernel(Cin1WArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char c1w_lds[];
+template <int CI, int CB>
+__global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad_kernel(NarrowWArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char nw_lds[];
+    constexpr int COLS = 27 * CI, NB = (COLS + 31) / 32, SLOT = CI * 3 * NW_PLANE, NE = ((NW_TH + 2) * 66 * CI + 255) / 256;
+    char* const xr = nw_lds;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, half = lane >> 5;
-    char* slot = c1w_lds + wv * (2 * CB * 1024);                                         // two dz buffers of this wave
-    unsigned short* xt = reinterpret_cast<unsigned short*>(c1w_lds + 4 * 2 * CB * 1024);  // [18][RS]
+    char* const slot = xr + 4 * SLOT + wv * (2 * CB * 1024);
     const int co0 = blockIdx.y * (32 * CB);
-    const int tap = l32 < 27 ? l32 : 26;   // columns 27..31 repeat tap 26 and are not written
-    const int kd = tap / 9, kh = (tap / 3) % 3, kw = tap % 3;
-    const int xoff = (kd * 6 + kh + wv) * a.RS + kw + 8 * half;
+    int t = blockIdx.x;
+    const int seg = t % a.segs;
+    t /= a.segs;
+    const int tw = t % a.ntw;
+    t /= a.ntw;
+    const int h0 = t % a.nth * NW_TH, n = t / a.nth, w0 = tw * 16 * a.G;
+    const int d0 = seg * a.L, d1 = min(d0 + a.L, a.D);
+
+    // x: this thread's elements of a slice (offset in the slice, -1 outside; offset in the ring)
+    int go[NE], lo[NE];
+    const int re = (16 * a.G + 2) * CI;   // elements of a staged row
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int e = tid + 256 * i, r = e / re, j = e - r * re, jw = j / CI, ci = j - jw * CI;
+        const int h = h0 - 1 + r, w = w0 - 1 + jw;
+        go[i] = (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W ? (h * a.W + w) * a.ldx + ci : -1;
+        lo[i] = r < NW_TH + 2 ? ci * (3 * NW_PLANE) + r * NW_ROW + jw * 2 : -1;
+    }
+    const int64_t xslice = (int64_t)a.H * a.W * a.ldx;
+    const bf16_t* const xs = a.x + (int64_t)n * a.D * xslice;
+    bf16_t px[NE];
+    auto fetch_x = [&](int d) __attribute__((always_inline)) {
+        const bool in = (unsigned)d < (unsigned)a.D;
+        const bf16_t* p = xs + (int64_t)(in ? d : 0) * xslice;
+#pragma unroll
+        for (int i = 0; i < NE; ++i) px[i] = in && lo[i] >= 0 && go[i] >= 0 ? p[go[i]] : (bf16_t)0;
+    };
+    auto stage_x = [&](int d) __attribute__((always_inline)) {
+        char* q = xr + ((d + 4) & 3) * SLOT;
+#pragma unroll
+        for (int i = 0; i < NE; ++i)
+            if (lo[i] >= 0)
+#pragma unroll   // (a voxel left or right of a row's 64 falls into the padding)
+                for (int kw = 0; kw < 3; ++kw) *reinterpret_cast<bf16_t*>(q + lo[i] + kw * (NW_PLANE - 2)) = px[i];
+    };
+    // dz: voxel of the group and 16-byte piece of its 64 bytes
+    const int vx = lane >> 2, piece = lane & 3, hrow = h0 + wv * 2;
+    const bf16_t* const dzs = a.dz + ((int64_t)n * a.D * a.H * a.W + (int64_t)hrow * a.W + w0 + vx) * a.lddz + co0 + piece * 8;
+    uint4 q[8][CB];
+    auto fetch_z = [&](int i, int d) __attribute__((always_inline)) {
+        const bool in = d < d1 && hrow + (i >> 2) < a.H && w0 + 16 * (i & 3) + vx < a.W;
+        const bf16_t* p = dzs + (((int64_t)d * a.H + (i >> 2)) * a.W + 16 * (i & 3)) * a.lddz;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            q[i][cb] = make_uint4(0, 0, 0, 0);
+            if (in && co0 + 32 * cb + piece * 8 < a.Co) q[i][cb] = *reinterpret_cast<const uint4*>(p + 32 * cb);
+        }
+    };
+    // columns of this lane: offset in a slice of the ring, which slice
+    int col[NB], ckd[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int c = b * 32 + l32 < COLS ? b * 32 + l32 : COLS - 1;   // columns past the end are computed and not written
+        const int tap = c / CI, ci = c - tap * CI;
+        ckd[b] = tap / 9;
+        col[b] = (ci * 3 + tap % 3) * NW_PLANE + (wv * 2 + tap / 3 % 3) * NW_ROW + 16 * half;
+    }
     // lane part of a transposing fragment read: voxel row 8*(b/2) + s/4, channel bytes 32*(b%2) + 8*(s%4)
     const int b16 = lane >> 4, s16 = lane & 15;
     const uint32_t loff = (uint32_t)((8 * (b16 >> 1) + (s16 >> 2)) * 64 + 32 * (b16 & 1) + 8 * (s16 & 3));
-    const int vx = lane >> 2, piece = lane & 3;   // dz copy: voxel of the group, 16-byte piece of its 64 bytes
 
-    c1_f32x16 acc[CB];
+    c1_f32x16 acc[CB][NB], sum[CB][NB];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][b][r] = sum[cb][b][r] = 0.f;
 
-    const int hblocks = (a.H + 3) >> 2;
-    const int per_n = a.D * hblocks;
-    const int nblk = a.N * per_n;
-    const int total_e = 18 * a.WP;
-    for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-        const int n = blk / per_n, rblk = blk - n * per_n;
-        const int d = rblk / hblocks, h0 = (rblk - d * hblocks) << 2;
-        const bf16_t* xs = a.x + (int64_t)n * a.D * a.H * a.W * a.ldx;
-        unsigned short stg[NE];
+#pragma unroll 1
+    for (int k = -1; k <= 1; ++k) {
+        fetch_x(d0 + k);
+        stage_x(d0 + k);
+    }
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int e = tid + 256 * i;
-            const int r = (int)(((uint64_t)(uint32_t)e * a.mWP) >> a.sWP), j = e - r * a.WP;
-            const int skd = r / 6, hh = r - skd * 6;
-            const int id = d + skd - 1, ih = h0 - 1 + hh, iw = j - 1;
-            const bool in = e < total_e && id >= 0 && id < a.D && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
-            stg[i] = in ? xs[(((int64_t)id * a.H + ih) * a.W + iw) * a.ldx] : (unsigned short)0;
+    for (int i = 0; i < 8; ++i)
+        if ((i & 3) < a.G) fetch_z(i, d0);
+    __syncthreads();
+    for (int d = d0; d < d1; ++d) {
+        const bool more = d + 1 < d1;
+        if (more) fetch_x(d + 2);
+        const char* xb[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) xb[b] = xr + ((d + 3 + ckd[b]) & 3) * SLOT + col[b];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if ((i & 3) >= a.G) continue;
+            char* buf = slot + (i & 1) * (CB * 1024);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<uint4*>(buf + cb * 1024 + vx * 64 + piece * 16) = q[i][cb];
+            if (more) fetch_z(i, d + 1);
+            __builtin_amdgcn_wave_barrier();
+            c1_bf16x8 xf[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) xf[b] = *reinterpret_cast<const c1_bf16x8*>(xb[b] + (i >> 2) * NW_ROW + (i & 3) * 32);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                const c1_bf16x8 zf = c1_frag_tr(buf + cb * 1024 + loff);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[cb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zf, xf[b], acc[cb][b], 0, 0, 0);
+            }
+            __builtin_amdgcn_wave_barrier();
         }
-        __syncthreads();  // every wave is done with the previous block's rows
+        if (more) stage_x(d + 2);   // the slice that every wave left behind the last barrier
+        if (((d - d0) & 1) || !more) {
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int e = tid + 256 * i;
-            const int r = (int)(((uint64_t)(uint32_t)e * a.mWP) >> a.sWP), j = e - r * a.WP;
-            if (e < total_e) xt[r * a.RS + j] = stg[i];
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    sum[cb][b] += acc[cb][b];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[cb][b][r] = 0.f;
+                }
         }
         __syncthreads();
-        const int h = h0 + wv;
-        if (h < a.H) {
-            const bf16_t* dzrow = a.dz + ((((int64_t)n * a.D + d) * a.H + h) * a.W) * a.lddz + co0 + piece * 8;
-            auto fetch = [&](int g, uint4 (&q)[CB]) {
-                const int w = 16 * g + vx;
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    q[cb] = make_uint4(0, 0, 0, 0);
-                    if (g < a.G && w < a.W) q[cb] = *reinterpret_cast<const uint4*>(dzrow + (int64_t)w * a.lddz + 32 * cb);
-                }
-            };
-            uint4 q0[CB], q1[CB];
-            fetch(0, q0);
-            fetch(1, q1);
-            for (int g = 0; g < a.G; ++g) {
-                char* buf = slot + (g & 1) * (CB * 1024);
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<uint4*>(buf + cb * 1024 + vx * 64 + piece * 16) = q0[cb];
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) q0[cb] = q1[cb];
-                fetch(g + 2, q1);
-                __builtin_amdgcn_wave_barrier();
-                uint32_t r[4];
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const uint32_t lo = xt[xoff + 16 * g + 2 * e2], hi = xt[xoff + 16 * g + 2 * e2 + 1];
-                    r[e2] = lo | (hi << 16);
-                }
-                const c1_bf16x8 b = __builtin_bit_cast(c1_bf16x8, make_uint4(r[0], r[1], r[2], r[3]));
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c1_frag_tr(buf + cb * 1024 + loff), b, acc[cb], 0, 0, 0);
-            }
-        }
     }
-    if (l32 < 27) {
-        float* pb = a.part + ((int64_t)blockIdx.x * 4 + wv) * a.Co * 27;
+    // the four waves: 2 and 3 to 0 and 1, then 1 to 0
+    static_assert(2 * CB * NB * 4096 <= 4 * SLOT, "two waves' sums fit the ring");
+#pragma unroll
+    for (int k = 2; k >= 1; k >>= 1) {
+        float4* sh = reinterpret_cast<float4*>(xr);
+        if (wv >= k && wv < 2 * k) {
+            float4* o = sh + (wv - k) * (CB * NB * 256) + lane;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        o[((cb * NB + b) * 4 + r) * 64] = make_float4(sum[cb][b][4 * r], sum[cb][b][4 * r + 1], sum[cb][b][4 * r + 2], sum[cb][b][4 * r + 3]);
+        }
+        __syncthreads();
+        if (wv < k) {
+            const float4* o = sh + wv * (CB * NB * 256) + lane;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float4 v = o[((cb * NB + b) * 4 + r) * 64];
+                        sum[cb][b][4 * r] += v.x; sum[cb][b][4 * r + 1] += v.y; sum[cb][b][4 * r + 2] += v.z; sum[cb][b][4 * r + 3] += v.w;
+                    }
+        }
+        __syncthreads();
+    }
+    if (wv) return;
+    float* pb = a.part + (int64_t)blockIdx.x * a.Co * COLS;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int c = b * 32 + l32;
+        if (c >= COLS) continue;
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int co = co0 + 32 * cb + 8 * (r / 4) + 4 * half + (r % 4);
-                pb[(int64_t)co * 27 + l32] = acc[cb][r];
+                if (co < a.Co) pb[(int64_t)co * COLS + c] = sum[cb][b][r];
             }
     }
 }
@@ -547,46 +626,55 @@ static lamp_status cin1_tile_fwd(const lamp_tensor_desc* xd, const void* x, cons
     if (stats_out) return launch_stats_finalize(a.partial, a.counts, parts, zd->n, zd->c, eps, stats_out, s, true);
     return LAMP_OK;
 }
-// ---- tiled Cin == 1 weight gradient: launch geometry, workspace, dispatch ----
-static int cin1_wtile_groups(const lamp_tensor_desc* xd) { return (xd->w + 15) / 16; }
-static int cin1_wtile_ne(const lamp_tensor_desc* xd) { return (18 * (16 * cin1_wtile_groups(xd) + 2) + 255) / 256; }
-static bool cin1_wtile_ok(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, const void* dz) {
-    return (dzd->c == 32 || dzd->c == 64 || dzd->c == 128) && dzd->ldc % 8 == 0 && aligned16(dz) && cin1_wtile_ne(xd) <= 40 &&
-           (int64_t)xd->n * xd->d * ((xd->h + 3) / 4) < ((int64_t)1 << 31);
+// ---- weight gradient of 1 to 4 input channels: launch geometry, workspace, dispatch ----
+struct NarrowWPlan { int nth, ntw, G, segs, L, cb; int64_t walks; };
+static NarrowWPlan narrow_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
+    NarrowWPlan p;
+    p.cb = xd->c <= 2 && dzd->c > 32 ? 2 : 1;   // as many sums as registers hold twice
+    p.nth = cdiv(xd->h, NW_TH);
+    p.ntw = cdiv(xd->w, 64);
+    p.G = cdiv(cdiv(xd->w, p.ntw), 16);
+    // Three workgroups a CU; a walk of two slices at least (its first step waits for three slices of x).
+    const int64_t tiles = (int64_t)xd->n * p.nth * p.ntw, steps = tiles * xd->d * cdiv(dzd->c, 32 * p.cb);
+    int64_t l = (steps + 767) / 768;
+    if (l < 2) l = 2;
+    if (l > xd->d) l = xd->d;
+    p.segs = cdiv(xd->d, l);
+    p.L = cdiv(xd->d, p.segs);
+    p.segs = cdiv(xd->d, p.L);
+    p.walks = tiles * p.segs;
+    return p;
 }
-static int cin1_wtile_gridx(const lamp_tensor_desc* xd) {
-    const int64_t nblk = (int64_t)xd->n * xd->d * ((xd->h + 3) / 4);
-    return (int)(nblk < 1024 ? nblk : 1024);
+static bool narrow_ok(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
+    return xd->dtype == LAMP_BF16 && xd->c <= 4 && dzd->c % 8 == 0 && dzd->ldc % 8 == 0 && (int64_t)xd->h * xd->w * xd->ldc < ((int64_t)1 << 31) &&
+           narrow_plan(xd, dzd).walks * dzd->c * 27 * xd->c <= ((int64_t)16 << 20) && cdiv(dzd->c, 32) <= 65535;   // partials up to 64 MB
 }
-static size_t cin1_wtile_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
-    return align_up((size_t)cin1_wtile_gridx(xd) * 4 * dzd->c * 27 * sizeof(float));
+static size_t narrow_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
+    return align_up((size_t)narrow_plan(xd, dzd).walks * dzd->c * 27 * xd->c * sizeof(float));
 }
-template <int CB>
-static void cin1_wtile_launch(int ne, dim3 grid, size_t lds, hipStream_t s, const Cin1WArgs& a) {
-    if (ne <= 12) hipLaunchKernelGGL((conv3d_cin1_wgrad_tile_kernel<CB, 12>), grid, dim3(256), lds, s, a);
-    else if (ne <= 20) hipLaunchKernelGGL((conv3d_cin1_wgrad_tile_kernel<CB, 20>), grid, dim3(256), lds, s, a);
-    else hipLaunchKernelGGL((conv3d_cin1_wgrad_tile_kernel<CB, 40>), grid, dim3(256), lds, s, a);
-}
-static lamp_status cin1_wtile(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dzd, const void* dz, float* dw,
-                              float beta, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (!ws || ws_bytes < cin1_wtile_ws_bytes(xd, dzd)) return LAMP_ERR_WORKSPACE;
-    Cin1WArgs a;
-    a.x = (const bf16_t*)x; a.ldx = xd->ldc; a.dz = (const bf16_t*)dz; a.lddz = dzd->ldc; a.part = (float*)ws;
-    a.N = xd->n; a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Co = dzd->c;
-    a.G = cin1_wtile_groups(xd);
-    a.WP = 16 * a.G + 2;
-    a.RS = a.WP;
-    div_magic(a.WP, &a.mWP, &a.sWP);
-    const int cb = dzd->c >= 128 ? 4 : (dzd->c >= 64 ? 2 : 1);   // channels per workgroup column: 32 * cb
-    const int gx = cin1_wtile_gridx(xd);
-    const dim3 grid(gx, dzd->c / (32 * cb));
-    const size_t lds = (size_t)4 * 2 * cb * 1024 + (size_t)18 * a.RS * sizeof(unsigned short);
-    const int ne = cin1_wtile_ne(xd);
-    if (cb == 1) cin1_wtile_launch<1>(ne, grid, lds, s, a);
-    else if (cb == 2) cin1_wtile_launch<2>(ne, grid, lds, s, a);
-    else cin1_wtile_launch<4>(ne, grid, lds, s, a);
+template <int CI, int CB>
+static lamp_status narrow_launch(const NarrowWArgs& a, dim3 grid, hipStream_t s) {
+    const size_t lds = narrow_lds(CI, CB);
+    if (ensure_dyn_lds((const void*)conv3d_narrow_wgrad_kernel<CI, CB>, (int)lds) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL((conv3d_narrow_wgrad_kernel<CI, CB>), grid, dim3(256), lds, s, a);
     LAMP_CHECK_LAUNCH();
-    return launch_reduce_partials((const float*)ws, gx * 4, (int64_t)dzd->c * 27, dw, beta, s);
+    return LAMP_OK;
+}
+static lamp_status narrow_wgrad(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dzd, const void* dz, float* dw,
+                                float beta, void* ws, size_t ws_bytes, hipStream_t s) {
+    if (!ws || ws_bytes < narrow_ws_bytes(xd, dzd)) return LAMP_ERR_WORKSPACE;
+    const NarrowWPlan p = narrow_plan(xd, dzd);
+    NarrowWArgs a;
+    a.x = (const bf16_t*)x; a.ldx = xd->ldc; a.dz = (const bf16_t*)dz; a.lddz = dzd->ldc; a.part = (float*)ws;
+    a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Co = dzd->c;
+    a.nth = p.nth; a.ntw = p.ntw; a.G = p.G; a.segs = p.segs; a.L = p.L;
+    const dim3 grid((unsigned)p.walks, cdiv(dzd->c, 32 * p.cb));
+    const lamp_status st = xd->c == 1   ? (p.cb == 2 ? narrow_launch<1, 2>(a, grid, s) : narrow_launch<1, 1>(a, grid, s))
+                           : xd->c == 2 ? (p.cb == 2 ? narrow_launch<2, 2>(a, grid, s) : narrow_launch<2, 1>(a, grid, s))
+                           : xd->c == 3 ? narrow_launch<3, 1>(a, grid, s)
+                                        : narrow_launch<4, 1>(a, grid, s);
+    if (st != LAMP_OK) return st;
+    return launch_reduce_partials((const float*)ws, (int)p.walks, (int64_t)dzd->c * 27 * xd->c, dw, beta, s);
 }
 static bool cin1_wgrad_ok(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd, const lamp_norm_in* xnorm) {
     const bool nm = xnorm && xnorm->mean_rstd && xnorm->c_norm > 0;
@@ -962,8 +1050,8 @@ extern "C" size_t lamp_conv3d_wgrad_workspace_bytes(const lamp_tensor_desc* xd, 
         const size_t e = align_up((size_t)cin1_wgrad_blocks(nvox(xd)) * 4 * dzd->c * 27 * sizeof(float));
         if (e > a) a = e;
     }
-    if (xd->dtype == LAMP_BF16 && xd->c == 1) {
-        const size_t e = cin1_wtile_ws_bytes(xd, dzd);
+    if (narrow_ok(xd, dzd)) {
+        const size_t e = narrow_ws_bytes(xd, dzd);
         if (e > a) a = e;
     }
     lamp_tensor_desc xp;
@@ -994,8 +1082,7 @@ extern "C" lamp_status lamp_conv3d_wgrad(const lamp_tensor_desc* xd, const void*
         return mfma_wgrad(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
     if (f32_wgrad_supported(xd, dzd))
         return f32_wgrad(xd, (const float*)x, make_norm(xnorm), dzd, (const float*)dz, dw, beta, ws, ws_bytes, s);
-    if (xd->dtype == LAMP_BF16 && xd->c == 1 && !(xnorm && xnorm->mean_rstd && xnorm->c_norm > 0) && cin1_wtile_ok(xd, dzd, dz))
-        return cin1_wtile(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
+    if (!has_norm(xnorm) && narrow_ok(xd, dzd)) return narrow_wgrad(xd, x, dzd, dz, dw, beta, ws, ws_bytes, s);
     if (cin1_wgrad_ok(xd, dzd, xnorm)) {
         const int64_t groups = nvox(xd) / 16;
         const int blocks = cin1_wgrad_blocks(nvox(xd));
