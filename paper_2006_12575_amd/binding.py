@@ -134,18 +134,23 @@ def _check(status, where):
         raise LampError(status, where)
 
 
+_CODES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    code = _CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def desc(t: torch.Tensor) -> TensorDesc:
     """Descriptor of a dense NDHWC tensor or of a channel slice buf[..., a:b] of one."""
-    assert t.dim() == 5, "expected [N,D,H,W,C]"
-    n, d, h, w, c = t.shape
+    shape = t.shape
+    assert len(shape) == 5, "expected [N,D,H,W,C]"
+    n, d, h, w, c = shape
+    if t.is_contiguous():   # nothing to check: 1.3 us where the strides one by one take 4.7, twice a call or more
+        return TensorDesc(n, d, h, w, c, c, _dtype_code(t))
     assert c == 1 or t.stride(4) == 1, "channels must be contiguous"
     ext = [d * h * w, h * w, w, 1]  # voxels spanned by one step of dims 0..3
     ldc = c
@@ -160,11 +165,12 @@ def desc(t: torch.Tensor) -> TensorDesc:
 
 
 def _ptr(t):
-    return None if t is None else c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # the argument type makes it a pointer
 
 
 def _stream():
-    return c_void_p(torch.cuda.current_stream().cuda_stream)
+    # torch.cuda.current_stream().cuda_stream without the two Python objects in between
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _norm(nm):
@@ -205,8 +211,8 @@ def lamp_rmsprop_step(w, v, g, w_out=None, lr=1e-3, alpha=0.99, eps=1e-8):
 
 def lamp_conv3d_fwd(x, w, z, bias=None, xnorm=None, stats_out=None, eps=1e-5, ws=None):
     xd, zd = desc(x), desc(z)
-    need = lib().lamp_conv3d_fwd_workspace_bytes(ctypes.byref(xd), ctypes.byref(zd), 1 if stats_out is not None else 0)
-    ws = ws if ws is not None else _ws(need, x.device)
+    if ws is None:
+        ws = _ws(lib().lamp_conv3d_fwd_workspace_bytes(ctypes.byref(xd), ctypes.byref(zd), 1 if stats_out is not None else 0), x.device)
     _check(lib().lamp_conv3d_fwd(ctypes.byref(xd), _ptr(x), _norm(xnorm), _ptr(w), _ptr(bias), ctypes.byref(zd), _ptr(z),
                                  _ptr(stats_out), eps, _ptr(ws), ws.numel(), _stream()), "lamp_conv3d_fwd")
     return z
@@ -214,8 +220,8 @@ def lamp_conv3d_fwd(x, w, z, bias=None, xnorm=None, stats_out=None, eps=1e-5, ws
 
 def lamp_conv3d_dgrad(dz, w, dx, ws=None):
     dzd, dxd = desc(dz), desc(dx)
-    need = lib().lamp_conv3d_dgrad_workspace_bytes(ctypes.byref(dzd), ctypes.byref(dxd))
-    ws = ws if ws is not None else _ws(need, dz.device)
+    if ws is None:
+        ws = _ws(lib().lamp_conv3d_dgrad_workspace_bytes(ctypes.byref(dzd), ctypes.byref(dxd)), dz.device)
     _check(lib().lamp_conv3d_dgrad(ctypes.byref(dzd), _ptr(dz), _ptr(w), ctypes.byref(dxd), _ptr(dx), _ptr(ws), ws.numel(),
                                    _stream()), "lamp_conv3d_dgrad")
     return dx
@@ -225,8 +231,8 @@ def lamp_conv3d_dgrad_inorm_relu_bwd(dz, w, g, z, stats, dzb, gamma=None, beta=N
     """g = data gradient of the conv (dz, w); dzb = InstanceNorm + ReLU backward of g through the layer below (z, stats);
     dzb may be g."""
     dzd, gd, zd, dzbd = desc(dz), desc(g), desc(z), desc(dzb)
-    need = lib().lamp_conv3d_dgrad_inorm_relu_bwd_workspace_bytes(ctypes.byref(dzd), ctypes.byref(gd))
-    ws = ws if ws is not None else _ws(need, dz.device)
+    if ws is None:
+        ws = _ws(lib().lamp_conv3d_dgrad_inorm_relu_bwd_workspace_bytes(ctypes.byref(dzd), ctypes.byref(gd)), dz.device)
     _check(lib().lamp_conv3d_dgrad_inorm_relu_bwd(ctypes.byref(dzd), _ptr(dz), _ptr(w), ctypes.byref(gd), _ptr(g), ctypes.byref(zd),
                                                   _ptr(z), _ptr(stats), _ptr(gamma), _ptr(beta), ctypes.byref(dzbd), _ptr(dzb),
                                                   _ptr(dgamma), _ptr(dbeta), beta_acc, _ptr(ws), ws.numel(), _stream()),
@@ -236,8 +242,8 @@ def lamp_conv3d_dgrad_inorm_relu_bwd(dz, w, g, z, stats, dzb, gamma=None, beta=N
 
 def lamp_conv3d_wgrad(x, dz, dw, dbias=None, beta=0.0, xnorm=None, ws=None):
     xd, dzd = desc(x), desc(dz)
-    need = lib().lamp_conv3d_wgrad_workspace_bytes(ctypes.byref(xd), ctypes.byref(dzd))
-    ws = ws if ws is not None else _ws(need, x.device)
+    if ws is None:
+        ws = _ws(lib().lamp_conv3d_wgrad_workspace_bytes(ctypes.byref(xd), ctypes.byref(dzd)), x.device)
     _check(lib().lamp_conv3d_wgrad(ctypes.byref(xd), _ptr(x), _norm(xnorm), ctypes.byref(dzd), _ptr(dz), _ptr(dw),
                                    _ptr(dbias), beta, _ptr(ws), ws.numel(), _stream()), "lamp_conv3d_wgrad")
     return dw
@@ -245,8 +251,8 @@ def lamp_conv3d_wgrad(x, dz, dw, dbias=None, beta=0.0, xnorm=None, ws=None):
 
 def lamp_inorm_relu(z, y, stats, gamma=None, beta=None, eps=1e-5, stats_given=False, ws=None):
     zd, yd = desc(z), desc(y)
-    need = lib().lamp_inorm_relu_workspace_bytes(ctypes.byref(zd))
-    ws = ws if ws is not None else _ws(need, z.device)
+    if ws is None:
+        ws = _ws(lib().lamp_inorm_relu_workspace_bytes(ctypes.byref(zd)), z.device)
     _check(lib().lamp_inorm_relu(ctypes.byref(zd), _ptr(z), _ptr(gamma), _ptr(beta), eps, ctypes.byref(yd), _ptr(y),
                                  _ptr(stats), 1 if stats_given else 0, _ptr(ws), ws.numel(), _stream()), "lamp_inorm_relu")
     return y
@@ -262,8 +268,8 @@ def lamp_inorm_relu_noalloc(z, y, stats, gamma=None, beta=None, eps=1e-5):
 
 def lamp_inorm_relu_bwd(dy, z, stats, dz, gamma=None, beta=None, dgamma=None, dbeta=None, beta_acc=0.0, ws=None):
     dyd, zd, dzd = desc(dy), desc(z), desc(dz)
-    need = lib().lamp_inorm_relu_bwd_workspace_bytes(ctypes.byref(zd))
-    ws = ws if ws is not None else _ws(need, z.device)
+    if ws is None:
+        ws = _ws(lib().lamp_inorm_relu_bwd_workspace_bytes(ctypes.byref(zd)), z.device)
     _check(lib().lamp_inorm_relu_bwd(ctypes.byref(dyd), _ptr(dy), ctypes.byref(zd), _ptr(z), _ptr(stats), _ptr(gamma),
                                      _ptr(beta), ctypes.byref(dzd), _ptr(dz), _ptr(dgamma), _ptr(dbeta), beta_acc,
                                      _ptr(ws), ws.numel(), _stream()), "lamp_inorm_relu_bwd")
@@ -314,8 +320,8 @@ def lamp_maxpool2_bwd(x, dy, dx, add=None, xnorm=None):
 
 def lamp_convtr3d(x, wt, y, bias=None, xnorm=None, ws=None):
     xd, yd = desc(x), desc(y)
-    need = lib().lamp_convtr3d_workspace_bytes(ctypes.byref(xd), ctypes.byref(yd))
-    ws = ws if ws is not None else _ws(need, x.device)
+    if ws is None:
+        ws = _ws(lib().lamp_convtr3d_workspace_bytes(ctypes.byref(xd), ctypes.byref(yd)), x.device)
     _check(lib().lamp_convtr3d(ctypes.byref(xd), _ptr(x), _norm(xnorm), _ptr(wt), _ptr(bias), ctypes.byref(yd), _ptr(y),
                                _ptr(ws), ws.numel(), _stream()), "lamp_convtr3d")
     return y
@@ -324,8 +330,8 @@ def lamp_convtr3d(x, wt, y, bias=None, xnorm=None, ws=None):
 def lamp_convtr3d_bwd(x, wt, dy, dx=None, dwt=None, dbias=None, beta=0.0, xnorm=None, ws=None):
     xd, dyd = desc(x), desc(dy)
     dxd = desc(dx) if dx is not None else None
-    need = lib().lamp_convtr3d_bwd_workspace_bytes(ctypes.byref(xd), ctypes.byref(dyd))
-    ws = ws if ws is not None else _ws(need, x.device)
+    if ws is None:
+        ws = _ws(lib().lamp_convtr3d_bwd_workspace_bytes(ctypes.byref(xd), ctypes.byref(dyd)), x.device)
     _check(lib().lamp_convtr3d_bwd(ctypes.byref(xd), _ptr(x), _norm(xnorm), _ptr(wt), ctypes.byref(dyd), _ptr(dy),
                                    ctypes.byref(dxd) if dxd is not None else None, _ptr(dx), _ptr(dwt), _ptr(dbias), beta,
                                    _ptr(ws), ws.numel(), _stream()), "lamp_convtr3d_bwd")
@@ -342,8 +348,8 @@ def lamp_head_fwd(x, wh, bh, logits, xnorm=None):
 def lamp_head_ce(x, wh, bh, labels, loss, logits=None, dx=None, dwh=None, dbh=None, beta=0.0, xnorm=None, ws=None):
     xd = desc(x)
     dxd = desc(dx) if dx is not None else None
-    need = lib().lamp_head_ce_workspace_bytes(ctypes.byref(xd), wh.shape[0])
-    ws = ws if ws is not None else _ws(need, x.device)
+    if ws is None:
+        ws = _ws(lib().lamp_head_ce_workspace_bytes(ctypes.byref(xd), wh.shape[0]), x.device)
     _check(lib().lamp_head_ce(ctypes.byref(xd), _ptr(x), _norm(xnorm), _ptr(wh), _ptr(bh), wh.shape[0], _ptr(labels),
                               _ptr(logits), _ptr(loss), ctypes.byref(dxd) if dxd is not None else None, _ptr(dx), _ptr(dwh),
                               _ptr(dbh), beta, _ptr(ws), ws.numel(), _stream()), "lamp_head_ce")
@@ -434,7 +440,7 @@ def lamp_unet_pipeline_fwd_bwd(ud, cut, micro_batches, params, x, labels, loss, 
     ws = ws if ws is not None else _ws(lamp_unet_pipeline_workspace_bytes(ud, cut, micro_batches), x.device)
     _check(lib().lamp_unet_pipeline_fwd_bwd(ctypes.byref(ud), cut, micro_batches, _ptr_table(params), _ptr(x), _ptr(labels),
                                             _ptr(logits), _ptr(loss), _ptr_table(grads), beta, _ptr(ws), ws.numel(),
-                                            _stream(), c_void_p(aux_stream.cuda_stream)), "lamp_unet_pipeline_fwd_bwd")
+                                            _stream(), aux_stream.cuda_stream), "lamp_unet_pipeline_fwd_bwd")
     return loss
 
 
@@ -444,8 +450,8 @@ def lamp_sliding_window_count(D, H, W, patch, overlap=0.25):
 
 def lamp_sliding_window_fwd(patch_ud, params, vol, out, overlap=0.25, sigma_scale=0.125, ws=None):
     _, D, H, W, _ = vol.shape
-    need = lib().lamp_sliding_window_workspace_bytes(ctypes.byref(patch_ud), D, H, W)
-    ws = ws if ws is not None else _ws(need, vol.device)
+    if ws is None:
+        ws = _ws(lib().lamp_sliding_window_workspace_bytes(ctypes.byref(patch_ud), D, H, W), vol.device)
     _check(lib().lamp_sliding_window_fwd(ctypes.byref(patch_ud), _ptr_table(params), _ptr(vol), D, H, W, overlap,
                                          sigma_scale, _ptr(out), _ptr(ws), ws.numel(), _stream()), "lamp_sliding_window_fwd")
     return out
