@@ -45,11 +45,19 @@ static TileGeo pick_tile(int D, int H, int W, int vox, int halo) {
 // and the matrix unit adds its four products one after the other, each rounded: channels in chunks of 8, in a chunk the taps, in a tap
 // the channels -- bit for bit the sums of a thread that does so with fused multiply-adds (a chunk of 16 is walked as two of 8).
 // LDS voxel entries are padded (80, 48, 16 bytes) so that the 64 words of a fragment read fall on different banks.  32->32 on
-// 41 x 56 x 47 with the statistics: 430 -> 77 us (77 TFLOP/s; of 462 tiles a CU gets one or two, which alone is 12 %), data gradient
-// 385 -> 71 us, against scalar multiply-adds and a separate statistics pass; 16->8 on 2 x 64 x 48 x 80: 85 us, 8->8 46 us.
+// 41 x 56 x 47 with the statistics: 430 -> 73 us (82 TFLOP/s; of 462 tiles a CU gets one or two, which alone is 12 %), data gradient
+// 385 -> 73 us, against scalar multiply-adds and a separate statistics pass; 8->8 on 2 x 64 x 48 x 80: 46 us.
 // MAXK: halo pieces (4 channels of a voxel) a thread stages at most.
+// CF: 1 to 3 input channels, forward: a product contracts 4 consecutive (tap, channel) pairs, whatever tap they belong to -- the same
+// order, ceil(27 CF / 4) products instead of 27 with the channels padded to 4.  A lane's pair differs from product to product by more
+// than an immediate, so the offsets sit in registers.  2->16 bf16 on 2 x 64 x 80 x 96: 50 -> 38 us.
+// FAST: fp32 with whole 16-byte pieces and whole chunks of input channels.  Loads without a branch: a piece outside the volume comes
+// from 16 zero bytes, weights past the last output channel from the last ones (their rows are not stored).  A branch to every piece is
+// most of what a workgroup with one wave a SIMD does between two chunks (32->96 on 9 x 9 x 22, data gradient: 27 -> 22 us; one or two
+// chunks 10.0 -> 9.5).
 struct F32ConvArgs {
     const void* x; const void* w; const float* bias; void* z;   // storage type of the instantiation
+    const void* zero16;                // 16 zero bytes (FAST)
     float* partial; int32_t* counts;   // [N][tiles][Co][2], [tiles]; nullptr: no statistics
     NormIn nm;
     int ldx, ldz, N, D, H, W, Ci, Co;
@@ -59,6 +67,7 @@ struct F32ConvArgs {
     uint32_t mHW, mHH; int sHW, sHH;   // division by the halo's sides
 };
 
+__host__ __device__ constexpr int f32_flat(int cf) { return (27 * cf + 3) / 4; }
 __host__ __device__ constexpr int f32_est(int kc) { return kc == 16 ? 20 : kc == 8 ? 12 : 4; }
 // sum over the 16 lanes of a row
 __device__ __forceinline__ float row_sum16(float v) {
@@ -69,10 +78,12 @@ __device__ __forceinline__ float row_sum16(float v) {
     return v;
 }
 
-template <typename T, int KC, int CB, int VB, int MAXK, bool DGRAD>
+template <typename T, int KC, int CB, int VB, int MAXK, bool DGRAD, int CF = 0, bool FAST = false>
 __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32ConvArgs a) {
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
-    constexpr int EST = f32_est(KC), QE = KC / 4, KL = QE < 2 ? QE : 2, MAXW = (27 * QE * 16 * CB + 255) / 256;
+    static_assert(!CF || (KC == 4 && !DGRAD), "the forward pass of narrow inputs");
+    constexpr int NJ = CF ? f32_flat(CF) : 27;   // products of a quad of channels
+    constexpr int EST = CF ? CF : f32_est(KC), QE = KC / 4, KL = QE < 2 ? QE : 2, MAXW = (NJ * QE * 16 * CB + 255) / 256;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, l16 = lane & 15, g = lane >> 4;
     const int TD = 1 << a.t.ld, TH = 1 << a.t.lh, TW = 1 << a.t.lw;
     const int HH = TH + 2, HW = TW + 2, HV = (TD + 2) * HH * HW;
@@ -80,7 +91,7 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
     const int co0 = blockIdx.y * (16 * CB);
     float* st = f32_lds;                // [4][16 * CB][2]
     float* ws = f32_lds + 128 * CB;     // [27][CB][QE][16 channels out][4 channels in]
-    float* xs = ws + 27 * CB * 64 * QE; // [HV][EST]
+    float* xs = ws + NJ * CB * 64 * QE; // [HV][EST]
 
     // the halo pieces this thread stages: coordinates in the halo
     const int quad = tid & (QE - 1);
@@ -92,7 +103,8 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
         const uint32_t hd = (uint32_t)(((uint64_t)row * a.mHH) >> a.sHH), hh = row - hd * HH;
         hc[k] = (int)e < HV ? (int)(hd << 20 | hh << 10 | hw) : 1 << 30;
     }
-    float4 px[MAXK], pw[MAXW];
+    f32x4 px[MAXK], pw[MAXW];   // (vectors: a float4 is taken apart and put together again behind a wait for every load;
+                                      // 32->32 on 41 x 56 x 47, whole kernel: 80 -> 74 us)
     uint32_t pin = 0;   // pieces inside the volume (the padding is zero behind the normalisation)
     // once per tile: which pieces lie inside the volume, and where
     int vo[MAXK];
@@ -120,16 +132,20 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
         const int left = a.Ci - c0 - 4 * quad;
 #pragma unroll
         for (int k = 0; k < MAXK; ++k) {
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (pin >> k & 1) {
+            f32x4 q = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (FAST) {
+                const T* p = xt + ((int64_t)vo[k] * a.ldx + c0);
+                p = pin >> k & 1 ? p : reinterpret_cast<const T*>(a.zero16);
+                q = *reinterpret_cast<const f32x4*>(p);
+            } else if (pin >> k & 1) {
                 const T* p = xt + ((int64_t)vo[k] * a.ldx + c0);
                 if (sizeof(T) == 4 && a.xvec) {
-                    if (left > 0) q = *reinterpret_cast<const float4*>(p);
+                    if (left > 0) q = *reinterpret_cast<const f32x4*>(p);
                 } else {
-                    if (left > 0) q.x = io<T>::ld(p);
-                    if (left > 1) q.y = io<T>::ld(p + 1);
-                    if (left > 2) q.z = io<T>::ld(p + 2);
-                    if (left > 3) q.w = io<T>::ld(p + 3);
+                    if (left > 0) q[0] = io<T>::ld(p);
+                    if (left > 1) q[1] = io<T>::ld(p + 1);
+                    if (left > 2) q[2] = io<T>::ld(p + 2);
+                    if (left > 3) q[3] = io<T>::ld(p + 3);
                 }
             }
             px[k] = q;
@@ -146,9 +162,8 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
 #pragma unroll
                 for (int k = 0; k < MAXK; ++k)
                     if (pin >> k & 1) {
-                        float& v = j == 0 ? px[k].x : j == 1 ? px[k].y : j == 2 ? px[k].z : px[k].w;
-                        const float u = norm_u(v, na, nb);
-                        v = io<T>::rnd(!a.nm.relu || u > 0.f ? u : 0.f);
+                        const float u = norm_u(px[k][j], na, nb);
+                        px[k][j] = io<T>::rnd(!a.nm.relu || u > 0.f ? u : 0.f);
                     }
             }
         }
@@ -156,7 +171,14 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
         asm volatile("" : "+v"(ti));
 #pragma unroll
         for (int k = 0; k < MAXK; ++k)
-            if (hc[k] < 1 << 30) *reinterpret_cast<float4*>(xs + (ti + 256 * k) / QE * EST + 4 * quad) = px[k];
+            if (hc[k] < 1 << 30) {
+                float* o = xs + (ti + 256 * k) / QE * EST + 4 * quad;
+                if constexpr (CF) {
+                    o[0] = px[k][0];
+                    if constexpr (CF > 1) o[1] = px[k][1];
+                    if constexpr (CF > 2) o[2] = px[k][2];
+                } else *reinterpret_cast<f32x4*>(o) = px[k];
+            }
     };
     // Weight pieces of 4 floats along the contiguous index, the other channel fastest over the lanes (whole LDS rows, and 16 or more
     // lanes of a line): forward W[co][t][ci..], data gradient W[ci][26 - t][co..].  A thread's pieces differ in the tap only, by TS.
@@ -164,39 +186,70 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
     const int wk = DGRAD ? tid % KC : tid / 16 % QE * 4, wc = DGRAD ? tid / KC % (4 * CB) * 4 : tid % 16 + tid / (16 * QE) % CB * 16;
     const int wt0 = tid / (16 * QE * CB);
     const T* wp = DGRAD ? aw + ((int64_t)wk * 27 + (26 - wt0)) * a.Co + co0 + wc : aw + ((int64_t)(co0 + wc) * 27 + wt0) * a.Ci + wk;
+    const T* const wf0 = DGRAD ? aw + ((int64_t)wk * 27 + (26 - wt0)) * a.Co + min(co0 + wc, a.Co - 4)
+                               : aw + ((int64_t)min(co0 + wc, a.Co - 1) * 27 + wt0) * a.Ci + wk;   // FAST
     auto fetch_w = [&](int c0) __attribute__((always_inline)) {
+        if constexpr (CF) {   // W[co][27 * CF]: four consecutive pairs of a row
+#pragma unroll
+            for (int u = 0; u < MAXW; ++u) {
+                const int e = tid + 256 * u, co = co0 + e % (16 * CB), k = e / (16 * CB) * 4, left = co < a.Co ? 27 * CF - k : 0;
+                const T* p = aw + (int64_t)co * (27 * CF) + k;
+                f32x4 q = {0.f, 0.f, 0.f, 0.f};
+                if (left > 0) q[0] = io<T>::ld(p);
+                if (left > 1) q[1] = io<T>::ld(p + 1);
+                if (left > 2) q[2] = io<T>::ld(p + 2);
+                if (left > 3) q[3] = io<T>::ld(p + 3);
+                pw[u] = q;
+            }
+            return;
+        }
+        if constexpr (FAST) {
+            const T* p = wf0 + (DGRAD ? (int64_t)c0 * 27 * a.Co : (int64_t)c0);
+#pragma unroll
+            for (int u = 0; u < MAXW; ++u) {
+                const int dt = u < MAXW - 1 || wt0 + u * TS < 27 ? u * TS : 0;
+                pw[u] = *reinterpret_cast<const f32x4*>(p + (DGRAD ? -(int64_t)dt * a.Co : (int64_t)dt * a.Ci));
+            }
+            return;
+        }
         const int left = DGRAD ? a.Co - co0 - wc : a.Ci - c0 - wk;   // elements of the row from the piece's first on
         const bool on = left > 0 && (DGRAD ? c0 + wk < a.Ci : co0 + wc < a.Co);
         const T* p = wp + (DGRAD ? (int64_t)c0 * 27 * a.Co : (int64_t)c0);
         const int64_t step = DGRAD ? -(int64_t)TS * a.Co : (int64_t)TS * a.Ci;
 #pragma unroll
         for (int u = 0; u < MAXW; ++u) {
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            f32x4 q = {0.f, 0.f, 0.f, 0.f};
             if (on && wt0 + u * TS < 27) {
-                if (sizeof(T) == 4 && a.wvec) q = *reinterpret_cast<const float4*>(p + u * step);
+                if (sizeof(T) == 4 && a.wvec) q = *reinterpret_cast<const f32x4*>(p + u * step);
                 else {
-                    q.x = io<T>::ld(p + u * step);
-                    if (left > 1) q.y = io<T>::ld(p + u * step + 1);
-                    if (left > 2) q.z = io<T>::ld(p + u * step + 2);
-                    if (left > 3) q.w = io<T>::ld(p + u * step + 3);
+                    q[0] = io<T>::ld(p + u * step);
+                    if (left > 1) q[1] = io<T>::ld(p + u * step + 1);
+                    if (left > 2) q[2] = io<T>::ld(p + u * step + 2);
+                    if (left > 3) q[3] = io<T>::ld(p + u * step + 3);
                 }
             }
             pw[u] = q;
         }
     };
     auto stage_w = [&]() __attribute__((always_inline)) {
+        if constexpr (CF) {
+#pragma unroll
+            for (int u = 0; u < MAXW; ++u)
+                if (tid + 256 * u < NJ * 16 * CB) reinterpret_cast<f32x4*>(ws)[tid + 256 * u] = pw[u];
+            return;
+        }
         float* o0 = ws + ((wt0 * CB + wc / 16) * QE + wk / 4) * 64 + wc % 16 * 4 + wk % 4;
 #pragma unroll
         for (int u = 0; u < MAXW; ++u) {
             if (wt0 + u * TS >= 27) continue;
             float* o = o0 + u * (TS * CB * QE * 64);
             if constexpr (DGRAD) {
-                o[0] = pw[u].x;
-                o[4] = pw[u].y;
-                o[8] = pw[u].z;
-                o[12] = pw[u].w;
+                o[0] = pw[u][0];
+                o[4] = pw[u][1];
+                o[8] = pw[u][2];
+                o[12] = pw[u][3];
             } else {
-                *reinterpret_cast<float4*>(o) = pw[u];
+                *reinterpret_cast<f32x4*>(o) = pw[u];
             }
         }
     };
@@ -206,7 +259,17 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
     for (int vb = 0; vb < VB; ++vb) {
         const int p = (wid * VB + vb) * 16 + l16;
         const int w = p & (TW - 1), h = (p >> a.t.lw) & (TH - 1), d = p >> (a.t.lw + a.t.lh);
-        base[vb] = ((d * HH + h) * HW + w) * EST + g;
+        base[vb] = ((d * HH + h) * HW + w) * EST + (CF ? 0 : g);
+    }
+    int ko[CF ? NJ : 1];   // where the lane's pair of every product lies
+    if constexpr (CF) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            int k = 4 * j + g;
+            k = k < 27 * CF ? k : 27 * CF - 1;
+            const int t = k / CF;
+            ko[j] = ((t / 9 * HH + t / 3 % 3) * HW + t % 3) * EST + k - t * CF;
+        }
     }
     const float* wl = ws + l16 * 4 + g;
     f32x4 acc[CB][VB];
@@ -237,17 +300,27 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
             stage_x(n, ch * KC);
             if (nchunks > 1 || tile == t0) stage_w();
             __syncthreads();
-            if (ch + 1 < nchunks) fetch_x((ch + 1) * KC);
-            else if (tile + 1 < t1) {
-                locate(tile + 1);
-                fetch_x(0);
+            const bool last = ch + 1 == nchunks;
+            if (last && tile + 1 < t1) locate(tile + 1);
+            if (!last || tile + 1 < t1) {   // (one call of each: the results of two meet behind a wait for the loads)
+                fetch_x(last ? 0 : (ch + 1) * KC);
+                if (nchunks > 1) fetch_w(last ? 0 : (ch + 1) * KC);
             }
-            if (nchunks > 1) fetch_w(ch + 1 < nchunks ? (ch + 1) * KC : 0);
             __builtin_amdgcn_sched_barrier(0);
             // every step's fragments are read one step ahead; a step is a tap of 8 (4) channels
-            constexpr int STEPS = 27 * QE / KL;
+            constexpr int STEPS = NJ * QE / KL;
             float wf[2][CB][KL], b[2][VB][KL];
             auto frags = [&](int i) __attribute__((always_inline)) {
+                if constexpr (CF) {
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) wf[i & 1][cb][0] = wl[(i * CB + cb) * 64];
+#pragma unroll
+                    for (int vb = 0; vb < VB; ++vb) {
+                        const float v = xs[base[vb] + ko[i]];
+                        b[i & 1][vb][0] = i + 1 < NJ || g < 27 * CF - 4 * (NJ - 1) ? v : 0.f;   // pairs past the last are zero
+                    }
+                    return;
+                }
                 const int t = i % 27, q0 = i / 27 * KL;
                 const int toff = ((t / 9 * HH + t / 3 % 3) * HW + t % 3) * EST + q0 * 4;
 #pragma unroll
@@ -345,7 +418,7 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
 }
 
 // Input channels per chunk (4, 8, 16), voxel blocks per wave (4, 2, 1), blocks of 16 output channels per workgroup (2, 1).
-struct F32Plan { int kc, vb, cb; TileGeo t; };
+struct F32Plan { int kc, vb, cb, cf; TileGeo t; };   // cf: CF of the forward pass
 static F32Plan f32_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
     F32Plan p;
     p.cb = zd->c > 16 ? 2 : 1;
@@ -357,6 +430,7 @@ static F32Plan f32_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) 
     if (p.vb == 1 && p.cb == 2 && blocks(64) < 256) p.cb = 1;
     // chunks of 16 where they are filled and registers and LDS hold them beside the weights
     p.kc = xd->c <= 4 ? 4 : p.cb == 1 && p.vb < 4 && xd->c % 16 == 0 ? 16 : 8;
+    p.cf = xd->c < 4 ? xd->c : 0;
     const int vox = p.vb * 64;
     p.t = pick_tile(zd->d, zd->h, zd->w, vox, p.vb == 4 ? 648 : p.vb == 2 ? 432 : 256);
     return p;
@@ -378,15 +452,16 @@ bool f32_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) 
            (int64_t)zd->h * zd->w * 18 < ((int64_t)1 << 31);
 }
 
-static size_t f32_lds_bytes(const F32Plan& p) {
+static size_t f32_lds_bytes(const F32Plan& p, bool flat) {
     const int hv = ((1 << p.t.ld) + 2) * ((1 << p.t.lh) + 2) * ((1 << p.t.lw) + 2);
+    if (flat) return ((size_t)hv * p.cf + (size_t)f32_flat(p.cf) * p.cb * 64 + 128 * p.cb) * sizeof(float);
     return ((size_t)hv * f32_est(p.kc) + (size_t)27 * p.cb * 16 * p.kc + 128 * p.cb) * sizeof(float);
 }
-template <typename T, int KC, bool DGRAD>
+template <typename T, int KC, bool DGRAD, int CF = 0, bool FAST = false>
 static void f32_launch(const F32Plan& p, dim3 grid, hipStream_t s, const F32ConvArgs& a) {
     constexpr int Q = KC / 4;
-    const size_t lds = f32_lds_bytes(p);
-#define LAMP_F32(CB, VB, MK) hipLaunchKernelGGL((conv3d_f32_kernel<T, KC, CB, VB, MK, DGRAD>), grid, dim3(256), lds, s, a)
+    const size_t lds = f32_lds_bytes(p, CF != 0);
+#define LAMP_F32(CB, VB, MK) hipLaunchKernelGGL((conv3d_f32_kernel<T, KC, CB, VB, MK, DGRAD, CF, FAST>), grid, dim3(256), lds, s, a)
     constexpr int M4 = (648 * Q + 255) / 256, M2 = (432 * Q + 255) / 256, M1 = (256 * Q + 255) / 256;
     if constexpr (KC < 16)
         if (p.cb == 2) {
@@ -612,14 +687,29 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
         }
     }
     const dim3 grid((unsigned)((a.ntiles + a.per - 1) / a.per), cols);
-    if (dgrad) {
+    const bool fast = xd->dtype == LAMP_F32 && p.kc > 4 && a.xvec && a.wvec && xd->c % p.kc == 0 && zd->c >= 4;
+    a.zero16 = fast ? device_zero16(s) : nullptr;
+    if (fast && !a.zero16) return LAMP_ERR_HIP;
+    if (fast) {
+        if (dgrad) {
+            if (p.kc == 16) f32_launch<float, 16, true, 0, true>(p, grid, s, a);
+            else f32_launch<float, 8, true, 0, true>(p, grid, s, a);
+        } else if (p.kc == 16) f32_launch<float, 16, false, 0, true>(p, grid, s, a);
+        else f32_launch<float, 8, false, 0, true>(p, grid, s, a);
+    } else if (dgrad) {
         if (p.kc == 16) f32_launch<float, 16, true>(p, grid, s, a);
         else if (p.kc == 8) f32_launch<float, 8, true>(p, grid, s, a);
         else f32_launch<float, 4, true>(p, grid, s, a);
     } else {
         if (p.kc == 16) f32_launch<float, 16, false>(p, grid, s, a);
         else if (p.kc == 8) f32_launch<float, 8, false>(p, grid, s, a);
-        else if (xd->dtype == LAMP_F32) f32_launch<float, 4, false>(p, grid, s, a);
+        else if (xd->dtype == LAMP_F32) {
+            if (p.cf == 1) f32_launch<float, 4, false, 1>(p, grid, s, a);
+            else if (p.cf == 2) f32_launch<float, 4, false, 2>(p, grid, s, a);
+            else if (p.cf == 3) f32_launch<float, 4, false, 3>(p, grid, s, a);
+            else f32_launch<float, 4, false>(p, grid, s, a);
+        } else if (p.cf == 2) f32_launch<bf16_t, 4, false, 2>(p, grid, s, a);
+        else if (p.cf == 3) f32_launch<bf16_t, 4, false, 3>(p, grid, s, a);
         else f32_launch<bf16_t, 4, false>(p, grid, s, a);
     }
     LAMP_CHECK_LAUNCH();
@@ -637,8 +727,8 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
 // to the sum of those before them: the walks grow with the volume, and a single chain over them would round like sqrt(walk) (8->8 on
 // 2 x 128^3, walks of 4096 voxels: relative error 8.9e-7 in one chain, 1.9e-7 so, 3.8e-7 with a thread per weight over 864 voxels).
 // 16-channel slabs of 32 outputs keep half of these sums in LDS, where each thread has its own slots: all of them in registers spill
-// (32->32 on 41 x 56 x 47: 98 -> 106 us, with the slots 100).  With the reduction 32->32 on 41 x 56 x 47: 2450 -> 93 us against a
-// thread per weight; 16->8 on 2 x 64 x 48 x 80: 110 us.
+// (32->32 on 41 x 56 x 47: 98 -> 106 us, with the slots 100).  With the reduction 32->32 on 41 x 56 x 47: 2450 -> 87 us against a
+// thread per weight; 8->8 on 2 x 64 x 48 x 80: 50 us.
 struct F32WgradArgs {
     const float* x; const float* dz; float* part;   // part [splits * VG][Co][27][Ci]
     NormIn nm;
@@ -661,7 +751,7 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
     constexpr int MX = (F32W_HALO * QE + 255) / 256, MZ = F32W_VOX * CBO * 4 / 256;
     constexpr bool LS = CIC * CBO == 32;   // half of the sums in LDS
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, l16 = lane & 15, g = lane >> 4;
-    const int cg = wid % CG, vg = wid / CG;
+    const int cg = wid % CG, vg = wid / CG, vgu = __builtin_amdgcn_readfirstlane(vg);
     const int ci0 = (blockIdx.y / a.cochunks) * CIC, co0 = (blockIdx.y % a.cochunks) * (16 * CBO);
     const int TH = 1 << a.t.lh, TW = 1 << a.t.lw, TD = 1 << a.t.ld;
     const int HH = TH + 2, HW = TW + 2, HV = (TD + 2) * HH * HW;
@@ -706,7 +796,7 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
             else sum[cb][i] = acc[cb][i];
         }
 
-    float4 px[MX], pz[MZ];
+    f32x4 px[MX], pz[MZ];
     uint32_t pin = 0;   // halo pieces inside the volume (the padding is zero behind the normalisation)
     int pn = 0;         // their sample
     const int tiles = a.t.nd * a.t.nh * a.t.nw;
@@ -720,36 +810,36 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
         pn = n;
 #pragma unroll
         for (int k = 0; k < MX; ++k) {
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            f32x4 q = {0.f, 0.f, 0.f, 0.f};
             const int c = ci0 + xq;
             if (xc[k] < 1 << 30 && (unsigned)(d0 - 1 + (xc[k] >> 20)) < (unsigned)a.D &&
                 (unsigned)(h0 - 1 + (xc[k] >> 10 & 1023)) < (unsigned)a.H && (unsigned)(w0 - 1 + (xc[k] & 1023)) < (unsigned)a.W) {
                 pin |= 1u << k;
                 const float* p = a.x + (org + xo[k]) * a.ldx + c;
                 if (a.xvec) {
-                    if (c < a.Ci) q = *reinterpret_cast<const float4*>(p);
+                    if (c < a.Ci) q = *reinterpret_cast<const f32x4*>(p);
                 } else {
-                    if (c < a.Ci) q.x = p[0];
-                    if (xq + 1 < CIC && c + 1 < a.Ci) q.y = p[1];
-                    if (xq + 2 < CIC && c + 2 < a.Ci) q.z = p[2];
-                    if (xq + 3 < CIC && c + 3 < a.Ci) q.w = p[3];
+                    if (c < a.Ci) q[0] = p[0];
+                    if (xq + 1 < CIC && c + 1 < a.Ci) q[1] = p[1];
+                    if (xq + 2 < CIC && c + 2 < a.Ci) q[2] = p[2];
+                    if (xq + 3 < CIC && c + 3 < a.Ci) q[3] = p[3];
                 }
             }
             px[k] = q;
         }
 #pragma unroll
         for (int k = 0; k < MZ; ++k) {
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            f32x4 q = {0.f, 0.f, 0.f, 0.f};
             const int c = co0 + zq;
             if (d0 + (zc[k] >> 20) < a.D && h0 + (zc[k] >> 10 & 1023) < a.H && w0 + (zc[k] & 1023) < a.W) {
                 const float* p = a.dz + (org + zo[k]) * a.lddz + c;
                 if (a.zvec) {
-                    if (c < a.Co) q = *reinterpret_cast<const float4*>(p);
+                    if (c < a.Co) q = *reinterpret_cast<const f32x4*>(p);
                 } else {
-                    if (c < a.Co) q.x = p[0];
-                    if (c + 1 < a.Co) q.y = p[1];
-                    if (c + 2 < a.Co) q.z = p[2];
-                    if (c + 3 < a.Co) q.w = p[3];
+                    if (c < a.Co) q[0] = p[0];
+                    if (c + 1 < a.Co) q[1] = p[1];
+                    if (c + 2 < a.Co) q[2] = p[2];
+                    if (c + 3 < a.Co) q[3] = p[3];
                 }
             }
             pz[k] = q;
@@ -766,19 +856,18 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
 #pragma unroll
                 for (int k = 0; k < MX; ++k)
                     if (pin >> k & 1) {
-                        float& v = j == 0 ? px[k].x : j == 1 ? px[k].y : j == 2 ? px[k].z : px[k].w;
-                        const float u = norm_u(v, na, nb);
-                        v = !a.nm.relu || u > 0.f ? u : 0.f;
+                        const float u = norm_u(px[k][j], na, nb);
+                        px[k][j] = !a.nm.relu || u > 0.f ? u : 0.f;
                     }
             }
         }
 #pragma unroll
         for (int k = 0; k < MX; ++k)
-            if (xc[k] < 1 << 30) *reinterpret_cast<float4*>(xs + (tid + 256 * k) / QE * CS + xq) = px[k];
+            if (xc[k] < 1 << 30) *reinterpret_cast<f32x4*>(xs + (tid + 256 * k) / QE * CS + xq) = px[k];
 #pragma unroll
         for (int k = 0; k < MZ; ++k) {
             const int p = (tid + 256 * k) / (CBO * 4);
-            *reinterpret_cast<float4*>(zs + ((zq >> 4) * F32W_VOX + p) * 16 + (zq & 15)) = pz[k];
+            *reinterpret_cast<f32x4*>(zs + ((zq >> 4) * F32W_VOX + p) * 16 + (zq & 15)) = pz[k];
         }
     };
 
@@ -800,21 +889,25 @@ __global__ __launch_bounds__(256, 2) void conv3d_wgrad_f32_kernel(F32WgradArgs a
 #pragma unroll
             for (int i = 0; i < NBW; ++i) fb[i] = xs[col[i] + off];
         };
-        float fa[CBO], fb[NBW];
-        frags(vg, fa, fb);
-        for (int ks = vg; ks < F32W_VOX / 4; ks += VG) {
-            float ga[CBO], gb[NBW];
-            const int nx = ks + VG < F32W_VOX / 4 ? ks + VG : ks;   // the last step reads its own again
-            frags(nx, ga, gb);
-            if constexpr (LS) __builtin_amdgcn_sched_barrier(0);   // the reads stay in front of the multiplies, also where registers are short
+        // two register sets by turns, reads in front of the multiplies they do not belong to: with one set and copies, each copy waited
+        // for its read between the multiplies (32->32 on 41 x 56 x 47: 94 -> 81 us; 8->8 on 2 x 64 x 48 x 80: 59 -> 50)
+        constexpr int NK = F32W_VOX / 4 / VG;
+        float fa[2][CBO], fb[2][NBW];
+        auto mul = [&](const float (&fa)[CBO], const float (&fb)[NBW]) __attribute__((always_inline)) {
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < NBW; ++i)
 #pragma unroll
                 for (int cb = 0; cb < CBO; ++cb) acc[cb][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[cb], fb[i], acc[cb][i], 0, 0, 0);
-#pragma unroll
-            for (int cb = 0; cb < CBO; ++cb) fa[cb] = ga[cb];
-#pragma unroll
-            for (int i = 0; i < NBW; ++i) fb[i] = gb[i];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        frags(vgu, fa[0], fb[0]);
+#pragma unroll 1
+        for (int k = 0; k < NK; k += 2) {
+            frags(vgu + (k + 1) * VG, fa[1], fb[1]);
+            mul(fa[0], fb[0]);
+            if (k + 2 < NK) frags(vgu + (k + 2) * VG, fa[0], fb[0]);
+            mul(fa[1], fb[1]);
         }
         if (((t - t0) & (VG - 1)) == VG - 1 && t + 1 < t1) {
 #pragma unroll
