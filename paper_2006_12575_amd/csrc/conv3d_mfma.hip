@@ -153,14 +153,14 @@ struct ConvArgs {
     int N, D, H, W, Cin, Cout;
     int tiles_d, tiles_h, tiles_w, tiles_per_n, tiles_total, tiles_per_xcd;
     float* zpart;       // split reduction only: [splits][N*D*H*W][Cout] fp32 partial outputs
-    int cps;            // split reduction only: 16-channel input chunks per split (grid z = split)
+    int cps;            // split reduction only: 16-channel input chunks per split 
     // Two-part tensors (a concat that is never materialised).  Input: the 16-channel chunks from xsplit on
     // are read from x + xdelta (an element offset to the second tensor, same channel stride).  Output:
     // channels from zsplit on go to z2 (channel stride ldz2), counted from its channel 0.
     int64_t xdelta; int xsplit;
     bf16_t* z2; int ldz2, zsplit;
     // With very few tiles only the first XCD ranges hold work, and a workgroup's XCD is its flattened id
-    // modulo 8 = blockIdx.x & 7: rotating the range a workgroup serves by its channel-block / split index
+    // modulo 8 = blockIdx.x & 7: rotating the range a workgroup serves by its channel-block index
     // spreads the channel blocks of those few tiles over all eight XCDs.
     int xcd_rot;
     // Output-channel blocks inside a one-dimensional grid: workgroup id = (walker * cb_inner + channel block) * 8 + XCD,
@@ -524,7 +524,7 @@ __device__ __forceinline__ void conv_group(f32x16 (&acc)[COB][Geo<TDT>::ND], Fra
     column<COB, TDT, G, 2, PAR, GN, NORM>(acc, f, hb, wb, hbn, wbn, boff, c, hl, ht, wrel);
 }
 
-// SPLIT: the input-channel chunks are divided among gridDim.z workgroups per tile, each of which
+// SPLIT: the input-channel chunks are divided among several workgroups per tile, each of which
 // writes its fp32 partial sums; a second kernel adds them in a fixed order.  For small volumes with
 // many channels, where the tiles alone cannot fill the chip.
 // RAG: channel counts that are multiples of 8 but not of 16 (input) or 32 (output).  The weights are padded with zero rows and
@@ -548,11 +548,17 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
     const uint32_t tab_a = lds_a + LD::TAB_OFF;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int l32 = lane & 31, half = lane >> 5;
-    const int cbi = a.cb_inner ? (int)(blockIdx.x >> 3) % a.cb_inner : (int)blockIdx.y;   // output-channel block
+    // SPLIT: one (split, channel block, tile) to a workgroup, in this order, an eighth of them to each XCD: what an XCD's workgroups read
+    // is then few weights (and one split's channels of x), which its L2 fetches once.  With the tiles dealt to the XCDs every L2 fetched
+    // all the weights (512->512 on 2 x 8^3: 44 -> 26 us; 256->256 on 2 x 16^3: 33 -> 31).
+    const int item = SPLIT ? (int)(blockIdx.x & 7) * a.tiles_per_xcd + (int)(blockIdx.x >> 3) : 0;
+    const int combo = SPLIT ? item / a.tiles_total : 0, split = SPLIT ? combo / (a.Cout >> 6) : 0;
+    const int cbi = SPLIT ? combo - split * (a.Cout >> 6) : a.cb_inner ? (int)(blockIdx.x >> 3) % a.cb_inner : (int)blockIdx.y;   // output-channel block
     const int co0 = cbi * (32 * COB);
     const int nchunks = RAG ? (a.Cin + 15) >> 4 : a.Cin >> 4;
     auto tail = [&](int chunk) { return RAG && chunk * 16 + 8 >= a.Cin; };   // the chunk's upper 8 channels do not exist
-    const int c_lo = SPLIT ? (int)blockIdx.z * a.cps : 0;
+    const int c_lo = SPLIT ? split * a.cps : 0;
+    if (SPLIT && c_lo >= nchunks) return;   // past the last split
     const int c_hi = SPLIT ? min(c_lo + a.cps, nchunks) : nchunks;
     // element offset of a 16-channel chunk from channel 0 of the (first) input tensor
     auto choff = [&](int chunk) -> int64_t {
@@ -563,11 +569,11 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
     constexpr int WINSTR = 18 * WROWS / 64;       // wave-wide copies per kd group: 18 or 9
 
     // persistent walk over an XCD-contiguous range of tiles
-    const int xcd = (blockIdx.x + (a.xcd_rot ? blockIdx.y + blockIdx.z : 0u)) & 7;
-    const int local = a.cb_inner ? (int)(blockIdx.x >> 3) / a.cb_inner : (int)(blockIdx.x >> 3);
-    const int wg_per_xcd = a.cb_inner ? (int)(gridDim.x >> 3) / a.cb_inner : (int)(gridDim.x >> 3);
-    const int tile_lo = xcd * a.tiles_per_xcd;
-    const int tile_hi = min(tile_lo + a.tiles_per_xcd, a.tiles_total);
+    const int xcd = (blockIdx.x + (a.xcd_rot ? blockIdx.y : 0u)) & 7;
+    const int local = SPLIT ? 0 : a.cb_inner ? (int)(blockIdx.x >> 3) / a.cb_inner : (int)(blockIdx.x >> 3);
+    const int wg_per_xcd = SPLIT ? 1 : a.cb_inner ? (int)(gridDim.x >> 3) / a.cb_inner : (int)(gridDim.x >> 3);
+    const int tile_lo = SPLIT ? item - combo * a.tiles_total : xcd * a.tiles_per_xcd;
+    const int tile_hi = SPLIT ? tile_lo + 1 : min(tile_lo + a.tiles_per_xcd, a.tiles_total);
 
     // ---- lane -> voxel of a 32-voxel block (2 h-rows x 16 w).  A 16-byte LDS read runs at full rate when the 16
     // lanes served together -- the 8-lane groups {0-7,24-31}, then {8-15,16-23}, and the same in the upper half --
@@ -811,8 +817,8 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
             // fp32 partial sums straight from the accumulators: lane = voxel (bh, bw) of block vb, four
             // consecutive channels per register group
             static_assert(TDT == 4, "the split reduction uses the 4-deep tile");
-            float* zp = a.zpart + (int64_t)blockIdx.z * ((int64_t)a.N * a.D * a.H * a.W) * a.Cout;
-            if (a.bias && blockIdx.z == 0) {   // the first split's partial carries the bias
+            float* zp = a.zpart + (int64_t)split * ((int64_t)a.N * a.D * a.H * a.W) * a.Cout;
+            if (a.bias && split == 0) {   // the first split's partial carries the bias
 #pragma unroll
                 for (int cb = 0; cb < COB; ++cb)
 #pragma unroll
@@ -1415,7 +1421,8 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
         if (!cv.ok()) return LAMP_ERR_WORKSPACE;
         a.cps = ((xd->c / 16) + S - 1) / S;
         a.part = nullptr; a.counts = nullptr;
-        grid.z = S;
+        a.tiles_per_xcd = cdiv((int64_t)a.tiles_total * (zd->c / 64) * S, 8);
+        grid = dim3(8 * a.tiles_per_xcd);
         lamp_status st = launch_igemm<2, 4, true>(a, grid, s);
         if (st != LAMP_OK) return st;
         return launch_splitk_reduce(a.zpart, S, zd, z, eps, stats_out, sws, stats_ws_bytes(zd), s, a.z2, a.ldz2, a.zsplit);

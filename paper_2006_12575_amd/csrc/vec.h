@@ -192,21 +192,23 @@ template <int NV, int VEC> __device__ __forceinline__ void unstash(float (&v)[NV
 // hands each to put(set, channel of the block, sum).  All 256 threads add: with only the first row lane's cthreads threads at
 // work, a 16-channel bf16 tensor left 2 threads a serial chain of 2048 LDS reads, which was 45 of the 60 us of its backward sums
 // (2 x 64 x 80 x 96 voxels).  `red`: NV * 256 * VEC floats, `part`: 256 floats.  A fixed order for a given cthreads.  A: double in the
-// backward sums, whose chunks are the longest: these are the largest addends of a partial and round most.
-template <typename A = float, int NV, int VEC, typename F>
+// backward sums, whose chunks are the longest: these are the largest addends of a partial and round most.  NT: threads of the block, of which the first 256 have sums.
+template <typename A = float, int NT = 256, int NV, int VEC, typename F>
 __device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthreads, int rl, float* red, float* part, F put) {
     const int tid = threadIdx.x, nc = cthreads * VEC, nout = NV * nc;
+    const bool on = NT == 256 || tid < 256;
+    if (on)
 #pragma unroll
-    for (int k = 0; k < NV; ++k)
+        for (int k = 0; k < NV; ++k)
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) red[k * (256 * VEC) + tid * VEC + i] = v[k][i];
+            for (int i = 0; i < VEC; ++i) red[k * (256 * VEC) + tid * VEC + i] = v[k][i];
     __syncthreads();
     if (nout <= 128) {   // several threads per sum, each a share of the rows, then the shares in order
         const int P = 256 / nout, o = tid % nout, p = tid / nout, k = o / nc, e = o - k * nc;
         A t = 0;
-        if (p < P)
+        if (on && p < P)
             for (int r = p; r < rl; r += P) t += (A)red[k * (256 * VEC) + r * nc + e];
-        part[tid] = (float)t;
+        if (on) part[tid] = (float)t;
         __syncthreads();
         if (tid < nout) {
             t = (A)part[tid];
@@ -214,7 +216,7 @@ __device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthrea
             put(k, e, (float)t);
         }
     } else {
-        for (int o = tid; o < nout; o += 256) {
+        for (int o = on ? tid : nout; o < nout; o += 256) {
             const int k = o / nc, e = o - k * nc;
             A t = 0;
             for (int r = 0; r < rl; ++r) t += (A)red[k * (256 * VEC) + r * nc + e];
