@@ -1029,10 +1029,10 @@ extern "C" lamp_status lamp_conv3d_dgrad_inorm_relu_bwd(const lamp_tensor_desc* 
         // the sums at the tail of the workspace, the data gradient's own workspace in front of them
         const size_t cb = mfma_bsum_ws_bytes(dzd, gd);
         float* sums = (float*)((char*)ws + cb);
-        ConvBsum bs{z, stats, gamma, beta, sums};
+        ConvBsum bs{z, stats, gamma, beta, nullptr, 0};
         st = mfma_conv_fwd(dzd, dz, w, true, gd, g, nullptr, 0.f, ws, cb, s, nullptr, nullptr, nullptr, &bs);
         if (st != LAMP_OK) return st;
-        return launch_inorm_bwd_apply(gd, g, zd, z, stats, gamma, beta, sums, dzbd, dzb, dgamma, dbeta, beta_acc, s);
+        return launch_inorm_bwd_apply(gd, g, zd, z, stats, gamma, beta, bs.partial, bs.parts, stats, sums, dzbd, dzb, dgamma, dbeta, beta_acc, s);
     }
     st = lamp_conv3d_dgrad(dzd, dz, w, gd, g, ws, ws_bytes, stream);
     if (st != LAMP_OK) return st;

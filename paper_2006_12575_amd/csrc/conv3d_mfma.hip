@@ -1315,7 +1315,7 @@ size_t mfma_bsum_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd
 lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void* w, bool dgrad,
                           const lamp_tensor_desc* zd, void* z, float* stats_out, float eps, void* ws, size_t ws_bytes,
                           hipStream_t s, const ConvParts* parts, const float* bias, const lamp_norm_in* xnorm,
-                          const ConvBsum* bsum, int wcin) {
+                          ConvBsum* bsum, int wcin) {
     if (!wcin) wcin = xd->c;
     const bool rag = conv_ragged(xd->c, zd->c);
     const bool two_in = parts && parts->x2, two_out = parts && parts->z2;
@@ -1437,7 +1437,9 @@ lamp_status mfma_conv_fwd(const lamp_tensor_desc* xd, const void* x, const void*
         if (TDT == 8) st = cob == 2 ? launch_igemm<2, 8, false, false, true>(a, grid, s) : launch_igemm<1, 8, false, false, true>(a, grid, s);
         else st = cob == 2 ? launch_igemm<2, 4, false, false, true>(a, grid, s) : launch_igemm<1, 4, false, false, true>(a, grid, s);
         if (st != LAMP_OK) return st;
-        return launch_bsum_finalize(part, tiles_per_n, zd->n, zd->c, bsum->stats, bsum->sums_out, s);
+        bsum->partial = part;
+        bsum->parts = tiles_per_n;
+        return LAMP_OK;
     }
     if (rag) {
         if (TDT == 8) st = cob == 2 ? launch_igemm<2, 8, false, false, false, true>(a, grid, s) : launch_igemm<1, 8, false, false, false, true>(a, grid, s);

@@ -449,27 +449,81 @@ __global__ __launch_bounds__(256) void inorm_bwd_finalize_kernel(const float* __
     }
 }
 
+// The sums of one sample from its partials, by every block of the apply pass for itself: tot[2 * C], fp64, a fixed order.  zstats as in
+// inorm_bwd_finalize_kernel.  Three barriers a 256 outputs; every thread of the block calls it.
+__device__ __forceinline__ void fold_parts(const float* __restrict__ partial, int parts, int n, int C, const float* __restrict__ zstats,
+                                           double* sh, float* tot) {
+    const int tid = threadIdx.x, nout = 2 * C;
+    const float* pp = partial + (size_t)n * parts * nout;
+    for (int o0 = 0; o0 < nout; o0 += 256) {
+        const int w = min(256, nout - o0), lanes = 256 / w, o = tid % w, p = tid / w;
+        double t = 0.0;
+        if (p < lanes) {
+            const float* q = pp + o0 + o;
+            int k = p;
+            for (; k + 7 * lanes < parts; k += 8 * lanes) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = q[(size_t)(k + u * lanes) * nout];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t += (double)v[u];
+            }
+            for (; k < parts; k += lanes) t += (double)q[(size_t)k * nout];
+        }
+        sh[tid] = t;
+        __syncthreads();
+        if (tid < w) {
+            for (int k = 1; k < lanes; ++k) t += sh[k * w + tid];
+            sh[tid] = t;
+        }
+        __syncthreads();
+        if (tid < w) {
+            const int c = (o0 + tid) >> 1;
+            if (zstats && (tid & 1)) t = (double)zstats[((size_t)n * C + c) * 2 + 1] * (t - (double)zstats[((size_t)n * C + c) * 2] * sh[tid - 1]);
+            tot[o0 + tid] = (float)t;
+        }
+        __syncthreads();
+    }
+}
+// Where every block of the apply pass folds the partials itself: at most 4 loads a thread, which are in flight together, in place of a
+// launch of 3 to 5 us (training step of the 4-level base-8 fp32 net on 24 x 32 x 40: 848 -> 824 us; conv unit 64->32 on 3 x 10 x 11 x 12:
+// 64.2 -> 61.6; with 16 loads no more, and several samples' sums folded by the block that writes dgamma and dbeta cost what they save).
+static constexpr int FOLD_C = 512;
+static bool fold_in_apply(int parts, int N, int C, int vec, bool grads) {
+    return vec > 1 && C <= FOLD_C && (int64_t)parts * C <= 512 && (N == 1 || !grads);
+}
+
 // Bound: HBM.  64 channels at 128^3, sums and apply (1.34 GB): 262 -> 214 us with non-temporal accesses (loads too: both inputs are
 // read for the last time here).
-template <typename T, int VEC, bool NT>
+// FOLD: `sums` holds partials ([N][parts][C][2]), see fold_parts.
+template <typename T, int VEC, bool NT, bool FOLD>
 __global__ __launch_bounds__(256) void inorm_bwd_apply_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z,
                                                               int ldz, T* __restrict__ dz, int ldo, int64_t V, int C,
                                                               int cthreads, int rl, const float* __restrict__ stats,
                                                               const float* __restrict__ gamma,
                                                               const float* __restrict__ beta,
                                                               const float* __restrict__ sums, float* __restrict__ dgamma,
-                                                              float* __restrict__ dbeta, float beta_acc) {
+                                                              float* __restrict__ dbeta, float beta_acc, int parts,
+                                                              const float* __restrict__ zstats) {
+    __shared__ double fsh[FOLD ? 256 : 1];
+    __shared__ float tot[FOLD ? 2 * FOLD_C : 1];
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
     const int n = blockIdx.y;
+    if constexpr (FOLD) {
+        fold_parts(sums, parts, n, C, zstats, fsh, tot);
+    }
     if (r0 >= rl || cv * VEC >= C) return;
-    if (blockIdx.x == 0 && n == 0 && r0 == 0) affine_grads<VEC>(sums, gridDim.y, C, cv * VEC, dgamma, dbeta, beta_acc);
+    if (blockIdx.x == 0 && n == 0 && r0 == 0) affine_grads<VEC>(FOLD ? tot : sums, gridDim.y, C, cv * VEC, dgamma, dbeta, beta_acc);
     NormIn nm{stats, gamma, beta, C, 1};
     float a[VEC], b[VEC], mean[VEC], rstd[VEC], c1[VEC], c2[VEC];
     const float invV = 1.0f / (float)V;
     float sm[2 * VEC];
-    ld_floats<2 * VEC>(sums + ((size_t)n * C + cv * VEC) * 2, sm);
+    if constexpr (FOLD)
+#pragma unroll
+        for (int i = 0; i < 2 * VEC; ++i) sm[i] = tot[cv * VEC * 2 + i];
+    else ld_floats<2 * VEC>(sums + ((size_t)n * C + cv * VEC) * 2, sm);
     norm_coeffs_vec<VEC>(nm, n, cv * VEC, a, b, mean, rstd);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
@@ -604,37 +658,32 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
         }
     });
     LAMP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(inorm_bwd_finalize_kernel, dim3(zd->c, zd->n), dim3(256), 0, s, partial, chunks, zd->c, sums,
-                       (const float*)nullptr);
-    LAMP_CHECK_LAUNCH();
-    return launch_inorm_bwd_apply(dyd, dy, zd, z, stats, gamma, beta, sums, dzd, dz, dgamma, dbeta, beta_acc, s);
-}
-
-lamp_status lamp::launch_bsum_finalize(const float* partial, int parts, int N, int C, const float* zstats, float* sums, hipStream_t s) {
-    hipLaunchKernelGGL(inorm_bwd_finalize_kernel, dim3(C, N), dim3(256), 0, s, partial, parts, C, sums, zstats);
-    LAMP_CHECK_LAUNCH();
-    return LAMP_OK;
+    return launch_inorm_bwd_apply(dyd, dy, zd, z, stats, gamma, beta, partial, chunks, nullptr, sums, dzd, dz, dgamma, dbeta, beta_acc, s);
 }
 
 lamp_status lamp::launch_inorm_bwd_apply(const lamp_tensor_desc* dyd, const void* dy, const lamp_tensor_desc* zd, const void* z,
-                                   const float* stats, const float* gamma, const float* beta, const float* sums,
-                                   const lamp_tensor_desc* dzd, void* dz, float* dgamma, float* dbeta, float beta_acc,
-                                   hipStream_t s) {
+                                   const float* stats, const float* gamma, const float* beta, const float* partial, int parts,
+                                   const float* zstats, float* sums, const lamp_tensor_desc* dzd, void* dz, float* dgamma, float* dbeta,
+                                   float beta_acc, hipStream_t s) {
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
     const int vec = pick_vec(zd->dtype, zd->c, {zd->ldc, dyd->ldc, dzd->ldc}, {z, dy, dz});
     const bool nt = beyond_cache(3 * nvox(zd) * zd->c * (int64_t)esize(zd->dtype));
+    const bool fold = !nt && fold_in_apply(parts, zd->n, zd->c, vec, dgamma || dbeta);
+    if (!fold) {
+        hipLaunchKernelGGL(inorm_bwd_finalize_kernel, dim3(zd->c, zd->n), dim3(256), 0, s, partial, parts, zd->c, sums, zstats);
+        LAMP_CHECK_LAUNCH();
+    }
+#define LAMP_APPLY(NT, FOLD) \
+    hipLaunchKernelGGL((inorm_bwd_apply_kernel<T, VEC, NT, FOLD>), dim3(apply_blocks(V, m.rl), zd->n, m.ctiles), dim3(256), 0, s, \
+                       (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, zd->c, m.cthreads, m.rl, stats, gamma, beta, \
+                       fold ? partial : sums, dgamma, dbeta, beta_acc, parts, zstats)
     LAMP_DISPATCH_TV(zd->dtype, vec, {
         RowMap m = make_rowmap(zd->c, VEC);
-        if (nt) {
-            hipLaunchKernelGGL((inorm_bwd_apply_kernel<T, VEC, true>), dim3(apply_blocks(V, m.rl), zd->n, m.ctiles), dim3(256), 0,
-                           s, (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, zd->c, m.cthreads,
-                           m.rl, stats, gamma, beta, sums, dgamma, dbeta, beta_acc);
-        } else {
-            hipLaunchKernelGGL((inorm_bwd_apply_kernel<T, VEC, false>), dim3(apply_blocks(V, m.rl), zd->n, m.ctiles), dim3(256), 0,
-                           s, (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, zd->c, m.cthreads,
-                           m.rl, stats, gamma, beta, sums, dgamma, dbeta, beta_acc);
-        }
+        if (nt) LAMP_APPLY(true, false);
+        else if (VEC > 1 && fold) LAMP_APPLY(false, (VEC > 1));
+        else LAMP_APPLY(false, false);
     });
+#undef LAMP_APPLY
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }

@@ -25,7 +25,8 @@ def slice_of(t, extra, off):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("shape,affine,extra,off", [((2, 5, 7, 9, 24), True, 0, 0), ((1, 13, 12, 11, 48), True, 8, 0), ((3, 4, 5, 6, 96), True, 0, 0),
                                                     ((2, 3, 5, 7, 8), True, 0, 0), ((1, 40, 41, 43, 16), False, 0, 0), ((2, 6, 7, 5, 12), True, 0, 1),
-                                                    ((1, 2, 2, 2, 40), True, 0, 0), ((2, 9, 8, 7, 72), False, 0, 3)], ids=str)
+                                                    ((1, 2, 2, 2, 40), True, 0, 0), ((2, 9, 8, 7, 72), False, 0, 3),
+                                                    ((2, 6, 5, 7, 64), False, 0, 0), ((1, 6, 5, 7, 256), True, 0, 0), ((3, 7, 8, 9, 8), False, 8, 0)], ids=str)
 def test_inorm_relu_rows(L, dtype, shape, affine, extra, off):
     g = torch.Generator(device="cuda").manual_seed(sum(shape) + extra)
     n, c = shape[0], shape[4]
