@@ -302,7 +302,8 @@ __global__ __launch_bounds__(256) void conv3d_cin1_fwd_tile_kernel(Cin1Args a) {
 // with the voxels as the reduction dimension.  Per step a wave multiplies A = dz^T (32 channels x 16
 // voxels of one W-row) by B = the gathered neighbours (16 voxels x 32 taps, taps 27..31 zero); both
 // fragments come straight from global memory (dz is read once, x is cache-resident).  Every wave
-// owns a run of 16-voxel groups and writes its own partial [Co][27] slab.
+// owns a run of 16-voxel groups and writes its own partial [Co][27] slab.  For what conv3d_narrow_wgrad_kernel leaves: voxels of dz
+// that do not start on 16 bytes, partials of its walks beyond 64 MB.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 struct U16x8 { unsigned short e[8]; };
@@ -845,9 +846,10 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const bf16_t* __res
 
 // ---- channel counts that are no multiple of 8 on the matrix-core kernels ---------------------------
 // The matrix-core kernels copy 16-byte pieces (8 channels).  An input with fewer channels than that, or whose voxels do
-// not start on 16 bytes -- a two- or four-channel image in front of a first layer -- is copied once into whole pieces with
-// zero channels behind the real ones: 16 bytes written per voxel and piece, against the 2 * C_out bytes that the conv
-// writes: for the data gradient and the weight gradient (weight gradient of 2->16 channels on 2 x 64 x 80 x 96 voxels: 1.2 ms -> 58 us).
+// not start on 16 bytes is copied once into whole pieces with zero channels behind the real ones: 16 bytes written per voxel and
+// piece, against the 2 * C_out bytes that the conv writes.  For the data gradient and the weight gradient; the weight gradient of 1
+// to 4 channels has a kernel without padding (conv3d_narrow_wgrad_kernel, 2->16 on 2 x 64 x 80 x 96 voxels: 25 us against 58) and
+// comes here only where that one's partials would pass 64 MB.
 // The forward pass keeps the scalar kernel's order of sums, on saturated image regions a sum that rounds the other way moves whole
 // regions over the ReLU: 2 to 4 channels on the fp32 matrix instruction (conv3d_f32.hip), 1 on kernels of its own, the rest, which are
 // no images, on the scalar kernels, where they always were.

@@ -445,7 +445,8 @@ size_t f32_conv_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd,
 }
 // The grid's limits, and 32-bit voxel offsets inside the halo of a tile.
 bool f32_conv_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* zd) {
-    // bf16: the forward pass of two to four input channels, in the order of the scalar kernel (whole unit 2->16: 716 -> 151 us)
+    // bf16: the forward pass of two to four input channels, in the order of the scalar kernel (whole unit 2->16: 716 -> 151 us,
+    // 111 with CF here and conv3d_narrow_wgrad_kernel in its backward)
     if (xd->dtype != LAMP_F32 && (xd->c < 2 || xd->c > 4 || zd->ldc % 4)) return false;
     const F32Plan p = f32_plan(xd, zd);
     return (int64_t)p.t.nd * p.t.nh * p.t.nw * zd->n < ((int64_t)1 << 31) && cdiv(zd->c, 16) <= 65535 &&

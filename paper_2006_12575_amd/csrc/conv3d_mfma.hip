@@ -1631,9 +1631,9 @@ __device__ __forceinline__ void wgrad_tile(f32x16 (&acc)[COB][4], WFrags<COB>& f
 
 // FOLD (channel counts outside the multiples of 32): a walk leaves its sums as a partial every `fold` tiles, so that a chain is as
 // long as in the thread-per-weight kernel that served these counts before (wgrad_splits: 256 voxels where 32 MB of partials allow
-// it), where one chain over a walk rounds more the larger the volume.  Relative error of 2->16 on 2 x 64 x 80 x 96: 7.9e-8 a thread
-// per weight, 3.2e-7 a chain per walk (55 us), 7.9e-8 with partials every three tiles (62 us); 48->96 on 83 x 61 x 97: 5.7e-7, 6.6e-7
-// (161 us), 4.5e-7 (164 us).  Up to 16 outputs use half of a block's accumulator rows, and the chains go to sums in fp64 for those
+// it), where one chain over a walk rounds more the larger the volume.  Relative error of 2->16 on 2 x 64 x 80 x 96 (padded
+// to 8, as 5 to 7 channels still are; 1 to 4 have conv3d_narrow_wgrad_kernel): 7.9e-8 a thread per weight, 3.2e-7 a chain per walk
+// (55 us), 7.9e-8 with partials every three tiles (62 us); 48->96 on 83 x 61 x 97: 5.7e-7, 6.6e-7 (161 us), 4.5e-7 (164 us).  Up to 16 outputs use half of a block's accumulator rows, and the chains go to sums in fp64 for those
 // (S64): a walk is one partial again (2->16: 7.6e-8, 58 us).
 template <int COB, bool FOLD, bool S64>
 __global__ __launch_bounds__(512) void conv3d_wgrad_kernel(WgradArgs a) {
