@@ -88,17 +88,22 @@ __global__ __launch_bounds__(256) void repack_weights_kernel(const bf16_t* __res
     repack_tile_gran(w, wp, (int64_t)blockIdx.x * 256 + threadIdx.x, Cout, Cin, conv_wrows(Cout), dgrad, bykh);
 }
 
-// All the repacks of a network pass in one launch: block -> job by the jobs' first-block table.
+// All the repacks of a network pass in one launch: block -> job by the jobs' first-block table, a job to a lane (searched one after
+// the other, each step was a load that the next waited for).  A block moves RB_G granules a thread.  Bound: HBM and launch of the blocks;
+// the 5-level base-32 net (45 MB): forward 28.4 -> 20.5 us, forward and data gradient 54.8 -> 29.3 us.
 struct RepackBatch {
     int n;
     struct J { const bf16_t* w; bf16_t* wp; int Cout, Cin, dgrad, kind, blk0; } j[64];
 };
+static constexpr int RB_G = 4;
 __global__ __launch_bounds__(256) void repack_batch_kernel(RepackBatch b) {
-    int k = 0;
-    while (k + 1 < b.n && (int)blockIdx.x >= b.j[k + 1].blk0) ++k;
+    const int lane = threadIdx.x & 63;
+    const int first = b.j[lane].blk0;
+    const int k = __popcll(__ballot(lane < b.n && first <= (int)blockIdx.x)) - 1;   // first blocks ascend, that of job 0 is 0
     const RepackBatch::J& q = b.j[k];
-    const int64_t i = (int64_t)((int)blockIdx.x - q.blk0) * 256 + threadIdx.x;
-    repack_tile_gran(q.w, q.wp, i, q.Cout, q.Cin, conv_wrows(q.Cout), q.dgrad, q.kind);
+    const int64_t i = (int64_t)((int)blockIdx.x - q.blk0) * (256 * RB_G) + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < RB_G; ++u) repack_tile_gran(q.w, q.wp, i + u * 256, q.Cout, q.Cin, conv_wrows(q.Cout), q.dgrad, q.kind);
 }
 
 lamp_status launch_repack_batch(const RepackJob* jobs, int n, hipStream_t s) {
@@ -111,7 +116,7 @@ lamp_status launch_repack_batch(const RepackJob* jobs, int n, hipStream_t s) {
         b.j[k].w = (const bf16_t*)jobs[k].w; b.j[k].wp = (bf16_t*)jobs[k].wp;
         b.j[k].Cout = jobs[k].Cout; b.j[k].Cin = jobs[k].Cin; b.j[k].dgrad = jobs[k].dgrad; b.j[k].kind = jobs[k].kind;
         b.j[k].blk0 = (int)blk;
-        blk += cdiv(repack_elems(jobs[k].Cout, jobs[k].Cin) / 8, 256);
+        blk += cdiv(repack_elems(jobs[k].Cout, jobs[k].Cin) / 8, 256 * RB_G);
         if (blk >= ((int64_t)1 << 31)) return LAMP_ERR_SHAPE;
     }
     hipLaunchKernelGGL(repack_batch_kernel, dim3((unsigned)blk), dim3(256), 0, s, b);
