@@ -415,19 +415,21 @@ static lamp_status ct_fwd_lds_launch(const CtArgs& a, int64_t nv, hipStream_t s)
 }
 
 // Data gradient.  One wave = 64 coarse voxels x RB blocks of 32 input channels; the reduction runs
-// over units of (tap, 32 output channels).  The 64-byte pieces of dy are gathered one unit ahead
+// over units of (tap, 32 output channels), in this order whatever RB is.  The 64-byte pieces of dy are gathered PF units ahead
 // into registers and handed to the matrix-core fragment order through the wave's double buffer.
-// SPLIT: the four waves of a workgroup share one group of 64 voxels, a quarter of the units each, and the first adds the four sums up
-// in order: a small volume has few voxel groups and, deep in the net, many units, whose gathers are one chain of memory latencies
-// (512->256 on 2 x 8^3: 57 -> 22 us).
+// PF = 4, RB = 1, a wave to a workgroup: for small volumes, which have few voxel groups and, deep in the net, many units, whose gathers
+// one unit ahead were one chain of memory latencies (512->256 on 2 x 8^3, forward and backward: 138 -> 77 us with the forward's part of it;
+// 256->128 on 2 x 16^3 96 -> 78).  Four waves with a quarter of the units each were no faster (75 and 86 us) and rounded some elements
+// of dx the other way, which the bf16 layers below amplified: 4e-3 in the deepest weight gradients of the 5-level base-32 net.
 // Requires Co % 32 == 0, Ci % 32 == 0.
-template <int RB, bool SPLIT = false>
-__global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
-    __shared__ __attribute__((aligned(16))) char tb[4][2][64 * CT_ROW];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+template <int RB, int PF = 1>
+__global__ __launch_bounds__(PF > 1 ? 64 : 256) void convtr_dgrad32_kernel(CtArgs a) {
+    constexpr int WV = PF > 1 ? 1 : 4;
+    __shared__ __attribute__((aligned(16))) char tb[WV][2][64 * CT_ROW];
+    const int lane = threadIdx.x & 63, wv = WV > 1 ? threadIdx.x >> 6 : 0;
     const int l32 = lane & 31, half = lane >> 5;
     const int64_t nvox = (int64_t)a.N * a.D * a.H * a.W;
-    const int64_t v0 = SPLIT ? (int64_t)blockIdx.x * 64 : ((int64_t)blockIdx.x * 4 + wv) * 64;
+    const int64_t v0 = ((int64_t)blockIdx.x * WV + wv) * 64;
     if (v0 >= nvox) return;
     const int r0 = blockIdx.y * (32 * RB);
     const int nrb = min(RB, (a.rows - r0) >> 5);
@@ -436,24 +438,10 @@ __global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         vs[it] = v0 + it * 16 + (lane >> 2);
-        fs[it] = vs[it] < nvox ? ct_fine_origin(a, vs[it]) : -1;
+        fs[it] = ct_fine_origin(a, vs[it] < nvox ? vs[it] : nvox - 1);   // past the end: the last voxel again, not stored
     }
     const bf16_t* arow = a.a + (int64_t)(r0 + l32) * a.K + 8 * half;
-    const int cpt = a.Co >> 5, u0 = SPLIT ? wv * 2 * cpt : 0, units = SPLIT ? u0 + 2 * cpt : 8 * cpt;
-
-    auto gather = [&](int u, uint4 (&q)[4]) {
-        const int tap = u / cpt, c0 = (u - tap * cpt) << 5;
-        const int64_t to = ct_tap_off(a, tap);
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            q[it] = make_uint4(0, 0, 0, 0);
-            if (fs[it] >= 0) q[it] = *reinterpret_cast<const uint4*>(a.b + (fs[it] + to) * a.ldb + c0 + (lane & 3) * 8);
-        }
-    };
-    auto put = [&](char* buf, const uint4 (&q)[4]) {
-#pragma unroll
-        for (int it = 0; it < 4; ++it) *reinterpret_cast<uint4*>(buf + (it * 16 + (lane >> 2)) * CT_ROW + (lane & 3) * 16) = q[it];
-    };
+    const int cpt = a.Co >> 5, units = 8 * cpt;
 
     f32x16 acc[RB][2];
 #pragma unroll
@@ -463,55 +451,79 @@ __global__ __launch_bounds__(256) void convtr_dgrad32_kernel(CtArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[rb][vb][r] = 0.f;
 
-    uint4 q[4];
-    gather(u0, q);
-    put(tb[wv][u0 & 1], q);
-    __builtin_amdgcn_wave_barrier();
-    for (int u = u0; u < units; ++u) {
-        if (u + 1 < units) gather(u + 1, q);
-        const char* cur = tb[wv][u & 1];
+    auto multiply = [&](const char* cur, const bf16x8 (&af)[RB], int ks) __attribute__((always_inline)) {
+        bf16x8 bf[2];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 bf[2], af[RB];
+        for (int vb = 0; vb < 2; ++vb)
+            bf[vb] = *reinterpret_cast<const bf16x8*>(cur + (vb * 32 + l32) * CT_ROW + ks * 32 + half * 16);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int vb = 0; vb < 2; ++vb)
-                bf[vb] = *reinterpret_cast<const bf16x8*>(cur + (vb * 32 + l32) * CT_ROW + ks * 32 + half * 16);
+                if (rb < nrb) acc[rb][vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[vb], acc[rb][vb], 0, 0, 0);
+    };
+    if constexpr (PF > 1) {
+        static_assert(RB == 1 && 8 % PF == 0, "the units are a multiple of 8");
+        vec_u32x4 q[PF][4];   // (vectors, and loads without a branch: nothing is taken apart behind a wait)
+        bf16x8 af[PF][2][1];
+        const bf16_t* src[4];
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) af[rb] = gfrag(arow + (int64_t)rb * 32 * a.K + u * 32 + ks * 16, rb < nrb);
+        for (int it = 0; it < 4; ++it) src[it] = a.b + fs[it] * a.ldb + (lane & 3) * 8;
+        auto fetch = [&](int u, int p) __attribute__((always_inline)) {
+            const int tap = u / cpt;
+            const int64_t o = ct_tap_off(a, tap) * a.ldb + ((u - tap * cpt) << 5);
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
+            for (int it = 0; it < 4; ++it) q[p][it] = *reinterpret_cast<const vec_u32x4*>(src[it] + o);
 #pragma unroll
-                for (int vb = 0; vb < 2; ++vb)
-                    if (rb < nrb) acc[rb][vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[vb], acc[rb][vb], 0, 0, 0);
-        }
-        if (u + 1 < units) put(tb[wv][(u + 1) & 1], q);
+            for (int ks = 0; ks < 2; ++ks) af[p][ks][0] = *reinterpret_cast<const bf16x8*>(arow + u * 32 + ks * 16);
+        };
+#pragma unroll
+        for (int p = 0; p < PF; ++p) fetch(p, p);
+#pragma unroll 1
+        for (int u = 0; u < units; u += PF)
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                char* cur = tb[wv][p & 1];
+#pragma unroll
+                for (int it = 0; it < 4; ++it)
+                    *reinterpret_cast<vec_u32x4*>(cur + (it * 16 + (lane >> 2)) * CT_ROW + (lane & 3) * 16) = q[p][it];
+                __builtin_amdgcn_wave_barrier();
+                multiply(cur, af[p][0], 0);
+                multiply(cur, af[p][1], 1);
+                fetch(u + p + PF < units ? u + p + PF : u + p, p);   // the last ones again: no branch
+                __builtin_amdgcn_wave_barrier();
+            }
+    } else {
+        auto gather = [&](int u, uint4 (&q)[4]) __attribute__((always_inline)) {
+            const int tap = u / cpt, c0 = (u - tap * cpt) << 5;
+            const int64_t to = ct_tap_off(a, tap);
+#pragma unroll
+            for (int it = 0; it < 4; ++it) q[it] = *reinterpret_cast<const uint4*>(a.b + (fs[it] + to) * a.ldb + c0 + (lane & 3) * 8);
+        };
+        auto put = [&](char* buf, const uint4 (&q)[4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int it = 0; it < 4; ++it) *reinterpret_cast<uint4*>(buf + (it * 16 + (lane >> 2)) * CT_ROW + (lane & 3) * 16) = q[it];
+        };
+        uint4 q[4];
+        gather(0, q);
+        put(tb[wv][0], q);
         __builtin_amdgcn_wave_barrier();
+        for (int u = 0; u < units; ++u) {
+            if (u + 1 < units) gather(u + 1, q);
+            const char* cur = tb[wv][u & 1];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                bf16x8 af[RB];
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) af[rb] = gfrag(arow + (int64_t)rb * 32 * a.K + u * 32 + ks * 16, rb < nrb);
+                multiply(cur, af, ks);
+            }
+            if (u + 1 < units) put(tb[wv][(u + 1) & 1], q);
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 
-    if constexpr (SPLIT) {
-        static_assert(RB == 1, "two sums of 16 registers a wave");
-        float4* sh = reinterpret_cast<float4*>(tb[0][0]);   // [3][8][64]: 24 KB of the four buffers
-        __syncthreads();
-        if (wv)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const f32x16& v = acc[0][i >> 2];
-                const int r = 4 * (i & 3);
-                sh[((wv - 1) * 8 + i) * 64 + lane] = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
-            }
-        __syncthreads();
-        if (wv) return;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float4 o = sh[(k * 8 + i) * 64 + lane];
-                f32x16& v = acc[0][i >> 2];
-                const int r = 4 * (i & 3);
-                v[r] += o.x; v[r + 1] += o.y; v[r + 2] += o.z; v[r + 3] += o.w;
-            }
-    }
-    char* mine = SPLIT ? tb[3][0] : tb[wv][0];
+    char* mine = tb[wv][0];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         if (rb >= nrb) break;
@@ -626,7 +638,7 @@ lamp_status mfma_convtr_dgrad(const lamp_tensor_desc* xd, const void* wt, const 
         dim3 grid(cdiv(nvox(xd), 256), cdiv(a.rows, 32 * rb));
         if (rb == 4) hipLaunchKernelGGL((convtr_dgrad32_kernel<4>), grid, dim3(256), 0, s, a);
         else if (rb == 2) hipLaunchKernelGGL((convtr_dgrad32_kernel<2>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((convtr_dgrad32_kernel<1, true>), dim3(cdiv(nvox(xd), 64), grid.y), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((convtr_dgrad32_kernel<1, 4>), dim3(cdiv(nvox(xd), 64), grid.y), dim3(64), 0, s, a);
         LAMP_CHECK_LAUNCH();
         return LAMP_OK;
     }
