@@ -43,19 +43,16 @@ int stats_chunks(int64_t v) {
     return (int)((v + r - 1) / r);
 }
 
-// Rows of one partial sum of the two-tensor reductions (backward sums, squeeze).  1024 chunks are four blocks to a CU, which is what
-// their registers allow; 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's
-// backward 126 -> 118).  At least four rows to every row lane, which are in flight together: with 32 rows whatever the width, a
-// 16-channel chunk (128 row lanes) kept a quarter of its threads busy with one row (backward sums of 16 channels on 3 x 28 x 43 x 39: 13.8 -> 6.3 us; squeeze of 16 channels on 3 x 45 x 44 x 92: 19.2 -> 10.4).
-static int bwd_rows(int64_t v, int C, int dtype) {
-    const int vec = dtype == LAMP_BF16 ? 8 : 4;
-    const int rl = C % vec ? 8 : make_rowmap(C, vec).rl;
-    int64_t r = (v + 1023) / 1024;
-    if (r < 4 * rl) r = 4 * rl;
+// Chunks of the two-tensor reductions (backward sums, squeeze): 1024 blocks are four to a CU, which is what their registers allow;
+// 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's backward 126 -> 118).
+// The chunks do not depend on the width: other chunks are other roundings of the sums, and a bf16 net amplifies these layer by layer
+// (four rows to every row lane moved the deepest weight gradients of the 5-level base-32 net by 4e-3).
+static int bwd_rows(int64_t v) {
+    const int64_t r = (v + 1023) / 1024;
     return (int)(r < 32 ? 32 : r);
 }
-int bwd_chunks(int64_t v, int C, int dtype) {
-    const int r = bwd_rows(v, C, dtype);
+int bwd_chunks(int64_t v) {
+    const int r = bwd_rows(v);
     return (int)((v + r - 1) / r);
 }
 
@@ -593,7 +590,7 @@ extern "C" lamp_status lamp_inorm_relu(const lamp_tensor_desc* zd, const void* z
     const int vec = pick_vec(zd->dtype, zd->c, {zd->ldc, yd->ldc}, {z, y});
     const bool nt = beyond_cache(2 * nvox(zd) * zd->c * (int64_t)esize(zd->dtype));
     LAMP_DISPATCH_TV(zd->dtype, vec, {
-        RowMap m = make_rowmap(zd->c, VEC);
+        RowMap m = make_rowmap(zd->c, VEC, true);
         if (nt) {
             hipLaunchKernelGGL((inorm_apply_kernel<T, VEC, true>), dim3(apply_blocks(V, m.rl), zd->n, m.ctiles), dim3(256), 0, s,
                            (const T*)z, zd->ldc, (T*)y, yd->ldc, V, zd->c, m.cthreads, m.rl, stats, gamma, beta);
@@ -623,7 +620,7 @@ extern "C" lamp_status lamp_inorm_relu_noalloc(const lamp_tensor_desc* zd, const
 extern "C" size_t lamp_inorm_relu_bwd_workspace_bytes(const lamp_tensor_desc* zd) {
     if (!desc_ok(zd)) return 0;
     int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    int ch = bwd_chunks(V, zd->c, zd->dtype);
+    int ch = bwd_chunks(V);
     return align_up((size_t)zd->n * ch * zd->c * 2 * sizeof(float)) + align_up((size_t)zd->n * zd->c * 2 * sizeof(float));
 }
 
@@ -640,7 +637,7 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
     if (!ws || ws_bytes < lamp_inorm_relu_bwd_workspace_bytes(zd)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int chunks = bwd_chunks(V, zd->c, zd->dtype);
+    const int chunks = bwd_chunks(V);
     float* partial = (float*)ws;
     float* sums = (float*)((char*)ws + align_up((size_t)zd->n * chunks * zd->c * 2 * sizeof(float)));
     const int vec = pick_vec(zd->dtype, zd->c, {zd->ldc, dyd->ldc, dzd->ldc}, {z, dy, dz});
@@ -649,11 +646,11 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
         RowMap m = make_rowmap(zd->c, VEC);
         if (nt) {
             hipLaunchKernelGGL((inorm_bwd_partial_kernel<T, VEC, true>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s,
-                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V, zd->c, zd->dtype),
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V),
                            stats, gamma, beta, partial);
         } else {
             hipLaunchKernelGGL((inorm_bwd_partial_kernel<T, VEC, false>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s,
-                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V, zd->c, zd->dtype),
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V),
                            stats, gamma, beta, partial);
         }
     });
@@ -678,7 +675,7 @@ lamp_status lamp::launch_inorm_bwd_apply(const lamp_tensor_desc* dyd, const void
                        (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, (T*)dz, dzd->ldc, V, zd->c, m.cthreads, m.rl, stats, gamma, beta, \
                        fold ? partial : sums, dgamma, dbeta, beta_acc, parts, zstats)
     LAMP_DISPATCH_TV(zd->dtype, vec, {
-        RowMap m = make_rowmap(zd->c, VEC);
+        RowMap m = make_rowmap(zd->c, VEC, true);
         if (nt) LAMP_APPLY(true, false);
         else if (VEC > 1 && fold) LAMP_APPLY(false, (VEC > 1));
         else LAMP_APPLY(false, false);

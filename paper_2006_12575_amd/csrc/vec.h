@@ -114,13 +114,13 @@ template <int VEC> __device__ __forceinline__ void affine_grads(const float* sum
 struct RowMap {
     int cthreads, rl, ctiles;
 };
-inline RowMap make_rowmap(int C, int VEC) {
+inline RowMap make_rowmap(int C, int VEC, bool lines = false) {
     RowMap m;
     int cv = C / VEC;
     m.cthreads = cv < 256 ? cv : 256;
     m.rl = 256 / m.cthreads;
-    // whole 128-byte lines to a round of rows where that idles a sixteenth of the threads at most
-    if (VEC > 1)
+    // whole 128-byte lines to a round of rows where that idles a sixteenth of the threads at most (not in sums, whose order it would change)
+    if (lines && VEC > 1)
         for (int r = m.rl; r * 16 >= m.rl * 15; --r)
             if (r * m.cthreads % 8 == 0) { m.rl = r; break; }
     m.ctiles = (cv + 255) / 256;
