@@ -511,8 +511,9 @@ __global__ __launch_bounds__(256) void inorm_bwd_apply_kernel(const T* __restric
     if constexpr (FOLD) {
         fold_parts(sums, parts, n, C, zstats, fsh, tot);
     }
+    // (FOLD with gradients is for one sample: `tot` holds no other)
+    if (n == 0) affine_grads(FOLD ? tot : sums, FOLD ? 1 : gridDim.y, C, blockIdx.z * 256 * VEC, min(C - (int)blockIdx.z * 256 * VEC, 256 * VEC), dgamma, dbeta, beta_acc);
     if (r0 >= rl || cv * VEC >= C) return;
-    if (blockIdx.x == 0 && n == 0 && r0 == 0) affine_grads<VEC>(FOLD ? tot : sums, gridDim.y, C, cv * VEC, dgamma, dbeta, beta_acc);
     NormIn nm{stats, gamma, beta, C, 1};
     float a[VEC], b[VEC], mean[VEC], rstd[VEC], c1[VEC], c2[VEC];
     const float invV = 1.0f / (float)V;

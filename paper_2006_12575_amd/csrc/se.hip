@@ -285,8 +285,8 @@ __global__ __launch_bounds__(256) void se_bwd_apply_kernel(const T* __restrict__
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
     const int n = blockIdx.y;
+    if (n == 0) affine_grads(sums2, gridDim.y, C, blockIdx.z * 256 * VEC, min(C - (int)blockIdx.z * 256 * VEC, 256 * VEC), dgamma, dbeta, beta_acc);
     if (r0 >= rl || cv * VEC >= C) return;
-    if (blockIdx.x == 0 && n == 0 && r0 == 0) affine_grads<VEC>(sums2, gridDim.y, C, cv * VEC, dgamma, dbeta, beta_acc);
     NormIn nm{stats, gamma, beta, C, 1};
     float a[VEC], b[VEC], mean[VEC], rstd[VEC], c1[VEC], c2[VEC], e[VEC], dm[VEC];
     const float invV = 1.0f / (float)V;

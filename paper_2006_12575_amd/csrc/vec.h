@@ -92,19 +92,26 @@ template <int VEC> __device__ __forceinline__ void norm_coeffs_vec(const NormIn&
     norm_coeffs_vec<VEC>(nm, n, c0, a, b, mean, rstd);
 }
 
-// dgamma, dbeta of VEC channels: the backward sums over the samples, fp64, in order.  By one block of the apply pass (a launch of its
-// own took 1.2 to 5 us).
-template <int VEC> __device__ __forceinline__ void affine_grads(const float* sums, int N, int C, int c0, float* dgamma, float* dbeta,
-                                                                float beta_acc) {
+// dgamma, dbeta of channels [c0, c0 + nc): the backward sums over the samples, fp64, in order, by the threads of the apply pass's blocks
+// of the first sample, a thread to a channel and sum, the sums of eight samples in flight (a launch of its own took 1.2 to 5 us; one
+// thread with eight channels one after the other waited 8 N times in front of its first row).  Called by whole blocks; nothing is read
+// where neither is wanted.
+__device__ __forceinline__ void affine_grads(const float* sums, int N, int C, int c0, int nc, float* dgamma, float* dbeta, float beta_acc) {
+    if (!dgamma && !dbeta) return;
+    for (int o = blockIdx.x * 256 + threadIdx.x; o < 2 * nc; o += gridDim.x * 256) {
+        const float* p = sums + 2 * c0 + o;
+        double t = 0.0;
+        for (int n = 0; n < N; n += 8) {
+            float v[8];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-        double s = 0.0, q = 0.0;
-        for (int n = 0; n < N; ++n) {
-            s += (double)sums[((size_t)n * C + c0 + i) * 2 + 0];
-            q += (double)sums[((size_t)n * C + c0 + i) * 2 + 1];
+            for (int u = 0; u < 8; ++u) v[u] = p[(size_t)min(n + u, N - 1) * C * 2];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (n + u < N) t += (double)v[u];
         }
-        if (dbeta) dbeta[c0 + i] = (beta_acc != 0.f ? beta_acc * dbeta[c0 + i] : 0.f) + (float)s;
-        if (dgamma) dgamma[c0 + i] = (beta_acc != 0.f ? beta_acc * dgamma[c0 + i] : 0.f) + (float)q;
+        float* out = o & 1 ? dgamma : dbeta;
+        const int c = c0 + (o >> 1);
+        if (out) out[c] = (beta_acc != 0.f ? beta_acc * out[c] : 0.f) + (float)t;
     }
 }
 
