@@ -457,15 +457,14 @@ __device__ __forceinline__ void fold_parts(const float* __restrict__ partial, in
         double t = 0.0;
         if (p < lanes) {
             const float* q = pp + o0 + o;
-            int k = p;
-            for (; k + 7 * lanes < parts; k += 8 * lanes) {
+            for (int k = p; k < parts; k += 8 * lanes) {
                 float v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = q[(size_t)(k + u * lanes) * nout];
+                for (int u = 0; u < 8; ++u) v[u] = q[(size_t)min(k + u * lanes, parts - 1) * nout];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t += (double)v[u];
+                for (int u = 0; u < 8; ++u)
+                    if (k + u * lanes < parts) t += (double)v[u];
             }
-            for (; k < parts; k += lanes) t += (double)q[(size_t)k * nout];
         }
         sh[tid] = t;
         __syncthreads();
@@ -482,9 +481,10 @@ __device__ __forceinline__ void fold_parts(const float* __restrict__ partial, in
         __syncthreads();
     }
 }
-// Where every block of the apply pass folds the partials itself: at most 4 loads a thread, which are in flight together, in place of a
-// launch of 3 to 5 us (training step of the 4-level base-8 fp32 net on 24 x 32 x 40: 848 -> 824 us; conv unit 64->32 on 3 x 10 x 11 x 12:
-// 64.2 -> 61.6; with 16 loads no more, and several samples' sums folded by the block that writes dgamma and dbeta cost what they save).
+// Where every block of the apply pass folds the partials itself: at most 7 loads a thread (68 channels, 7 partials), which are in flight
+// together, in place of a launch (sums and apply of bf16, folded and with the launch: 64 channels on 4^3 7.8 and 9.7 us, 32 on 8^3 8.7 and
+// 10.3, 64 on 3 x 6 x 7 x 5 without gradients 8.4 and 9.7, 48 on 6 x 7 x 8 no difference).  Not where several samples' gradients are
+// wanted: the block that writes these would fold all samples.
 static constexpr int FOLD_C = 512;
 static bool fold_in_apply(int parts, int N, int C, int vec, bool grads) {
     return vec > 1 && C <= FOLD_C && (int64_t)parts * C <= 512 && (N == 1 || !grads);
