@@ -398,8 +398,9 @@ static lamp_status ct_fwd_lds_launch(const CtArgs& a, int64_t nv, hipStream_t s)
     const size_t lds = ct_fwd_lds(pb, KS);
     // as many workgroups as are resident at a time, fewer where the volume has fewer groups
     const int per_cu = KS <= 4 ? 2 : 1;
-    int64_t walkers = 256 * per_cu / nblocks;
+    int64_t walkers = 256 * per_cu / nblocks;   // 0 where the row blocks alone are more than are resident
     if (walkers > cdiv(nv, 256)) walkers = cdiv(nv, 256);
+    if (walkers < 1) walkers = 1;
     walkers = (walkers + 7) / 8 * 8;
     const dim3 grid((unsigned)(walkers * nblocks));
     const bool nt = beyond_cache(nv * (a.Ci + 8 * (int64_t)a.Co) * 2);

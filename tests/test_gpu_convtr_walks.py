@@ -74,3 +74,17 @@ def test_convtr_walks(L, shape, co, extra, woff):
     dw4, db4 = torch.empty_like(dwt), torch.empty_like(db)
     L.lamp_convtr3d_bwd(x, wt, dy, dwt=dw4, dbias=db4)
     assert rel(dw4, r[2]) <= 1e-5 and rel(db4, r[3]) <= 1e-5
+
+
+# more row blocks than workgroups are resident: 258 of 128 inputs, 513 of 16
+@pytest.mark.parametrize("ci,co", [(128, 8256), (16, 16416)])
+def test_convtr_fwd_many_outputs(L, ci, co):
+    g = torch.Generator(device="cuda").manual_seed(co)
+    x = torch.randn((1, 1, 2, 3, ci), generator=g, device="cuda").to(BF)
+    wt = (torch.randn((ci, 2, 2, 2, co), generator=g, device="cuda") * ci ** -0.5).to(BF)
+    b = torch.randn((co,), generator=g, device="cuda")
+    y = torch.full((1, 2, 4, 6, co), 7.0, device="cuda").to(BF)
+    L.lamp_convtr3d(x, wt, y, bias=b)
+    r = (x.double().reshape(-1, ci) @ wt.double().reshape(ci, 8 * co)).reshape(1, 1, 2, 3, 2, 2, 2, co)
+    r = r.permute(0, 1, 4, 2, 5, 3, 6, 7).reshape(y.shape) + b.double()
+    assert rel(y, r) <= 2.0 ** -8   # one rounding to bf16
