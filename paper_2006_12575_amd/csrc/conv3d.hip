@@ -371,10 +371,14 @@ __global__ __launch_bounds__(256) void conv3d_cin1_wgrad_kernel(const bf16_t* __
 // 8 x 16 G outputs (h, w; G up to 4), two rows to each of its four waves.  x: a ring of four slices in LDS, every channel three times,
 // shifted by kw, so that the 8 consecutive voxels of a fragment are one aligned 16-byte read for every tap; rows are padded to 144 bytes
 // to spread the taps of a read over the banks.  The slice after next is fetched during a step: one barrier a step.  dz: one 16-byte
-// load a lane and 16 voxels x 32 channels, a whole step ahead, through a private LDS slot to the transposing read.
-// Chains of additions: two steps (256 voxels) into a second register set, the four waves at the end, one partial a walk.
+// load a lane and 16 voxels x 32 channels, half a step ahead, through a private LDS slot to the transposing read (a whole step ahead
+// took 16 registers more a block of channels, which spilled: 2->16 and 1->64).
+// Chains of additions: the 8 products of a step, then sums in S over the walk and over the four waves, one partial a walk.  fp64 where
+// registers hold them, with one input channel and up to 16 outputs (whose accumulators are half empty, ROWS = 8), fp32 else.  Relative
+// error of 2->16 on 1 x 192 x 160 x 128: 6.8e-8, in chains of two steps and fp32 sums 1.05e-7, with padding 8.8e-8; 1->32 on
+// 64 x 80 x 96: 6.3e-8, 9.0e-8, 6.6e-8 (rows of a wave in one chain); 2->64 on 2 x 64 x 80 x 96: 8.5e-8, 8.8e-8, 8.5e-8.
 // Bound: HBM (dz is read once) and the instructions per 16 voxels.  2->16 on 2 x 64 x 80 x 96: 58 us with padding and
-// reduction -> 25; 1->32 on 2 x 128^3 (268 MB): 139 us, staging all three slices anew for every four rows, -> 69 (3.9 TB/s).
+// reduction -> 22; 1->32 on 2 x 128^3 (268 MB): 139 us, staging all three slices anew for every four rows, -> 61 (4.4 TB/s).
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short c1_s16x4;
 __device__ __forceinline__ c1_bf16x8 c1_frag_tr(const char* p) {
     typedef __attribute__((address_space(3))) c1_s16x4 lds_s16x4;
@@ -394,10 +398,12 @@ struct NarrowWArgs {
     int segs, L;      // walks of a tile, slices of a walk
 };
 static constexpr int NW_TH = 8, NW_ROW = 144, NW_PLANE = (NW_TH + 2) * NW_ROW;
+// workgroups a CU that the registers allow
+__host__ __device__ constexpr int narrow_per_cu(int ci, int cb) { return ci <= 2 && cb == 1 ? 3 : 2; }
 static size_t narrow_lds(int ci, int cb) { return (size_t)4 * ci * 3 * NW_PLANE + 4 * 2 * cb * 1024; }
 
-template <int CI, int CB>
-__global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad_kernel(NarrowWArgs a) {
+template <int CI, int CB, typename S, int ROWS>
+__global__ __launch_bounds__(256, narrow_per_cu(CI, CB)) void conv3d_narrow_wgrad_kernel(NarrowWArgs a) {
     extern __shared__ __attribute__((aligned(16))) char nw_lds[];
     constexpr int COLS = 27 * CI, NB = (COLS + 31) / 32, SLOT = CI * 3 * NW_PLANE, NE = ((NW_TH + 2) * 66 * CI + 255) / 256;
     char* const xr = nw_lds;
@@ -442,14 +448,14 @@ __global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad
     // dz: voxel of the group and 16-byte piece of its 64 bytes
     const int vx = lane >> 2, piece = lane & 3, hrow = h0 + wv * 2;
     const bf16_t* const dzs = a.dz + ((int64_t)n * a.D * a.H * a.W + (int64_t)hrow * a.W + w0 + vx) * a.lddz + co0 + piece * 8;
-    uint4 q[8][CB];
+    uint4 q[4][CB];
     auto fetch_z = [&](int i, int d) __attribute__((always_inline)) {
         const bool in = d < d1 && hrow + (i >> 2) < a.H && w0 + 16 * (i & 3) + vx < a.W;
         const bf16_t* p = dzs + (((int64_t)d * a.H + (i >> 2)) * a.W + 16 * (i & 3)) * a.lddz;
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-            q[i][cb] = make_uint4(0, 0, 0, 0);
-            if (in && co0 + 32 * cb + piece * 8 < a.Co) q[i][cb] = *reinterpret_cast<const uint4*>(p + 32 * cb);
+            q[i & 3][cb] = make_uint4(0, 0, 0, 0);
+            if (in && co0 + 32 * cb + piece * 8 < a.Co) q[i & 3][cb] = *reinterpret_cast<const uint4*>(p + 32 * cb);
         }
     };
     // columns of this lane: offset in a slice of the ring, which slice
@@ -465,13 +471,13 @@ __global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad
     const int b16 = lane >> 4, s16 = lane & 15;
     const uint32_t loff = (uint32_t)((8 * (b16 >> 1) + (s16 >> 2)) * 64 + 32 * (b16 & 1) + 8 * (s16 & 3));
 
-    c1_f32x16 acc[CB][NB], sum[CB][NB];
+    S sum[CB][NB][ROWS];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[cb][b][r] = sum[cb][b][r] = 0.f;
+            for (int r = 0; r < ROWS; ++r) sum[cb][b][r] = 0;
 
 #pragma unroll 1
     for (int k = -1; k <= 1; ++k) {
@@ -479,8 +485,8 @@ __global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad
         stage_x(d0 + k);
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-        if ((i & 3) < a.G) fetch_z(i, d0);
+    for (int i = 0; i < 4; ++i)
+        if (i < a.G) fetch_z(i, d0);
     __syncthreads();
     for (int d = d0; d < d1; ++d) {
         const bool more = d + 1 < d1;
@@ -488,13 +494,21 @@ __global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad
         const char* xb[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) xb[b] = xr + ((d + 3 + ckd[b]) & 3) * SLOT + col[b];
+        c1_f32x16 acc[CB][NB];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[cb][b][r] = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             if ((i & 3) >= a.G) continue;
             char* buf = slot + (i & 1) * (CB * 1024);
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<uint4*>(buf + cb * 1024 + vx * 64 + piece * 16) = q[i][cb];
-            if (more) fetch_z(i, d + 1);
+            for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<uint4*>(buf + cb * 1024 + vx * 64 + piece * 16) = q[i & 3][cb];
+            if (i < 4) fetch_z(i + 4, d);
+            else if (more) fetch_z(i - 4, d + 1);
             __builtin_amdgcn_wave_barrier();
             c1_bf16x8 xf[NB];
 #pragma unroll
@@ -508,45 +522,37 @@ __global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad
             __builtin_amdgcn_wave_barrier();
         }
         if (more) stage_x(d + 2);   // the slice that every wave left behind the last barrier
-        if (((d - d0) & 1) || !more) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    sum[cb][b] += acc[cb][b];
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[cb][b][r] = 0.f;
-                }
-        }
+                for (int r = 0; r < ROWS; ++r) sum[cb][b][r] += (S)acc[cb][b][r];
         __syncthreads();
     }
     // the four waves: 2 and 3 to 0 and 1, then 1 to 0
-    static_assert(2 * CB * NB * 4096 <= 4 * SLOT, "two waves' sums fit the ring");
+    static_assert(2 * CB * NB * ROWS * 64 * sizeof(S) <= 4 * SLOT + 8 * CB * 1024, "two waves' sums fit the ring and the slots");
 #pragma unroll
     for (int k = 2; k >= 1; k >>= 1) {
-        float4* sh = reinterpret_cast<float4*>(xr);
+        S* sh = reinterpret_cast<S*>(xr);
         if (wv >= k && wv < 2 * k) {
-            float4* o = sh + (wv - k) * (CB * NB * 256) + lane;
+            S* o = sh + (wv - k) * (CB * NB * ROWS * 64) + lane;
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        o[((cb * NB + b) * 4 + r) * 64] = make_float4(sum[cb][b][4 * r], sum[cb][b][4 * r + 1], sum[cb][b][4 * r + 2], sum[cb][b][4 * r + 3]);
+                    for (int r = 0; r < ROWS; ++r) o[((cb * NB + b) * ROWS + r) * 64] = sum[cb][b][r];
         }
         __syncthreads();
         if (wv < k) {
-            const float4* o = sh + wv * (CB * NB * 256) + lane;
+            const S* o = sh + wv * (CB * NB * ROWS * 64) + lane;
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float4 v = o[((cb * NB + b) * 4 + r) * 64];
-                        sum[cb][b][4 * r] += v.x; sum[cb][b][4 * r + 1] += v.y; sum[cb][b][4 * r + 2] += v.z; sum[cb][b][4 * r + 3] += v.w;
-                    }
+                    for (int r = 0; r < ROWS; ++r) sum[cb][b][r] += o[((cb * NB + b) * ROWS + r) * 64];
         }
         __syncthreads();
     }
@@ -559,9 +565,9 @@ __global__ __launch_bounds__(256, CI * CB <= 2 ? 3 : 2) void conv3d_narrow_wgrad
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < ROWS; ++r) {
                 const int co = co0 + 32 * cb + 8 * (r / 4) + 4 * half + (r % 4);
-                if (co < a.Co) pb[(int64_t)co * COLS + c] = sum[cb][b][r];
+                if (co < a.Co) pb[(int64_t)co * COLS + c] = (float)sum[cb][b][r];
             }
     }
 }
@@ -631,17 +637,16 @@ static lamp_status cin1_tile_fwd(const lamp_tensor_desc* xd, const void* x, cons
 struct NarrowWPlan { int nth, ntw, G, segs, L, cb; int64_t walks; };
 static NarrowWPlan narrow_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
     NarrowWPlan p;
-    p.cb = xd->c <= 2 && dzd->c > 32 ? 2 : 1;   // as many sums as registers hold twice
+    p.cb = xd->c <= 2 && dzd->c > 32 ? 2 : 1;   // as many sums as registers hold (2->64 on 128^3: 61 us, a block of 32 outputs a workgroup 82)
     p.nth = cdiv(xd->h, NW_TH);
     p.ntw = cdiv(xd->w, 64);
     p.G = cdiv(cdiv(xd->w, p.ntw), 16);
-    // Three workgroups a CU; a walk of two slices at least (its first step waits for three slices of x).
-    const int64_t tiles = (int64_t)xd->n * p.nth * p.ntw, steps = tiles * xd->d * cdiv(dzd->c, 32 * p.cb);
-    int64_t l = (steps + 767) / 768;
-    if (l < 2) l = 2;
-    if (l > xd->d) l = xd->d;
-    p.segs = cdiv(xd->d, l);
-    p.L = cdiv(xd->d, p.segs);
+    const int64_t tiles = (int64_t)xd->n * p.nth * p.ntw, cols = tiles * cdiv(dzd->c, 32 * p.cb), fit = 256 * narrow_per_cu(xd->c, p.cb);
+    // One round of resident workgroups (2->64 on 128^3, two to a CU: 61 us, one and a half rounds 88; 4->64 97 and 133); a walk of two
+    // slices at least (its first step waits for three slices of x).
+    int64_t segs = fit / cols < 1 ? 1 : fit / cols;
+    p.L = cdiv(xd->d, segs);
+    if (p.L < 2) p.L = xd->d < 2 ? xd->d : 2;
     p.segs = cdiv(xd->d, p.L);
     p.walks = tiles * p.segs;
     return p;
@@ -653,11 +658,11 @@ static bool narrow_ok(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
 static size_t narrow_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
     return align_up((size_t)narrow_plan(xd, dzd).walks * dzd->c * 27 * xd->c * sizeof(float));
 }
-template <int CI, int CB>
+template <int CI, int CB, typename S, int ROWS = 16>
 static lamp_status narrow_launch(const NarrowWArgs& a, dim3 grid, hipStream_t s) {
     const size_t lds = narrow_lds(CI, CB);
-    if (ensure_dyn_lds((const void*)conv3d_narrow_wgrad_kernel<CI, CB>, (int)lds) != LAMP_OK) return LAMP_ERR_HIP;
-    hipLaunchKernelGGL((conv3d_narrow_wgrad_kernel<CI, CB>), grid, dim3(256), lds, s, a);
+    if (ensure_dyn_lds((const void*)conv3d_narrow_wgrad_kernel<CI, CB, S, ROWS>, (int)lds) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL((conv3d_narrow_wgrad_kernel<CI, CB, S, ROWS>), grid, dim3(256), lds, s, a);
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }
@@ -670,10 +675,17 @@ static lamp_status narrow_wgrad(const lamp_tensor_desc* xd, const void* x, const
     a.D = xd->d; a.H = xd->h; a.W = xd->w; a.Co = dzd->c;
     a.nth = p.nth; a.ntw = p.ntw; a.G = p.G; a.segs = p.segs; a.L = p.L;
     const dim3 grid((unsigned)p.walks, cdiv(dzd->c, 32 * p.cb));
-    const lamp_status st = xd->c == 1   ? (p.cb == 2 ? narrow_launch<1, 2>(a, grid, s) : narrow_launch<1, 1>(a, grid, s))
-                           : xd->c == 2 ? (p.cb == 2 ? narrow_launch<2, 2>(a, grid, s) : narrow_launch<2, 1>(a, grid, s))
-                           : xd->c == 3 ? narrow_launch<3, 1>(a, grid, s)
-                                        : narrow_launch<4, 1>(a, grid, s);
+    lamp_status st;
+    if (dzd->c <= 16)
+        st = xd->c == 1   ? narrow_launch<1, 1, double, 8>(a, grid, s)
+             : xd->c == 2 ? narrow_launch<2, 1, double, 8>(a, grid, s)
+             : xd->c == 3 ? narrow_launch<3, 1, double, 8>(a, grid, s)
+                          : narrow_launch<4, 1, double, 8>(a, grid, s);
+    else
+        st = xd->c == 1   ? (p.cb == 2 ? narrow_launch<1, 2, double>(a, grid, s) : narrow_launch<1, 1, double>(a, grid, s))
+             : xd->c == 2 ? (p.cb == 2 ? narrow_launch<2, 2, float>(a, grid, s) : narrow_launch<2, 1, float>(a, grid, s))
+             : xd->c == 3 ? narrow_launch<3, 1, float>(a, grid, s)
+                          : narrow_launch<4, 1, float>(a, grid, s);
     if (st != LAMP_OK) return st;
     return launch_reduce_partials((const float*)ws, (int)p.walks, (int64_t)dzd->c * 27 * xd->c, dw, beta, s);
 }
