@@ -168,9 +168,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()   # the argument type makes it a pointer
 
 
+# torch.cuda.current_stream().cuda_stream without the two Python objects in between, where torch has these (they are not public)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    # torch.cuda.current_stream().cuda_stream without the two Python objects in between
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _norm(nm):
