@@ -921,57 +921,68 @@ lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const l
 }
 
 // ------------------------------------------------------------------------------------------------
-// Data gradient and weight gradient (with the bias gradient) in one pass over dy, for 64 input and 32 output channels, the widest
-// volume of a base-32 net.  A workgroup (8 waves, one per CU) walks chunks of 64 coarse voxels, three stages of x and dy (40 KB
-// each) in LDS, so that two chunks are in flight while one is multiplied; waves 0-3 take a quadrant (32 input channels x 32 voxels) of
-// the data gradient each, its 16 weight fragments in registers for the whole walk, waves 4-7 two taps of the weight gradient each.
-// LDS rows are 128 bytes (64 channels of x; both voxels of a w pair of dy, which are 128 consecutive bytes of memory, so a copy
-// instruction fetches 1 KB in a row), their 16-byte pieces in an order that turns with the voxel pair, so that neither the plain reads
-// (16 voxels side by side) nor the transposing ones (4 voxels x 32 bytes) meet in a bank.
-// Sums of the weight gradient: chains of `fold` chunks, added to a second register set; a partial per workgroup.
-// Bound: HBM.  64->32 on 2 x 64^3: 402 MB, 182 us as separate data and weight gradients (dy read twice) and two reductions
-// -> 71 us and one of 5.
+// Data gradient and weight gradient (with the bias gradient) in one pass over dy, for 32 or 64 input and 16 or 32 output channels: the
+// last levels of a decoder, where the volume is.  (Wider ones: 64 x 8 x 32 sums and the chain's registers behind them are what eight
+// waves hold; 128->64 has four times as many.  Narrower ones leave the 32 rows of a product half empty.)
+// A workgroup (8 waves) walks chunks of 64 coarse voxels, three stages of x and dy (20 to 40 KB each) in LDS, so that two chunks are in
+// flight while one is multiplied; waves 0-3 (0-1 for 32 inputs) take a quadrant (32 input channels x 32 voxels) of the data gradient
+// each, its weight fragments in registers for the whole walk, waves 4-7 two taps of the weight gradient each, a w pair, whose 2 * Co
+// columns lie side by side.
+// LDS rows are the channels of x, and both voxels of a w pair of dy (consecutive bytes of memory, so a copy instruction fetches 1 KB in
+// a row), 64 or 128 bytes, their 16-byte pieces in an order that turns with the voxel pair, so that neither the plain reads (16 voxels
+// side by side) nor the transposing ones (4 voxels x 32 bytes) meet in a bank.
+// Sums of the weight gradient: chains of `fold` chunks, added in fp64; a partial per workgroup.  Relative error against the separate
+// kernel's: 64->32 on 2 x 64^3 7.5e-8 and 1.4e-7, on 2 x 32^3 4.9e-8 and 5.3e-8; 32->16 on 2 x 64^3 4.8e-8 and 7.7e-8.
+// Bound: HBM.  Data, weight and bias gradient with all launches, against separate kernels (dy read twice): 64->32 on 2 x 64^3 (402 MB)
+// 162 -> 83 us, on 2 x 32^3 40 -> 22; 32->16 on 2 x 64^3 146 -> 37, on 2 x 16^3 22 -> 10; 32->32 on 2 x 64^3 144 -> 66, 64->16 165 -> 55.
 struct CtBArgs {
     const bf16_t* x; const bf16_t* wt; const bf16_t* dy; bf16_t* dx;
     const bf16_t* zero16;
-    float* part;          // [workgroup][64][8][32], then [32] bias sums where `bias`
+    float* part;          // [workgroup][CI][8][CO], then [CO] bias sums where `bias`
     int slab;             // floats of a workgroup's partial
     int ldx, lddx, bias, fold;
     CtArgs g;             // geometry: dims and reciprocals, ldb = channel stride of dy
 };
-static constexpr int CTB_X = 64 * 128, CTB_STAGE = CTB_X + 4 * 64 * 128, CTB_PATCH = 32 * CT_ROW;
-static constexpr int CTB_LDS = 3 * CTB_STAGE + 4 * CTB_PATCH;
+static constexpr int CTB_PATCH = 32 * CT_ROW;
+__host__ __device__ constexpr int ctb_stage(int ci, int co) { return 64 * ci * 2 + 4 * 64 * co * 4; }
+__host__ __device__ constexpr int ctb_lds(int ci, int co) { return 3 * ctb_stage(ci, co) + 4 * CTB_PATCH; }
+__host__ __device__ constexpr int ctb_per_cu(int ci, int co) { return ci * co <= 512 ? 2 : 1; }   // workgroups: LDS and registers
+__device__ __forceinline__ int ctb_turn(int v, int pieces) { return (v >> 1) & (pieces - 1); }
 
-__global__ __launch_bounds__(512, 2) void convtr_bwd_kernel(CtBArgs a) {
+template <int CI, int CO>
+__global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel(CtBArgs a) {
     extern __shared__ __attribute__((aligned(16))) char ctl[];
+    constexpr int XROW = CI * 2, DROW = CO * 4, PX = XROW / 16, PD = DROW / 16;   // bytes and 16-byte pieces of a row
+    constexpr int XB = 64 * XROW, STAGE = ctb_stage(CI, CO), VI = 64 / PD, ND = 32 / VI;   // voxels a copy of dy, copies of a wave
+    constexpr int NKS = CO / 2, KP = CO / 8, RB = CI / 32, TB = CO / 16;   // 16-deep steps of the data gradient, of a w pair; blocks of 32
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
     const int nvox = a.g.N * a.g.D * a.g.H * a.g.W, nchunks = (nvox + 63) >> 6;
     const int first = blockIdx.x, wgs = gridDim.x, mine = (nchunks - first + wgs - 1) / wgs;
 
-    // copies of a wave: 8 voxels of x, 4 x 8 voxels of one (i, j) row pair of dy
-    const int cij = wv >> 1, csub = wv & 1, cvox = lane >> 3;
+    // copies of a wave: 8 voxels of x, 32 voxels of one (i, j) row pair of dy
+    const int cij = wv >> 1, csub = wv & 1;
     const int64_t cijoff = ct_tap_off(a.g, cij * 2);
     auto stage = [&](int chunk, int buf) __attribute__((always_inline)) {
         const int v0 = chunk * 64;
-        char* st = ctl + buf * CTB_STAGE;
-        {
-            const int lv = wv * 8 + cvox, v = v0 + lv, pc = (lane & 7) ^ ((lv >> 1) & 7);
-            g2lds16_ct(v < nvox ? a.x + (int64_t)v * a.ldx + pc * 8 : a.zero16, st + wv * 1024);
+        char* st = ctl + buf * STAGE;
+        if (lane < 8 * PX) {
+            const int lv = wv * 8 + lane / PX, v = v0 + lv, pc = (lane & (PX - 1)) ^ ctb_turn(lv, PX);
+            g2lds16_ct(v < nvox ? a.x + (int64_t)v * a.ldx + pc * 8 : a.zero16, st + wv * 8 * XROW);
         }
         const uint32_t fo = (uint32_t)ct_fine_origin(a.g, min(v0 + lane, nvox - 1));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int lv = (csub * 4 + i) * 8 + cvox, pc = (lane & 7) ^ ((lv >> 1) & 7);
+        for (int i = 0; i < ND; ++i) {
+            const int lv = (csub * ND + i) * VI + lane / PD, pc = (lane & (PD - 1)) ^ ctb_turn(lv, PD);
             const uint32_t f = (uint32_t)__builtin_amdgcn_ds_bpermute(lv * 4, (int)fo);
-            const bf16_t* src = a.dy + ((int64_t)f + cijoff + (pc >> 2)) * a.g.ldb + (pc & 3) * 8;
-            g2lds16_ct(v0 + lv < nvox ? src : a.zero16, st + CTB_X + (cij * 64 + (csub * 4 + i) * 8) * 128);
+            const bf16_t* src = a.dy + ((int64_t)f + cijoff + pc / KP) * a.g.ldb + (pc & (KP - 1)) * 8;
+            g2lds16_ct(v0 + lv < nvox ? src : a.zero16, st + XB + (cij * 64 + (csub * ND + i) * VI) * DROW);
         }
     };
-    // transposing reads: voxel rows rr (and rr + 4), 32 channels of the lower or upper half of a 128-byte row
+    // transposing reads: voxel rows rr (and rr + 4), 32 channels (64 bytes) of a row
     const int b16 = lane >> 4, s16 = lane & 15, rr = 8 * (b16 >> 1) + (s16 >> 2), pc0 = 2 * (b16 & 1) + ((s16 & 3) >> 1);
-    const uint32_t tlo = rr * 128 + ((pc0 ^ ((rr >> 1) & 7)) << 4) + (s16 & 1) * 8;
-    const uint32_t thi = (rr + 4) * 128 + ((pc0 ^ (((rr + 4) >> 1) & 7)) << 4) + (s16 & 1) * 8;
-    auto frag2 = [&](const char* p, uint32_t h64) __attribute__((always_inline)) {
+    auto toff = [&](int r, int row, int pieces) { return (uint32_t)(r * row + ((pc0 ^ ctb_turn(r, pieces)) << 4) + (s16 & 1) * 8); };
+    const uint32_t xlo = toff(rr, XROW, PX), xhi = toff(rr + 4, XROW, PX), dlo = toff(rr, DROW, PD), dhi = toff(rr + 4, DROW, PD);
+    auto frag2 = [&](const char* p, uint32_t tlo, uint32_t thi, uint32_t h64) __attribute__((always_inline)) {
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + (tlo ^ h64)));
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + (thi ^ h64)));
@@ -983,11 +994,14 @@ __global__ __launch_bounds__(512, 2) void convtr_bwd_kernel(CtBArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = 0.f;
     };
-    // Entering chunk k of the walk: its copies have landed for every wave (the 5 youngest of a wave are the next chunk's; what a wave
+    // Entering chunk k of the walk: its copies have landed for every wave (the 1 + ND youngest of a wave are the next chunk's; what a wave
     // has stored since only makes it wait longer), every wave is done with chunk k - 1, whose buffer takes chunk k + 2.
     auto enter = [&](int k) __attribute__((always_inline)) {
-        if (k + 1 < mine) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (k + 1 < mine) {
+            if constexpr (ND == 4) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+        } else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        static_assert(ND == 4 || ND == 2, "the waits above");
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -996,23 +1010,25 @@ __global__ __launch_bounds__(512, 2) void convtr_bwd_kernel(CtBArgs a) {
     };
 
     if (wv < 4) {
-        const int cb = wv & 1, vb = wv >> 1, row = vb * 32 + l32;
-        bf16x8 wf[16];
+        const int cb = wv & (RB - 1), vb = wv / RB & 1, row = vb * 32 + l32;
+        const bool on = wv < 2 * RB;   // (wave-uniform; the others copy only)
+        bf16x8 wf[NKS];
 #pragma unroll
-        for (int ks = 0; ks < 16; ++ks) wf[ks] = *reinterpret_cast<const bf16x8*>(a.wt + (cb * 32 + l32) * 256 + ks * 16 + half * 8);
-        const uint32_t ro = row * 128 + ((half ^ ((row >> 1) & 7)) << 4);
-        char* const patch = ctl + 3 * CTB_STAGE + wv * CTB_PATCH;
+        for (int ks = 0; ks < NKS; ++ks) wf[ks] = *reinterpret_cast<const bf16x8*>(a.wt + (cb * 32 + l32) * (8 * CO) + ks * 16 + half * 8);
+        const uint32_t ro = row * DROW + ((half ^ ctb_turn(row, PD)) << 4);
+        char* const patch = ctl + 3 * STAGE + wv * CTB_PATCH;
         stage(first, 0);
         if (mine > 1) stage(first + wgs, 1);
         for (int k = 0; k < mine; ++k) {
             enter(k);
-            const char* st = ctl + (k % 3) * CTB_STAGE + CTB_X;
+            if (!on) continue;
+            const char* st = ctl + (k % 3) * STAGE + XB;
             f32x16 acc;
             zero(acc);
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks)   // tap ks / 2, 16 of its 32 channels
+            for (int ks = 0; ks < NKS; ++ks)   // (tap, channel) in order, 16 of them
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    wf[ks], *reinterpret_cast<const bf16x8*>(st + (ks >> 2) * 8192 + (ro ^ (uint32_t)((ks & 3) << 5))), acc, 0, 0, 0);
+                    wf[ks], *reinterpret_cast<const bf16x8*>(st + ks / KP * (64 * DROW) + (ro ^ (uint32_t)((ks & (KP - 1)) << 5))), acc, 0, 0, 0);
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg)
                 *reinterpret_cast<uint2*>(patch + l32 * CT_ROW + (rg * 8 + half * 4) * 2) =
@@ -1029,104 +1045,129 @@ __global__ __launch_bounds__(512, 2) void convtr_bwd_kernel(CtBArgs a) {
         if (a.bias) __syncthreads();
     } else {
         const int ij = wv - 4;
-        f32x16 acc[2][2], sum[2][2];
+        f32x16 acc[RB][TB];
+        double sum[RB][TB][16];
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < TB; ++t) {
                 zero(acc[rb][t]);
-                zero(sum[rb][t]);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[rb][t][r] = 0.0;
             }
+        int chain = 0;
         double bsum = 0.0;
         stage(first, 0);
         if (mine > 1) stage(first + wgs, 1);
-        int chain = 0;
         for (int k = 0; k < mine; ++k) {
             enter(k);
-            const char* st = ctl + (k % 3) * CTB_STAGE;
-            f32x16 bacc;
-            zero(bacc);
+            const char* st = ctl + (k % 3) * STAGE;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                bf16x8 af[2], bf[2];
+                bf16x8 af[RB], bf[TB];
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb) af[rb] = frag2(st + ks * 2048, rb * 64);
+                for (int rb = 0; rb < RB; ++rb) af[rb] = frag2(st + ks * (16 * XROW), xlo, xhi, rb * 64);
 #pragma unroll
-                for (int t = 0; t < 2; ++t) bf[t] = frag2(st + CTB_X + ij * 8192 + ks * 2048, t * 64);
+                for (int t = 0; t < TB; ++t) bf[t] = frag2(st + XB + ij * (64 * DROW) + ks * (16 * DROW), dlo, dhi, t * 64);
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
+                for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) acc[rb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[t], acc[rb][t], 0, 0, 0);
-                if (a.bias) {   // the column sums of dy: products with a row of ones
-                    const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) bacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, one), bf[t], bacc, 0, 0, 0);
-                }
+                    for (int t = 0; t < TB; ++t) acc[rb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[t], acc[rb][t], 0, 0, 0);
             }
-            bsum += (double)bacc[0];   // every row is the sum
             if (++chain == a.fold || k + 1 == mine) {
                 chain = 0;
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
+                for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        sum[rb][t] += acc[rb][t];
+                    for (int t = 0; t < TB; ++t) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) sum[rb][t][r] += (double)acc[rb][t][r];
                         zero(acc[rb][t]);
                     }
             }
-        }
-        float* pb = a.part + (int64_t)blockIdx.x * a.slab + (4 * half * 8 + ij * 2) * 32 + l32;
+            if (a.bias) {   // the column sums of dy: products with a row of ones, every row of which is the sum
+                __builtin_amdgcn_sched_barrier(0);   // (the fragments are read again: kept, they spill)
+                const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+#pragma unroll 1
+                for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+                    for (int t = 0; t < TB; ++t) {
+                        const bf16x8 bf = frag2(st + XB + ij * (64 * DROW) + ks * (16 * DROW), dlo, dhi, t * 64);
+                        f32x16 bacc;
+                        zero(bacc);
+                        bsum += (double)__builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, one), bf, bacc, 0, 0, 0)[0];
+                    }
+            }
+        }
+        float* pb = a.part + (int64_t)blockIdx.x * a.slab + (4 * half * 8 + ij * 2) * CO + l32;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < TB; ++t)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) pb[((rb * 32 + 8 * rg + r) * 8 + t) * 32] = sum[rb][t][4 * rg + r];
+                    for (int r = 0; r < 4; ++r) pb[(rb * 32 + 8 * rg + r) * (8 * CO) + t * 32] = (float)sum[rb][t][4 * rg + r];
         if (a.bias) {
-            double* bs = reinterpret_cast<double*>(ctl + 3 * CTB_STAGE + 2 * CTB_PATCH);   // where waves 2 and 3 have their patches
+            double* bs = reinterpret_cast<double*>(ctl + 3 * STAGE + 2 * CTB_PATCH);   // where waves 2 and 3 have their patches
             __syncthreads();
             if (half == 0) bs[ij * 32 + l32] = bsum;
         }
     }
-    if (a.bias) {
+    if (a.bias) {   // columns l32 of the four row pairs; with 16 channels the pair's second voxel behind the first's
         __syncthreads();
-        const double* bs = reinterpret_cast<const double*>(ctl + 3 * CTB_STAGE + 2 * CTB_PATCH);
-        if (tid < 32) a.part[(int64_t)blockIdx.x * a.slab + 64 * 8 * 32 + tid] = (float)(((bs[tid] + bs[32 + tid]) + bs[64 + tid]) + bs[96 + tid]);
+        const double* bs = reinterpret_cast<const double*>(ctl + 3 * STAGE + 2 * CTB_PATCH);
+        if (tid < CO) {
+            double t = ((bs[tid] + bs[32 + tid]) + bs[64 + tid]) + bs[96 + tid];
+            if (CO == 16) t += ((bs[16 + tid] + bs[48 + tid]) + bs[80 + tid]) + bs[112 + tid];
+            a.part[(int64_t)blockIdx.x * a.slab + CI * 8 * CO + tid] = (float)t;
+        }
     }
 }
 
-bool mfma_convtr_bwd_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_tensor_desc* dxd, const lamp_norm_in* xnorm) {
-    return mfma_convtr_wgrad_supported(xd, dyd, xnorm) && xd->c == 64 && dyd->c == 32 && dxd && dxd->ldc % 8 == 0 && nvox(xd) < ((int64_t)1 << 29);
+static bool ctb_channels(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
+    return (xd->c == 32 || xd->c == 64) && (dyd->c == 16 || dyd->c == 32);
 }
-static int ctb_wgs(const lamp_tensor_desc* xd) {
-    const int64_t chunks = (nvox(xd) + 63) / 64;
-    return (int)(chunks < 256 ? chunks : 256);
+bool mfma_convtr_bwd_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd, const lamp_tensor_desc* dxd, const lamp_norm_in* xnorm) {
+    return mfma_convtr_wgrad_supported(xd, dyd, xnorm) && ctb_channels(xd, dyd) && dxd && dxd->ldc % 8 == 0 && nvox(xd) < ((int64_t)1 << 29);
+}
+static int ctb_wgs(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
+    const int64_t chunks = (nvox(xd) + 63) / 64, fit = 256 * ctb_per_cu(xd->c, dyd->c);
+    return (int)(chunks < fit ? chunks : fit);
 }
 size_t mfma_convtr_bwd_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
-    if (!mfma_convtr_wgrad_supported(xd, dyd, nullptr) || xd->c != 64 || dyd->c != 32) return 0;
-    return align_up((size_t)ctb_wgs(xd) * (64 * 8 * 32 + 32) * sizeof(float));
+    if (!mfma_convtr_wgrad_supported(xd, dyd, nullptr) || !ctb_channels(xd, dyd)) return 0;
+    return align_up((size_t)ctb_wgs(xd, dyd) * (xd->c * 8 * dyd->c + dyd->c) * sizeof(float));
+}
+template <int CI, int CO>
+static lamp_status ctb_launch(const CtBArgs& a, int wgs, hipStream_t s) {
+    if (ensure_dyn_lds((const void*)convtr_bwd_kernel<CI, CO>, ctb_lds(CI, CO)) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL((convtr_bwd_kernel<CI, CO>), dim3(wgs), dim3(512), ctb_lds(CI, CO), s, a);
+    LAMP_CHECK_LAUNCH();
+    return LAMP_OK;
 }
 lamp_status mfma_convtr_bwd(const lamp_tensor_desc* xd, const void* x, const void* wt, const lamp_tensor_desc* dyd, const void* dy,
                             const lamp_tensor_desc* dxd, void* dx, float* dwt, float* dbias, float beta, void* ws, size_t ws_bytes,
                             hipStream_t s) {
     if (ws_bytes < mfma_convtr_bwd_ws_bytes(xd, dyd)) return LAMP_ERR_WORKSPACE;
+    const int Ci = xd->c, Co = dyd->c;
     CtBArgs a;
     a.x = (const bf16_t*)x; a.wt = (const bf16_t*)wt; a.dy = (const bf16_t*)dy; a.dx = (bf16_t*)dx; a.part = (float*)ws;
     a.ldx = xd->ldc; a.lddx = dxd->ldc; a.bias = dbias ? 1 : 0;
-    a.slab = 64 * 8 * 32 + (dbias ? 32 : 0);
-    a.fold = 8;   // 512 voxels, half of what the separate weight gradient chains on 2 x 64^3
+    a.slab = Ci * 8 * Co + (dbias ? Co : 0);
+    // 64->32 pays for its fp64 additions (2 x 64^3: 88 us with one chunk a chain, 82 with four); short walks have few partials to hide
+    // the longer chains behind (2 x 32^3: relative error 4.9e-8 with one, 7.0e-8 with four).
+    a.fold = Ci * Co == 2048 && (nvox(xd) + 63) / 64 > 8 * 256 ? 4 : 1;
     a.zero16 = device_zero16(s);
     if (!a.zero16) return LAMP_ERR_HIP;
     a.g = CtArgs{};
-    a.g.N = xd->n; a.g.D = xd->d; a.g.H = xd->h; a.g.W = xd->w; a.g.Ci = 64; a.g.Co = 32; a.g.ldb = dyd->ldc;
+    a.g.N = xd->n; a.g.D = xd->d; a.g.H = xd->h; a.g.W = xd->w; a.g.Ci = Ci; a.g.Co = Co; a.g.ldb = dyd->ldc;
     ct_set_magic(a.g);
-    const int wgs = ctb_wgs(xd);
-    if (ensure_dyn_lds((const void*)convtr_bwd_kernel, CTB_LDS) != LAMP_OK) return LAMP_ERR_HIP;
-    hipLaunchKernelGGL(convtr_bwd_kernel, dim3(wgs), dim3(512), CTB_LDS, s, a);
-    LAMP_CHECK_LAUNCH();
-    return launch_reduce_partials((const float*)ws, wgs, a.slab, dwt, beta, s, dbias, 64 * 8 * 32);
+    const int wgs = ctb_wgs(xd, dyd);
+    const lamp_status st = Ci == 64 ? (Co == 32 ? ctb_launch<64, 32>(a, wgs, s) : ctb_launch<64, 16>(a, wgs, s))
+                                    : (Co == 32 ? ctb_launch<32, 32>(a, wgs, s) : ctb_launch<32, 16>(a, wgs, s));
+    if (st != LAMP_OK) return st;
+    return launch_reduce_partials((const float*)ws, wgs, a.slab, dwt, beta, s, dbias, Ci * 8 * Co);
 }
 
 }  // namespace lamp
