@@ -461,7 +461,7 @@ __global__ __launch_bounds__(PF > 1 ? 64 : 256) void convtr_dgrad32_kernel(CtArg
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int vb = 0; vb < 2; ++vb)
-                if (rb < nrb) acc[rb][vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[vb], acc[rb][vb], 0, 0, 0);
+                acc[rb][vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[vb], acc[rb][vb], 0, 0, 0);
     };
     if constexpr (PF > 1) {
         static_assert(RB == 1 && 8 % PF == 0, "the units are a multiple of 8");
@@ -495,31 +495,36 @@ __global__ __launch_bounds__(PF > 1 ? 64 : 256) void convtr_dgrad32_kernel(CtArg
                 __builtin_amdgcn_wave_barrier();
             }
     } else {
-        auto gather = [&](int u, uint4 (&q)[4]) __attribute__((always_inline)) {
+        auto gather = [&](int u, vec_u32x4 (&q)[4]) __attribute__((always_inline)) {
             const int tap = u / cpt, c0 = (u - tap * cpt) << 5;
             const int64_t to = ct_tap_off(a, tap);
 #pragma unroll
-            for (int it = 0; it < 4; ++it) q[it] = *reinterpret_cast<const uint4*>(a.b + (fs[it] + to) * a.ldb + c0 + (lane & 3) * 8);
+            for (int it = 0; it < 4; ++it) q[it] = *reinterpret_cast<const vec_u32x4*>(a.b + (fs[it] + to) * a.ldb + c0 + (lane & 3) * 8);
         };
-        auto put = [&](char* buf, const uint4 (&q)[4]) __attribute__((always_inline)) {
+        auto put = [&](char* buf, const vec_u32x4 (&q)[4]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int it = 0; it < 4; ++it) *reinterpret_cast<uint4*>(buf + (it * 16 + (lane >> 2)) * CT_ROW + (lane & 3) * 16) = q[it];
+            for (int it = 0; it < 4; ++it) *reinterpret_cast<vec_u32x4*>(buf + (it * 16 + (lane >> 2)) * CT_ROW + (lane & 3) * 16) = q[it];
         };
-        uint4 q[4];
+        vec_u32x4 q[4];
         gather(0, q);
         put(tb[wv][0], q);
         __builtin_amdgcn_wave_barrier();
+        // No branch in the loop, which would make every wait one for all loads: past the last unit the last one again, past the last block
+        // of rows its weights again, whose products are not stored.
         for (int u = 0; u < units; ++u) {
-            if (u + 1 < units) gather(u + 1, q);
+            // the unit's weights in front of the next unit's dy: loads return in order, and a weight behind dy would wait for it
+            bf16x8 af[2][RB];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) af[ks][rb] = *reinterpret_cast<const bf16x8*>(arow + (int64_t)min(rb, nrb - 1) * 32 * a.K + u * 32 + ks * 16);
+            __builtin_amdgcn_sched_barrier(0);
+            gather(u + 1 < units ? u + 1 : u, q);
+            __builtin_amdgcn_sched_barrier(0);
             const char* cur = tb[wv][u & 1];
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                bf16x8 af[RB];
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) af[rb] = gfrag(arow + (int64_t)rb * 32 * a.K + u * 32 + ks * 16, rb < nrb);
-                multiply(cur, af, ks);
-            }
-            if (u + 1 < units) put(tb[wv][(u + 1) & 1], q);
+            multiply(cur, af[0], 0);
+            multiply(cur, af[1], 1);
+            put(tb[wv][(u + 1) & 1], q);
             __builtin_amdgcn_wave_barrier();
         }
     }
@@ -554,8 +559,9 @@ static void ct_set_magic(CtArgs& a) {
 
 // 32 rows per wave when the volume is small (more workgroups), up to 128 otherwise (measured: from 32768
 // voxels on the fewer re-reads of dy win)
+static constexpr int64_t CT_SMALL = 32768;
 static int ct_row_blocks(int64_t nv, int rows) {
-    if (nv < 32768) return 1;
+    if (nv < CT_SMALL) return 1;
     return rows >= 128 ? 4 : (rows >= 64 ? 2 : 1);
 }
 
@@ -637,9 +643,10 @@ lamp_status mfma_convtr_dgrad(const lamp_tensor_desc* xd, const void* wt, const 
         ct_set_magic(a);
         const int rb = ct_row_blocks(nvox(xd), a.rows);
         dim3 grid(cdiv(nvox(xd), 256), cdiv(a.rows, 32 * rb));
-        if (rb == 4) hipLaunchKernelGGL((convtr_dgrad32_kernel<4>), grid, dim3(256), 0, s, a);
+        if (nvox(xd) < CT_SMALL) hipLaunchKernelGGL((convtr_dgrad32_kernel<1, 4>), dim3(cdiv(nvox(xd), 64), grid.y), dim3(64), 0, s, a);
+        else if (rb == 4) hipLaunchKernelGGL((convtr_dgrad32_kernel<4>), grid, dim3(256), 0, s, a);
         else if (rb == 2) hipLaunchKernelGGL((convtr_dgrad32_kernel<2>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((convtr_dgrad32_kernel<1, 4>), dim3(cdiv(nvox(xd), 64), grid.y), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL((convtr_dgrad32_kernel<1>), grid, dim3(256), 0, s, a);
         LAMP_CHECK_LAUNCH();
         return LAMP_OK;
     }

@@ -18,7 +18,7 @@ def L():
 # The gradient of a coarse voxel takes its eight fine voxels alone: the first slices of a large volume (several row blocks a wave) and
 # these slices as a volume of their own (a row block a wave, units fetched further ahead) give the same bits.
 @pytest.mark.parametrize("ci,co,dims,part", [(128, 64, (32, 32, 32), 16), (64, 32, (35, 31, 31), 7), (256, 128, (33, 32, 31), 1), (96, 32, (37, 30, 30), 5),
-                                             (512, 256, (33, 32, 32), 2)], ids=str)
+                                             (512, 256, (33, 32, 32), 2), (160, 32, (33, 32, 33), 3), (32, 32, (33, 32, 33), 3)], ids=str)
 def test_convtr_dgrad_small_volume(L, ci, co, dims, part):
     g = torch.Generator(device="cuda").manual_seed(ci + part)
     d, h, w = dims
