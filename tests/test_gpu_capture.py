@@ -19,6 +19,14 @@ ws = torch.empty(1 << 27, dtype=torch.uint8, device="cuda")
 if kind == "wgrad":
     dy, dw = torch.randn((*shape[:4], co), device="cuda").to(dt), torch.empty((co, 3, 3, 3, shape[4]), device="cuda")
     call = lambda: L.lamp_conv3d_wgrad(x, dy, dw, ws=ws)
+elif kind == "fwd":
+    wt, dw, st = torch.randn((co, 3, 3, 3, shape[4]), device="cuda").to(dt), torch.empty((*shape[:4], co), device="cuda", dtype=dt), torch.empty((shape[0], co, 2), device="cuda")
+    call = lambda: L.lamp_conv3d_fwd(x, wt, dw, stats_out=st, ws=ws)
+elif kind == "convtr all":
+    wt = torch.randn((shape[4], 2, 2, 2, co), device="cuda").to(dt)
+    dy, dx, db = torch.randn((shape[0], *(2 * s for s in shape[1:4]), co), device="cuda").to(dt), torch.empty_like(x), torch.empty(co, device="cuda")
+    dw = torch.empty(wt.shape, device="cuda")
+    call = lambda: L.lamp_convtr3d_bwd(x, wt, dy, dx=dx, dwt=dw, dbias=db, ws=ws)
 else:
     wt = torch.randn((shape[4], 2, 2, 2, co), device="cuda").to(dt)
     dy, dw = torch.randn((shape[0], *(2 * s for s in shape[1:4]), co), device="cuda").to(dt), torch.empty(wt.shape, device="cuda")
@@ -43,7 +51,8 @@ print("replays equal")
 
 
 @pytest.mark.parametrize("kind,dtype,shape,co", [("wgrad", "bfloat16", (2, 20, 24, 32, 2), 16), ("wgrad", "bfloat16", (1, 20, 24, 28, 24), 40),
-                                                 ("wgrad", "float32", (1, 20, 24, 28, 32), 32), ("convtr", "bfloat16", (1, 10, 12, 14, 16), 8)], ids=str)
+                                                 ("wgrad", "float32", (1, 20, 24, 28, 32), 32), ("convtr", "bfloat16", (1, 10, 12, 14, 16), 8),
+                                                 ("fwd", "float32", (1, 10, 12, 14, 32), 32), ("convtr all", "bfloat16", (1, 10, 12, 14, 32), 16)], ids=str)
 def test_first_call_in_a_capture(kind, dtype, shape, co):
     import conftest
     r = subprocess.run([sys.executable, "-c", CHILD % conftest.ROOT, kind, dtype, str(shape), str(co)], capture_output=True, text=True, timeout=90)
