@@ -13,7 +13,7 @@ lamp_status ensure_dyn_lds(const void* fn, int bytes);
 // ---- norm.hip -------------------------------------------------------------------------------
 // Number of row chunks the stand-alone statistics pass uses for a tensor of `v` voxels per sample.
 int stats_chunks(int64_t v);
-int bwd_chunks(int64_t v);   // of the backward sums
+int bwd_chunks(int64_t v, int C, int dtype);   // of the backward sums
 // Bytes of workspace for the stand-alone statistics pass (partials [N][chunks][C][2] fp32).
 size_t stats_ws_bytes(const lamp_tensor_desc* zd);
 lamp_status launch_splitk_reduce(const float* zpart, int S, const lamp_tensor_desc* zd, void* z, float eps, float* stats,

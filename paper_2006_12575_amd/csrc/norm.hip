@@ -43,16 +43,23 @@ int stats_chunks(int64_t v) {
     return (int)((v + r - 1) / r);
 }
 
-// Chunks of the two-tensor reductions (backward sums, squeeze): 1024 blocks are four to a CU, which is what their registers allow;
-// 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's backward 126 -> 118).
-// The chunks do not depend on the width: other chunks are other roundings of the sums, and a bf16 net amplifies these layer by layer
-// (four rows to every row lane moved the deepest weight gradients of the 5-level base-32 net by 4e-3).
-static int bwd_rows(int64_t v) {
-    const int64_t r = (v + 1023) / 1024;
-    return (int)(r < 32 ? 32 : r);
+// Rows of one partial sum of the two-tensor reductions (backward sums, squeeze).  1024 chunks are four blocks to a CU, which is what
+// their registers allow; 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's
+// backward 126 -> 118).  fp32: at least four rows to every row lane, which are in flight together (training step of the 3-level base-8
+// net on 2 x 64 x 48 x 80: 1297 -> 1273 us).  bf16: the same chunks whatever the width; other chunks are other roundings of the sums, and
+// the layers below amplify these (four rows to every row lane moved weight gradients of a 4-level base-16 net by 3e-3; where it pays
+// most, 16 channels on 3 x 28 x 43 x 39, forward and backward 86 -> 76 us).
+static int bwd_rows(int64_t v, int C, int dtype) {
+    int64_t r = (v + 1023) / 1024;
+    if (r < 32) r = 32;
+    if (dtype == LAMP_F32) {
+        const int rl = C % 4 ? 8 : make_rowmap(C, 4).rl;
+        if (r < 4 * rl) r = 4 * rl;
+    }
+    return (int)r;
 }
-int bwd_chunks(int64_t v) {
-    const int r = bwd_rows(v);
+int bwd_chunks(int64_t v, int C, int dtype) {
+    const int r = bwd_rows(v, C, dtype);
     return (int)((v + r - 1) / r);
 }
 
@@ -621,7 +628,7 @@ extern "C" lamp_status lamp_inorm_relu_noalloc(const lamp_tensor_desc* zd, const
 extern "C" size_t lamp_inorm_relu_bwd_workspace_bytes(const lamp_tensor_desc* zd) {
     if (!desc_ok(zd)) return 0;
     int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    int ch = bwd_chunks(V);
+    int ch = bwd_chunks(V, zd->c, zd->dtype);
     return align_up((size_t)zd->n * ch * zd->c * 2 * sizeof(float)) + align_up((size_t)zd->n * zd->c * 2 * sizeof(float));
 }
 
@@ -638,7 +645,7 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
     if (!ws || ws_bytes < lamp_inorm_relu_bwd_workspace_bytes(zd)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int chunks = bwd_chunks(V);
+    const int chunks = bwd_chunks(V, zd->c, zd->dtype);
     float* partial = (float*)ws;
     float* sums = (float*)((char*)ws + align_up((size_t)zd->n * chunks * zd->c * 2 * sizeof(float)));
     const int vec = pick_vec(zd->dtype, zd->c, {zd->ldc, dyd->ldc, dzd->ldc}, {z, dy, dz});
@@ -647,11 +654,11 @@ extern "C" lamp_status lamp_inorm_relu_bwd(const lamp_tensor_desc* dyd, const vo
         RowMap m = make_rowmap(zd->c, VEC);
         if (nt) {
             hipLaunchKernelGGL((inorm_bwd_partial_kernel<T, VEC, true>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s,
-                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V),
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V, zd->c, zd->dtype),
                            stats, gamma, beta, partial);
         } else {
             hipLaunchKernelGGL((inorm_bwd_partial_kernel<T, VEC, false>), dim3(chunks, zd->n, m.ctiles), dim3(256), 0, s,
-                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V),
+                           (const T*)dy, dyd->ldc, (const T*)z, zd->ldc, V, zd->c, m.cthreads, m.rl, bwd_rows(V, zd->c, zd->dtype),
                            stats, gamma, beta, partial);
         }
     });

@@ -377,7 +377,7 @@ extern "C" size_t lamp_inorm_relu_se_workspace_bytes(const lamp_tensor_desc* zd,
     if (!zd || se_check(zd, cr) != LAMP_OK) return 0;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
     const size_t nc = (size_t)zd->n * zd->c;
-    return align_up(nc * bwd_chunks(V) * 3 * sizeof(float)) + align_up(nc * 3 * sizeof(float)) +
+    return align_up(nc * bwd_chunks(V, zd->c, zd->dtype) * 3 * sizeof(float)) + align_up(nc * 3 * sizeof(float)) +
            align_up(nc * 2 * sizeof(float)) + 2 * align_up(nc * sizeof(float)) +
            align_up((size_t)zd->n * cr * sizeof(float)) + 256;
 }
@@ -400,7 +400,7 @@ extern "C" lamp_status lamp_inorm_relu_se(const lamp_tensor_desc* zd, const void
     if (!ws || ws_bytes < lamp_inorm_relu_se_workspace_bytes(zd, cr)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int C = zd->c, chunks = bwd_chunks(V);
+    const int C = zd->c, chunks = bwd_chunks(V, zd->c, zd->dtype);
     const int rpc = (int)((V + chunks - 1) / chunks);
     Carver cv(ws, ws_bytes);
     float* partial = (float*)cv.take((size_t)zd->n * C * chunks * 3 * sizeof(float));
@@ -458,7 +458,7 @@ extern "C" lamp_status lamp_inorm_relu_se_bwd(const lamp_tensor_desc* dyd, const
     if (!ws || ws_bytes < lamp_inorm_relu_se_workspace_bytes(zd, cr)) return LAMP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t V = (int64_t)zd->d * zd->h * zd->w;
-    const int C = zd->c, N = zd->n, chunks = bwd_chunks(V);
+    const int C = zd->c, N = zd->n, chunks = bwd_chunks(V, zd->c, zd->dtype);
     const int rpc = (int)((V + chunks - 1) / chunks);
     const size_t nc = (size_t)N * C;
     Carver cv(ws, ws_bytes);
