@@ -552,7 +552,7 @@ def net_bench(wl, args, torch, np, S, L, steps, warm, cpu=True):
         run()
     torch.cuda.synchronize()
     if wl == "tiny" and args.graph:
-        # about 60 kernels of a few microseconds: the forward is captured once as a HIP graph on a side stream
+        # 27 kernels of a few microseconds: the forward is captured once as a HIP graph on a side stream
         # (the library only enqueues kernels, so the call is capturable as it stands) and a step replays it
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
@@ -588,11 +588,11 @@ def net_bench(wl, args, torch, np, S, L, steps, warm, cpu=True):
     del ws
     torch.cuda.empty_cache()
     if wl == "tiny":
-        # a chain of about 60 launches on 32^3 ... 8^3 voxels: bound by per-kernel latency; stated against the HBM
+        # a chain of 27 launches on 32^3 ... 8^3 voxels: bound by per-kernel latency; stated against the HBM
         # roofline with the algorithmic bytes of the whole forward, timed through the entry point (no single
         # kernel dominates)
         alg = unet_ideal_bytes(levels, base, 1, K, N, D, H, W, 4)
-        out["roofline"] = {"bound": "hbm", "kernel": "whole forward (a chain of about 60 small fp32 kernels; latency-bound, no dominant kernel)",
+        out["roofline"] = {"bound": "hbm", "kernel": "whole forward (a chain of 27 small fp32 kernels; latency-bound, no dominant kernel)",
                            "achieved": alg / dtm / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": alg / dtm / 1e9 / PEAK_HBM_GBS,
                            "traffic": None, "algorithmic_bytes": alg}
     elif dom is not None:

@@ -860,7 +860,7 @@ __global__ __launch_bounds__(256) void conv3d_regtile_kernel(const bf16_t* __res
 // The matrix-core kernels copy 16-byte pieces (8 channels).  An input with fewer channels than that, or whose voxels do
 // not start on 16 bytes is copied once into whole pieces with zero channels behind the real ones: 16 bytes written per voxel and
 // piece, against the 2 * C_out bytes that the conv writes.  For the data gradient and the weight gradient; the weight gradient of 1
-// to 4 channels has a kernel without padding (conv3d_narrow_wgrad_kernel, 2->16 on 2 x 64 x 80 x 96 voxels: 25 us against 58) and
+// to 4 channels has a kernel without padding (conv3d_narrow_wgrad_kernel, 2->16 on 2 x 64 x 80 x 96 voxels: 22 us against 58) and
 // comes here only where that one's partials would pass 64 MB.
 // The forward pass keeps the scalar kernel's order of sums, on saturated image regions a sum that rounds the other way moves whole
 // regions over the ReLU: 2 to 4 channels on the fp32 matrix instruction (conv3d_f32.hip), 1 on kernels of its own, the rest, which are
