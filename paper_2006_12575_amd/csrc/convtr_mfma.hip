@@ -945,7 +945,7 @@ lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const l
 struct CtBArgs {
     const bf16_t* x; const bf16_t* wt; const bf16_t* dy; bf16_t* dx;
     const bf16_t* zero16;
-    float* part;          // [workgroup][CI][8][CO], then [CO] bias sums where `bias`
+    float* part;          // [workgroup][CI][8][CO], then [2][CO] bias sums (in two floats each) where `bias`
     int slab;             // floats of a workgroup's partial
     int ldx, lddx, bias, fold;
     CtArgs g;             // geometry: dims and reciprocals, ldb = channel stride of dy
@@ -1127,7 +1127,9 @@ __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel
         if (tid < CO) {
             double t = ((bs[tid] + bs[32 + tid]) + bs[64 + tid]) + bs[96 + tid];
             if (CO == 16) t += ((bs[16 + tid] + bs[48 + tid]) + bs[80 + tid]) + bs[112 + tid];
-            a.part[(int64_t)blockIdx.x * a.slab + CI * 8 * CO + tid] = (float)t;
+            float* o = a.part + (int64_t)blockIdx.x * a.slab + CI * 8 * CO + tid;
+            o[0] = (float)t;
+            o[CO] = (float)(t - (double)(float)t);
         }
     }
 }
@@ -1144,7 +1146,7 @@ static int ctb_wgs(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
 }
 size_t mfma_convtr_bwd_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dyd) {
     if (!mfma_convtr_wgrad_supported(xd, dyd, nullptr) || !ctb_channels(xd, dyd)) return 0;
-    return align_up((size_t)ctb_wgs(xd, dyd) * (xd->c * 8 * dyd->c + dyd->c) * sizeof(float));
+    return align_up((size_t)ctb_wgs(xd, dyd) * (xd->c * 8 * dyd->c + 2 * dyd->c) * sizeof(float));
 }
 template <int CI, int CO>
 static lamp_status ctb_launch(const CtBArgs& a, int wgs, hipStream_t s) {
@@ -1161,7 +1163,7 @@ lamp_status mfma_convtr_bwd(const lamp_tensor_desc* xd, const void* x, const voi
     CtBArgs a;
     a.x = (const bf16_t*)x; a.wt = (const bf16_t*)wt; a.dy = (const bf16_t*)dy; a.dx = (bf16_t*)dx; a.part = (float*)ws;
     a.ldx = xd->ldc; a.lddx = dxd->ldc; a.bias = dbias ? 1 : 0;
-    a.slab = Ci * 8 * Co + (dbias ? Co : 0);
+    a.slab = Ci * 8 * Co + (dbias ? 2 * Co : 0);
     // 64->32 pays for its fp64 additions (2 x 64^3: 88 us with one chunk a chain, 82 with four); short walks have few partials to hide
     // the longer chains behind (2 x 32^3: relative error 4.9e-8 with one, 7.0e-8 with four).
     a.fold = Ci * Co == 2048 && (nvox(xd) + 63) / 64 > 8 * 256 ? 4 : 1;
@@ -1174,7 +1176,7 @@ lamp_status mfma_convtr_bwd(const lamp_tensor_desc* xd, const void* x, const voi
     const lamp_status st = Ci == 64 ? (Co == 32 ? ctb_launch<64, 32>(a, wgs, s) : ctb_launch<64, 16>(a, wgs, s))
                                     : (Co == 32 ? ctb_launch<32, 32>(a, wgs, s) : ctb_launch<32, 16>(a, wgs, s));
     if (st != LAMP_OK) return st;
-    return launch_reduce_partials((const float*)ws, wgs, a.slab, dwt, beta, s, dbias, Ci * 8 * Co);
+    return launch_reduce_partials((const float*)ws, wgs, Ci * 8 * Co + (dbias ? Co : 0), dwt, beta, s, dbias, Ci * 8 * Co);
 }
 
 }  // namespace lamp

@@ -51,7 +51,7 @@ lamp_status launch_repack_batch(const RepackJob* jobs, int n, hipStream_t s);
 void set_repack_table(const RepackTable* t);
 const bf16_t* find_prepacked(const void* w, bool dgrad, int kind, int Cout, int Cin);
 const bf16_t* device_zero16(hipStream_t s);  // 16 zero bytes on the current device, nullptr on failure
-// out2: the outputs from O1 on go there (nullptr: one tensor of O).
+// out2: the outputs from O1 on go there (nullptr: one tensor of O); a part holds two floats of each, all high ones, then all low ones.
 lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s, float* out2 = nullptr,
                                    int64_t O1 = 0);
 // Column sums of a [rows, C] tensor with row stride ld: out[c] = beta*out[c] + sum_r t[r][c].

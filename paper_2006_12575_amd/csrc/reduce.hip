@@ -40,7 +40,8 @@ const bf16_t* device_zero16(hipStream_t s) {
 // Bound: HBM (the parts are read once).  VO = 4 makes a part's row a run of whole 64-byte pieces also where SL lanes leave a block
 // few outputs (64->32 transposed conv, 512 parts of 16384: 37 -> 12 us, with the right number of lanes less), and gives a thread
 // enough in flight where there are few parts of many outputs (256->256 conv weights, 4 parts of 1.8 M: 21.6 -> 10.6 us).
-template <int SL, int VO>
+// LO: the outputs from O1 on come in two floats a part, high parts and, as many outputs behind them, what these leave of the sum.
+template <int SL, int VO, bool LO>
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ part, int S, int64_t O,
                                                               float* __restrict__ out, float beta, float* __restrict__ out2, int64_t O1) {
     constexpr int GPB = 256 / SL;
@@ -57,23 +58,27 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 #pragma unroll
         for (int i = 0; i < VO; ++i) acc[i] += (double)v[i];
     };
-    if (o < O) {
-        // eight loads in flight, added in the order of the parts: a loop of load-then-add is a chain of memory latencies
-        const float* p = part + o;
+    const int64_t ld = LO ? 2 * O - O1 : O;
+    // eight loads in flight, added in the order of the parts: a loop of load-then-add is a chain of memory latencies
+    auto walk = [&](const float* p) __attribute__((always_inline)) {
         int s = sl;
         for (; s + 7 * SL < S; s += 8 * SL) {
             raw v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = Vec<float, VO>::raw_load(p + (int64_t)(s + u * SL) * O);
+            for (int u = 0; u < 8; ++u) v[u] = Vec<float, VO>::raw_load(p + (int64_t)(s + u * SL) * ld);
 #pragma unroll
             for (int u = 0; u < 8; ++u) add(v[u]);
         }
         for (; s + SL < S; s += 2 * SL) {
-            const raw v0 = Vec<float, VO>::raw_load(p + (int64_t)s * O), v1 = Vec<float, VO>::raw_load(p + (int64_t)(s + SL) * O);
+            const raw v0 = Vec<float, VO>::raw_load(p + (int64_t)s * ld), v1 = Vec<float, VO>::raw_load(p + (int64_t)(s + SL) * ld);
             add(v0);
             add(v1);
         }
-        if (s < S) add(Vec<float, VO>::raw_load(p + (int64_t)s * O));
+        if (s < S) add(Vec<float, VO>::raw_load(p + (int64_t)s * ld));
+    };
+    if (o < O) {
+        walk(part + o);
+        if (LO && o >= O1) walk(part + o + (O - O1));
     }
     if constexpr (SL > 1) {
 #pragma unroll
@@ -109,13 +114,13 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 // short blocks of many lanes take turns, and their many small reads of every part's row cost more than a longer loop over the parts
 // (27648 outputs, 256 parts: 64 lanes 11.0 us, 32 to 8 lanes 3.7, one lane 14.8; 16384 x 512: 12.3, 4.3 with 32).  64 lanes pay for
 // a few outputs only (32 x 4096: 4.4 us, with 32 lanes 6.0; 864 x 3000: 6.9 and 5.4).
-template <int VO>
+template <int VO, bool LO>
 static void reduce_launch(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s, float* out2, int64_t O1) {
     const int64_t g = O / VO;
     int sl = 1;
     while (2 * sl <= (O <= 256 ? 64 : 32) && 2 * sl <= S && (g * 2 * sl + 255) / 256 < 1024) sl *= 2;
 #define LAMP_REDUCE(SL) \
-    case SL: hipLaunchKernelGGL((reduce_partials_kernel<SL, VO>), dim3(cdiv(g, 256 / SL)), dim3(256), 0, s, part, S, O, out, beta, out2, O1); break
+    case SL: hipLaunchKernelGGL((reduce_partials_kernel<SL, VO, LO>), dim3(cdiv(g, 256 / SL)), dim3(256), 0, s, part, S, O, out, beta, out2, O1); break
     switch (sl) {
         LAMP_REDUCE(1);
         LAMP_REDUCE(2);
@@ -129,9 +134,13 @@ static void reduce_launch(const float* part, int S, int64_t O, float* out, float
 }
 
 lamp_status launch_reduce_partials(const float* part, int S, int64_t O, float* out, float beta, hipStream_t s, float* out2, int64_t O1) {
-    if (!out2) O1 = O;
-    if (O % 4 == 0 && O1 % 4 == 0 && aligned16(part) && aligned16(out) && aligned16(out2)) reduce_launch<4>(part, S, O, out, beta, s, out2, O1);
-    else reduce_launch<1>(part, S, O, out, beta, s, out2, O1);
+    const bool lo = out2 != nullptr;
+    if (!lo) O1 = O;
+    const bool vec = O % 4 == 0 && O1 % 4 == 0 && aligned16(part) && aligned16(out) && aligned16(out2);
+    if (vec && lo) reduce_launch<4, true>(part, S, O, out, beta, s, out2, O1);
+    else if (vec) reduce_launch<4, false>(part, S, O, out, beta, s, out2, O1);
+    else if (lo) reduce_launch<1, true>(part, S, O, out, beta, s, out2, O1);
+    else reduce_launch<1, false>(part, S, O, out, beta, s, out2, O1);
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }
