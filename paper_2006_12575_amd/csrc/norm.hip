@@ -46,7 +46,9 @@ int stats_chunks(int64_t v) {
 // Rows of one partial sum of the two-tensor reductions (backward sums, squeeze).  1024 chunks are four blocks to a CU, which is what
 // their registers allow; 2048 at three to a CU left a third round two thirds full (64 channels at 128^3: squeeze 77 -> 65 us, gate's
 // backward 126 -> 118).  fp32: at least four rows to every row lane, which are in flight together (training step of the 3-level base-8
-// net on 2 x 64 x 48 x 80: 1297 -> 1273 us).  bf16: the same chunks whatever the width; other chunks are other roundings of the sums, and
+// net on 2 x 64 x 48 x 80: 1297 -> 1273 us), and a thread's sums in fp64, without which they round more than over 32 rows (dgamma and
+// dbeta of 8 channels on 24 x 32 x 40, relative to the square root of the rows: 5.9e-8 and 3.9e-8 over 32 rows, 6.5e-8 and 5.4e-8 in
+// fp32, 5.0e-8 and 3.9e-8 so; the time is the same).  bf16: the same chunks whatever the width; other chunks are other roundings of the sums, and
 // the layers below amplify these (four rows to every row lane moved weight gradients of a 4-level base-16 net by 3e-3; where it pays
 // most, 16 channels on 3 x 28 x 43 x 39, forward and backward 86 -> 76 us).
 static int bwd_rows(int64_t v, int C, int dtype) {
@@ -349,7 +351,8 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
                                                                 const float* __restrict__ gamma,
                                                                 const float* __restrict__ beta,
                                                                 float* __restrict__ partial) {
-    __shared__ float red[2 * 256 * VEC], part[256];
+    typedef typename SumOf<T>::type S;
+    __shared__ S red[2 * 256 * VEC], part[256];
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
@@ -357,10 +360,10 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
     const int64_t rbeg = (int64_t)chunk * rows_per_chunk;
     int64_t rend = rbeg + rows_per_chunk;
     if (rend > V) rend = V;
-    float sq[2][VEC];
+    S sq[2][VEC];
     auto &s = sq[0], &q = sq[1];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) { s[i] = 0.f; q[i] = 0.f; }
+    for (int i = 0; i < VEC; ++i) { s[i] = 0; q[i] = 0; }
     if (r0 < rl && cv * VEC < C) {
         NormIn nm{stats, gamma, beta, C, 1};
         float a[VEC], b[VEC], mean[VEC], rstd[VEC];
@@ -373,15 +376,15 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
                 float u = norm_u(v[i], a[i], b[i]);
                 float gg = u > 0.f ? g[i] : 0.f;
                 float zh = (v[i] - mean[i]) * rstd[i];
-                s[i] += gg;
-                q[i] = fmaf(gg, zh, q[i]);
+                s[i] += (S)gg;
+                q[i] = sum_fma(gg, zh, q[i]);
             }
         };
         int64_t r = rbeg + r0;
         // Four rows in flight; the additions keep the row order.  The first half of the rows leaves its sums in the thread's own slots
-        // of `red`, so that a chain is no longer than with twice as many chunks (128 channels on 96^3, fp32: relative error of dgamma
-        // 1.1e-7 with 2048 chunks, 1.5e-7 with 1024 in one chain, 1.0e-7 so).
-        const bool halves = rows_per_chunk >= 16 * rl;   // a chain worth cutting
+        // of `red`, so that a chain is no longer than with twice as many chunks (128 channels on 96^3: relative error of dgamma 1.1e-7 with
+        // 2048 chunks, 1.5e-7 with 1024 in one chain, 1.0e-7 so).  fp64 sums need no cut.
+        const bool halves = sizeof(S) == 4 && rows_per_chunk >= 16 * rl;   // a chain worth cutting
 #pragma unroll 1
         for (int half = halves ? 0 : 1; half < 2; ++half) {
             const int64_t stop = half ? rend : half_rows(rbeg, rows_per_chunk, rl, rend);
@@ -400,7 +403,8 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
                     add_row(v, g);
                 }
             }
-            if (half == 0) stash(sq, red);
+            if constexpr (sizeof(S) == 4)
+                if (half == 0) stash(sq, red);
         }
         for (; r < rend; r += rl) {
             float v[VEC], g[VEC];
@@ -408,7 +412,8 @@ __global__ __launch_bounds__(256, 4) void inorm_bwd_partial_kernel(const T* __re
             Vec<T, VEC>::load(gb + r * ldg, g);
             add_row(v, g);
         }
-        if (halves) unstash(sq, red);
+        if constexpr (sizeof(S) == 4)
+            if (halves) unstash(sq, red);
     }
     block_fold<double>(sq, cthreads, rl, red, part, [&](int k, int e, float t) {
         const int c = blockIdx.z * 256 * VEC + e;

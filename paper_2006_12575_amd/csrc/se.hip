@@ -19,13 +19,15 @@ namespace lamp {
 // MODE 1 (backward): sum dy*a, sum dy*mask, sum dy*mask*zhat
 // partial[((n*chunks + chunk)*C + c)*3 + k]
 // NT (backward): z is read past the caches, so that what they hold at the end is dy for the apply pass.
+// fp32 backward: three blocks a CU hold its fp64 sums (64 channels on 2 x 96^3, whole case: 660 us, 725 with four and spills).
 template <typename T, int VEC, int MODE, bool NT>
-__global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z, int ldz,
+__global__ __launch_bounds__(256, sizeof(T) == 4 && MODE == 1 ? 3 : 4) void se_partial_kernel(const T* __restrict__ dy, int ldg, const T* __restrict__ z, int ldz,
                                                          int64_t V, int C, int cthreads, int rl, int rows_per_chunk,
                                                          const float* __restrict__ stats, const float* __restrict__ gamma,
                                                          const float* __restrict__ beta, float* __restrict__ partial) {
     constexpr int K = 3;
-    __shared__ float red[K * 256 * VEC], part[256];
+    typedef typename SumOf<T>::type S;
+    __shared__ S red[K * 256 * VEC], part[256];
     const int tid = threadIdx.x;
     const int cl = tid % cthreads, r0 = tid / cthreads;
     const int cv = blockIdx.z * 256 + cl;
@@ -33,11 +35,11 @@ __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict_
     const int64_t rbeg = (int64_t)chunk * rows_per_chunk;
     int64_t rend = rbeg + rows_per_chunk;
     if (rend > V) rend = V;
-    float s[K][VEC];
+    S s[K][VEC];
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) s[k][i] = 0.f;
+        for (int i = 0; i < VEC; ++i) s[k][i] = 0;
     if (r0 < rl && cv * VEC < C) {
         NormIn nm{stats, gamma, beta, C, 1};
         float a[VEC], b[VEC], mean[VEC], rstd[VEC];
@@ -51,20 +53,20 @@ __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict_
                 const bool on = u > 0.f;
                 const float zh = (v[i] - mean[i]) * rstd[i];
                 if (MODE == 0) {
-                    s[0][i] += on ? u : 0.f;
-                    s[1][i] += on ? 1.f : 0.f;
-                    s[2][i] += on ? zh : 0.f;
+                    s[0][i] += (S)(on ? u : 0.f);
+                    s[1][i] += (S)(on ? 1.f : 0.f);
+                    s[2][i] += (S)(on ? zh : 0.f);
                 } else {
                     const float gg = on ? g[i] : 0.f;
-                    s[0][i] = fmaf(gg, u, s[0][i]);
-                    s[1][i] += gg;
-                    s[2][i] = fmaf(gg, zh, s[2][i]);
+                    s[0][i] = sum_fma(gg, u, s[0][i]);
+                    s[1][i] += (S)gg;
+                    s[2][i] = sum_fma(gg, zh, s[2][i]);
                 }
             }
         };
         int64_t r = rbeg + r0;
         // four rows in flight; the additions keep the row order, in two halves as in the backward sums of norm.hip
-        const bool halves = rows_per_chunk >= 16 * rl;   // a chain worth cutting
+        const bool halves = sizeof(S) == 4 && rows_per_chunk >= 16 * rl;   // a chain worth cutting
 #pragma unroll 1
         for (int half = halves ? 0 : 1; half < 2; ++half) {
             const int64_t stop = half ? rend : half_rows(rbeg, rows_per_chunk, rl, rend);
@@ -83,7 +85,8 @@ __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict_
                     add_row(v, g);
                 }
             }
-            if (half == 0) stash(s, red);
+            if constexpr (sizeof(S) == 4)
+                if (half == 0) stash(s, red);
         }
         for (; r < rend; r += rl) {
             float v[VEC], g[VEC];
@@ -91,7 +94,8 @@ __global__ __launch_bounds__(256, 4) void se_partial_kernel(const T* __restrict_
             if (MODE == 1) Vec<T, VEC>::load(gb + r * ldg, g);
             add_row(v, g);
         }
-        if (halves) unstash(s, red);
+        if constexpr (sizeof(S) == 4)
+            if (halves) unstash(s, red);
     }
     block_fold<double>(s, cthreads, rl, red, part, [&](int k, int e, float t) {
         const int c = blockIdx.z * 256 * VEC + e;

@@ -195,13 +195,20 @@ template <int NV, int VEC> __device__ __forceinline__ void unstash(float (&v)[NV
         for (int i = 0; i < VEC; ++i) v[k][i] += red[k * (256 * VEC) + threadIdx.x * VEC + i];
 }
 
+// Type of a thread's backward sums: fp64 for fp32 tensors, whose chunks have several rows to a thread, fp32 for bf16 (bwd_rows, norm.hip).
+template <typename T> struct SumOf { typedef float type; };
+template <> struct SumOf<float> { typedef double type; };
+__device__ __forceinline__ float sum_fma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double sum_fma(float a, float b, double c) { return fma((double)a, (double)b, c); }
+
 // Sums NV sets of VEC values per thread over the row lanes of a block (thread = row lane * cthreads + channel-vector lane) and
 // hands each to put(set, channel of the block, sum).  All 256 threads add: with only the first row lane's cthreads threads at
 // work, a 16-channel bf16 tensor left 2 threads a serial chain of 2048 LDS reads, which was 45 of the 60 us of its backward sums
 // (2 x 64 x 80 x 96 voxels).  `red`: NV * 256 * VEC floats, `part`: 256 floats.  A fixed order for a given cthreads.  A: double in the
 // backward sums, whose chunks are the longest: these are the largest addends of a partial and round most.  NT: threads of the block, of which the first 256 have sums.
-template <typename A = float, int NT = 256, int NV, int VEC, typename F>
-__device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthreads, int rl, float* red, float* part, F put) {
+// V: type of the threads' sums, `red` and `part`.
+template <typename A = float, int NT = 256, int NV, int VEC, typename V, typename F>
+__device__ __forceinline__ void block_fold(const V (&v)[NV][VEC], int cthreads, int rl, V* red, V* part, F put) {
     const int tid = threadIdx.x, nc = cthreads * VEC, nout = NV * nc;
     const bool on = NT == 256 || tid < 256;
     if (on)
@@ -215,7 +222,7 @@ __device__ __forceinline__ void block_fold(const float (&v)[NV][VEC], int cthrea
         A t = 0;
         if (on && p < P)
             for (int r = p; r < rl; r += P) t += (A)red[k * (256 * VEC) + r * nc + e];
-        if (on) part[tid] = (float)t;
+        if (on) part[tid] = (V)t;
         __syncthreads();
         if (tid < nout) {
             t = (A)part[tid];

@@ -32,18 +32,21 @@ def test_convtr_dgrad_small_volume(L, ci, co, dims, part):
     assert torch.equal(small, dx[:, :part])
 
 
-# dgamma of one sample, every sum written out: chunks of max(32, V / 1024) rows whatever the width (fp32, which has no roundings to
-# amplify: at least four to a row lane), the row lanes of a 256-thread block, each a chain of fused multiply-adds, folded in fp64 (up to 64 channels in 256 / (2 C) shares, rounded to fp32), the chunks in fp64.
+# dgamma of one sample, every rounding of its sum written out: chunks of max(32, V / 1024) rows whatever the width, the row lanes of a
+# 256-thread block, each a chain of fused multiply-adds, folded in fp64 (up to 64 channels in 256 / (2 C) shares, rounded to fp32), the
+# chunks in fp64.  fp32 tensors: at least four rows to a row lane, fp64 within a chunk.
 def dgamma_of(dy, z, mean, rstd, vec):
     v, c = z.shape
     f = np.float32
     rl = 256 // min(c // vec, 256)
     rows = max(32, -(-v // 1024), 4 * rl if vec == 4 else 0)
     chunks = -(-v // rows)
-    rounds = -(-rows // rl)
     zh = ((z - mean) * rstd).astype(f).astype(np.float64)
     g = np.zeros((chunks * rows, c)); g[:v] = dy
     h = np.zeros((chunks * rows, c)); h[:v] = zh
+    if vec == 4:
+        return (g * h).reshape(chunks, rows, c).sum(1).astype(f).astype(np.float64).sum(0).astype(f)
+    rounds = -(-rows // rl)
     acc = np.zeros((chunks, rl, c), f)
     for k in range(rounds):
         n = min(rl, rows - k * rl)
