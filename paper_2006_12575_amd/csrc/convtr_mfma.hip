@@ -941,7 +941,7 @@ lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const l
 // Sums of the weight gradient: chains of `fold` chunks, added in fp64; a partial per workgroup.  Relative error against the separate
 // kernel's: 64->32 on 2 x 64^3 7.5e-8 and 1.4e-7, on 2 x 32^3 4.9e-8 and 5.3e-8; 32->16 on 2 x 64^3 4.8e-8 and 7.7e-8.
 // Bound: HBM.  Data, weight and bias gradient with all launches, against separate kernels (dy read twice): 64->32 on 2 x 64^3 (402 MB)
-// 162 -> 83 us, on 2 x 32^3 40 -> 22; 32->16 on 2 x 64^3 146 -> 37, on 2 x 16^3 22 -> 10; 32->32 on 2 x 64^3 144 -> 66, 64->16 165 -> 55.
+// 162 -> 83 us, on 2 x 32^3 40 -> 23; 32->16 on 2 x 64^3 146 -> 37, on 2 x 16^3 22 -> 10; 32->32 on 2 x 64^3 144 -> 67, 64->16 165 -> 51.
 struct CtBArgs {
     const bf16_t* x; const bf16_t* wt; const bf16_t* dy; bf16_t* dx;
     const bf16_t* zero16;
@@ -1064,6 +1064,13 @@ __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel
             }
         int chain = 0;
         double bsum = 0.0;
+        constexpr bool APART = RB * TB == 4;   // no registers left for the bias products beside the others
+        auto bias_add = [&](const bf16x8& d) __attribute__((always_inline)) {   // column sums of dy: a row of ones times dy, every row of which is the sum
+            const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+            f32x16 z;
+            zero(z);
+            bsum += (double)__builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, one), d, z, 0, 0, 0)[0];
+        };
         stage(first, 0);
         if (mine > 1) stage(first + wgs, 1);
         for (int k = 0; k < mine; ++k) {
@@ -1080,6 +1087,9 @@ __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel
                 for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                     for (int t = 0; t < TB; ++t) acc[rb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bf[t], acc[rb][t], 0, 0, 0);
+                if (!APART && a.bias)
+#pragma unroll
+                    for (int t = 0; t < TB; ++t) bias_add(bf[t]);
             }
             if (++chain == a.fold || k + 1 == mine) {
                 chain = 0;
@@ -1092,18 +1102,12 @@ __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel
                         zero(acc[rb][t]);
                     }
             }
-            if (a.bias) {   // the column sums of dy: products with a row of ones, every row of which is the sum
+            if (APART && a.bias) {
                 __builtin_amdgcn_sched_barrier(0);   // (the fragments are read again: kept, they spill)
-                const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
 #pragma unroll 1
                 for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                    for (int t = 0; t < TB; ++t) {
-                        const bf16x8 bf = frag2(st + XB + ij * (64 * DROW) + ks * (16 * DROW), dlo, dhi, t * 64);
-                        f32x16 bacc;
-                        zero(bacc);
-                        bsum += (double)__builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, one), bf, bacc, 0, 0, 0)[0];
-                    }
+                    for (int t = 0; t < TB; ++t) bias_add(frag2(st + XB + ij * (64 * DROW) + ks * (16 * DROW), dlo, dhi, t * 64));
             }
         }
         float* pb = a.part + (int64_t)blockIdx.x * a.slab + (4 * half * 8 + ij * 2) * CO + l32;
