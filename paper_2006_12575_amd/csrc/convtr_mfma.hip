@@ -938,8 +938,8 @@ lamp_status mfma_convtr_wgrad(const lamp_tensor_desc* xd, const void* x, const l
 // LDS rows are the channels of x, and both voxels of a w pair of dy (consecutive bytes of memory, so a copy instruction fetches 1 KB in
 // a row), 64 or 128 bytes, their 16-byte pieces in an order that turns with the voxel pair, so that neither the plain reads (16 voxels
 // side by side) nor the transposing ones (4 voxels x 32 bytes) meet in a bank.
-// Sums of the weight gradient: chains of `fold` chunks, added in fp64; a partial per workgroup.  Relative error against the separate
-// kernel's: 64->32 on 2 x 64^3 7.5e-8 and 1.4e-7, on 2 x 32^3 4.9e-8 and 5.3e-8; 32->16 on 2 x 64^3 4.8e-8 and 7.7e-8.
+// Sums of the weight gradient: chains of `fold` chunks, added in S; a partial per workgroup.  Relative error against the separate
+// kernel's: 64->32 on 2 x 64^3 9.0e-8 and 1.4e-7, on 2 x 32^3 4.9e-8 and 5.3e-8; 32->16 on 2 x 64^3 4.8e-8 and 7.7e-8.
 // Bound: HBM.  Data, weight and bias gradient with all launches, against separate kernels (dy read twice): 64->32 on 2 x 64^3 (402 MB)
 // 162 -> 83 us, on 2 x 32^3 40 -> 23; 32->16 on 2 x 64^3 146 -> 37, on 2 x 16^3 22 -> 10; 32->32 on 2 x 64^3 144 -> 67, 64->16 165 -> 51.
 struct CtBArgs {
@@ -956,7 +956,7 @@ __host__ __device__ constexpr int ctb_lds(int ci, int co) { return 3 * ctb_stage
 __host__ __device__ constexpr int ctb_per_cu(int ci, int co) { return ci * co <= 512 ? 2 : 1; }   // workgroups: LDS and registers
 __device__ __forceinline__ int ctb_turn(int v, int pieces) { return (v >> 1) & (pieces - 1); }
 
-template <int CI, int CO>
+template <int CI, int CO, typename S>
 __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel(CtBArgs a) {
     extern __shared__ __attribute__((aligned(16))) char ctl[];
     constexpr int XROW = CI * 2, DROW = CO * 4, PX = XROW / 16, PD = DROW / 16;   // bytes and 16-byte pieces of a row
@@ -1053,18 +1053,18 @@ __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel
     } else {
         const int ij = wv - 4;
         f32x16 acc[RB][TB];
-        double sum[RB][TB][16];
+        S sum[RB][TB][16];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int t = 0; t < TB; ++t) {
                 zero(acc[rb][t]);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sum[rb][t][r] = 0.0;
+                for (int r = 0; r < 16; ++r) sum[rb][t][r] = 0;
             }
         int chain = 0;
         double bsum = 0.0;
-        constexpr bool APART = RB * TB == 4;   // no registers left for the bias products beside the others
+        constexpr bool APART = sizeof(S) == 8 && RB * TB == 4;   // no registers left for the bias products beside the others
         auto bias_add = [&](const bf16x8& d) __attribute__((always_inline)) {   // column sums of dy: a row of ones times dy, every row of which is the sum
             const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
             f32x16 z;
@@ -1098,7 +1098,7 @@ __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel
 #pragma unroll
                     for (int t = 0; t < TB; ++t) {
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) sum[rb][t][r] += (double)acc[rb][t][r];
+                        for (int r = 0; r < 16; ++r) sum[rb][t][r] += (S)acc[rb][t][r];
                         zero(acc[rb][t]);
                     }
             }
@@ -1152,10 +1152,10 @@ size_t mfma_convtr_bwd_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_de
     if (!mfma_convtr_wgrad_supported(xd, dyd, nullptr) || !ctb_channels(xd, dyd)) return 0;
     return align_up((size_t)ctb_wgs(xd, dyd) * (xd->c * 8 * dyd->c + 2 * dyd->c) * sizeof(float));
 }
-template <int CI, int CO>
+template <int CI, int CO, typename S = double>
 static lamp_status ctb_launch(const CtBArgs& a, int wgs, hipStream_t s) {
-    if (ensure_dyn_lds((const void*)convtr_bwd_kernel<CI, CO>, ctb_lds(CI, CO)) != LAMP_OK) return LAMP_ERR_HIP;
-    hipLaunchKernelGGL((convtr_bwd_kernel<CI, CO>), dim3(wgs), dim3(512), ctb_lds(CI, CO), s, a);
+    if (ensure_dyn_lds((const void*)convtr_bwd_kernel<CI, CO, S>, ctb_lds(CI, CO)) != LAMP_OK) return LAMP_ERR_HIP;
+    hipLaunchKernelGGL((convtr_bwd_kernel<CI, CO, S>), dim3(wgs), dim3(512), ctb_lds(CI, CO), s, a);
     LAMP_CHECK_LAUNCH();
     return LAMP_OK;
 }
@@ -1168,8 +1168,10 @@ lamp_status mfma_convtr_bwd(const lamp_tensor_desc* xd, const void* x, const voi
     a.x = (const bf16_t*)x; a.wt = (const bf16_t*)wt; a.dy = (const bf16_t*)dy; a.dx = (bf16_t*)dx; a.part = (float*)ws;
     a.ldx = xd->ldc; a.lddx = dxd->ldc; a.bias = dbias ? 1 : 0;
     a.slab = Ci * 8 * Co + (dbias ? 2 * Co : 0);
-    // 64->32 pays for its fp64 additions (2 x 64^3: 88 us with one chunk a chain, 82 with four); short walks have few partials to hide
-    // the longer chains behind (2 x 32^3: relative error 4.9e-8 with one, 7.0e-8 with four).
+    // 64->32 pays for its fp64 sums, which leave no registers for the bias products beside the others: in long walks chains of four chunks
+    // and fp32 sums (2 x 64^3, forward and backward: 145.8 us, 147.3 with fp64 sums; relative error 9.0e-8 and 7.5e-8, separate kernels
+    // 1.4e-7; on 2 x 96^3 1.2e-7 and 2.9e-7).  Short walks have few partials to hide this behind (2 x 32^3: 4.9e-8 so, 7.0e-8 with chains
+    // of four, separate kernels 5.3e-8).
     a.fold = Ci * Co == 2048 && (nvox(xd) + 63) / 64 > 8 * 256 ? 4 : 1;
     a.zero16 = device_zero16(s);
     if (!a.zero16) return LAMP_ERR_HIP;
@@ -1177,7 +1179,7 @@ lamp_status mfma_convtr_bwd(const lamp_tensor_desc* xd, const void* x, const voi
     a.g.N = xd->n; a.g.D = xd->d; a.g.H = xd->h; a.g.W = xd->w; a.g.Ci = Ci; a.g.Co = Co; a.g.ldb = dyd->ldc;
     ct_set_magic(a.g);
     const int wgs = ctb_wgs(xd, dyd);
-    const lamp_status st = Ci == 64 ? (Co == 32 ? ctb_launch<64, 32>(a, wgs, s) : ctb_launch<64, 16>(a, wgs, s))
+    const lamp_status st = Ci == 64 ? (Co == 32 ? (a.fold > 1 ? ctb_launch<64, 32, float>(a, wgs, s) : ctb_launch<64, 32>(a, wgs, s)) : ctb_launch<64, 16>(a, wgs, s))
                                     : (Co == 32 ? ctb_launch<32, 32>(a, wgs, s) : ctb_launch<32, 16>(a, wgs, s));
     if (st != LAMP_OK) return st;
     return launch_reduce_partials((const float*)ws, wgs, Ci * 8 * Co + (dbias ? Co : 0), dwt, beta, s, dbias, Ci * 8 * Co);
