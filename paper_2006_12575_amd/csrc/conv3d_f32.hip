@@ -1,39 +1,9 @@
 // 3x3x3 convolution of fp32 tensors (and the forward pass of narrow bf16 inputs) on the fp32 matrix instruction: forward, data gradient and weight gradient, any channel counts.
 // Products and sums stay fp32 (v_mfma_f32_16x16x4_f32, 256 flops per cycle and CU, twice the vector units' rate).
-#include "internal.h"
+#include "f32_tile.h"
 #include "vec.h"
 
 namespace lamp {
-
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-
-// A tile of output voxels, each side a power of two (log2), and the tiles a sample needs.
-struct TileGeo {
-    int ld, lh, lw;      // log2 of the tile's sides
-    int nd, nh, nw;      // tiles along each axis
-};
-// All sides' products equal `vox` (a power of two), w side at least 4, halo at most `halo` voxels: the fewest tiles, then the
-// smallest halo.
-static TileGeo pick_tile(int D, int H, int W, int vox, int halo) {
-    TileGeo best{0, 0, 2, 0, 0, 0};
-    int64_t bt = -1;
-    int bh = 0, lv = 0;
-    while ((1 << lv) < vox) ++lv;
-    for (int lw = 2; lw <= 5 && lw <= lv; ++lw)
-        for (int lh = 0; lh + lw <= lv && lh <= 4; ++lh) {
-            const int ld = lv - lw - lh;
-            const int hv = ((1 << ld) + 2) * ((1 << lh) + 2) * ((1 << lw) + 2);
-            if (ld > 4 || hv > halo) continue;
-            const int nd = cdiv(D, 1 << ld), nh = cdiv(H, 1 << lh), nw = cdiv(W, 1 << lw);
-            const int64_t t = (int64_t)nd * nh * nw;
-            if (bt < 0 || t < bt || (t == bt && hv < bh)) {
-                bt = t;
-                bh = hv;
-                best = TileGeo{ld, lh, lw, nd, nh, nw};
-            }
-        }
-    return best;
-}
 
 // ---- forward and data gradient --------------------------------------------------------------------
 // Bound: the fp32 matrix rate (157 TFLOP/s; 32 input channels are 432 flops a byte).  D[co][voxel] += W[co][ci] * X[ci][voxel + tap]
@@ -69,14 +39,6 @@ struct F32ConvArgs {
 
 __host__ __device__ constexpr int f32_flat(int cf) { return (27 * cf + 3) / 4; }
 __host__ __device__ constexpr int f32_est(int kc) { return kc == 16 ? 20 : kc == 8 ? 12 : 4; }
-// sum over the 16 lanes of a row
-__device__ __forceinline__ float row_sum16(float v) {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, true));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, true));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, true));
-    return v;
-}
 
 template <typename T, int KC, int CB, int VB, int MAXK, bool DGRAD, int CF = 0, bool FAST = false>
 __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32ConvArgs a) {
@@ -651,6 +613,7 @@ static void f32_wide_launch(const lamp_tensor_desc* xd, const float* x, const fl
 lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm, const void* w, const float* bias, bool dgrad,
                      const lamp_tensor_desc* zd, void* z, float* stats_out, float eps, void* ws, size_t ws_bytes, hipStream_t s) {
     if (!f32_conv_supported(xd, zd)) return LAMP_ERR_UNSUPPORTED;
+    if (dgrad && split_dgrad_takes(xd, x, zd, w)) return split_dgrad(xd, (const float*)x, (const float*)w, zd, (float*)z, s);
     if (xd->dtype == LAMP_F32 && f32_wide(xd, zd, nm, dgrad)) {
         f32_wide_launch(xd, (const float*)x, (const float*)w, bias, zd, (float*)z, s);
         LAMP_CHECK_LAUNCH();

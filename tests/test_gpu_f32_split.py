@@ -1,0 +1,82 @@
+"""fp32 data gradients with operands in bf16 pieces, at the edges of their tiles: every tile and block of outputs, ragged volumes and channel
+counts, channel slices, one and several tiles a workgroup, against 64-bit torch; values at the ends of the fp32 range."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def L():
+    import paper_2006_12575_amd as L
+    L.lib()
+    return L
+
+
+def shifted(x, t):
+    D, H, W = x.shape[1:4]
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1, 1, 1))
+    return xp[:, t // 9:t // 9 + D, t // 3 % 3:t // 3 % 3 + H, t % 3:t % 3 + W].reshape(-1, x.shape[4])
+
+
+def conv(x, w27):   # w27 [co][27][ci]
+    return sum(shifted(x, t) @ w27[:, t].t() for t in range(27)).reshape(*x.shape[:4], -1)
+
+
+def sliced(t, extra):
+    buf = torch.full((*t.shape[:4], t.shape[4] + extra), float("nan"), device="cuda")
+    buf[..., :t.shape[4]] = t
+    return buf[..., :t.shape[4]]
+
+
+def rel(a, b):
+    return ((a.double() - b).norm() / b.norm()).item()
+
+
+# An instruction rounds its sum of 32 products a few times, two units each at most: chains of 27 co / 32 such roundings of random sign,
+# four units, and the rounding of the result.
+@pytest.mark.parametrize("shape,co,extra", [
+    ((1, 37, 35, 41, 8), 8, 0), ((2, 49, 31, 33, 4), 8, 4), ((1, 36, 40, 44, 16), 16, 0), ((2, 32, 25, 23, 12), 16, 8),
+    ((1, 35, 36, 37, 24), 32, 0), ((1, 13, 11, 17, 20), 24, 0), ((1, 19, 23, 29, 48), 32, 4), ((1, 50, 40, 33, 32), 32, 0),
+    ((1, 9, 7, 65, 96), 40, 0), ((3, 9, 10, 12, 64), 64, 0), ((1, 12, 9, 11, 72), 128, 0), ((1, 3, 64, 65, 8), 24, 0), ((1, 70, 29, 5, 24), 8, 0),
+    ((2, 49, 3, 50, 48), 16, 12), ((1, 100, 61, 55, 16), 8, 0), ((1, 17, 16, 16, 32), 256, 0), ((1, 8, 8, 8, 32), 32, 0), ((1, 1, 2, 3, 8), 24, 0),
+    ((1, 46, 47, 41, 8), 40, 0), ((2, 40, 70, 75, 8), 8, 0)], ids=str)
+def test_f32_split(L, shape, co, extra):
+    g = torch.Generator(device="cuda").manual_seed(sum(shape) + co)
+    ci = shape[4]
+    x = sliced(torch.randn(shape, generator=g, device="cuda"), extra)
+    dz = sliced(torch.randn((*shape[:4], co), generator=g, device="cuda"), extra)
+    w = torch.randn((co, 3, 3, 3, ci), generator=g, device="cuda") * (2.0 / (27 * ci)) ** 0.5
+    dx = sliced(torch.zeros_like(x), extra)
+    L.lamp_conv3d_dgrad(dz, w, dx)
+    assert rel(dx, conv(dz, w.double().reshape(co, 27, ci).flip(1).permute(2, 1, 0))) <= 4 * U * (27 * co / 32) ** 0.5 + U
+    assert torch.isnan(dx.as_strided((*shape[:4], ci + extra), dx.stride())[..., ci:]).all()   # nothing beside the slice
+
+
+@pytest.mark.parametrize("ci,co", [(8, 8), (16, 16), (40, 32)], ids=str)
+def test_ends_of_the_range(L, ci, co):
+    """Infinities, NaN and the largest values come out of the data gradient as with fp32 products; powers of two move no bit."""
+    g = torch.Generator(device="cuda").manual_seed(ci)
+    shape = (1, 37, 36, 41, co)
+    dz = torch.randn(shape, generator=g, device="cuda")
+    w = torch.randn((co, 3, 3, 3, ci), generator=g, device="cuda") * 0.1
+    x = torch.randn((*shape[:4], ci), generator=g, device="cuda")
+    dx0, dx = (torch.empty((*shape[:4], ci), device="cuda") for _ in range(2))
+    L.lamp_conv3d_dgrad(dz, w, dx0)
+    for s in (2.0 ** -90, 2.0 ** 60):
+        L.lamp_conv3d_dgrad(dz * s, w, dx)
+        assert torch.equal(dx, dx0 * s)
+    dz[0, 5, 6, 7, 1], dz[0, 20, 20, 20, 0], dz[0, 30, 5, 9, co - 1] = float("inf"), float("-inf"), float("nan")
+    dz[0, 10, 30, 30, 2] = 3.4e38   # rounds to an infinity in bf16
+    w[2] = 0.01
+    L.lamp_conv3d_dgrad(dz, w, dx)
+    # data gradient: the conv with taps reversed and channels exchanged
+    dr = torch.nn.functional.conv3d(dz.cpu().permute(0, 4, 1, 2, 3), w.cpu().permute(4, 0, 1, 2, 3).flip(2, 3, 4), padding=1).permute(0, 2, 3, 4, 1).cuda()
+    assert torch.equal(torch.isnan(dx), torch.isnan(dr)) and torch.equal(torch.isinf(dx), torch.isinf(dr))
+    inf, fin = torch.isinf(dr), torch.isfinite(dr)
+    assert inf.sum().item() == 2 * 27 * ci and torch.equal(dx[inf], dr[inf])
+    big = fin & (dr.abs() > 1e30)
+    assert big.sum().item() == 27 * ci and ((dx[big] - dr[big]) / dr[big]).abs().max().item() <= 4 * U
+    rest = fin & ~big
+    assert (dx[rest] - dr[rest]).abs().max().item() <= 1e-4
