@@ -925,7 +925,8 @@ static F32WPlan f32w_plan(const lamp_tensor_desc* xd, const lamp_tensor_desc* dz
 size_t f32_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
     if (xd->dtype != LAMP_F32) return 0;
     const F32WPlan p = f32w_plan(xd, dzd);
-    return align_up((size_t)p.splits * p.vgs * dzd->c * 27 * xd->c * sizeof(float));
+    const size_t b = align_up((size_t)p.splits * p.vgs * dzd->c * 27 * xd->c * sizeof(float)), c = split_wgrad_ws_bytes(xd, dzd);
+    return b > c ? b : c;
 }
 
 bool f32_wgrad_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
@@ -957,6 +958,7 @@ lamp_status f32_wgrad(const lamp_tensor_desc* xd, const float* x, const NormIn& 
     const F32WPlan p = f32w_plan(xd, dzd);
     if (!ws || ws_bytes < f32_wgrad_ws_bytes(xd, dzd)) return LAMP_ERR_WORKSPACE;
     if (!f32_wgrad_supported(xd, dzd)) return LAMP_ERR_UNSUPPORTED;
+    if (split_wgrad_takes(xd, x, dzd, dz)) return split_wgrad(xd, x, nm, dzd, dz, dw, beta, ws, ws_bytes, s);
     F32WgradArgs a;
     a.x = x; a.dz = dz; a.part = (float*)ws; a.nm = nm;
     a.ldx = xd->ldc; a.lddz = dzd->ldc;

@@ -122,9 +122,14 @@ lamp_status f32_wgrad(const lamp_tensor_desc* xd, const float* x, const NormIn& 
                       float* dw, float beta, void* ws, size_t ws_bytes, hipStream_t s);
 
 // ---- conv3d_split.hip -----------------------------------------------------------------------
-// Data gradient of fp32 tensors with operands in bf16 pieces: what it takes is faster there than with fp32 products, and no less exact.
+// Data and weight gradient of fp32 tensors with operands in bf16 pieces: what they take is faster there than with fp32 products, and no
+// less exact.
 bool split_dgrad_takes(const lamp_tensor_desc* dzd, const void* dz, const lamp_tensor_desc* dxd, const void* w);
 lamp_status split_dgrad(const lamp_tensor_desc* dzd, const float* dz, const float* w, const lamp_tensor_desc* dxd, float* dx, hipStream_t s);
+bool split_wgrad_takes(const lamp_tensor_desc* xd, const void* x, const lamp_tensor_desc* dzd, const void* dz);
+size_t split_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd);
+lamp_status split_wgrad(const lamp_tensor_desc* xd, const float* x, const NormIn& nm, const lamp_tensor_desc* dzd, const float* dz,
+                        float* dw, float beta, void* ws, size_t ws_bytes, hipStream_t s);
 
 // ---- convtr_mfma.hip ------------------------------------------------------------------------
 bool mfma_convtr_supported(const lamp_tensor_desc* xd, const lamp_tensor_desc* yd, const lamp_norm_in* xnorm);
