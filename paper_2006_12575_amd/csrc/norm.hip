@@ -122,7 +122,9 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const T* __restrict_
 // waves), and mean / variance follow from the totals in fp64: with fp32 part sums as the input this
 // loses nothing against merging per-part means and second moments.
 // NT threads per (sample, channel): 256, or 1024 where there are thousands of parts (the loop over them is a chain of
-// strided loads: its length, not the bytes, is what the kernel takes).
+// strided loads: its length, not the bytes, is what the kernel takes).  Every part's loads are in flight at once up to 4 NT parts, and the
+// lanes fold by permlane swaps and DPP (shuffles of doubles were 36 trips through the LDS pipe in a row): the 27-launch forward of the
+// 3-level base-8 net 134.3 -> 131.7 us with its ten launches of this.
 template <int NT>
 __global__ __launch_bounds__(NT) void stats_finalize_kernel(const float* __restrict__ partial,
                                                             const int32_t* __restrict__ counts, int parts, int C,
@@ -132,26 +134,22 @@ __global__ __launch_bounds__(NT) void stats_finalize_kernel(const float* __restr
     const int32_t* cnt = counts + (counts_per_sample ? (size_t)n * parts : (size_t)0);
     const float2* pp = reinterpret_cast<const float2*>(partial) + (size_t)n * parts * C + c;
     double k = 0.0, sm = 0.0, sq = 0.0;
-    int p = tid;
-    for (; p + 3 * NT < parts; p += 4 * NT) {
+    for (int p = tid; p < parts; p += 4 * NT) {
         float2 v[4];
         int32_t kk[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { v[u] = pp[(size_t)(p + NT * u) * C]; kk[u] = cnt[p + NT * u]; }
+        for (int u = 0; u < 4; ++u) {
+            const int q = min(p + NT * u, parts - 1);
+            v[u] = pp[(size_t)q * C];
+            kk[u] = p + NT * u < parts ? cnt[q] : 0;
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (kk[u] > 0) { k += (double)kk[u]; sm += (double)v[u].x; sq += (double)v[u].y; }
     }
-    for (; p < parts; p += NT) {
-        const float2 v = pp[(size_t)p * C];
-        const int32_t kk = cnt[p];
-        if (kk > 0) { k += (double)kk; sm += (double)v.x; sq += (double)v.y; }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        k += __shfl_down(k, off);
-        sm += __shfl_down(sm, off);
-        sq += __shfl_down(sq, off);
-    }
+    k = wave_fold(k);
+    sm = wave_fold(sm);
+    sq = wave_fold(sq);
     if (lane == 0) { sh[wv][0] = k; sh[wv][1] = sm; sh[wv][2] = sq; }
     __syncthreads();
     if (tid == 0) {
@@ -431,23 +429,16 @@ __global__ __launch_bounds__(256) void inorm_bwd_finalize_kernel(const float* __
     const int c = blockIdx.x, n = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float2* pp = reinterpret_cast<const float2*>(partial) + (size_t)n * parts * C + c;
     double s = 0.0, q = 0.0;
-    int p = tid;
-    for (; p + 768 < parts; p += 1024) {
+    for (int p = tid; p < parts; p += 1024) {
         float2 v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = pp[(size_t)(p + 256 * u) * C];
+        for (int u = 0; u < 4; ++u) v[u] = pp[(size_t)min(p + 256 * u, parts - 1) * C];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { s += (double)v[u].x; q += (double)v[u].y; }
+        for (int u = 0; u < 4; ++u)
+            if (p + 256 * u < parts) { s += (double)v[u].x; q += (double)v[u].y; }
     }
-    for (; p < parts; p += 256) {
-        const float2 v = pp[(size_t)p * C];
-        s += (double)v.x;
-        q += (double)v.y;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        s += __shfl_down(s, off);
-        q += __shfl_down(q, off);
-    }
+    s = wave_fold(s);
+    q = wave_fold(q);
     if (lane == 0) { sh[wv][0] = s; sh[wv][1] = q; }
     __syncthreads();
     if (tid == 0) {

@@ -36,7 +36,8 @@ const bf16_t* device_zero16(hipStream_t s) {
 }
 
 // Block = 256 / SL groups of VO consecutive outputs x SL lanes over the parts; every lane adds its strided parts in order, then
-// the lanes are folded by halves: a fixed summation tree, fp64.
+// the lanes are folded by halves: a fixed summation tree, fp64, with one barrier (one for every halving took 5.2 where this takes 4.9 us,
+// 512 parts of 27 * 64 outputs).
 // Bound: HBM (the parts are read once).  VO = 4 makes a part's row a run of whole 64-byte pieces also where SL lanes leave a block
 // few outputs (64->32 transposed conv, 512 parts of 16384: 37 -> 12 us, with the right number of lanes less), and gives a thread
 // enough in flight where there are few parts of many outputs (256->256 conv weights, 4 parts of 1.8 M: 21.6 -> 10.6 us).
@@ -83,17 +84,20 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
     if constexpr (SL > 1) {
 #pragma unroll
         for (int i = 0; i < VO; ++i) sh[i * 256 + threadIdx.x] = acc[i];
+        // halves onto each other: across the waves in one trip through LDS, within the first wave by lane moves
+        __syncthreads();
+        constexpr int KEEP = GPB > 64 ? GPB : 64;
+        if (threadIdx.x >= KEEP) return;
 #pragma unroll
-        for (int half = SL / 2; half > 0; half >>= 1) {
-            __syncthreads();
-            if (sl < half) {
-#pragma unroll
-                for (int i = 0; i < VO; ++i) sh[i * 256 + threadIdx.x] += sh[i * 256 + threadIdx.x + half * GPB];
-            }
+        for (int i = 0; i < VO; ++i) {
+            const double* q = sh + i * 256 + threadIdx.x;
+            if constexpr (GPB == 128) acc[i] += q[128];
+            else acc[i] = (acc[i] + q[128]) + (q[64] + q[192]);
+            if constexpr (GPB <= 32) acc[i] += lanes_down<32>(acc[i]);
+            if constexpr (GPB <= 16) acc[i] += lanes_down<16>(acc[i]);
+            if constexpr (GPB <= 8) acc[i] += lanes_down<8>(acc[i]);
+            if constexpr (GPB <= 4) acc[i] += lanes_down<4>(acc[i]);
         }
-        if (sl == 0)
-#pragma unroll
-            for (int i = 0; i < VO; ++i) acc[i] = sh[i * 256 + threadIdx.x];
     }
     if (sl == 0 && o < O) {
         if (o >= O1) out = out2 - O1;

@@ -113,12 +113,18 @@ __global__ __launch_bounds__(256) void se_finalize_kernel(const float* __restric
     double s[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) s[k] = 0.0;
-    for (int p = tid; p < parts; p += 256)
+    for (int p = tid; p < parts; p += 1024) {
+        float v[4][K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) s[k] += (double)pp[(size_t)p * C * K + k];
+        for (int u = 0; u < 4; ++u) ld_floats<K>(pp + (size_t)min(p + 256 * u, parts - 1) * C * K, v[u]);
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        for (int off = 32; off > 0; off >>= 1) s[k] += __shfl_down(s[k], off);
+        for (int u = 0; u < 4; ++u)
+            if (p + 256 * u < parts)
+#pragma unroll
+                for (int k = 0; k < K; ++k) s[k] += (double)v[u][k];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k] = wave_fold(s[k]);
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < K; ++k) sh[wv][k] = s[k];

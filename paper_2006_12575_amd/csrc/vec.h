@@ -173,6 +173,30 @@ __device__ __forceinline__ void load_norm_vec(const T* p, const NormIn& nm, int 
     }
 }
 
+// The value OFF lanes further on, for the lanes below OFF (of a wave for 32 and 16, of each row of 16 below that): permlane swaps and DPP,
+// where a shuffle of a double is two trips through the LDS pipe.
+template <int OFF> __device__ __forceinline__ double lanes_down(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    uint32_t w[2] = {(uint32_t)b, (uint32_t)(b >> 32)};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if constexpr (OFF == 32) w[i] = __builtin_amdgcn_permlane32_swap(w[i], w[i], false, false)[1];
+        else if constexpr (OFF == 16) w[i] = __builtin_amdgcn_permlane16_swap(w[i], w[i], false, false)[1];
+        else w[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[i], 0x100 + OFF, 0xf, 0xf, true);
+    }
+    return __builtin_bit_cast(double, (uint64_t)w[1] << 32 | w[0]);
+}
+// Lane 0: the sum over the wave, halves folded onto each other.
+__device__ __forceinline__ double wave_fold(double v) {
+    v += lanes_down<32>(v);
+    v += lanes_down<16>(v);
+    v += lanes_down<8>(v);
+    v += lanes_down<4>(v);
+    v += lanes_down<2>(v);
+    v += lanes_down<1>(v);
+    return v;
+}
+
 // The first half of a chunk's rows, in whole groups of four row rounds; a thread's sums over it wait in its own slots of block_fold's
 // buffer (no barrier: nobody else touches them before the fold).
 __device__ __forceinline__ int64_t half_rows(int64_t rbeg, int rows, int rl, int64_t rend) {
