@@ -11,12 +11,16 @@ namespace lamp {
 typedef uint16_t bf16_t;  // raw bfloat16 bits
 
 __device__ __forceinline__ float bf2f(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
-// round-to-nearest-even; NaN/Inf are out of contract
-__device__ __forceinline__ bf16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
+// Two values rounded to nearest even, lo in the low half: one instruction (v_cvt_pk_bf16_f32), the same bits as the four integer ones a
+// value that it replaces, for every finite value, denormals among them (all 2^32 patterns compared).  Head with ten classes and its backward
+// on 2 x 128^3 x 32 162.7 -> 155.6 us, conv unit 2->16 on 2 x 64 x 80 x 96 110.8 -> 109.5.  NaN/Inf are out of contract.
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+    typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+__device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
 template <typename T> struct io;
 template <> struct io<float> {

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void conv3d_cin1_fwd_kernel(const bf16_t* __re
             for (int e = 0; e < 8; ++e) acc[e] = fmaf(xv[t], wsh[t * Cout + c8 + e], acc[e]);
         uint32_t pk[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) pk[e] = (uint32_t)f2bf(acc[2 * e]) | ((uint32_t)f2bf(acc[2 * e + 1]) << 16);
+        for (int e = 0; e < 4; ++e) pk[e] = f2bf2(acc[2 * e], acc[2 * e + 1]);
         *reinterpret_cast<uint4*>(zp + c8) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
     }
 }
@@ -133,13 +133,6 @@ __global__ __launch_bounds__(256) void conv3d_cin1_fwd_kernel(const bf16_t* __re
 // rounded outputs are accumulated on the way for the instance-norm statistics.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 c1_bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float c1_f32x16;
-typedef __attribute__((__vector_size__(2 * sizeof(float)))) float c1_f32x2;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 c1_bf16x2;
-__device__ __forceinline__ uint32_t c1_pack(float lo, float hi) {
-    c1_f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, c1_bf16x2));
-}
-
 struct Cin1Args {
     const bf16_t* x; int ldx;
     const bf16_t* w;
@@ -252,8 +245,8 @@ __global__ __launch_bounds__(256) void conv3d_cin1_fwd_tile_kernel(Cin1Args a) {
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[cb][1], b[1], acc, 0, 0, 0);
 #pragma unroll
                     for (int q4 = 0; q4 < 2; ++q4) {
-                        const uint4 pk = make_uint4(c1_pack(acc[8 * q4 + 0], acc[8 * q4 + 1]), c1_pack(acc[8 * q4 + 2], acc[8 * q4 + 3]),
-                                                    c1_pack(acc[8 * q4 + 4], acc[8 * q4 + 5]), c1_pack(acc[8 * q4 + 6], acc[8 * q4 + 7]));
+                        const uint4 pk = make_uint4(f2bf2(acc[8 * q4 + 0], acc[8 * q4 + 1]), f2bf2(acc[8 * q4 + 2], acc[8 * q4 + 3]),
+                                                    f2bf2(acc[8 * q4 + 4], acc[8 * q4 + 5]), f2bf2(acc[8 * q4 + 6], acc[8 * q4 + 7]));
                         *reinterpret_cast<uint4*>(tb + l32 * C1_TROW + half * 32 + q4 * 16) = pk;
                     }
                     __builtin_amdgcn_wave_barrier();

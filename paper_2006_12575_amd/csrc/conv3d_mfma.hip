@@ -66,13 +66,6 @@ template <int TDT, int COB> struct Lds {
     static_assert(LDS_BYTES <= 160 * 1024, "the layout fits the LDS of a compute unit");
 };
 
-// Two floats to a pair of bf16 (round to nearest even) with the hardware conversion.
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-    typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
-    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-    const f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
 // v of the lane N places further round in its row of 16 lanes (a DPP row rotation).
 template <int N> __device__ __forceinline__ float row_ror(float v) {
     const int r = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF, false);
@@ -271,7 +264,7 @@ __device__ __forceinline__ void halo_norm(char* __restrict__ hb, const HaloLane&
                 // the matrix cores cannot see (both are zero)
                 const float u0 = fmaxf(fmaf(__uint_as_float(r[e] << 16), c.x, c.y), relu_floor);
                 const float u1 = fmaxf(fmaf(__uint_as_float(r[e] & 0xFFFF0000u), c.z, c.w), relu_floor);
-                o[e] = in ? pack_bf16(u0, u1) : r[e];
+                o[e] = in ? f2bf2(u0, u1) : r[e];
             }
             *p = make_uint4(o[0], o[1], o[2], o[3]);
         }
@@ -937,8 +930,8 @@ __global__ __launch_bounds__(512) void conv3d_igemm_kernel(ConvArgs a) {
                 for (int cb = 0; cb < COB; ++cb)
 #pragma unroll
                     for (int rg = 0; rg < 4; ++rg) {
-                        const uint32_t p0 = pack_bf16(acc[cb][vb][rg * 4 + 0], acc[cb][vb][rg * 4 + 1]);
-                        const uint32_t p1 = pack_bf16(acc[cb][vb][rg * 4 + 2], acc[cb][vb][rg * 4 + 3]);
+                        const uint32_t p0 = f2bf2(acc[cb][vb][rg * 4 + 0], acc[cb][vb][rg * 4 + 1]);
+                        const uint32_t p1 = f2bf2(acc[cb][vb][rg * 4 + 2], acc[cb][vb][rg * 4 + 3]);
                         *reinterpret_cast<uint2*>(patch + l32 * ROWB + (cb * 32 + rg * 8 + half * 4) * 2) = make_uint2(p0, p1);
                         if constexpr (!ZERO_START) {
 #pragma unroll

@@ -129,18 +129,14 @@ __global__ __launch_bounds__(256) void convtr_gemm_kernel(CtArgs a) {
                 if (MODE == 0) {
                     const int tap = row / a.Co, co = row - tap * a.Co;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float bv = a.bias ? a.bias[co + e] : 0.f;
-                        const uint32_t b = f2bf(acc[rb][vb][rg * 4 + e] + bv);
-                        if (e & 1) pk[e >> 1] |= b << 16; else pk[e >> 1] = b;
+                    for (int e = 0; e < 2; ++e) {
+                        const float b0 = a.bias ? a.bias[co + 2 * e] : 0.f, b1 = a.bias ? a.bias[co + 2 * e + 1] : 0.f;
+                        pk[e] = f2bf2(acc[rb][vb][rg * 4 + 2 * e] + b0, acc[rb][vb][rg * 4 + 2 * e + 1] + b1);
                     }
                     *reinterpret_cast<uint2*>(a.out + (fine[vb] + tap_off(tap)) * a.ldo + co) = make_uint2(pk[0], pk[1]);
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t b = f2bf(acc[rb][vb][rg * 4 + e]);
-                        if (e & 1) pk[e >> 1] |= b << 16; else pk[e >> 1] = b;
-                    }
+                    for (int e = 0; e < 2; ++e) pk[e] = f2bf2(acc[rb][vb][rg * 4 + 2 * e], acc[rb][vb][rg * 4 + 2 * e + 1]);
                     *reinterpret_cast<uint2*>(a.out + vq[vb] * a.ldo + row) = make_uint2(pk[0], pk[1]);
                 }
             }
@@ -155,12 +151,6 @@ __global__ __launch_bounds__(256) void convtr_gemm_kernel(CtArgs a) {
 // lanes of 16 bytes side by side -- instead of one 8-byte piece per lane.  A per-wave LDS buffer
 // transposes between that memory order and the matrix-core fragment order; only the owning wave
 // touches its buffer, so no workgroup barrier is needed.
-typedef __attribute__((__vector_size__(2 * sizeof(float)))) float ct_f32x2;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 ct_bf16x2;
-__device__ __forceinline__ uint32_t ct_pack(float lo, float hi) {
-    ct_f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, ct_bf16x2));
-}
 
 static constexpr int CT_ROW = 80;  // bytes per voxel row in the transposing buffer: 64 of data, padded
 
@@ -273,8 +263,8 @@ __global__ __launch_bounds__(256) void convtr_fwd32_kernel(CtArgs a) {
             const float4 bv = *reinterpret_cast<const float4*>(&bsh[wv][co0 + c]);
 #pragma unroll
             for (int vb = 0; vb < VB; ++vb) {
-                const uint2 pk = make_uint2(ct_pack(acc[rb][vb][rg * 4 + 0] + bv.x, acc[rb][vb][rg * 4 + 1] + bv.y),
-                                            ct_pack(acc[rb][vb][rg * 4 + 2] + bv.z, acc[rb][vb][rg * 4 + 3] + bv.w));
+                const uint2 pk = make_uint2(f2bf2(acc[rb][vb][rg * 4 + 0] + bv.x, acc[rb][vb][rg * 4 + 1] + bv.y),
+                                            f2bf2(acc[rb][vb][rg * 4 + 2] + bv.z, acc[rb][vb][rg * 4 + 3] + bv.w));
                 *reinterpret_cast<uint2*>(mine + (vb * 32 + l32) * CT_ROW + c * 2) = pk;
             }
         }
@@ -380,8 +370,8 @@ __global__ __launch_bounds__(512, KS <= 4 ? 4 : 2) void convtr_fwd_lds_kernel(Ct
                     const int c = u * 32 + rg * 8 + half * 4;
                     const float4 bv = *reinterpret_cast<const float4*>(bl + m * 64 + c);
                     *reinterpret_cast<uint2*>(patch + l32 * CT_PROW + c * 2) =
-                        make_uint2(ct_pack(acc[u][rg * 4 + 0] + bv.x, acc[u][rg * 4 + 1] + bv.y),
-                                   ct_pack(acc[u][rg * 4 + 2] + bv.z, acc[u][rg * 4 + 3] + bv.w));
+                        make_uint2(f2bf2(acc[u][rg * 4 + 0] + bv.x, acc[u][rg * 4 + 1] + bv.y),
+                                   f2bf2(acc[u][rg * 4 + 2] + bv.z, acc[u][rg * 4 + 3] + bv.w));
                 }
             __builtin_amdgcn_wave_barrier();
             const int off = po[m * 8 + (lane & 7)];
@@ -537,8 +527,8 @@ __global__ __launch_bounds__(PF > 1 ? 64 : 256) void convtr_dgrad32_kernel(CtArg
         for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
             for (int vb = 0; vb < 2; ++vb) {
-                const uint2 pk = make_uint2(ct_pack(acc[rb][vb][rg * 4 + 0], acc[rb][vb][rg * 4 + 1]),
-                                            ct_pack(acc[rb][vb][rg * 4 + 2], acc[rb][vb][rg * 4 + 3]));
+                const uint2 pk = make_uint2(f2bf2(acc[rb][vb][rg * 4 + 0], acc[rb][vb][rg * 4 + 1]),
+                                            f2bf2(acc[rb][vb][rg * 4 + 2], acc[rb][vb][rg * 4 + 3]));
                 *reinterpret_cast<uint2*>(mine + (vb * 32 + l32) * CT_ROW + (rg * 8 + half * 4) * 2) = pk;
             }
         __builtin_amdgcn_wave_barrier();
@@ -1039,7 +1029,7 @@ __global__ __launch_bounds__(512, 2 * ctb_per_cu(CI, CO)) void convtr_bwd_kernel
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg)
                 *reinterpret_cast<uint2*>(patch + l32 * CT_ROW + (rg * 8 + half * 4) * 2) =
-                    make_uint2(ct_pack(acc[rg * 4 + 0], acc[rg * 4 + 1]), ct_pack(acc[rg * 4 + 2], acc[rg * 4 + 3]));
+                    make_uint2(f2bf2(acc[rg * 4 + 0], acc[rg * 4 + 1]), f2bf2(acc[rg * 4 + 2], acc[rg * 4 + 3]));
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int it = 0; it < 2; ++it) {

@@ -143,8 +143,6 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 hbf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float hf32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float hf32x4;
 
-__device__ __forceinline__ uint32_t head_pack_bf16(float lo, float hi) { return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16); }
-
 // MODE 0: logits only.  MODE 1: + loss, dx, per-wave partials of dWh and dbh.
 // NCB: 32-channel blocks the instantiation holds (C <= 32 * NCB).
 // NORM: x is a raw conv output; InstanceNorm (+ ReLU) is applied while it is loaded, rounded to bf16 as the
@@ -340,8 +338,8 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
                 bk[j] = half == 0 ? dl[j] : rcv[j];
                 bk[4 + j] = half == 0 ? rcv[j] : dl[4 + j];
             }
-            const hbf16x8 bdl = __builtin_bit_cast(hbf16x8, make_uint4(head_pack_bf16(bk[0], bk[1]), head_pack_bf16(bk[2], bk[3]),
-                                                                         head_pack_bf16(bk[4], bk[5]), head_pack_bf16(bk[6], bk[7])));
+            const hbf16x8 bdl = __builtin_bit_cast(hbf16x8, make_uint4(f2bf2(bk[0], bk[1]), f2bf2(bk[2], bk[3]),
+                                                                         f2bf2(bk[4], bk[5]), f2bf2(bk[6], bk[7])));
             if (dx) {
 #pragma unroll
                 for (int cb = 0; cb < NCB; ++cb) {
@@ -356,7 +354,7 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
 #pragma unroll
                         for (int rg = 0; rg < 4; ++rg)
                             *reinterpret_cast<uint2*>(tp + l32 * 80 + (8 * rg + 4 * half) * 2) =
-                                make_uint2(head_pack_bf16(a2[rg * 4 + 0], a2[rg * 4 + 1]), head_pack_bf16(a2[rg * 4 + 2], a2[rg * 4 + 3]));
+                                make_uint2(f2bf2(a2[rg * 4 + 0], a2[rg * 4 + 1]), f2bf2(a2[rg * 4 + 2], a2[rg * 4 + 3]));
                         __builtin_amdgcn_wave_barrier();
 #pragma unroll
                         for (int it = 0; it < 2; ++it) {

@@ -40,7 +40,7 @@ template <> struct Vec<bf16_t, 8> {
     static __device__ __forceinline__ raw pack(const float (&v)[8]) {
         uint32_t r[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = (uint32_t)f2bf(v[2 * i]) | ((uint32_t)f2bf(v[2 * i + 1]) << 16);
+        for (int i = 0; i < 4; ++i) r[i] = f2bf2(v[2 * i], v[2 * i + 1]);
         return make_uint4(r[0], r[1], r[2], r[3]);
     }
     template <bool NT = false> static __device__ __forceinline__ void raw_store(bf16_t* p, const raw& q) { st16<NT>(p, q); }
