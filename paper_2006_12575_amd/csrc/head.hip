@@ -148,6 +148,10 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float hf32x4;
 // NORM: x is a raw conv output; InstanceNorm (+ ReLU) is applied while it is loaded, rounded to bf16 as the
 // stored activation would be (every 32-voxel group lies inside one sample: Vs % 32 == 0).
 // NI: classes a lane works on (4 serves up to 8 classes: 4*half + i; 6 serves 10, 8 serves 16).
+// Bound: HBM (172 bytes a voxel of 32 channels and ten classes), with about 500 vector instructions a group of 32 voxels beside it.  The labels
+// come a group ahead like the activations, lanes exchange by permlane swaps, and classes past the last need no branch: 2 x 128^3 x 32,
+// ten classes, 148 us with the labels loaded where they are used, shuffles through the LDS pipe and a branch to every class, 133 so
+// (5.4 TB/s).
 template <int MODE, int NCB, bool NORM = false, int NI = 8>
 __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfma_kernel(const bf16_t* __restrict__ x, int ldx, const bf16_t* __restrict__ wh,
                                                         const float* __restrict__ bh, int K, int C, int64_t Vtot,
@@ -185,13 +189,16 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
         }
         abw[cb] = __builtin_bit_cast(hbf16x8, make_uint4(r[0], r[1], r[2], r[3]));
     }
-    // this lane's 8 classes and their biases
-    int cls[8];
+    // this lane's 8 classes and their biases; a class past the last takes a bias that is below every logit, so that its exponential and its
+    // gradient are zero without a test, no label meets it, and its logit goes behind the group's in LDS
+    auto slot_class = [](int i) __attribute__((always_inline)) { return 8 * (i >> 2) + (i & 3); };   // + 4 * half
+    bool own[8];
     float bias[8];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        cls[i] = 8 * (i >> 2) + 4 * half + (i & 3);
-        bias[i] = (bh && cls[i] < K) ? bh[cls[i]] : 0.f;
+        const int k = slot_class(i) + 4 * half;
+        own[i] = k < K;
+        bias[i] = own[i] ? (bh ? bh[k] : 0.f) : -3.0e38f;
     }
     if (MODE == 1) {
         for (int i = lane; i < 32 * 17; i += 64) (&dls[wv][0][0])[i] = 0.f;   // classes no lane writes stay zero
@@ -227,6 +234,12 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
         }
     };
     if constexpr (AHEAD) fetch_x(g_lo, xnext);
+    auto fetch_label = [&](int64_t g) __attribute__((always_inline)) {
+        const int64_t v = g * 32 + l32;
+        const int l = g < g_hi && v < Vtot ? labels[v] : -1;
+        return (l < K ? l : -1) - 4 * half;   // (one past the last class meets none)
+    };
+    int lab_next = MODE == 1 ? fetch_label(g_lo) : 0;
     for (int64_t g = g_lo; g < g_hi; g += g_step) {
         const int64_t v = g * 32 + l32;
         const bool valid = v < Vtot;
@@ -285,58 +298,57 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
             const int64_t left = Vtot - g * 32;   // valid voxels of the group (wave-uniform)
             if (left >= 32) {
 #pragma unroll
-                for (int i = 0; i < NI; ++i)
-                    if (cls[i] < K) pk[l32 * K + cls[i]] = lg[i];
+                for (int i = 0; i < NI; ++i) pk[(own[i] ? l32 * K + 4 * half : 32 * K) + slot_class(i)] = lg[i];
                 __builtin_amdgcn_wave_barrier();
-                float* dst = logits + g * 32 * K;
-                for (int q4 = lane; q4 < 8 * K; q4 += 64)
-                    st16<true>(dst + 4 * q4, *reinterpret_cast<const float4*>(pk + 4 * q4));
+                float* dst = logits + g * 32 * K + 4 * lane;
+#pragma unroll
+                for (int it = 0; it < 2; ++it)   // up to 16 classes
+                    if (64 * it + lane < 8 * K) st16<true>(dst + 256 * it, *reinterpret_cast<const float4*>(pk + 256 * it + 4 * lane));
                 __builtin_amdgcn_wave_barrier();
             } else if (valid) {
 #pragma unroll
                 for (int i = 0; i < NI; ++i)
-                    if (cls[i] < K) logits[v * K + cls[i]] = lg[i];
+                    if (own[i]) logits[v * K + slot_class(i) + 4 * half] = lg[i];
             }
         }
         if (MODE == 1) {
+            auto both = [](float u) __attribute__((always_inline)) {   // the values of the two lanes that share a voxel
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
+                return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+            };
             float m = -3.0e38f;
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
-                if (cls[i] < K) m = lg[i] > m ? lg[i] : m;
-            const float mo = __shfl_xor(m, 32);
-            m = mo > m ? mo : m;
+            for (int i = 0; i < NI; ++i) m = lg[i] > m ? lg[i] : m;
+            const float2 m2 = both(m);
+            m = m2.y > m2.x ? m2.y : m2.x;
             float se = 0.f, ex[8];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                ex[i] = cls[i] < K ? expf(lg[i] - m) : 0.f;
+                ex[i] = expf(lg[i] - m);
                 se += ex[i];
             }
-            se += __shfl_xor(se, 32);
+            const float2 se2 = both(se);
+            se = se2.x + se2.y;
             const float lse = m + logf(se), rse = 1.0f / se;
-            const int lab = valid ? labels[v] : -1;
+            const int lab = lab_next;
+            lab_next = fetch_label(g + g_step);
             float ll = 0.f, dl[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                dl[i] = 0.f;
-                if (cls[i] < K && valid) {
-                    if (cls[i] == lab) ll = lg[i];
-                    dl[i] = (ex[i] * rse - (cls[i] == lab ? 1.f : 0.f)) * invV;
-                }
+                const bool hit = lab == slot_class(i);
+                if (hit) ll = lg[i];
+                dl[i] = valid ? (ex[i] * rse - (hit ? 1.f : 0.f)) * invV : 0.f;
                 dbsum[i] += dl[i];
             }
-            ll += __shfl_xor(ll, 32);
-            if (valid && half == 0) lsum += (lse - ll) * invV;
+            const float2 ll2 = both(ll);
+            if (valid && half == 0) lsum += (lse - (ll2.x + ll2.y)) * invV;
             // dlogits^T as the B operand of the dx product: this lane needs classes 8*half .. 8*half+7
-            float snd[4], rcv[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) snd[j] = half == 0 ? dl[4 + j] : dl[j];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) rcv[j] = __shfl_xor(snd[j], 32);
             float bk[8];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                bk[j] = half == 0 ? dl[j] : rcv[j];
-                bk[4 + j] = half == 0 ? rcv[j] : dl[4 + j];
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(dl[j]), __float_as_uint(dl[4 + j]), false, false);
+                bk[j] = __uint_as_float(r[0]);
+                bk[4 + j] = __uint_as_float(r[1]);
             }
             const hbf16x8 bdl = __builtin_bit_cast(hbf16x8, make_uint4(f2bf2(bk[0], bk[1]), f2bf2(bk[2], bk[3]),
                                                                          f2bf2(bk[4], bk[5]), f2bf2(bk[6], bk[7])));
@@ -371,7 +383,7 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
                 // stage dlogits [voxel][class] and x [voxel][channel] as it is stored, for the voxel-reduction product; a 4-byte
                 // read holds an even and an odd channel, one for each of a block's two products
 #pragma unroll
-                for (int i = 0; i < NI; ++i) dls[wv][l32][cls[i]] = dl[i];
+                for (int i = 0; i < NI; ++i) dls[wv][l32][slot_class(i) + 4 * half] = dl[i];
 #pragma unroll
                 for (int kc = 0; kc < 2 * NCB; ++kc)
                     if (kc < CK) *reinterpret_cast<uint4*>(xb[wv] + l32 * XR + kc * 32 + half * 16) = xq[kc];
@@ -419,20 +431,20 @@ __global__ __launch_bounds__(256, NCB == 1 ? 4 : NCB == 2 ? 3 : 1) void head_mfm
             for (int i = 0; i < NI; ++i) {
 #pragma unroll
                 for (int m = 1; m < 32; m <<= 1) dbsum[i] += __shfl_xor(dbsum[i], m);
-                if (l32 == 0 && cls[i] < K) bpart[(size_t)slot * K + cls[i]] = dbsum[i];
+                if (l32 == 0 && own[i]) bpart[(size_t)slot * K + slot_class(i) + 4 * half] = dbsum[i];
             }
         }
     }
 }
 
 // Adds up the partials of one call in one launch: dWh (slots of K*C), dbh (slots of K) and the loss (one per workgroup).  A block
-// is 4 outputs x 64 lanes over the slots, eight loads in flight, lanes folded by halves: a fixed summation tree, fp64.  (As three
-// launches: 8 us more.)
-__global__ __launch_bounds__(256) void head_reduce_kernel(const float* __restrict__ wpart, const float* __restrict__ bpart,
+// is 16 outputs (64 bytes of a slot) x 64 lanes over the slots, 32 loads in flight, lanes folded by halves: a fixed summation tree, fp64.
+// (4 outputs a block fetch every line four times: 4096 slots of 331 outputs 8.4 us, 7.5 so; as three launches 8 us more.)
+__global__ __launch_bounds__(1024) void head_reduce_kernel(const float* __restrict__ wpart, const float* __restrict__ bpart,
                                                           const float* __restrict__ lpart, int slots, int lslots, int KC, int K,
                                                           float* dwh, float* dbh, float* loss, float beta, float loss_beta) {
-    __shared__ double sh[256];
-    const int gl = threadIdx.x & 3, sl = threadIdx.x >> 2, o = blockIdx.x * 4 + gl;
+    __shared__ double sh[1024];
+    const int gl = threadIdx.x & 15, sl = threadIdx.x >> 4, o = blockIdx.x * 16 + gl;
     const float* p = nullptr;
     float* out = nullptr;
     int n = 0, stride = 0;
@@ -441,22 +453,29 @@ __global__ __launch_bounds__(256) void head_reduce_kernel(const float* __restric
     else if (o < KC + K) { p = bpart + (o - KC); out = dbh + (o - KC); n = slots; stride = K; }
     else if (o == KC + K) { p = lpart; out = loss; n = lslots; stride = 1; b = loss_beta; }
     double acc = 0.0;
-    int s = sl;
-    for (; s + 7 * 64 < n; s += 8 * 64) {
-        float v[8];
+    if (p)
+        for (int s = sl; s < n; s += 32 * 64) {
+            float v[32];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(s + 64 * u) * stride];
+            for (int u = 0; u < 32; ++u) v[u] = p[(int64_t)min(s + 64 * u, n - 1) * stride];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += (double)v[u];
-    }
-    for (; s < n; s += 64) acc += (double)p[(int64_t)s * stride];
+            for (int u = 0; u < 32; ++u)
+                if (s + 64 * u < n) acc += (double)v[u];
+        }
     sh[threadIdx.x] = acc;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    double a[16];
 #pragma unroll
-    for (int h = 32; h > 0; h >>= 1) {
-        __syncthreads();
-        if (sl < h) sh[threadIdx.x] += sh[threadIdx.x + 4 * h];
-    }
-    if (sl == 0 && out) *out = (b != 0.f ? b * *out : 0.f) + (float)sh[threadIdx.x];
+    for (int k = 0; k < 16; ++k) a[k] = sh[threadIdx.x + 64 * k];
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+        for (int k = 0; k < h; ++k) a[k] += a[k + h];
+    acc = a[0];
+    acc += lanes_down<32>(acc);
+    acc += lanes_down<16>(acc);
+    if (sl == 0 && out) *out = (b != 0.f ? b * *out : 0.f) + (float)acc;
 }
 
 static bool head_mfma_ok(const lamp_tensor_desc* xd, const void* x, const lamp_norm_in* xnorm, const void* wh, int classes,
@@ -633,7 +652,7 @@ lamp_status lamp::head_ce_run(const lamp_tensor_desc* xd, const void* x, const l
 #undef LAMP_HEAD_BWD
         LAMP_CHECK_LAUNCH();
         const int KC = dwh ? K * C : 0, KB = dbh ? K : 0;
-        hipLaunchKernelGGL(head_reduce_kernel, dim3(cdiv(KC + KB + 1, 4)), dim3(256), 0, s, wpart, bpart, lpart, nbm * 4, nbm, KC, KB, dwh,
+        hipLaunchKernelGGL(head_reduce_kernel, dim3(cdiv(KC + KB + 1, 16)), dim3(1024), 0, s, wpart, bpart, lpart, nbm * 4, nbm, KC, KB, dwh,
                            dbh, loss, beta, loss_beta);
         LAMP_CHECK_LAUNCH();
         return LAMP_OK;
