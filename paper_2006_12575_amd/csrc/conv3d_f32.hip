@@ -20,7 +20,8 @@ namespace lamp {
 // MAXK: halo pieces (4 channels of a voxel) a thread stages at most.
 // CF: 1 to 3 input channels, forward: a product contracts 4 consecutive (tap, channel) pairs, whatever tap they belong to -- the same
 // order, ceil(27 CF / 4) products instead of 27 with the channels padded to 4.  A lane's pair differs from product to product by more
-// than an immediate, so the offsets sit in registers.  2->16 bf16 on 2 x 64 x 80 x 96: 50 -> 38 us.
+// than an immediate, so the offsets sit in registers.  2->16 bf16 on 2 x 64 x 80 x 96: 50 -> 38 us, with loads by buffer instructions (no
+// branch to a channel of a voxel, both channels at once) 35.6 -> 32.5 of the launch alone; 3->32 on 83 x 61 x 97 52.5 -> 46.8.
 // FAST: fp32 with whole 16-byte pieces and whole chunks of input channels.  Loads without a branch: a piece outside the volume comes
 // from 16 zero bytes, weights past the last output channel from the last ones (their rows are not stored).  A branch to every piece is
 // most of what a workgroup with one wave a SIMD does between two chunks (32->96 on 9 x 9 x 22, data gradient: 27 -> 22 us; one or two
@@ -33,8 +34,9 @@ struct F32ConvArgs {
     int ldx, ldz, N, D, H, W, Ci, Co;
     TileGeo t;
     int ntiles, per;                   // tiles of all samples; tiles per workgroup
-    int xvec, wvec, zvec;              // 16-byte accesses possible
-    uint32_t mHW, mHH; int sHW, sHH;   // division by the halo's sides
+    int xvec, wvec, zvec;              // 16-byte accesses possible (xvec, CF 2: both channels of a voxel in one load)
+    uint32_t mHW, mHH, mT, mNw, mNh;   // division by the halo's sides, by the tiles of a sample, along w, along h
+    uint8_t sHW, sHH, sT, sNw, sNh;
 };
 
 __host__ __device__ constexpr int f32_flat(int cf) { return (27 * cf + 3) / 4; }
@@ -68,37 +70,87 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
     f32x4 px[MAXK], pw[MAXW];   // (vectors: a float4 is taken apart and put together again behind a wait for every load;
                                       // 32->32 on 41 x 56 x 47, whole kernel: 80 -> 74 us)
     uint32_t pin = 0;   // pieces inside the volume (the padding is zero behind the normalisation)
-    // once per tile: which pieces lie inside the volume, and where
-    int vo[MAXK];
+    // once per tile: which pieces lie inside the volume, and where.  CF, and FAST with two blocks of outputs (one has no registers for it):
+    // by buffer loads, a lane's byte offset from the halo's first voxel, which stays for the walk, or SKIP, past the end, which loads zeros;
+    // else voxel offsets.
+    constexpr bool BUF = CF || (FAST && CB == 2);
+    constexpr int SKIP = (int)0x80000000u, END = 0x7FFFFFF0;
+    int vo[MAXK], xo[BUF ? MAXK : 1];
+    if constexpr (BUF)
+#pragma unroll
+        for (int k = 0; k < MAXK; ++k)
+            vo[k] = ((((hc[k] >> 20) * a.H + (hc[k] >> 10 & 1023)) * a.W + (hc[k] & 1023)) * a.ldx + 4 * quad) * (int)sizeof(T);
     const T* const ax = static_cast<const T*>(a.x);
     const T* const aw = static_cast<const T*>(a.w);
     const T* xt = ax;
+    // sample and first voxel of a tile (by division where one tile a workgroup is the rule and its constants would come late)
+    auto where = [&](int tile, int& n, int& d0, int& h0, int& w0) __attribute__((always_inline)) {
+        if constexpr (BUF) {
+            n = (int)((uint64_t)(uint32_t)tile * a.mT >> a.sT);
+            const uint32_t r0 = (uint32_t)(tile - n * tiles), r1 = (uint32_t)((uint64_t)r0 * a.mNw >> a.sNw);
+            const uint32_t r2 = (uint32_t)((uint64_t)r1 * a.mNh >> a.sNh);
+            d0 = (int)(r2 << a.t.ld);
+            h0 = (int)((r1 - r2 * a.t.nh) << a.t.lh);
+            w0 = (int)((r0 - r1 * a.t.nw) << a.t.lw);
+        } else {
+            n = tile / tiles;
+            tile -= n * tiles;
+            const int iw = tile % a.t.nw, r1 = tile / a.t.nw, ih = r1 % a.t.nh, idd = r1 / a.t.nh;
+            d0 = idd << a.t.ld;
+            h0 = ih << a.t.lh;
+            w0 = iw << a.t.lw;
+        }
+    };
     auto locate = [&](int tile) __attribute__((always_inline)) {
-        const int n = tile / tiles;
-        tile -= n * tiles;
-        const int iw = tile % a.t.nw, r1 = tile / a.t.nw, ih = r1 % a.t.nh, idd = r1 / a.t.nh;
-        const int d0 = (idd << a.t.ld) - 1, h0 = (ih << a.t.lh) - 1, w0 = (iw << a.t.lw) - 1;
-        xt = ax + ((((int64_t)n * a.D + d0) * a.H + h0) * a.W + w0) * a.ldx + 4 * quad;
+        int n, d0, h0, w0;
+        where(tile, n, d0, h0, w0);
+        --d0, --h0, --w0;
+        xt = ax + ((((int64_t)n * a.D + d0) * a.H + h0) * a.W + w0) * a.ldx + (BUF ? 0 : 4 * quad);
         pin = 0;
 #pragma unroll
         for (int k = 0; k < MAXK; ++k) {
             asm volatile("" : "+v"(hc[k]));   // its parts are not worth registers of their own across the walk
             const int hd = hc[k] >> 20, hh = hc[k] >> 10 & 1023, hw = hc[k] & 1023;
-            vo[k] = (hd * a.H + hh) * a.W + hw;
-            if (hc[k] < 1 << 30 && (unsigned)(d0 + hd) < (unsigned)a.D && (unsigned)(h0 + hh) < (unsigned)a.H &&
-                (unsigned)(w0 + hw) < (unsigned)a.W)
-                pin |= 1u << k;
+            const bool in = hc[k] < 1 << 30 && (unsigned)(d0 + hd) < (unsigned)a.D && (unsigned)(h0 + hh) < (unsigned)a.H &&
+                            (unsigned)(w0 + hw) < (unsigned)a.W;
+            if constexpr (BUF) xo[k] = in ? vo[k] : SKIP;
+            else {
+                vo[k] = (hd * a.H + hh) * a.W + hw;
+                if (in) pin |= 1u << k;
+            }
         }
     };
+    auto inside = [&](int k) __attribute__((always_inline)) { return BUF ? xo[BUF ? k : 0] != SKIP : (pin >> k & 1) != 0; };
     auto fetch_x = [&](int c0) __attribute__((always_inline)) {
         const int left = a.Ci - c0 - 4 * quad;
+        const auto rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(xt), 0, END, 0x00020000);
 #pragma unroll
         for (int k = 0; k < MAXK; ++k) {
             f32x4 q = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (FAST) {
+            if constexpr (FAST && BUF) {
+                q = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, xo[k], 4 * c0, 0));
+            } else if constexpr (FAST) {
                 const T* p = xt + ((int64_t)vo[k] * a.ldx + c0);
                 p = pin >> k & 1 ? p : reinterpret_cast<const T*>(a.zero16);
                 q = *reinterpret_cast<const f32x4*>(p);
+            } else if constexpr (CF) {
+                if (CF == 2 && a.xvec) {
+                    if constexpr (sizeof(T) == 4) {
+                        typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+                        const f32x2 u = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rx, xo[k], 0, 0));
+                        q[0] = u[0];
+                        q[1] = u[1];
+                    } else {
+                        const uint32_t u = __builtin_amdgcn_raw_buffer_load_b32(rx, xo[k], 0, 0);
+                        q[0] = __uint_as_float(u << 16);
+                        q[1] = __uint_as_float(u & 0xFFFF0000u);
+                    }
+                } else
+#pragma unroll
+                    for (int j = 0; j < CF; ++j) {
+                        if constexpr (sizeof(T) == 4) q[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, xo[k], 4 * j, 0));
+                        else q[j] = __uint_as_float((uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rx, xo[k], 2 * j, 0) << 16);
+                    }
             } else if (pin >> k & 1) {
                 const T* p = xt + ((int64_t)vo[k] * a.ldx + c0);
                 if (sizeof(T) == 4 && a.xvec) {
@@ -123,7 +175,7 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
                 norm_coeffs(a.nm, n, c, na, nb);
 #pragma unroll
                 for (int k = 0; k < MAXK; ++k)
-                    if (pin >> k & 1) {
+                    if (inside(k)) {
                         const float u = norm_u(px[k][j], na, nb);
                         px[k][j] = io<T>::rnd(!a.nm.relu || u > 0.f ? u : 0.f);
                     }
@@ -244,7 +296,7 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
     fetch_x(0);
     fetch_w(0);
     for (int tile = t0; tile < t1; ++tile) {
-        const int n = tile / tiles, tl = tile - n * tiles;
+        const int n = BUF ? (int)((uint64_t)(uint32_t)tile * a.mT >> a.sT) : tile / tiles, tl = tile - n * tiles;
         float bs[CB][4];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
@@ -309,8 +361,8 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 2) void conv3d_f32_kernel(F32Con
             }
         }
 
-        const int iw = tl % a.t.nw, r1 = tl / a.t.nw, ih = r1 % a.t.nh, idd = r1 / a.t.nh;
-        const int d0 = idd << a.t.ld, h0 = ih << a.t.lh, w0 = iw << a.t.lw;
+        int nn, d0, h0, w0;
+        where(tile, nn, d0, h0, w0);
         float s[CB][4], q[CB][4];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
@@ -630,8 +682,16 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
     a.xvec = aligned16(x) && xd->c % 4 == 0 && xd->ldc % 4 == 0;
     a.zvec = aligned16(z) && zd->ldc % 4 == 0;
     a.wvec = aligned16(w) && (dgrad ? zd->c : xd->c) % 4 == 0;
-    div_magic((1 << p.t.lw) + 2, &a.mHW, &a.sHW);
-    div_magic((1 << p.t.lh) + 2, &a.mHH, &a.sHH);
+    auto magic = [](int d, uint32_t* m, uint8_t* sh) {
+        int k;
+        div_magic(d, m, &k);
+        *sh = (uint8_t)k;
+    };
+    magic((1 << p.t.lw) + 2, &a.mHW, &a.sHW);
+    magic((1 << p.t.lh) + 2, &a.mHH, &a.sHH);
+    magic(tiles, &a.mT, &a.sT);
+    magic(p.t.nw, &a.mNw, &a.sNw);
+    magic(p.t.nh, &a.mNh, &a.sNh);
     a.partial = nullptr; a.counts = nullptr;
     if (stats_out) {
         if (!ws || ws_bytes < f32_conv_ws_bytes(xd, zd, 1)) return LAMP_ERR_WORKSPACE;
@@ -651,7 +711,11 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
         }
     }
     const dim3 grid((unsigned)((a.ntiles + a.per - 1) / a.per), cols);
-    const bool fast = xd->dtype == LAMP_F32 && p.kc > 4 && a.xvec && a.wvec && xd->c % p.kc == 0 && zd->c >= 4;
+    // (buffer loads: a tile's byte offsets in 32 bits)
+    const bool near = (int64_t)xd->h * xd->w * 18 * xd->ldc * (int64_t)esize(xd->dtype) < ((int64_t)1 << 31);
+    const int cf = near ? p.cf : 0;
+    if (cf == 2) a.xvec = xd->ldc % 2 == 0 && ((uintptr_t)x & (xd->dtype == LAMP_F32 ? 7u : 3u)) == 0;
+    const bool fast = near && xd->dtype == LAMP_F32 && p.kc > 4 && a.xvec && a.wvec && xd->c % p.kc == 0 && zd->c >= 4;
     a.zero16 = fast ? device_zero16(s) : nullptr;
     if (fast && !a.zero16) return LAMP_ERR_HIP;
     if (fast) {
@@ -668,12 +732,12 @@ lamp_status f32_conv(const lamp_tensor_desc* xd, const void* x, const NormIn& nm
         if (p.kc == 16) f32_launch<float, 16, false>(p, grid, s, a);
         else if (p.kc == 8) f32_launch<float, 8, false>(p, grid, s, a);
         else if (xd->dtype == LAMP_F32) {
-            if (p.cf == 1) f32_launch<float, 4, false, 1>(p, grid, s, a);
-            else if (p.cf == 2) f32_launch<float, 4, false, 2>(p, grid, s, a);
-            else if (p.cf == 3) f32_launch<float, 4, false, 3>(p, grid, s, a);
+            if (cf == 1) f32_launch<float, 4, false, 1>(p, grid, s, a);
+            else if (cf == 2) f32_launch<float, 4, false, 2>(p, grid, s, a);
+            else if (cf == 3) f32_launch<float, 4, false, 3>(p, grid, s, a);
             else f32_launch<float, 4, false>(p, grid, s, a);
-        } else if (p.cf == 2) f32_launch<bf16_t, 4, false, 2>(p, grid, s, a);
-        else if (p.cf == 3) f32_launch<bf16_t, 4, false, 3>(p, grid, s, a);
+        } else if (cf == 2) f32_launch<bf16_t, 4, false, 2>(p, grid, s, a);
+        else if (cf == 3) f32_launch<bf16_t, 4, false, 3>(p, grid, s, a);
         else f32_launch<bf16_t, 4, false>(p, grid, s, a);
     }
     LAMP_CHECK_LAUNCH();
