@@ -401,8 +401,8 @@ lamp_status split_dgrad(const lamp_tensor_desc* xd, const float* x, const float*
 // shifted by the products that the matrix unit cuts off (32->32 on 41 x 56 x 47, dz from an InstanceNorm backward: relative error 1.8e-7
 // with fp32 products in chains of 128, 8.5e-7 with split3, 1.4e-7 with grids of single threads, 6.5e-8 so; 8->8 on 2 x 64 x 48 x 80 1.8e-7 ->
 // 5.8e-8, 256->256 on 3 x 28 x 27 x 26 2.9e-7 -> 1.0e-7).
-// With the reduction, us, fp32 products -> this: 32->32 on 41 x 56 x 47 81 -> 59, 8->8 on 2 x 64 x 48 x 80 53 -> 29, 16->16 91 -> 55,
-// 128->256 on 25 x 28 x 16 214 -> 130, 48->64 on 53 x 64 x 29 198 -> 126.  256 / 384 / 512 / 768 workgroups: 61 / 62 / 58 / 75 us, 71 / 67 /
+// With the reduction, us, fp32 products -> this: 32->32 on 41 x 56 x 47 81 -> 54, 8->8 on 2 x 64 x 48 x 80 53 -> 28, 16->16 91 -> 51,
+// 128->256 on 25 x 28 x 16 214 -> 115, 48->64 on 53 x 64 x 29 198 -> 110.  256 / 384 / 512 / 768 workgroups: 61 / 62 / 58 / 75 us, 71 / 67 /
 // 52 / 55 us (the first and the third of these shapes).
 struct SplitWgradArgs {
     const float* x; const float* dz; float* part;   // part [splits * VG][Co][27][Ci]
@@ -592,14 +592,26 @@ __global__ __launch_bounds__(256, 2) void conv3d_split_wgrad_kernel(SplitWgradAr
     };
     clear();
     float* const pb = a.part + ((int64_t)blockIdx.x * VG + vg) * a.Co * 27 * a.Ci;
+    // Buffer accesses: a lane's output and channel in its offset, block, tap and row in scalars (a branch and a 64-bit address to every value
+    // were 1100 instructions a wave and dump).
     auto dump = [&](bool add) __attribute__((always_inline)) {
-        int lo = l16;
-        asm volatile("" : "+v"(lo));
+        const auto rp = __builtin_amdgcn_make_buffer_rsrc(pb, 0, END, 0x00020000);
+        const int tl = CIC == 16 ? 0 : l16 >> 3, ci = ci0 + l16 % CIC;
+        int vo[CBO];
+#pragma unroll
+        for (int cb = 0; cb < CBO; ++cb) vo[cb] = ci < a.Ci && co0 + 16 * cb + 4 * g < a.Co ? ((4 * g * 27 + tl) * a.Ci + ci) * 4 : SKIP;
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const int c = (cg * NB + i) * 16 + lo, t = c / CIC, ci = ci0 + c % CIC;
+            const int t = (cg * NB + i) * (16 / CIC);   // the block's (first) tap
+            if (t >= 27) continue;
 #pragma unroll
-            for (int cb = 0; cb < CBO; ++cb)
+            for (int cb = 0; cb < CBO; ++cb) {
+                const int o = CIC < 16 && t + tl >= 27 ? SKIP : vo[cb];
+                float old[4] = {0.f, 0.f, 0.f, 0.f};
+                if (add)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        old[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rp, o, ((co0 + 16 * cb + r) * 27 + t) * a.Ci * 4, 0));
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     float q = rest[cb][i][r];
@@ -607,13 +619,10 @@ __global__ __launch_bounds__(256, 2) void conv3d_split_wgrad_kernel(SplitWgradAr
                         const float u = acc[cb][i][r] + q;
                         q += __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false)[1]);
                     }
-                    const int co = co0 + 16 * cb + 4 * g + r;
-                    float v = join_hl(acc[cb][i][r], q);
-                    if (t < 27 && ci < a.Ci && co < a.Co) {
-                        float* o = pb + ((int64_t)co * 27 + t) * a.Ci + ci;
-                        *o = add ? *o + v : v;
-                    }
+                    const float v = join_hl(acc[cb][i][r], q);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(add ? old[r] + v : v), rp, o, ((co0 + 16 * cb + r) * 27 + t) * a.Ci * 4, 0);
                 }
+            }
         }
     };
 
@@ -707,7 +716,8 @@ bool split_wgrad_takes(const lamp_tensor_desc* xd, const void* x, const lamp_ten
     const SplitWgradPlan p = split_wgrad_plan(xd, dzd);
     if (p.cic * p.cbo == 32 ? p.ntiles * p.cichunks * p.cochunks < 512 : p.ntiles < 32) return false;
     return p.ntiles < ((int64_t)1 << 31) && (int64_t)p.cichunks * p.cochunks <= 65535 &&
-           (int64_t)xd->h * xd->w * 18 * (xd->ldc > dzd->ldc ? xd->ldc : dzd->ldc) < ((int64_t)1 << 29);   // byte offsets in a tile
+           (int64_t)xd->h * xd->w * 18 * (xd->ldc > dzd->ldc ? xd->ldc : dzd->ldc) < ((int64_t)1 << 29) &&   // byte offsets in a tile, in dw
+           (int64_t)xd->c * dzd->c < ((int64_t)1 << 24);
 }
 size_t split_wgrad_ws_bytes(const lamp_tensor_desc* xd, const lamp_tensor_desc* dzd) {
     if (xd->dtype != LAMP_F32) return 0;
