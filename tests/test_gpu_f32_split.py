@@ -125,3 +125,43 @@ def test_ends_of_the_range(L, ci, co):
     L.lamp_conv3d_wgrad(x, dz, dw)
     bad, good = [0, 1, co - 1], list(range(3, co - 1))   # (channel 2: 3.4e38 times an input above 1 overflows in any arithmetic)
     assert not torch.isfinite(dw[bad]).any() and rel(dw[good], dw0[good].double()) <= 4 * U * 16
+
+
+CHILD = """
+import sys
+import torch
+sys.path.insert(0, %r)
+import paper_2006_12575_amd as L
+L.lib()
+torch.manual_seed(5)
+x, dz = (torch.randn((1, 30, 31, 33, 32), device="cuda") for _ in range(2))
+w, dx, dw = torch.randn((32, 3, 3, 3, 32), device="cuda"), torch.empty_like(x), torch.empty((32, 3, 3, 3, 32), device="cuda")
+ws = torch.empty(1 << 27, dtype=torch.uint8, device="cuda")
+
+def call():
+    L.lamp_conv3d_dgrad(dz, w, dx, ws=ws)
+    L.lamp_conv3d_wgrad(x, dz, dw, ws=ws)
+torch.cuda.synchronize()
+g = torch.cuda.CUDAGraph()
+with torch.cuda.graph(g):
+    call()
+got = []
+for _ in range(3):
+    dx.fill_(float("nan")), dw.fill_(float("nan"))
+    g.replay()
+    torch.cuda.synchronize()
+    got.append((dx.clone(), dw.clone()))
+call()
+torch.cuda.synchronize()
+assert all(torch.equal(a, dx) and torch.equal(b, dw) for a, b in got) and torch.isfinite(dx).all() and torch.isfinite(dw).all()
+print("replays equal")
+"""
+
+
+def test_first_call_in_a_capture():
+    import subprocess
+    import sys
+
+    import conftest
+    r = subprocess.run([sys.executable, "-c", CHILD % conftest.ROOT], capture_output=True, text=True, timeout=90)
+    assert r.returncode == 0 and "replays equal" in r.stdout, r.stderr[-2000:]
