@@ -30,7 +30,8 @@
  *     floating-point atomics; every reduction has a fixed order).
  *   - Non-finite values: out of contract in bf16.  In fp32 they are carried, but may reach more outputs than the formulas
  *     say: the kernels form products with the zeros that pad a volume and that fill up a tile, so an infinity or NaN in a
- *     conv's input, weight or gradient can make NaN of border voxels and of weight gradients that do not depend on it.
+ *     conv's input, weight or gradient can make NaN of border voxels and of weight gradients that do not depend on it;
+ *     a weight gradient that depends on an infinity can be NaN where the formula has an infinity.
  *   - Workspace: each call states its need through the matching *_workspace_bytes query;
  *     pointers must be 16-byte aligned (hipMalloc / torch allocations are).
  *   - One tuning switch, read once per process from the environment: LAMP_TUNE="key=value,...".
